@@ -227,7 +227,7 @@ struct Emitter {
         // tensors far larger than the caches leave with non-temporal stores, like the plain row stores
         // (transposes of 256-512 MB: 2-5 % faster; 16 MB and u8: not)
         const bool nt = dtype_size(e.dtype) >= 2 && (uint64_t)g.nodes[e.node].rows * g.nodes[e.node].cols * dtype_size(e.dtype) >= (32ull << 20);
-        os << indent << "fs_store_tile_transposed<" << e.dtype << ", " << tmpl_row() << ", WG, TCW, C, " << (nt ? "true" : "false") << ">(" << nm << ", lds_tile, a.p[" << e.arg
+        os << indent << "fs_store_tile_transposed<" << e.dtype << ", " << tmpl_row() << ", WG, TCW, " << (nt ? "true" : "false") << ">(" << nm << ", lds_tile, a.p[" << e.arg
            << "], R, row - rg, lir, rg, vbase);\n";
       } else
         os << indent << "fs_store_row_transposed<" << e.dtype << ", " << tmpl_row() << ">(" << nm << ", a.p[" << e.arg
@@ -458,7 +458,7 @@ struct Emitter {
     else os << "    " << (gp.s.resident ? "_Pragma(\"unroll 1\") " : "") << "for (int ch = CT - 1; ch >= 0; --ch) {\n";
     ++n_passes;
     // (inside a pass the chunk's own sizes shadow the body's: the building blocks read them by name)
-    os << "      constexpr int NVL = NVLC, E = NVLC * V;\n      constexpr bool RAGGED = RAGC;\n"
+    os << "      constexpr int NVL = NVLC, E = NVLC * V;\n      constexpr int RAGGED = RAGC;\n"
        << "      const int vbase = RESV + ch * (NVL * L);\n      (void)RAGGED;\n";
     if (lds_a.empty()) {
       emit_pass_body(mem, ext, lds_a, store_outputs, tail);
@@ -483,7 +483,7 @@ struct Emitter {
 
   // inside a pass: fold the chunk's elements into the running lane partials q<b> of the stage's reductions
   void emit_chunk_accumulate(const std::vector<int>& batch) {
-    const std::string col_ok = "(!RAGGED || (vbase + (e / V) * L + lir) < NV)";
+    const std::string col_ok = "fs_owned<V, NV, RAGGED>(vbase + (e / V) * L + lir, e % V)";
     for (int b : batch) {
       const fs_node& bn = g.nodes[b];
       const std::string q = "q" + std::to_string(loc(b));
@@ -817,13 +817,15 @@ struct Emitter {
     os << kname << "(const " << kname << "_args a) {\n";
     os << "  constexpr int V = " << s.V << ", NVL = " << s.NVL << ", L = " << s.L << ", NV = " << s.NV << ", E = NVL * V, WG = " << s.WG
        << ", G = WG / L, C = " << C << ", CT = " << s.CT << ";\n";
-    os << "  constexpr bool RAGGED = " << (s.ragged ? "true" : "false") << ";\n";
+    // (0: all vectors lie inside the row; else 1 + what the last vector overlaps its neighbour by)
+    const int over = s.NV * s.V - C;
+    os << "  constexpr int RAGGED = " << (s.ragged ? 1 + over : 0) << ";\n";
     os << "  const int tid = (int)threadIdx.x, lir = tid & (L - 1), rg = tid / L;\n";
     os << "  const long R = a.R;\n";
     os << "  (void)lir; (void)rg; (void)R; (void)C; (void)G; (void)CT;\n";
     if (xwave) os << "  __shared__ float lds_rr[2 * G * " << WPR << " * " << KB << "];\n  int parity = 0;\n";
     if (s.chunked) {
-      os << "  constexpr int NVLC = " << s.NVLC << ", RESV = " << s.RESV << ";\n  constexpr bool RAGC = " << (s.ragged_chunks ? "true" : "false")
+      os << "  constexpr int NVLC = " << s.NVLC << ", RESV = " << s.RESV << ";\n  constexpr int RAGC = " << (s.ragged_chunks ? 1 + over : 0)
          << ";\n";
       if (s.stage_chunks > 0 && !gp.stage_slots.empty()) {
         long bytes = 0;
@@ -844,10 +846,10 @@ struct Emitter {
     // CW columns are folded together: the whole row, or one column tile
     // (RB, the number of workgroups that fold together, only where something is folded: a kernel without column
     // reductions has the same text, hence the same compiled code, whatever the number of rows)
-    os << "  constexpr int CW = " << (ctile ? "NVL * L * V" : "C") << ", NVF = CW / V, RB = " << (K > 0 || ctile ? s.RB : 1) << ";\n";
+    os << "  constexpr int CW = " << (ctile ? "NVL * L * V" : "(C + 3) / 4 * 4") << ", RB = " << (K > 0 || ctile ? s.RB : 1) << ";\n";
     if (ctile) os << "  const int tile = (int)blockIdx.x % CT, rb = (int)blockIdx.x / CT, vbase = tile * (NVL * L);\n";
     else os << "  const int tile = 0, rb = (int)blockIdx.x;\n";
-    os << "  (void)tile; (void)rb; (void)CW; (void)NVF; (void)RB;\n";
+    os << "  (void)tile; (void)rb; (void)CW; (void)RB;\n";
     // One LDS pool, shared by lifetime: the row loop's buffers (transpose tile, staged [1,C]
     // operands) and the epilogue's column-fold area never live at the same time.
     if (K > 0 || s.tile_transpose || s.stage_rowv) {
@@ -1062,7 +1064,7 @@ struct Emitter {
       if (lx != ly) return lx < ly;
       return (int)is_rr(x) < (int)is_rr(y);
     });
-    const std::string col_ok = "(!RAGGED || ((e / V) * L + lir) < NV)";
+    const std::string col_ok = "fs_owned<V, NV, RAGGED>((e / V) * L + lir, e % V)";
     // the statements after the last exchange are emitted vector by vector (see `strip`) when the
     // lane holds several vectors and they are plain elementwise work and stores
     size_t tail_start = 0;
@@ -1206,13 +1208,13 @@ struct Emitter {
 
     // ---- epilogue: finish the column reductions ----
     if (K > 0) {
-      const int CW = ctile ? s.NVL * s.L * s.V : C;
+      const int CW = ctile ? s.NVL * s.L * s.V : (C + 3) / 4 * 4;
       const int FV = CW % 4 == 0 ? 4 : CW % 2 == 0 ? 2 : 1;
       os << "  {\n    constexpr int FV = " << FV << ";\n    typedef fs_colfold<" << K << ", CW, WG, FV> S;\n    float cv[S::CPT][FV];\n";
       for (int k = 0; k < K; ++k) {
         const int m = gp.col_reduces[k];
-        os << "    fs_colred_fold_wg<" << g.nodes[m].attr_i << ", " << k << ", " << K << ", V, NVL, L, NVF, CW, WG, FV, PC>(ca" << loc(m)
-           << ", cv, lds_col, lir, rg);\n";
+        os << "    fs_colred_fold_wg<" << g.nodes[m].attr_i << ", " << k << ", " << K << ", V, NVL, L, C, CW, WG, FV, PC>(ca" << loc(m)
+           << ", cv, lds_col, lir, rg, " << (ctile ? "vbase" : "0") << ");\n";
       }
       os << "    if (fs_colred_fold_grid<" << K << ", CW, WG, FV, " << s.fan_in << ", " << kname << "_kinds>(cv, a.part + (long)tile * "
          << s.part_stride_floats << "L, a.tickets + tile * " << s.ticket_stride << ", &lds_flag, (fs_u32)rb, (fs_u32)RB)) {\n";

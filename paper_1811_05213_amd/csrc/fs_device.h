@@ -44,6 +44,12 @@ template <> struct fs_elem<FS_DT_U8> { typedef fs_u8 type; };
 
 template <typename T, int N> struct fs_vec { typedef T type __attribute__((ext_vector_type(N))); };
 template <typename T> struct fs_vec<T, 1> { typedef T type; };
+// the same vector at an address that is only aligned to its elements (global memory takes 4-, 8- and 16-byte accesses at any
+// address: one instruction either way)
+template <typename T, int N> struct fs_vec_ua {
+  typedef typename fs_vec<T, N>::type vec;
+  typedef vec type __attribute__((aligned(alignof(T))));
+};
 
 // ------------------------------------------------------------------------------------------
 // scalar conversions
@@ -130,11 +136,22 @@ FS_DEV float fs_gelu_tanh(float z) {
 // vector memory access: V elements of dtype DT per access (16 bytes for the widest dtype of
 // the group).  Invalid rows / columns load zeros and store nothing.
 // ------------------------------------------------------------------------------------------
-template <int DT, int V, bool NT = false> FS_DEV void fs_load_vec(float* dst, const void* base, long elem_index) {
+// UA: the address is aligned to the element only.
+template <int DT, int V, bool NT = false, bool UA = false>
+FS_DEV typename fs_vec<typename fs_elem<DT>::type, V>::type fs_load_raw(const void* base, long elem_index) {
   typedef typename fs_elem<DT>::type T;
-  typedef typename fs_vec<T, V>::type VT;
-  const VT* p = reinterpret_cast<const VT*>(static_cast<const T*>(base) + elem_index);
-  const VT raw = NT ? __builtin_nontemporal_load(p) : *p;
+  if constexpr (UA) {
+    typedef typename fs_vec_ua<T, V>::type VT;
+    const VT* p = reinterpret_cast<const VT*>(static_cast<const T*>(base) + elem_index);
+    return NT ? __builtin_nontemporal_load(p) : *p;
+  } else {
+    typedef typename fs_vec<T, V>::type VT;
+    const VT* p = reinterpret_cast<const VT*>(static_cast<const T*>(base) + elem_index);
+    return NT ? __builtin_nontemporal_load(p) : *p;
+  }
+}
+template <int DT, int V, bool NT = false, bool UA = false> FS_DEV void fs_load_vec(float* dst, const void* base, long elem_index) {
+  const auto raw = fs_load_raw<DT, V, NT, UA>(base, elem_index);
   if constexpr (V == 1) {
     dst[0] = fs_to_f32<DT>(raw);
   } else {
@@ -143,7 +160,7 @@ template <int DT, int V, bool NT = false> FS_DEV void fs_load_vec(float* dst, co
   }
 }
 
-template <int DT, int V, bool NT = false> FS_DEV void fs_store_vec(const float* src, void* base, long elem_index) {
+template <int DT, int V, bool NT = false, bool UA = false> FS_DEV void fs_store_vec(const float* src, void* base, long elem_index) {
   typedef typename fs_elem<DT>::type T;
   typedef typename fs_vec<T, V>::type VT;
   VT raw;
@@ -153,26 +170,53 @@ template <int DT, int V, bool NT = false> FS_DEV void fs_store_vec(const float* 
 #pragma unroll
     for (int k = 0; k < V; ++k) raw[k] = fs_from_f32<DT>(src[k]);
   }
-  VT* p = reinterpret_cast<VT*>(static_cast<T*>(base) + elem_index);
-  if constexpr (NT) __builtin_nontemporal_store(raw, p);
-  else *p = raw;
+  if constexpr (UA) {
+    typedef typename fs_vec_ua<T, V>::type VU;
+    VU* p = reinterpret_cast<VU*>(static_cast<T*>(base) + elem_index);
+    if constexpr (NT) __builtin_nontemporal_store(raw, p);
+    else *p = raw;
+  } else {
+    VT* p = reinterpret_cast<VT*>(static_cast<T*>(base) + elem_index);
+    if constexpr (NT) __builtin_nontemporal_store(raw, p);
+    else *p = raw;
+  }
+}
+
+// Rows whose width is no multiple of V keep V-wide accesses: a row of C columns is NV = ceil(C / V) vectors, and the last one
+// covers its LAST V columns, C-V .. C-1, so its first `skip` elements repeat columns of the vector before it.  An element of a
+// lane's slice is owned when it is the one its column is counted by: reductions and column accumulators' folds take owned
+// elements only; stores write the repeated ones twice, with the same bits.  The rows then start at any multiple of the element
+// size, which global memory accesses allow: measured on 512 MB copies, 16-byte accesses run at 95 % of the aligned rate at
+// 4-byte offsets and at 92 % at 2-byte offsets, where element-wise accesses reach 82 % (4 bytes) and 42 % (2 bytes).
+// RAGGED: 0 = every vector index of the slice lies inside a row of NV whole vectors; 1 + D = indices may fall beyond the row,
+// and the last vector overlaps its neighbour by D elements (C = NV*V - D).
+constexpr int fs_overlap(int ragged) { return ragged > 0 ? ragged - 1 : 0; }
+constexpr int fs_cols(int v, int nv, int ragged) { return nv * v - fs_overlap(ragged); }
+// One expression serves both the clamp of vectors beyond the row and the overlapping last vector.
+template <int V, int C> FS_DEV int fs_vec_col(int vi) { return vi * V < C - V ? vi * V : C - V; }
+template <int V, int C> FS_DEV int fs_vec_skip(int vi) { return vi * V < C - V ? 0 : vi * V - (C - V); }
+// is element k of vector vi counted by this lane?
+template <int V, int NV, int RAGGED> FS_DEV bool fs_owned(int vi, int k) {
+  if constexpr (RAGGED == 0) return true;
+  else if constexpr (fs_overlap(RAGGED) == 0) return vi < NV;
+  else return k >= fs_vec_skip<V, fs_cols(V, NV, RAGGED)>(vi);
 }
 
 // Load the lane's slice of one row tile: vectors vbase + j*L + lir, j < NVL (vbase = 0 unless a
 // row is cut into several column tiles).  `row_elem0` is the element index of the first column
 // of a VALID row (callers clamp the row index instead of predicating the load).  NV = vectors
-// per row; RAGGED says some of those vector indices can fall beyond NV: they are clamped too.
+// per row; RAGGED (above) says some of those vector indices can fall beyond NV: they are clamped too.
 // Nothing here branches, so all loads of a body are issued back to back and waited for once;
 // lanes outside the tensor hold duplicates that are never stored and never reduced.
 // (the _vec forms handle vector j of the slice alone: a body that is emitted vector by vector
 // keeps fewer registers live)
-template <int DT, int V, int NVL, int L, int NV, bool RAGGED, bool NT = false>
+template <int DT, int V, int NVL, int L, int NV, int RAGGED, bool NT = false>
 FS_DEV void fs_load_row_vec(float (&dst)[NVL * V], const void* base, long row_elem0, int lir, int vbase, int j) {
-  int vi = vbase + j * L + lir;
-  if (RAGGED) vi = vi < NV ? vi : NV - 1;
-  fs_load_vec<DT, V, NT>(&dst[j * V], base, row_elem0 + (long)vi * V);
+  const int vi = vbase + j * L + lir;
+  const int col = RAGGED ? fs_vec_col<V, fs_cols(V, NV, RAGGED)>(vi) : vi * V;
+  fs_load_vec<DT, V, NT, fs_overlap(RAGGED) != 0>(&dst[j * V], base, row_elem0 + col);
 }
-template <int DT, int V, int NVL, int L, int NV, bool RAGGED, bool NT = false>
+template <int DT, int V, int NVL, int L, int NV, int RAGGED, bool NT = false>
 FS_DEV void fs_load_row(float (&dst)[NVL * V], const void* base, long row_elem0, int lir, int vbase) {
 #pragma unroll
   for (int j = 0; j < NVL; ++j) fs_load_row_vec<DT, V, NVL, L, NV, RAGGED, NT>(dst, base, row_elem0, lir, vbase, j);
@@ -182,7 +226,7 @@ FS_DEV void fs_load_row(float (&dst)[NVL * V], const void* base, long row_elem0,
 // b is [R,CB], the row is a's row followed by b's (SPLIT and CB are multiples of V: no vector straddles the seam).
 // AXIS 0 (rows): rows below SPLIT come from a, the others from b, both NV*V columns wide.  The source is chosen
 // by selecting the address, not by branching: every lane issues exactly one load per vector.
-template <int DT, int V, int NVL, int L, int NV, bool RAGGED, int AXIS, long SPLIT, long CB>
+template <int DT, int V, int NVL, int L, int NV, int RAGGED, int AXIS, long SPLIT, long CB>
 FS_DEV void fs_load_row_concat(float (&dst)[NVL * V], const void* a, const void* b, long row, int lir, int vbase) {
 #pragma unroll
   for (int j = 0; j < NVL; ++j) {
@@ -195,13 +239,14 @@ FS_DEV void fs_load_row_concat(float (&dst)[NVL * V], const void* a, const void*
   }
 }
 
-template <int DT, int V, int NVL, int L, int NV, bool RAGGED, bool NT = false>
+template <int DT, int V, int NVL, int L, int NV, int RAGGED, bool NT = false>
 FS_DEV void fs_store_row_vec(const float (&src)[NVL * V], void* base, long row_elem0, int lir, int vbase, bool rok, int j) {
   const int vi = vbase + j * L + lir;
   const bool ok = rok && (!RAGGED || vi < NV);
-  if (ok) fs_store_vec<DT, V, NT>(&src[j * V], base, row_elem0 + (long)vi * V);
+  const int col = fs_overlap(RAGGED) != 0 ? fs_vec_col<V, fs_cols(V, NV, RAGGED)>(vi) : vi * V;
+  if (ok) fs_store_vec<DT, V, NT, fs_overlap(RAGGED) != 0>(&src[j * V], base, row_elem0 + col);
 }
-template <int DT, int V, int NVL, int L, int NV, bool RAGGED, bool NT = false>
+template <int DT, int V, int NVL, int L, int NV, int RAGGED, bool NT = false>
 FS_DEV void fs_store_row(const float (&src)[NVL * V], void* base, long row_elem0, int lir, int vbase, bool rok) {
 #pragma unroll
   for (int j = 0; j < NVL; ++j) fs_store_row_vec<DT, V, NVL, L, NV, RAGGED, NT>(src, base, row_elem0, lir, vbase, rok, j);
@@ -217,16 +262,15 @@ template <int DT, int V, int NVL, int L> FS_DEV void fs_stage_row_chunk(void* ld
 }
 // fs_load_row and fs_stage_row_chunk in one: the vectors go to LDS as they came from memory (when `stage`), so nothing is
 // spent on converting fp32 registers back to the dtype, and what a later stage reads back is the same bytes.
-template <int DT, int V, int NVL, int L, int NV, bool RAGGED, bool NT = false>
+template <int DT, int V, int NVL, int L, int NV, int RAGGED, bool NT = false>
 FS_DEV void fs_load_row_staging(float (&dst)[NVL * V], const void* base, long row_elem0, int lir, int vbase, void* lds_chunk, bool stage) {
   typedef typename fs_elem<DT>::type T;
   typedef typename fs_vec<T, V>::type VT;
 #pragma unroll
   for (int j = 0; j < NVL; ++j) {
-    int vi = vbase + j * L + lir;
-    if (RAGGED) vi = vi < NV ? vi : NV - 1;
-    const VT* p = reinterpret_cast<const VT*>(static_cast<const T*>(base) + row_elem0 + (long)vi * V);
-    const VT raw = NT ? __builtin_nontemporal_load(p) : *p;
+    const int vi = vbase + j * L + lir;
+    const int col = RAGGED ? fs_vec_col<V, fs_cols(V, NV, RAGGED)>(vi) : vi * V;
+    const VT raw = fs_load_raw<DT, V, NT, fs_overlap(RAGGED) != 0>(base, row_elem0 + col);
     if (stage) *reinterpret_cast<VT*>(static_cast<T*>(lds_chunk) + (long)(j * L + lir) * V) = raw;
     if constexpr (V == 1) {
       dst[j] = fs_to_f32<DT>(raw);
@@ -242,16 +286,17 @@ template <int DT, int V, int NVL, int L> FS_DEV void fs_load_row_chunk_lds(float
 }
 
 // Transposing store of the lane's slice of row `row` of a [R,C] value into a [C,R] tensor.
-template <int DT, int V, int NVL, int L, int NV, bool RAGGED>
+template <int DT, int V, int NVL, int L, int NV, int RAGGED>
 FS_DEV void fs_store_row_transposed(const float (&src)[NVL * V], void* base, long R, long row, int lir, int vbase, bool rok) {
   typedef typename fs_elem<DT>::type T;
 #pragma unroll
   for (int j = 0; j < NVL; ++j) {
     const int vi = vbase + j * L + lir;
     const bool ok = rok && (!RAGGED || vi < NV);
+    const int col = RAGGED ? fs_vec_col<V, fs_cols(V, NV, RAGGED)>(vi) : vi * V;
     if (ok) {
 #pragma unroll
-      for (int k = 0; k < V; ++k) static_cast<T*>(base)[(long)(vi * V + k) * R + row] = fs_from_f32<DT>(src[j * V + k]);
+      for (int k = 0; k < V; ++k) static_cast<T*>(base)[(long)(col + k) * R + row] = fs_from_f32<DT>(src[j * V + k]);
     }
   }
 }
@@ -267,13 +312,13 @@ FS_DEV void fs_store_row_transposed(const float (&src)[NVL * V], void* base, lon
 // apart, a few KB from L2 once per workgroup.  SLOT = NVL*L*V floats per vector.
 template <int DT, int V, int L, int C, int WG> FS_DEV void fs_stage_rowvec(float* lds, const void* src) {
   if constexpr (V % 4 == 0) {
-    constexpr int Q = V / 4, NVS = C / V;  // 16-byte pieces per vector access, vectors per row
+    constexpr int Q = V / 4, NVS = (C + V - 1) / V;  // 16-byte pieces per vector access, vectors per row
     constexpr int P = ((NVS + L - 1) / L) * Q * L;  // LDS positions (16-byte pieces) of the slot, tail included
     for (int p = (int)threadIdx.x; p < P; p += WG) {
       const int l = p % L, jq = p / L, j = jq / Q, q = jq % Q, vi = j * L + l;
       if (vi >= NVS) continue;
       float tmp[4];
-      fs_load_vec<DT, 4>(tmp, src, (vi * Q + q) * 4);
+      fs_load_vec<DT, 4, false, C % V != 0>(tmp, src, fs_vec_col<V, C>(vi) + q * 4);
       typedef float f4 __attribute__((ext_vector_type(4)));
       f4 t4;
 #pragma unroll
@@ -292,14 +337,14 @@ template <int DT, int V, int L, int C, int WG> FS_DEV void fs_stage_rowvec(float
 // instead of once per element of every row.
 template <int DTA, int DTB, bool NEGA, bool NEGB, int V, int L, int C, int WG> FS_DEV void fs_stage_rowvec_sum(float* lds, const void* a, const void* b) {
   if constexpr (V % 4 == 0) {
-    constexpr int Q = V / 4, NVS = C / V;
+    constexpr int Q = V / 4, NVS = (C + V - 1) / V;
     constexpr int P = ((NVS + L - 1) / L) * Q * L;
     for (int p = (int)threadIdx.x; p < P; p += WG) {
       const int l = p % L, jq = p / L, j = jq / Q, q = jq % Q, vi = j * L + l;
       if (vi >= NVS) continue;
       float ta[4], tb[4];
-      fs_load_vec<DTA, 4>(ta, a, (vi * Q + q) * 4);
-      fs_load_vec<DTB, 4>(tb, b, (vi * Q + q) * 4);
+      fs_load_vec<DTA, 4, false, C % V != 0>(ta, a, fs_vec_col<V, C>(vi) + q * 4);
+      fs_load_vec<DTB, 4, false, C % V != 0>(tb, b, fs_vec_col<V, C>(vi) + q * 4);
       typedef float f4 __attribute__((ext_vector_type(4)));
       f4 t4;
 #pragma unroll
@@ -316,7 +361,7 @@ template <int DTA, int DTB, bool NEGA, bool NEGB, int V, int L, int C, int WG> F
   }
 }
 // The lane's slice of a staged vector (same element ownership as fs_load_row).
-template <int V, int NVL, int L, int NV, bool RAGGED>
+template <int V, int NVL, int L, int NV, int RAGGED>
 FS_DEV void fs_read_staged_vec(float (&dst)[NVL * V], const float* lds, int lir, int j) {
   if constexpr (V % 4 == 0) {
     constexpr int Q = V / 4;
@@ -331,13 +376,13 @@ FS_DEV void fs_read_staged_vec(float (&dst)[NVL * V], const float* lds, int lir,
       }
     }
   } else {
-    int vi = j * L + lir;
-    if (RAGGED) vi = vi < NV ? vi : NV - 1;
+    const int vi = j * L + lir;
+    const int col = RAGGED ? fs_vec_col<V, fs_cols(V, NV, RAGGED)>(vi) : vi * V;
 #pragma unroll
-    for (int k = 0; k < V; ++k) dst[j * V + k] = lds[vi * V + k];
+    for (int k = 0; k < V; ++k) dst[j * V + k] = lds[col + k];
   }
 }
-template <int V, int NVL, int L, int NV, bool RAGGED>
+template <int V, int NVL, int L, int NV, int RAGGED>
 FS_DEV void fs_read_staged(float (&dst)[NVL * V], const float* lds, int lir) {
 #pragma unroll
   for (int j = 0; j < NVL; ++j) fs_read_staged_vec<V, NVL, L, NV, RAGGED>(dst, lds, lir, j);
@@ -353,14 +398,19 @@ template <int DT> FS_DEV void fs_store1_fwd(void* base, long i, float x) {
 // elements instead of single elements R apart.  LDS holds TC x (G+1) floats (the +1 keeps the
 // column-wise writes of the row-groups of a wavefront on distinct banks).  vbase = col0 / V is the
 // tile's first vector in the row.  Every lane of the workgroup must call it.
-template <int DT, int V, int NVL, int L, int NV, bool RAGGED, int WG, int TC, int CTOT, bool NT = false>
+template <int DT, int V, int NVL, int L, int NV, int RAGGED, int WG, int TC, bool NT = false>
 FS_DEV void fs_store_tile_transposed(const float (&src)[NVL * V], float* lds, void* base, long R, long tile_row0, int lir, int rg, int vbase) {
-  constexpr int G = WG / L, P = G + 1;
+  constexpr int G = WG / L, P = G + 1, C = fs_cols(V, NV, RAGGED);
   __syncthreads();  // the tile may still be read by its previous use
 #pragma unroll
   for (int j = 0; j < NVL; ++j) {
     const int vi = j * L + lir;
-    if (!RAGGED || vbase + vi < NV) {
+    if constexpr (fs_overlap(RAGGED) != 0) {  // (owned elements only: the repeated ones may belong to the tile before)
+      const int skip = fs_vec_skip<V, C>(vbase + vi);
+#pragma unroll
+      for (int k = 0; k < V; ++k)
+        if (k >= skip) lds[(vi * V + k - skip) * P + rg] = src[j * V + k];
+    } else if (!RAGGED || vbase + vi < NV) {
 #pragma unroll
       for (int k = 0; k < V; ++k) lds[(vi * V + k) * P + rg] = src[j * V + k];
     }
@@ -370,18 +420,17 @@ FS_DEV void fs_store_tile_transposed(const float (&src)[NVL * V], float* lds, vo
   constexpr int WANT = 16 / (int)sizeof(typename fs_elem<DT>::type);
   constexpr int RUN = (G % WANT == 0) ? WANT : (G % 4 == 0) ? 4 : 1;
   constexpr int RPC = G / RUN;  // runs per output row
-  const bool vec_ok = RUN > 1 && (R % RUN) == 0;
   const int col0 = vbase * V;
   for (int i = (int)threadIdx.x; i < TC * RPC; i += WG) {
     const int c = i / RPC, g0 = (i % RPC) * RUN;
     const long r = tile_row0 + g0;
-    if (col0 + c >= CTOT) continue;
+    if (col0 + c >= C) continue;
     float tmp[RUN];
 #pragma unroll
     for (int q = 0; q < RUN; ++q) tmp[q] = lds[c * P + g0 + q];
     const long o = (long)(col0 + c) * R + r;
-    if (RUN > 1 && vec_ok && r + RUN - 1 < R) {
-      fs_store_vec<DT, RUN, NT>(tmp, base, o);
+    if (RUN > 1 && r + RUN - 1 < R) {  // (runs start at any multiple of the element size when R is no multiple of RUN)
+      fs_store_vec<DT, RUN, NT, true>(tmp, base, o);
     } else {
 #pragma unroll
       for (int q = 0; q < RUN; ++q)
@@ -408,14 +457,14 @@ template <int KIND> FS_DEV float fs_red_op(float a, float b) {
 }
 
 // Serial reduction of the lane's own E elements (masked columns contribute the identity).
-template <int KIND, int V, int NVL, int L, int NV, bool RAGGED>
+template <int KIND, int V, int NVL, int L, int NV, int RAGGED>
 FS_DEV float fs_lane_reduce(const float (&v)[NVL * V], int lir, int vbase = 0) {
   float acc = fs_red_identity<KIND>();
 #pragma unroll
   for (int j = 0; j < NVL; ++j) {
-    const bool ok = !RAGGED || (vbase + j * L + lir) < NV;
+    const int vi = vbase + j * L + lir;
 #pragma unroll
-    for (int k = 0; k < V; ++k) acc = fs_red_op<KIND>(acc, ok ? v[j * V + k] : fs_red_identity<KIND>());
+    for (int k = 0; k < V; ++k) acc = fs_red_op<KIND>(acc, fs_owned<V, NV, RAGGED>(vi, k) ? v[j * V + k] : fs_red_identity<KIND>());
   }
   return acc;
 }
@@ -559,8 +608,10 @@ FS_DEV float fs_shfl_xor(float v, int mask) {
 // l+L, l+2L, ... own the same columns), so the LDS area holds one row per wavefront (GL = WG/64
 // rows), not one per row-group.  The C columns go through the area PC columns at a time (PC a
 // multiple of 8, or C itself): wide rows need no more LDS than narrow ones, only more barriers.
-template <int KIND, int KIDX, int K, int V, int NVL, int L, int NV, int C, int WG, int FV, int PC, int CPT>
-FS_DEV void fs_colred_fold_wg(const float (&acc_in)[NVL * V], float (&vals)[CPT][FV], float* lds /* GL*PC floats */, int lir, int rg) {
+// CT columns are in the row, C in the fold (one column tile, or the row rounded up to whole 16-byte chunks: what no element
+// owns is never written to LDS, folds to garbage and is not stored).
+template <int KIND, int KIDX, int K, int V, int NVL, int L, int CT, int C, int WG, int FV, int PC, int CPT>
+FS_DEV void fs_colred_fold_wg(const float (&acc_in)[NVL * V], float (&vals)[CPT][FV], float* lds /* GL*PC floats */, int lir, int rg, int vbase) {
   typedef fs_colfold<K, C, WG, FV> S;
   static_assert(CPT == S::CPT, "chunks per thread");
   static_assert(PC == C || PC % 8 == 0, "piece width");
@@ -588,7 +639,12 @@ FS_DEV void fs_colred_fold_wg(const float (&acc_in)[NVL * V], float (&vals)[CPT]
 #pragma unroll
       for (int j = 0; j < NVL; ++j) {
         const int vi = j * L + lir;
-        if (vi < NV) {
+        if constexpr (CT % V != 0) {
+          const int skip = fs_vec_skip<V, CT>(vbase + vi);
+#pragma unroll
+          for (int k = 0; k < V; ++k)
+            if (k >= skip) lds[slot * C + vi * V + k - skip] = acc[j * V + k];
+        } else if (vbase + vi < CT / V) {
 #pragma unroll
           for (int k = 0; k < V; ++k) lds[slot * C + vi * V + k] = acc[j * V + k];
         }
@@ -615,10 +671,18 @@ FS_DEV void fs_colred_fold_wg(const float (&acc_in)[NVL * V], float (&vals)[CPT]
     if (writer) {
 #pragma unroll
       for (int j = 0; j < NVL; ++j) {
-        const int vi = j * L + lir, col = vi * V - p0;
-        if (vi < NV && col >= 0 && col < PC) {
+        const int vi = j * L + lir;
+        if constexpr (CT % V != 0) {
+          const int skip = fs_vec_skip<V, CT>(vbase + vi), col = vi * V - skip - p0;
 #pragma unroll
-          for (int k = 0; k < V; ++k) lds[slot * PC + col + k] = acc[j * V + k];
+          for (int k = 0; k < V; ++k)
+            if (k >= skip && col + k >= 0 && col + k < PC) lds[slot * PC + col + k] = acc[j * V + k];
+        } else {
+          const int col = vi * V - p0;
+          if (vbase + vi < CT / V && col >= 0 && col < PC) {
+#pragma unroll
+            for (int k = 0; k < V; ++k) lds[slot * PC + col + k] = acc[j * V + k];
+          }
         }
       }
     }

@@ -148,15 +148,21 @@ struct Scheduler {
       if (e.kind == KIND_FULL) max_es = std::max(max_es, dtype_size(e.dtype));
     if (max_es == 0) max_es = 4;
     V = 16 / max_es;
-    while (C % V) V /= 2;
     has_concat = false;
+    for (int m : gp->members) has_concat |= g.nodes[m].opcode == FS_CONCAT;
+    // A width that V does not divide keeps 16-byte accesses: the last vector of a row overlaps the one before it (fs_vec_col).
+    // Rows of at most 32 bytes belong to one lane each and are read element by element or in the vectors that fit.  A vector
+    // access must not straddle the seam of a concat, so there V divides the widths; so it does in column folds of tensors below
+    // 16 MB, which are bound by latency (columns sums of [1133,1730] f32: 5 % slower with overlapping vectors).
+    const bool small_fold = !gp->col_reduces.empty() && (int64_t)R * C * max_es < (16 << 20);
+    // (and so it does where whole narrow rows leave transposed, in runs of a few elements: [65536,139] bf16 24.7 -> 29.3 us)
+    bool narrow_transposed = false;
+    for (const ExtTensor& e : gp->ext_out) narrow_transposed |= e.transposed && C <= 256;
+    while (has_concat || small_fold || narrow_transposed || C * max_es <= 32 ? C % V != 0 : V > C) V /= 2;
     for (int m : gp->members)
-      if (g.nodes[m].opcode == FS_CONCAT) {
-        has_concat = true;
-        if (g.nodes[m].attr_i == FS_CONCAT_COLS)  // a vector access must not straddle the seam
-          while (g.nodes[g.nodes[m].in[0]].cols % V) V /= 2;
-      }
-    NV = C / V;
+      if (g.nodes[m].opcode == FS_CONCAT && g.nodes[m].attr_i == FS_CONCAT_COLS)
+        while (g.nodes[g.nodes[m].in[0]].cols % V) V /= 2;
+    NV = (C + V - 1) / V;
     rowred = !gp->row_reduces.empty();
     colred = !gp->col_reduces.empty();
     return FS_OK;
@@ -252,11 +258,21 @@ struct Scheduler {
     // wavefront (32 lanes x 3: LayerNorm+GeLU bf16 [32768,768] 24.0 -> 20.9 us).
     // Below a quarter of the slots empty it does not pay (softmax fp32 [32768,640]: 27.7 us on 64 lanes
     // x 3 vectors with 17 % empty, 29.4 us on 32 x 5).
+    // How many vectors a lane may take for it: a wavefront's access then covers runs of l x 16 bytes, and what is left of a
+    // cache line is fetched again for the lane's next vector.  Two for short runs, three from 512 bytes on, or from 256 bytes on
+    // where a vector holds 8 elements and empty slots cost more arithmetic (masked softmax bf16 [22727,264]: 16 x 3 9.4 us, 32 x 2
+    // 10.8 us; softmax fp32 [35714,168]: 10.9 against 9.9 us)
+    // (softmax fp32 [500000,37], 10 vectors: 2 lanes x 5 122 us, 4 x 3 62 us, 8 x 2 30 us, 16 x 1 31 us; [400000,65]: 4 x 5
+    // 107 us, 16 x 2 38 us, 32 x 1 49 us; [200000,161]: 16 x 3 54 us, 32 x 2 45 us; masked softmax bf16 [32768,577]: 32 x 3
+    // 22.5 us, 64 x 2 25.7 us).  Runs of whole cache lines (rows of a multiple of 128 bytes, 8 lanes or more) have no such
+    // remainder: there the fewest empty slots win (masked softmax bf16 [32768,320]: 16 x 3 12.7 us, 32 x 2 14.9 us).
     if (rowred && !colred && L > l_min && l_min >= 1) {
       const auto waste = [&](int lanes) { return (int64_t)((NV + lanes - 1) / lanes) * lanes - NV; };
       if (waste(L) * 4 >= NV + waste(L))
-        for (int l = L; l >= l_min; l /= 2)
-          if (waste(l) < waste(L)) L = l;
+        for (int l = L / 2; l >= std::max(l_min, 4); l /= 2) {
+          const bool whole_lines = (int64_t)C * max_es % 128 == 0 && l >= 8;
+          if (whole_lines ? waste(l) < waste(L) : (NV + l - 1) / l <= (l >= 32 || (l >= 16 && V >= 8) ? 3 : 2) && waste(l) <= waste(L)) L = l;
+        }
     }
     if (rowred && !colred && C * max_es <= 32) L = 1;
     else if (rowred && !colred && V == 1 && NV >= 4) L = std::min(L, pow2_ceil(NV) / 2);
@@ -404,11 +420,11 @@ struct Scheduler {
     s.E = s.NVL * V;
     s.WG = WG;
     s.G = WG / L;
-    s.ragged = resident ? false : (int64_t)CT * NVL * L != NV;
+    s.ragged = C % V != 0 || (!resident && (int64_t)CT * NVL * L != NV);
     s.resident = resident;
     s.NVLC = NVLC;
     s.RESV = RESV;
-    s.ragged_chunks = chunked && (int64_t)RESV + (int64_t)CT * NVLC * L != NV;
+    s.ragged_chunks = chunked && ((int64_t)RESV + (int64_t)CT * NVLC * L != NV || C % V != 0);
     s.chunked = chunked;
     s.col_tiled = col_tiled;
     s.tiled_transpose = tiled_transpose;
@@ -507,7 +523,7 @@ struct Scheduler {
     int fixed = 0, loop_bytes = 0, fold_bytes = 0;
     if (rowred && L > 64) fixed += 2 * s.G * (L / 64) * gp->max_batched_reduces * 4;
     if (split_rows) fixed += 16 + (int)gp->row_reduces.size() * 4;
-    fold_width = col_tiled ? NVL * L * V : C;  // columns one workgroup folds
+    fold_width = col_tiled ? NVL * L * V : (C + 3) / 4 * 4;  // columns one workgroup folds (whole 16-byte chunks)
     s.fold_piece = fold_width;
     if (colred) {
       // the fold area takes at most half of the budget: wide rows pass through it in pieces
@@ -793,6 +809,12 @@ fs_status analyse_group(const Graph& g, const std::vector<int>& members, const s
   for (const ExtTensor& e : gp.ext_out) gp.min_hbm_bytes += (uint64_t)g.nodes[e.node].rows * g.nodes[e.node].cols * dtype_size(e.dtype);
 
   const fs_status st = choose_schedule(g, opt, &gp);
+  // Rows that are no multiple of a vector long share cache lines with their neighbours, which other wavefronts read: ordinary
+  // loads there.  LayerNorm+GeLU bf16 [30001,1021]: 24.5 -> 22.1 us right after the kernel that wrote the input (28.3 -> 28.7 us
+  // from cold memory); masked softmax bf16 [32768,577] 22.5 -> 20.4 us (22.5 -> 22.8 us).  Not for groups that only stream
+  // (no difference) or fold columns ([60001,515]: 33.3 -> 35.5 us).
+  if (st == FS_OK && gp.C % gp.s.V != 0 && !gp.row_reduces.empty() && gp.col_reduces.empty())
+    for (ExtTensor& e : gp.ext_in) e.streaming = false;
   if (st == FS_OK && gp.s.chunked)  // every stage reads the row again: keep it in the caches
     for (ExtTensor& e : gp.ext_in) e.streaming = false;
   return st;

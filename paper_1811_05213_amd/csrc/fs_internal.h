@@ -103,7 +103,7 @@ struct ExtTensor {
 
 struct Schedule {
   int V = 4;        // elements per vector access
-  int NV = 0;       // vectors per row = C / V
+  int NV = 0;       // vectors per row = ceil(C / V): the last one overlaps its neighbour when V does not divide C
   int L = 64;       // lanes per row (power of two)
   int NVL = 1;      // vectors per lane = ceil(NV / L)
   int E = 4;        // elements per lane = NVL * V
@@ -113,7 +113,7 @@ struct Schedule {
   int CT = 1;       // column tiles per row (> 1 only for groups without reductions: very long rows)
   int n_iters = 0;  // ceil(R * CT / G): loop trips over the whole grid
   int grid = 0;     // workgroups (`blocks` of Section 4.1)
-  bool ragged = false;  // some lane's vector index can fall beyond NV
+  bool ragged = false;  // some lane's vector index can fall beyond NV, or on an overlapping last vector
   int lds_bytes = 0;    // static LDS of the generated kernel
   int lds_planned = 0;  // ... as planned before code generation (an upper bound of lds_bytes)
   int fan_in = 32;  // column-reduction tree fan-in

@@ -65,9 +65,9 @@ __global__ void __launch_bounds__(256) fs_device_selftest_kernel(const void* in,
     const long row = (long)it * G + rg;
     const bool rok = row < R;
     float v[E];
-    fs_load_row<FS_DT_BF16, V, NVL, L, NV, true>(v, in, (rok ? row : 0) * C, lir, 0);
-    float q = fs_segment_allreduce<FS_K_SUM, 64>(fs_lane_reduce<FS_K_SUM, V, NVL, L, NV, true>(v, lir));
-    float m = fs_segment_allreduce<FS_K_MAX, 64>(fs_lane_reduce<FS_K_MAX, V, NVL, L, NV, true>(v, lir));
+    fs_load_row<FS_DT_BF16, V, NVL, L, NV, 1>(v, in, (rok ? row : 0) * C, lir, 0);
+    float q = fs_segment_allreduce<FS_K_SUM, 64>(fs_lane_reduce<FS_K_SUM, V, NVL, L, NV, 1>(v, lir));
+    float m = fs_segment_allreduce<FS_K_MAX, 64>(fs_lane_reduce<FS_K_MAX, V, NVL, L, NV, 1>(v, lir));
     const fs_xwave<2, 2> xw{lds_rr + (parity * G + rg) * 4, lir >> 6, (tid & 63) == 0};
     xw.put(0, q);
     xw.put(1, m);
@@ -80,14 +80,14 @@ __global__ void __launch_bounds__(256) fs_device_selftest_kernel(const void* in,
       ca[e] = rok ? ca[e] + v[e] : ca[e];
       cb[e] = rok ? fs_max(cb[e], v[e]) : cb[e];
     }
-    fs_store_row<FS_DT_BF16, V, NVL, L, NV, true>(v, out, row * C, lir, 0, rok);
-    fs_store_row_transposed<FS_DT_F32, V, NVL, L, NV, true>(v, out, R, row, lir, 0, rok);
+    fs_store_row<FS_DT_BF16, V, NVL, L, NV, 1>(v, out, row * C, lir, 0, rok);
+    fs_store_row_transposed<FS_DT_F32, V, NVL, L, NV, 1>(v, out, R, row, lir, 0, rok);
   }
   constexpr int FV = 4;
   typedef fs_colfold<2, C, WG, FV> S;
   float cv[S::CPT][FV];
-  fs_colred_fold_wg<FS_K_SUM, 0, 2, V, NVL, L, NV, C, WG, FV, C>(ca, cv, lds_col, lir, rg);
-  fs_colred_fold_wg<FS_K_MAX, 1, 2, V, NVL, L, NV, C, WG, FV, C>(cb, cv, lds_col, lir, rg);
+  fs_colred_fold_wg<FS_K_SUM, 0, 2, V, NVL, L, C, C, WG, FV, C>(ca, cv, lds_col, lir, rg, 0);
+  fs_colred_fold_wg<FS_K_MAX, 1, 2, V, NVL, L, C, C, WG, FV, C>(cb, cv, lds_col, lir, rg, 0);
   if (fs_colred_fold_grid<2, C, WG, FV, 32, fs_selftest_kinds>(cv, part, tickets, &flag, blockIdx.x, gridDim.x))
     for (int i = 0; i < S::CPT; ++i)
       if (tid + i * WG < S::NCH) fs_store1<FS_DT_F32>(out, (tid + i * WG) * FV, cv[i][0] + cv[i][3]);

@@ -959,6 +959,29 @@ def test_random_graph_sweep_with_views_and_concats(first):
         _random_graph_case(seed, rows, cols, 25 if rows * cols > 2_000_000 else 35, views=True)
 
 
+@pytest.mark.parametrize("rows,cols", [(5, 9), (130, 33), (77, 513), (260, 1025), (33, 2051), (9, 8195), (300, 1022)])
+def test_rows_whose_last_vector_overlaps_its_neighbour(rows, cols):
+    # widths that a 16-byte vector does not divide: reductions in both directions, broadcasts of [1,C] and [R,1] tensors, a u8
+    # output and a transposed output, in fp32 and bf16; one column past a multiple of a vector, of a wavefront's or a workgroup's share
+    from workloads import patterns
+    for dt in ("f32", "bf16"):
+        g = Graph()
+        x, v, w = g.input(rows, cols, dt), g.input(1, cols), g.input(rows, 1)
+        xf = g.unary("convert", x, "f32") if dt == "bf16" else x
+        y = g.binary("mul", g.binary("add", xf, g.bcast_rowvec(v, rows)), g.bcast_colvec(w, cols))
+        p = g.cmp("gt", xf, g.bcast_rowvec(v, rows))
+        g.set_outputs([g.unary("convert", y, dt) if dt == "bf16" else g.unary("neg", y), p, g.reduce_col("sum", xf), g.reduce_col("max", y),
+                       g.reduce_row("min", y), g.reduce_row("sum", g.binary("mul", xf, xf))])
+        xs = RNG.standard_normal((rows, cols)).astype(np.float32)
+        ins = [f32_to_bf16_bits(xs) if dt == "bf16" else xs, RNG.standard_normal((1, cols)).astype(np.float32),
+               RNG.standard_normal((rows, 1)).astype(np.float32)]
+        both_modes(g, ins, f"overlapping last vector {dt} {rows}x{cols}")
+        both_modes(patterns.transpose(rows, cols, dt), ins[:1], f"transpose {dt} {rows}x{cols}")
+    plan = fs.Plan(softmax_graph(rows, cols))
+    assert plan.group_info(0)["vec_elems"] == 4
+    plan.destroy()
+
+
 def test_gpu_matches_the_stored_small_cases():
     # the tiny hand-checkable cases of tests/golden/oracle_small_cases.json (written by the oracle alone), on the GPU
     import json
