@@ -932,8 +932,10 @@ struct Emitter {
     // names of a single tile: such bodies take one tile per trip)
     bool rowv_member_in_loop = false;
     for (int m : gp.members) rowv_member_in_loop |= rowv_in_loop && gp.level.at(m) < 0;
-    const int U = ((rowv_in_loop && !stage_before_loop) || s.CT > 1 || ctile || rowv_member_in_loop) ? 1 : std::max(1, s.U);
-    if (ctile) {
+    const int U = ((rowv_in_loop && !stage_before_loop) || (s.CT > 1 && !s.narrow_tiles) || (ctile && !s.narrow_tiles) || rowv_member_in_loop) ? 1 : std::max(1, s.U);
+    if (ctile && U > 1) {
+      os << "  for (int it0 = rb * " << U << "; it0 < a.n_iters; it0 += RB * " << U << ") {\n";
+    } else if (ctile) {
       os << "  for (int it = rb; it < a.n_iters; it += RB) {\n";
     } else if (U == 1) {
       os << "  for (int it = (int)blockIdx.x; it < a.n_iters; it += (int)gridDim.x) {\n";
@@ -944,7 +946,8 @@ struct Emitter {
       const std::string x = U == 1 ? "" : "_" + std::to_string(u);
       if (U > 1) os << "    const int it" << x << " = it0 + " << u << ";\n";
       if (ctile) {
-        os << "    const long row = (long)it * G + rg;\n";
+        os << "    const long row" << x << " = (long)it" << x << " * G + rg;\n";
+        if (U > 1) os << "    const int vbase" << x << " = vbase;\n";
       } else if (s.tiled_transpose) {
         // 2-D tiles: consecutive workgroups take consecutive column tiles of the same G rows
         if (s.tt_col_band > 0) {
@@ -1081,7 +1084,7 @@ struct Emitter {
       if (U > 1) {
         const std::string x = "_" + std::to_string(u);
         os << "    {\n    const long row = row" << x << "; const bool rok = rok" << x << "; const long row0 = row0" << x
-           << "; constexpr int vbase = 0; (void)row; (void)rok; (void)row0; (void)vbase;\n";
+           << "; (void)row; (void)rok; (void)row0;" << (ctile ? "" : " constexpr int vbase = 0; (void)vbase;") << "\n";
         for (const ExtTensor& e : gp.ext_in) {
           if (e.kind == KIND_FULL) os << "    float (&" << name(e.node, KIND_FULL) << ")[E] = " << name(e.node, KIND_FULL) << x << ";\n";
           else if (e.kind == KIND_COLV) os << "    const float " << name(e.node, KIND_COLV) << " = " << name(e.node, KIND_COLV) << x << ";\n";

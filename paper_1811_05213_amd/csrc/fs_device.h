@@ -195,6 +195,12 @@ constexpr int fs_cols(int v, int nv, int ragged) { return nv * v - fs_overlap(ra
 // One expression serves both the clamp of vectors beyond the row and the overlapping last vector.
 template <int V, int C> FS_DEV int fs_vec_col(int vi) { return vi * V < C - V ? vi * V : C - V; }
 template <int V, int C> FS_DEV int fs_vec_skip(int vi) { return vi * V < C - V ? 0 : vi * V - (C - V); }
+// column of vector vi, clamped into the row
+template <int V, int NV, int RAGGED> FS_DEV long fs_col_of(int vi) {
+  if constexpr (fs_overlap(RAGGED) != 0) return fs_vec_col<V, fs_cols(V, NV, RAGGED)>(vi);
+  if (RAGGED) vi = vi < NV ? vi : NV - 1;
+  return (long)vi * V;
+}
 // is element k of vector vi counted by this lane?
 template <int V, int NV, int RAGGED> FS_DEV bool fs_owned(int vi, int k) {
   if constexpr (RAGGED == 0) return true;
@@ -212,9 +218,7 @@ template <int V, int NV, int RAGGED> FS_DEV bool fs_owned(int vi, int k) {
 // keeps fewer registers live)
 template <int DT, int V, int NVL, int L, int NV, int RAGGED, bool NT = false>
 FS_DEV void fs_load_row_vec(float (&dst)[NVL * V], const void* base, long row_elem0, int lir, int vbase, int j) {
-  const int vi = vbase + j * L + lir;
-  const int col = RAGGED ? fs_vec_col<V, fs_cols(V, NV, RAGGED)>(vi) : vi * V;
-  fs_load_vec<DT, V, NT, fs_overlap(RAGGED) != 0>(&dst[j * V], base, row_elem0 + col);
+  fs_load_vec<DT, V, NT, fs_overlap(RAGGED) != 0>(&dst[j * V], base, row_elem0 + fs_col_of<V, NV, RAGGED>(vbase + j * L + lir));
 }
 template <int DT, int V, int NVL, int L, int NV, int RAGGED, bool NT = false>
 FS_DEV void fs_load_row(float (&dst)[NVL * V], const void* base, long row_elem0, int lir, int vbase) {
@@ -243,8 +247,7 @@ template <int DT, int V, int NVL, int L, int NV, int RAGGED, bool NT = false>
 FS_DEV void fs_store_row_vec(const float (&src)[NVL * V], void* base, long row_elem0, int lir, int vbase, bool rok, int j) {
   const int vi = vbase + j * L + lir;
   const bool ok = rok && (!RAGGED || vi < NV);
-  const int col = fs_overlap(RAGGED) != 0 ? fs_vec_col<V, fs_cols(V, NV, RAGGED)>(vi) : vi * V;
-  if (ok) fs_store_vec<DT, V, NT, fs_overlap(RAGGED) != 0>(&src[j * V], base, row_elem0 + col);
+  if (ok) fs_store_vec<DT, V, NT, fs_overlap(RAGGED) != 0>(&src[j * V], base, row_elem0 + (fs_overlap(RAGGED) != 0 ? fs_col_of<V, NV, RAGGED>(vi) : (long)vi * V));
 }
 template <int DT, int V, int NVL, int L, int NV, int RAGGED, bool NT = false>
 FS_DEV void fs_store_row(const float (&src)[NVL * V], void* base, long row_elem0, int lir, int vbase, bool rok) {
@@ -268,9 +271,7 @@ FS_DEV void fs_load_row_staging(float (&dst)[NVL * V], const void* base, long ro
   typedef typename fs_vec<T, V>::type VT;
 #pragma unroll
   for (int j = 0; j < NVL; ++j) {
-    const int vi = vbase + j * L + lir;
-    const int col = RAGGED ? fs_vec_col<V, fs_cols(V, NV, RAGGED)>(vi) : vi * V;
-    const VT raw = fs_load_raw<DT, V, NT, fs_overlap(RAGGED) != 0>(base, row_elem0 + col);
+    const VT raw = fs_load_raw<DT, V, NT, fs_overlap(RAGGED) != 0>(base, row_elem0 + fs_col_of<V, NV, RAGGED>(vbase + j * L + lir));
     if (stage) *reinterpret_cast<VT*>(static_cast<T*>(lds_chunk) + (long)(j * L + lir) * V) = raw;
     if constexpr (V == 1) {
       dst[j] = fs_to_f32<DT>(raw);
@@ -293,7 +294,7 @@ FS_DEV void fs_store_row_transposed(const float (&src)[NVL * V], void* base, lon
   for (int j = 0; j < NVL; ++j) {
     const int vi = vbase + j * L + lir;
     const bool ok = rok && (!RAGGED || vi < NV);
-    const int col = RAGGED ? fs_vec_col<V, fs_cols(V, NV, RAGGED)>(vi) : vi * V;
+    const int col = (int)fs_col_of<V, NV, RAGGED>(vi);
     if (ok) {
 #pragma unroll
       for (int k = 0; k < V; ++k) static_cast<T*>(base)[(long)(col + k) * R + row] = fs_from_f32<DT>(src[j * V + k]);
@@ -608,8 +609,8 @@ FS_DEV float fs_shfl_xor(float v, int mask) {
 // l+L, l+2L, ... own the same columns), so the LDS area holds one row per wavefront (GL = WG/64
 // rows), not one per row-group.  The C columns go through the area PC columns at a time (PC a
 // multiple of 8, or C itself): wide rows need no more LDS than narrow ones, only more barriers.
-// CT columns are in the row, C in the fold (one column tile, or the row rounded up to whole 16-byte chunks: what no element
-// owns is never written to LDS, folds to garbage and is not stored).
+// CT columns are in the row, C in the fold (one column tile, or the row rounded up to whole 16-byte chunks: columns beyond the
+// row hold repeated or unwritten values, which fold to something that is not stored).
 template <int KIND, int KIDX, int K, int V, int NVL, int L, int CT, int C, int WG, int FV, int PC, int CPT>
 FS_DEV void fs_colred_fold_wg(const float (&acc_in)[NVL * V], float (&vals)[CPT][FV], float* lds /* GL*PC floats */, int lir, int rg, int vbase) {
   typedef fs_colfold<K, C, WG, FV> S;
@@ -644,7 +645,7 @@ FS_DEV void fs_colred_fold_wg(const float (&acc_in)[NVL * V], float (&vals)[CPT]
 #pragma unroll
           for (int k = 0; k < V; ++k)
             if (k >= skip) lds[slot * C + vi * V + k - skip] = acc[j * V + k];
-        } else if (vbase + vi < CT / V) {
+        } else if (vi < C / V) {
 #pragma unroll
           for (int k = 0; k < V; ++k) lds[slot * C + vi * V + k] = acc[j * V + k];
         }
@@ -679,7 +680,7 @@ FS_DEV void fs_colred_fold_wg(const float (&acc_in)[NVL * V], float (&vals)[CPT]
             if (k >= skip && col + k >= 0 && col + k < PC) lds[slot * PC + col + k] = acc[j * V + k];
         } else {
           const int col = vi * V - p0;
-          if (vbase + vi < CT / V && col >= 0 && col < PC) {
+          if (vi < C / V && col >= 0 && col < PC) {
 #pragma unroll
             for (int k = 0; k < V; ++k) lds[slot * PC + col + k] = acc[j * V + k];
           }

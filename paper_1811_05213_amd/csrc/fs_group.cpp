@@ -119,7 +119,7 @@ struct Scheduler {
   bool has_concat = false, rowred = false, colred = false, has_transposed = false, tileable = false;
   // the form its rows take
   int ecap = 8, l_min = 1, l_max = 1;
-  bool few_long_rows = false, split_rows = false, resident = false, chunked = false, col_tiled = false, tiled_transpose = false;
+  bool few_long_rows = false, split_rows = false, resident = false, chunked = false, col_tiled = false, narrow_tiles = false, tiled_transpose = false;
   // lanes, vectors, workgroup
   int L = 64, tt_rows = 64, NVL = 1, CT = 1, NVLC = 0, RESV = 0, WG = 256;
   bool staged_loop = false;
@@ -152,13 +152,11 @@ struct Scheduler {
     for (int m : gp->members) has_concat |= g.nodes[m].opcode == FS_CONCAT;
     // A width that V does not divide keeps 16-byte accesses: the last vector of a row overlaps the one before it (fs_vec_col).
     // Rows of at most 32 bytes belong to one lane each and are read element by element or in the vectors that fit.  A vector
-    // access must not straddle the seam of a concat, so there V divides the widths; so it does in column folds of tensors below
-    // 16 MB, which are bound by latency (columns sums of [1133,1730] f32: 5 % slower with overlapping vectors).
-    const bool small_fold = !gp->col_reduces.empty() && (int64_t)R * C * max_es < (16 << 20);
-    // (and so it does where whole narrow rows leave transposed, in runs of a few elements: [65536,139] bf16 24.7 -> 29.3 us)
+    // access must not straddle the seam of a concat, so there V divides the widths
+    // (as it does where whole narrow rows leave transposed, in runs of a few elements: [65536,139] bf16 24.7 -> 29.3 us)
     bool narrow_transposed = false;
     for (const ExtTensor& e : gp->ext_out) narrow_transposed |= e.transposed && C <= 256;
-    while (has_concat || small_fold || narrow_transposed || C * max_es <= 32 ? C % V != 0 : V > C) V /= 2;
+    while (has_concat || narrow_transposed || C * max_es <= 32 ? C % V != 0 : V > C) V /= 2;
     for (int m : gp->members)
       if (g.nodes[m].opcode == FS_CONCAT && g.nodes[m].attr_i == FS_CONCAT_COLS)
         while (g.nodes[g.nodes[m].in[0]].cols % V) V /= 2;
@@ -233,6 +231,14 @@ struct Scheduler {
     // arrivers of the grid fold read 16 x C floats each.  Column sums of f32: [8192,8192] 58 -> 78 % of peak,
     // [16384,4096] 65 -> 69 %, [4096,16384] 71 -> 78 % (tiles of 256 lanes before), narrower rows unchanged.
     col_tiled = colred && !rowred && !has_transposed && (l_min > 1024 || (l_min > 64 && !has_concat));
+    // Folds of less than 16 MB are bound by latency, above all by the grid-wide fold (~4 us of a 7 us kernel).  Tiles of one
+    // 128-byte run let one workgroup, or up to 16 that fold in one level, walk all rows of its columns, and the columns of a
+    // tensor fold side by side; several column reductions, and what feeds them, then share a kernel however small it is
+    // (worth_fusing).  Whole plans, 256 workgroups and two fold levels -> narrow tiles: column sums + row norms f32 [4765,147]
+    // 17.3 -> 8.5 us, [127,1088] 13.4 -> 6.5 us; batch normalisation [1764,512] 21.8 -> 13.6 us, [352,5824] 25.4 -> 11.9 us;
+    // LayerNorm backward [318,1145] 17.0 -> 9.7 us.  From 16 MB on the wide tiles stream better ([65536,1024]).
+    narrow_tiles = colred && !rowred && !has_transposed && !has_concat && R > 1 && (int64_t)R * C * max_es < (16 << 20);
+    col_tiled |= narrow_tiles;
     if (l_min > 1024 && !tileable && !chunked && !col_tiled)
       FS_FAIL(FS_ERR_UNSUPPORTED, "rows of %d columns are too long for one workgroup in a group with %s", C,
               colred ? "row and column reductions" : "transposed outputs");
@@ -243,7 +249,7 @@ struct Scheduler {
     tiled_transpose = has_transposed && tileable && C > 256 && R > 1;
     if (split_rows) l_min = 256;
     else if (chunked) l_min = 1024;  // (measured: the largest workgroup keeps the fewest rows in flight, so re-reads hit the caches more often)
-    if (col_tiled) l_min = std::min(64, l_max);
+    if (col_tiled) l_min = std::min(narrow_tiles ? (R > 16384 ? 16 : 8) : 64, l_max);
     return FS_OK;
   }
 
@@ -333,6 +339,7 @@ struct Scheduler {
       // column tiles: 64 bytes of the narrowest input per lane and trip (bf16: 32 elements), not beyond the row
       // (bf16 column sums of [16384,4096]: 30.5 -> 26.7 us); 32 accumulators per column reduction at most
       if (col_tiled && gp->col_reduces.size() <= 2) NVLC = std::max(1, std::min(std::min(4, 32 / V), (NV + L - 1) / L));
+      if (narrow_tiles) NVLC = 1;
       NVL = resident ? std::max(1, (opt.wide_level >= 2 ? 48 : 32) / V) : NVLC;  // (64 resident elements plus a chunk in flight spill)
       RESV = resident ? NVL * L : 0;
       CT = (NV - RESV + NVLC * L - 1) / (NVLC * L);
@@ -343,7 +350,9 @@ struct Scheduler {
   // workgroup size; whether workgroups loop with their [1,C] operands staged once
   fs_status pick_workgroup() {
     const int64_t total_waves = std::max<int64_t>(1, (int64_t)R * CT * L / 64);
-    if (col_tiled) {
+    if (narrow_tiles) {
+      WG = std::max(64, std::min(1024, L * pow2_ceil(R)));
+    } else if (col_tiled) {
       WG = std::max(64, L);
       for (int w = 512; w >= 128; w /= 2)
         if (w >= L && (int64_t)R * L / w >= 8) {
@@ -427,6 +436,7 @@ struct Scheduler {
     s.ragged_chunks = chunked && ((int64_t)RESV + (int64_t)CT * NVLC * L != NV || C % V != 0);
     s.chunked = chunked;
     s.col_tiled = col_tiled;
+    s.narrow_tiles = narrow_tiles;
     s.tiled_transpose = tiled_transpose;
     // Bands whose rows are 4 KB runs of the narrowest input (8 tiles of f32, 16 of bf16), twice that when the tensor has
     // so few row tiles that a band would not fill the device.  Against plain order, f32: [8192,8192] 60 -> 75 % of peak,
@@ -496,17 +506,27 @@ struct Scheduler {
     }
     if (col_tiled) {  // RB workgroups per column tile, about `cap` workgroups in all
       s.RB = std::max(1, std::min(s.n_iters, std::max(1, cap / CT)));
+      // Narrow tiles: a workgroup takes the 4 trips whose loads it keeps in flight together, up to 8 where that keeps the fold
+      // at one level of 16 (measured over 19 shapes with 4, 8 and 16 trips: 4 is the fastest or within 3 % of it).
+      if (narrow_tiles && !(opt.has_hint && opt.hint.max_workgroups > 0)) {
+        const int want = (s.n_iters + 3) / 4;
+        if (want <= 32) s.RB = std::min(s.RB, std::min(want, 16));
+      }
       s.grid = s.RB * CT;
     }
     // Looping kernels that only fold columns have almost no arithmetic per trip: their rate is set by
     // the bytes in flight, and two row tiles per trip measured 13 % faster (28.1 -> 24.5 us on
     // [65536,512]).  With a row reduction in the body one tile per trip is the faster form.
     s.U = (colred && !rowred && s.grid < s.n_iters && CT == 1) ? 2 : 1;
+    if (narrow_tiles) {  // all loads of a few trips in flight
+      const int trips = (s.n_iters + s.RB - 1) / s.RB;
+      s.U = trips >= 4 ? 4 : trips >= 2 ? 2 : 1;
+    }
     if (opt.has_hint && opt.hint.tiles_per_trip >= 1 && opt.hint.tiles_per_trip <= 4) s.U = opt.hint.tiles_per_trip;
     if (has_concat) s.U = 1;
     // two fold levels at most: the smallest fan-in whose square covers the grid
     // (64 workgroups per fold: 16 measured 9 % faster than 8 on column sums of [16384,4096], 44.6 against 48.8 us)
-    s.fan_in = s.RB <= 32 ? 8 : s.RB <= 256 ? 16 : 32;
+    s.fan_in = s.RB <= 16 && narrow_tiles ? 16 : s.RB <= 32 ? 8 : s.RB <= 256 ? 16 : 32;
     return FS_OK;
   }
 
@@ -813,7 +833,8 @@ fs_status analyse_group(const Graph& g, const std::vector<int>& members, const s
   // loads there.  LayerNorm+GeLU bf16 [30001,1021]: 24.5 -> 22.1 us right after the kernel that wrote the input (28.3 -> 28.7 us
   // from cold memory); masked softmax bf16 [32768,577] 22.5 -> 20.4 us (22.5 -> 22.8 us).  Not for groups that only stream
   // (no difference) or fold columns ([60001,515]: 33.3 -> 35.5 us).
-  if (st == FS_OK && gp.C % gp.s.V != 0 && !gp.row_reduces.empty() && gp.col_reduces.empty())
+  // Tiles narrower than a pair of cache lines share lines with their neighbours, too.
+  if (st == FS_OK && ((gp.C % gp.s.V != 0 && !gp.row_reduces.empty() && gp.col_reduces.empty()) || gp.s.narrow_tiles))
     for (ExtTensor& e : gp.ext_in) e.streaming = false;
   if (st == FS_OK && gp.s.chunked)  // every stage reads the row again: keep it in the caches
     for (ExtTensor& e : gp.ext_in) e.streaming = false;
@@ -917,7 +938,12 @@ bool worth_fusing(const GroupPlan& merged) {
   // one kernel on 8 CUs, 38 us as three kernels that each fill the device; [32, 256K]: 73 -> 37 us;
   // from 64 rows on the single kernel is as fast or faster ([128, 64K]: 20 against 35 us).
   if (merged.members.size() > 1 && merged.s.few_long_rows && !merged.s.split_rows && merged.s.chunked && merged.R <= 32) return false;
-  return merged.col_reduces.empty() || merged.members.size() == 1 || merged.s.grid == 1 || merged.min_hbm_bytes >= kFoldWorthBytes;
+  // Narrow column tiles have no such fold to speak of; what feeds their reductions, and further reductions of the same tensors,
+  // join them at any size.  Not where the reductions are row reductions of transposed tensors: there the other consumers want
+  // the rows in one workgroup (the 200-node DAG: 29.4 us with those kept apart, 30.6 us without).
+  bool narrow = merged.s.narrow_tiles;
+  for (const auto& f : merged.tflag) narrow &= !f.second;
+  return merged.col_reduces.empty() || merged.members.size() == 1 || merged.s.grid == 1 || narrow || merged.min_hbm_bytes >= kFoldWorthBytes;
 }
 
 struct Former {

@@ -982,6 +982,29 @@ def test_rows_whose_last_vector_overlaps_its_neighbour(rows, cols):
     plan.destroy()
 
 
+@pytest.mark.parametrize("rows,cols", [(2, 31), (127, 33), (129, 64), (513, 65), (1030, 577), (2100, 36), (8300, 100), (17000, 31)])
+def test_small_column_folds_by_narrow_tiles(rows, cols):
+    # tiles of 128 bytes: one column past a tile, one row past a workgroup's trip, one / a few / many workgroups per tile, several
+    # trips with their loads in flight together; several reductions with [1,C] and [R,1] operands in one kernel; batch statistics
+    from workloads import patterns
+    for dt in ("f32", "bf16"):
+        g = Graph()
+        x, b, w = g.input(rows, cols, dt), g.input(1, cols), g.input(rows, 1)
+        xf = g.unary("convert", x, "f32") if dt == "bf16" else x
+        y = g.binary("mul", g.binary("add", xf, g.bcast_rowvec(b, rows)), g.bcast_colvec(w, cols))
+        g.set_outputs([g.reduce_col("sum", y), g.reduce_col("max", xf), g.reduce_col("mean", xf)])
+        plan = fs.Plan(g)
+        assert plan.stats()["num_launches"] == 1 and plan.group_info(0)["num_col_reduces"] == 3
+        plan.destroy()
+        v = (0.5 + RNG.standard_normal((rows, cols))).astype(np.float32)
+        ins = [f32_to_bf16_bits(v) if dt == "bf16" else v, RNG.standard_normal((1, cols)).astype(np.float32),
+               (1.0 + RNG.random((rows, 1))).astype(np.float32)]
+        both_modes(g, ins, f"narrow column tiles {dt} {rows}x{cols}")
+    gb = patterns.batchnorm(rows, cols)
+    both_modes(gb, [v, (1.0 + 0.1 * RNG.standard_normal((1, cols))).astype(np.float32), RNG.standard_normal((1, cols)).astype(np.float32)],
+               f"batchnorm {rows}x{cols}")
+
+
 def test_gpu_matches_the_stored_small_cases():
     # the tiny hand-checkable cases of tests/golden/oracle_small_cases.json (written by the oracle alone), on the GPU
     import json
