@@ -932,7 +932,7 @@ struct Emitter {
     // names of a single tile: such bodies take one tile per trip)
     bool rowv_member_in_loop = false;
     for (int m : gp.members) rowv_member_in_loop |= rowv_in_loop && gp.level.at(m) < 0;
-    const int U = ((rowv_in_loop && !stage_before_loop) || (s.CT > 1 && !s.narrow_tiles) || (ctile && !s.narrow_tiles) || rowv_member_in_loop) ? 1 : std::max(1, s.U);
+    const int U = ((rowv_in_loop && !stage_before_loop) || (s.CT > 1 && !s.narrow_tiles) || (ctile && !s.narrow_tiles) || s.tiled_transpose || rowv_member_in_loop) ? 1 : std::max(1, s.U);
     if (ctile && U > 1) {
       os << "  for (int it0 = rb * " << U << "; it0 < a.n_iters; it0 += RB * " << U << ") {\n";
     } else if (ctile) {

@@ -153,9 +153,9 @@ struct Scheduler {
     // A width that V does not divide keeps 16-byte accesses: the last vector of a row overlaps the one before it (fs_vec_col).
     // Rows of at most 32 bytes belong to one lane each and are read element by element or in the vectors that fit.  A vector
     // access must not straddle the seam of a concat, so there V divides the widths
-    // (as it does where whole narrow rows leave transposed, in runs of a few elements: [65536,139] bf16 24.7 -> 29.3 us)
+    // (as it does where whole rows of less than 16 elements leave transposed)
     bool narrow_transposed = false;
-    for (const ExtTensor& e : gp->ext_out) narrow_transposed |= e.transposed && C <= 256;
+    for (const ExtTensor& e : gp->ext_out) narrow_transposed |= e.transposed && C < 16;
     while (has_concat || narrow_transposed || C * max_es <= 32 ? C % V != 0 : V > C) V /= 2;
     for (int m : gp->members)
       if (g.nodes[m].opcode == FS_CONCAT && g.nodes[m].attr_i == FS_CONCAT_COLS)
@@ -245,8 +245,10 @@ struct Scheduler {
     if (has_concat && (chunked || col_tiled))
       FS_FAIL(FS_ERR_UNSUPPORTED, "a concat cannot be read by a kernel that walks rows of %d columns in chunks", C);
     if (tileable) l_min = std::min(l_min, 256);
-    // wide transposes: 2-D tiles through LDS
-    tiled_transpose = has_transposed && tileable && C > 256 && R > 1;
+    // transposes: 2-D tiles through LDS, down to rows of 16 elements (a tile of whole narrow rows holds few of them, so it leaves
+    // in runs of 16-64 bytes: [65536,256] bf16 85.0 -> 13.9 us as 2-D tiles, f32 93.8 -> 23.7 us; [65536,177] f32 64.5 -> 21.0 us;
+    // [65536,64] f32 8.1 -> 7.1 us)
+    tiled_transpose = has_transposed && tileable && C >= 16 && R > 1;
     if (split_rows) l_min = 256;
     else if (chunked) l_min = 1024;  // (measured: the largest workgroup keeps the fewest rows in flight, so re-reads hit the caches more often)
     if (col_tiled) l_min = std::min(narrow_tiles ? (R > 16384 ? 16 : 8) : 64, l_max);
@@ -299,6 +301,10 @@ struct Scheduler {
       L = std::min(1024 / tt_rows, l_max);
       // the tile holds one float per element: 16-element vectors (u8 alone) need narrower tiles to fit the budget
       while (L > 4 && (int64_t)L * V * (tt_rows + 1) * 4 > opt.lds_budget) L /= 2;
+      // narrower tiles, down to 64 columns, where a quarter of the tiles' columns would be empty ([65536,139] bf16 14.3 -> 12.3 us,
+      // f32 18.5 -> 17.6 us; [9000,130] f32 5.2 -> 3.6 us; 32 columns f32: 19.9 us)
+      const auto empty = [&](int lanes) { return (NV + lanes - 1) / lanes * lanes - NV; };
+      while (L * V > 64 && empty(L) * 4 >= NV + empty(L) && empty(L / 2) < empty(L)) L /= 2;
     }
     // small problems: more lanes per row until the device has ~8 wavefronts per CU
     // (a row that will be cut into column tiles anyway is not a small problem)

@@ -1005,6 +1005,27 @@ def test_small_column_folds_by_narrow_tiles(rows, cols):
                f"batchnorm {rows}x{cols}")
 
 
+@pytest.mark.parametrize("rows,cols", [(4097, 17), (333, 64), (70, 130), (1025, 139), (65, 255), (2, 16), (31, 65)])
+def test_narrow_transposes_by_tiles(rows, cols):
+    # 2-D tiles down to 16 columns: widths around a tile of 64 or 128 columns, rows around the 32 / 64 of a tile, runs that start at
+    # any element of the transposed rows; a value stored both ways, u8 beside f32
+    for dt in ("f32", "bf16", "u8"):
+        g = Graph()
+        x = g.input(rows, cols, dt)
+        if dt == "u8":
+            g.set_outputs([g.transpose(x)])
+            ins = [RNG.integers(0, 2, (rows, cols)).astype(np.uint8)]
+        else:
+            v = g.input(1, cols)
+            xf = g.unary("convert", x, "f32") if dt == "bf16" else x
+            y = g.binary("add", xf, g.bcast_rowvec(v, rows))
+            t = g.transpose(y)
+            g.set_outputs([y, g.unary("convert", t, dt) if dt == "bf16" else g.unary("neg", t)])
+            xs = RNG.standard_normal((rows, cols)).astype(np.float32)
+            ins = [f32_to_bf16_bits(xs) if dt == "bf16" else xs, RNG.standard_normal((1, cols)).astype(np.float32)]
+        both_modes(g, ins, f"narrow transpose {dt} {rows}x{cols}")
+
+
 def test_gpu_matches_the_stored_small_cases():
     # the tiny hand-checkable cases of tests/golden/oracle_small_cases.json (written by the oracle alone), on the GPU
     import json
