@@ -21,9 +21,10 @@ HIP_FLAGS = ["--offload-arch=gfx950", "-O2", "-std=c++17", "-fPIC", "-ffp-contra
 
 
 def _embed_device_header() -> str:
-    """Writes csrc/fs_device_src.cpp: the text of fs_device.h as a string constant."""
+    """Writes csrc/fs_device_src.cpp: the text of fs_device.h, without its comment lines, as a string constant."""
     with open(os.path.join(CSRC, "fs_device.h"), "r") as f:
-        text = f.read()
+        # (comment lines stay out: plan creation hashes this text for every plan, and the run-time compiler reads it)
+        text = "".join(ln for ln in f if not ln.lstrip().startswith("//"))
     out = os.path.join(CSRC, "fs_device_src.cpp")
     chunks = [text[i:i + 8000] for i in range(0, len(text), 8000)]
     body = "\n".join('R"FSDEV(' + c + ')FSDEV"' for c in chunks)
