@@ -932,9 +932,30 @@ struct Emitter {
     // names of a single tile: such bodies take one tile per trip)
     bool rowv_member_in_loop = false;
     for (int m : gp.members) rowv_member_in_loop |= rowv_in_loop && gp.level.at(m) < 0;
-    const int U = ((rowv_in_loop && !stage_before_loop) || (s.CT > 1 && !s.narrow_tiles) || (ctile && !s.narrow_tiles) || s.tiled_transpose || rowv_member_in_loop) ? 1 : std::max(1, s.U);
-    if (ctile && U > 1) {
-      os << "  for (int it0 = rb * " << U << "; it0 < a.n_iters; it0 += RB * " << U << ") {\n";
+    const int U = ((rowv_in_loop && !stage_before_loop) || s.CT > 1 || ctile || s.tiled_transpose || rowv_member_in_loop) ? 1 : std::max(1, s.U);
+    // (narrow column tiles: a trip's row tiles are an array, filled by one unrolled loop and consumed by another)
+    const int UN = s.narrow_tiles && !rowv_member_in_loop ? std::max(1, s.U) : 1;
+    const std::string un_row = "      const long row = (long)(it0 + u) * G + rg;\n      const bool rok = row < R;\n      const long row_ld = rok ? row : R - 1, row0 = row_ld * C;\n"
+                               "      (void)row0;\n";
+    if (UN > 1) {
+      os << "  for (int it0 = rb * " << UN << "; it0 < a.n_iters; it0 += RB * " << UN << ") {\n";
+      for (const ExtTensor& e : gp.ext_in) {
+        if (e.kind == KIND_FULL) os << "    float " << name(e.node, KIND_FULL) << "_u[" << UN << "][E];\n";
+        else if (e.kind == KIND_COLV) os << "    float " << name(e.node, KIND_COLV) << "_u[" << UN << "];\n";
+      }
+      os << "    _Pragma(\"unroll\") for (int u = 0; u < " << UN << "; ++u) {\n" << un_row;
+      for (const ExtTensor& e : gp.ext_in) {
+        if (e.kind == KIND_FULL)
+          os << "      float (&" << name(e.node, KIND_FULL) << ")[E] = " << name(e.node, KIND_FULL) << "_u[u];\n      fs_load_row<" << e.dtype << ", " << tmpl_row() << ", "
+             << (e.streaming ? "true" : "false") << ">(" << name(e.node, KIND_FULL) << ", a.p[" << e.arg << "], row0, lir, vbase);\n";
+        else if (e.kind == KIND_COLV)
+          os << "      " << name(e.node, KIND_COLV) << "_u[u] = fs_load1<" << e.dtype << ">(a.p[" << e.arg << "], row_ld);\n";
+      }
+      os << "    }\n    _Pragma(\"unroll\") for (int u = 0; u < " << UN << "; ++u) {\n" << un_row;
+      for (const ExtTensor& e : gp.ext_in) {
+        if (e.kind == KIND_FULL) os << "      const float (&" << name(e.node, KIND_FULL) << ")[E] = " << name(e.node, KIND_FULL) << "_u[u];\n";
+        else if (e.kind == KIND_COLV) os << "      const float " << name(e.node, KIND_COLV) << " = " << name(e.node, KIND_COLV) << "_u[u];\n";
+      }
     } else if (ctile) {
       os << "  for (int it = rb; it < a.n_iters; it += RB) {\n";
     } else if (U == 1) {
@@ -942,12 +963,11 @@ struct Emitter {
     } else {
       os << "  for (int it0 = (int)blockIdx.x * " << U << "; it0 < a.n_iters; it0 += (int)gridDim.x * " << U << ") {\n";
     }
-    for (int u = 0; u < U; ++u) {
+    for (int u = 0; u < U && UN == 1; ++u) {
       const std::string x = U == 1 ? "" : "_" + std::to_string(u);
       if (U > 1) os << "    const int it" << x << " = it0 + " << u << ";\n";
       if (ctile) {
-        os << "    const long row" << x << " = (long)it" << x << " * G + rg;\n";
-        if (U > 1) os << "    const int vbase" << x << " = vbase;\n";
+        os << "    const long row = (long)it * G + rg;\n";
       } else if (s.tiled_transpose) {
         // 2-D tiles: consecutive workgroups take consecutive column tiles of the same G rows
         if (s.tt_col_band > 0) {
@@ -1084,7 +1104,7 @@ struct Emitter {
       if (U > 1) {
         const std::string x = "_" + std::to_string(u);
         os << "    {\n    const long row = row" << x << "; const bool rok = rok" << x << "; const long row0 = row0" << x
-           << "; (void)row; (void)rok; (void)row0;" << (ctile ? "" : " constexpr int vbase = 0; (void)vbase;") << "\n";
+           << "; constexpr int vbase = 0; (void)row; (void)rok; (void)row0; (void)vbase;\n";
         for (const ExtTensor& e : gp.ext_in) {
           if (e.kind == KIND_FULL) os << "    float (&" << name(e.node, KIND_FULL) << ")[E] = " << name(e.node, KIND_FULL) << x << ";\n";
           else if (e.kind == KIND_COLV) os << "    const float " << name(e.node, KIND_COLV) << " = " << name(e.node, KIND_COLV) << x << ";\n";
@@ -1190,6 +1210,7 @@ struct Emitter {
       }
       if (U > 1) os << "    }\n";
     }
+    if (UN > 1) os << "    }\n";
     if (lazy_rowv)  // [1,C] members nothing in the body consumed (outputs only)
       for (int m : gp.members)
         if (gp.level.at(m) < 0) ensure_rowv(m);

@@ -236,8 +236,18 @@ struct Scheduler {
     // tensor fold side by side; several column reductions, and what feeds them, then share a kernel however small it is
     // (worth_fusing).  Whole plans, 256 workgroups and two fold levels -> narrow tiles: column sums + row norms f32 [4765,147]
     // 17.3 -> 8.5 us, [127,1088] 13.4 -> 6.5 us; batch normalisation [1764,512] 21.8 -> 13.6 us, [352,5824] 25.4 -> 11.9 us;
-    // LayerNorm backward [318,1145] 17.0 -> 9.7 us.  From 16 MB on the wide tiles stream better ([65536,1024]).
-    narrow_tiles = colred && !rowred && !has_transposed && !has_concat && R > 1 && (int64_t)R * C * max_es < (16 << 20);
+    // LayerNorm backward [318,1145] 17.0 -> 9.7 us.
+    // From there to 128 MB, tiles of 32 lanes for groups that only read one [R,C] tensor: batch normalisation [16384,1024] 56.4 ->
+    // 52.4 us, [2000,4096] 29.9 -> 26.6 us, column sums bf16 [16384,2048] 20.6 -> 14.7 us, f32 [8192,1024] 12.4 -> 9.7 us.  Not for
+    // tall tensors, whose tiles would need many workgroups and the two-level fold again (f32 [65536,500]: 94.8 -> 104.6 us, bf16
+    // [30000,1000]: 15.9 -> 16.6 us), nor where more than one [R,C] tensor streams (bias gradient [8192,2048]: 37.6 -> 42.6 us) or
+    // an [R,1] operand would be read again by every tile.  Beyond, the wide tiles stream as well ([65536,1024]).
+    int row_tensors = 0;  // [R,C] tensors, and [R,1] operands
+    for (const ExtTensor& e : gp->ext_in) row_tensors += e.kind == KIND_FULL || e.kind == KIND_COLV;
+    for (const ExtTensor& e : gp->ext_out) row_tensors += e.kind == KIND_FULL;
+    const int64_t bytes = (int64_t)R * C * max_es;
+    narrow_tiles = colred && !rowred && !has_transposed && !has_concat && R > 1 &&
+                   (bytes < (16 << 20) || (bytes < (128 << 20) && R <= 16384 && row_tensors == 1));
     col_tiled |= narrow_tiles;
     if (l_min > 1024 && !tileable && !chunked && !col_tiled)
       FS_FAIL(FS_ERR_UNSUPPORTED, "rows of %d columns are too long for one workgroup in a group with %s", C,
@@ -251,7 +261,7 @@ struct Scheduler {
     tiled_transpose = has_transposed && tileable && C >= 16 && R > 1;
     if (split_rows) l_min = 256;
     else if (chunked) l_min = 1024;  // (measured: the largest workgroup keeps the fewest rows in flight, so re-reads hit the caches more often)
-    if (col_tiled) l_min = std::min(narrow_tiles ? (R > 16384 ? 16 : 8) : 64, l_max);
+    if (col_tiled) l_min = std::min(narrow_tiles ? ((int64_t)R * C * max_es >= (16 << 20) ? 32 : R > 16384 ? 16 : 8) : 64, l_max);
     return FS_OK;
   }
 
@@ -839,8 +849,8 @@ fs_status analyse_group(const Graph& g, const std::vector<int>& members, const s
   // loads there.  LayerNorm+GeLU bf16 [30001,1021]: 24.5 -> 22.1 us right after the kernel that wrote the input (28.3 -> 28.7 us
   // from cold memory); masked softmax bf16 [32768,577] 22.5 -> 20.4 us (22.5 -> 22.8 us).  Not for groups that only stream
   // (no difference) or fold columns ([60001,515]: 33.3 -> 35.5 us).
-  // Tiles narrower than a pair of cache lines share lines with their neighbours, too.
-  if (st == FS_OK && ((gp.C % gp.s.V != 0 && !gp.row_reduces.empty() && gp.col_reduces.empty()) || gp.s.narrow_tiles))
+  // So do the narrow tiles of small column folds.
+  if (st == FS_OK && ((gp.C % gp.s.V != 0 && !gp.row_reduces.empty() && gp.col_reduces.empty()) || (gp.s.narrow_tiles && gp.s.L < 32)))
     for (ExtTensor& e : gp.ext_in) e.streaming = false;
   if (st == FS_OK && gp.s.chunked)  // every stage reads the row again: keep it in the caches
     for (ExtTensor& e : gp.ext_in) e.streaming = false;

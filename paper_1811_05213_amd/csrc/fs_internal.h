@@ -162,7 +162,7 @@ struct Schedule {
   // Column reductions over rows too wide for one workgroup: CT column tiles, each folded by its own
   // RB = grid / CT workgroups (tile = block % CT).  Strides of one tile's scratch in the workspace:
   bool col_tiled = false;
-  bool narrow_tiles = false;  // ... tiles of one 128-byte run, a workgroup or a few of them per tile (small tensors)
+  bool narrow_tiles = false;  // ... tiles of 8, 16 or 32 lanes with one vector each, a workgroup or a few of them per tile (tensors below 128 MB)
   int RB = 0;
   size_t part_stride_floats = 0;
   int ticket_stride = 0;
