@@ -152,8 +152,8 @@ struct Scheduler {
     for (int m : gp->members) has_concat |= g.nodes[m].opcode == FS_CONCAT;
     // A width that V does not divide keeps 16-byte accesses: the last vector of a row overlaps the one before it (fs_vec_col).
     // Rows of at most 32 bytes belong to one lane each and are read element by element or in the vectors that fit.  A vector
-    // access must not straddle the seam of a concat, so there V divides the widths
-    // (as it does where whole rows of less than 16 elements leave transposed)
+    // access must not straddle the seam of a concat, so there V divides the widths, as it does where whole rows of less than 16
+    // elements leave transposed.
     bool narrow_transposed = false;
     for (const ExtTensor& e : gp->ext_out) narrow_transposed |= e.transposed && C < 16;
     while (has_concat || narrow_transposed || C * max_es <= 32 ? C % V != 0 : V > C) V /= 2;
@@ -269,8 +269,8 @@ struct Scheduler {
   fs_status pick_lanes() {
     L = rowred ? std::min(64, l_max) : std::min(256, l_max);
     // Very narrow rows: a row of at most 32 bytes belongs to one lane (no cross-lane step at all;
-    // [4M,3] L2-normalise: 34.8 -> 17.6 us); rows that can only be read element by element (odd
-    // widths) get at least two elements per lane.
+    // [4M,3] L2-normalise: 34.8 -> 17.6 us); rows that can only be read element by element (concats
+    // with an odd seam) get at least two elements per lane.
     // A row that leaves part of a wavefront's last vector slots empty (768 bf16 columns: 96 vectors
     // on 64 lanes x 2) is better served by fewer lanes that it fills exactly, several rows per
     // wavefront (32 lanes x 3: LayerNorm+GeLU bf16 [32768,768] 24.0 -> 20.9 us).
@@ -367,7 +367,7 @@ struct Scheduler {
   fs_status pick_workgroup() {
     const int64_t total_waves = std::max<int64_t>(1, (int64_t)R * CT * L / 64);
     if (narrow_tiles) {
-      WG = std::max(64, std::min(1024, L * pow2_ceil(R)));
+      WG = (int)std::max<int64_t>(64, std::min<int64_t>(1024, (int64_t)L * pow2_ceil(std::min(R, 1024))));
     } else if (col_tiled) {
       WG = std::max(64, L);
       for (int w = 512; w >= 128; w /= 2)
@@ -540,7 +540,7 @@ struct Scheduler {
     }
     if (opt.has_hint && opt.hint.tiles_per_trip >= 1 && opt.hint.tiles_per_trip <= 4) s.U = opt.hint.tiles_per_trip;
     if (has_concat) s.U = 1;
-    // two fold levels at most: the smallest fan-in whose square covers the grid
+    // two fold levels at most: the smallest fan-in whose square covers the grid (one level for narrow tiles of up to 16 workgroups)
     // (64 workgroups per fold: 16 measured 9 % faster than 8 on column sums of [16384,4096], 44.6 against 48.8 us)
     s.fan_in = s.RB <= 16 && narrow_tiles ? 16 : s.RB <= 32 ? 8 : s.RB <= 256 ? 16 : 32;
     return FS_OK;
