@@ -525,7 +525,8 @@ struct Scheduler {
       // Narrow tiles: a workgroup takes the 4 trips whose loads it keeps in flight together, up to 8 where that keeps the fold
       // at one level of 16 (measured over 19 shapes with 4, 8 and 16 trips: 4 is the fastest or within 3 % of it).
       if (narrow_tiles && !(opt.has_hint && opt.hint.max_workgroups > 0)) {
-        const int want = (s.n_iters + 3) / 4;
+        // (one alone takes up to 3)
+        const int want = std::max((s.n_iters + 3) / 4, s.n_iters >= 4 ? 2 : 1);
         if (want <= 32) s.RB = std::min(s.RB, std::min(want, 16));
       }
       s.grid = s.RB * CT;
