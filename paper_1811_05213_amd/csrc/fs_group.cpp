@@ -81,6 +81,9 @@ struct Analyser {
   }
 };
 
+// [R,C] tensors far larger than the caches
+constexpr uint64_t kStreamBytes = 32ull << 20;
+
 void add_ext_in(GroupPlan& gp, int node, Kind k, int dtype) {
   for (const ExtTensor& e : gp.ext_in)
     if (e.node == node) return;
@@ -156,7 +159,14 @@ struct Scheduler {
     // elements leave transposed.
     bool narrow_transposed = false;
     for (const ExtTensor& e : gp->ext_out) narrow_transposed |= e.transposed && C < 16;
-    while (has_concat || narrow_transposed || C * max_es <= 32 ? C % V != 0 : V > C) V /= 2;
+    // So it does where row sums are one link of a chain of launch-bound kernels: the vector width decides the order of a sum, and
+    // what follows may cancel and amplify the last bits (outputs of the 200-node DAG at odd sizes: two orders of the same sums
+    // differ by up to 3e-5 of an output's rms, both as far from float64).  Such kernels are chains of latencies and gain little
+    // from wider accesses: DAG of [512,100] 26.6 -> 26.6 us, [333,256] 29.9 -> 27.7, [2047,384] (19 MB a kernel) 81.4 -> 78.4 us.
+    // A kernel that holds its whole plan keeps them ([60000,65] fp32 softmax 30.1 -> 8.4 us, [256,1001] 3.5 -> 3.0 us), and
+    // so does one that streams 32 MB or more.
+    const bool keeps_order = !gp->row_reduces.empty() && gp->exchanges && gp->min_hbm_bytes < kStreamBytes;
+    while (has_concat || narrow_transposed || keeps_order || C * max_es <= 32 ? C % V != 0 : V > C) V /= 2;
     for (int m : gp->members)
       if (g.nodes[m].opcode == FS_CONCAT && g.nodes[m].attr_i == FS_CONCAT_COLS)
         while (g.nodes[g.nodes[m].in[0]].cols % V) V /= 2;
@@ -818,7 +828,7 @@ fs_status analyse_group(const Graph& g, const std::vector<int>& members, const s
   // written back then, after the last wavefront, which costs a microsecond or two that a kernel of 5-10 us notices
   // (softmax f32 [4096,1024]: 8.0 -> 6.6 us, [2048,1024]: 5.8 -> 4.6 us; LayerNorm+GeLU bf16 [4096,1024]: 6.0 -> 5.1 us;
   // Adam [2048,2048]: 23.8 -> 21.2 us; 1 MB tensors: no difference).  Values that pass between kernels stay cacheable.
-  constexpr uint64_t kStreamBytes = 32ull << 20, kStreamOnceBytes = 2ull << 20;
+  constexpr uint64_t kStreamOnceBytes = 2ull << 20;
   auto bytes_of = [&](const ExtTensor& e) { return (uint64_t)g.nodes[e.node].rows * g.nodes[e.node].cols * dtype_size(e.dtype); };
   std::function<bool(int)> used_only_here = [&](int id) {
     for (int u : g.users[id]) {
@@ -844,6 +854,9 @@ fs_status analyse_group(const Graph& g, const std::vector<int>& members, const s
   gp.min_hbm_bytes = 0;
   for (const ExtTensor& e : gp.ext_in) gp.min_hbm_bytes += (uint64_t)g.nodes[e.node].rows * g.nodes[e.node].cols * dtype_size(e.dtype);
   for (const ExtTensor& e : gp.ext_out) gp.min_hbm_bytes += (uint64_t)g.nodes[e.node].rows * g.nodes[e.node].cols * dtype_size(e.dtype);
+  gp.exchanges = false;
+  for (const ExtTensor& e : gp.ext_in) gp.exchanges |= g.nodes[g.root_of[e.node]].opcode != FS_INPUT;
+  for (const ExtTensor& e : gp.ext_out) gp.exchanges |= !used_only_here(e.node);
 
   const fs_status st = choose_schedule(g, opt, &gp);
   // Rows that are no multiple of a vector long share cache lines with their neighbours, which other wavefronts read: ordinary

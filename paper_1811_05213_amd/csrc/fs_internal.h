@@ -198,6 +198,7 @@ struct GroupPlan {
   size_t ticket_offset = 0;
   int n_tickets = 0;
   uint64_t min_hbm_bytes = 0;
+  bool exchanges = false;  // reads what another kernel of the plan wrote, or writes what another one reads
   // generated kernel
   std::string kernel_name, source;
   std::string perf_key;  // filled on demand by fs_plan_group_perf_key

@@ -951,3 +951,26 @@ def test_concat_is_read_as_one_row_by_its_consumers():
     p = fs.Plan(g)
     assert p.stats()["num_launches"] == 1 and p.group_info(0)["dom_rows"] == 128
     p.destroy()
+
+
+@pytest.mark.parametrize("rows,k", [(512, 100), (333, 256), (61, 48), (1022, 200), (2047, 384)])
+def test_row_sums_between_launch_bound_kernels_keep_their_order(rows, k):
+    # the vector width decides the order of a row sum: kernels that exchange values with others of their plan sum in
+    # vectors that divide the row, also where a last vector could overlap its neighbour
+    p = fs.Plan(random_dag_graph(rows=rows, ks=(k // 4, k // 2, k)))
+    groups = [p.group_info(j) for j in range(p.stats()["num_groups"])]
+    summed = [gi for gi in groups if gi["num_row_reduces"] > 0]
+    assert len(groups) > 1 and any(gi["dom_cols"] % 4 for gi in summed)
+    for gi in summed:
+        assert gi["dom_cols"] % gi["vec_elems"] == 0, gi
+    p.destroy()
+
+
+def test_row_sums_alone_or_over_large_tensors_keep_16_byte_accesses():
+    p = fs.Plan(softmax_graph(256, 1001))
+    assert p.group_info(0)["vec_elems"] == 4
+    p.destroy()
+    p = fs.Plan(softmax_graph(20000, 1001), mode=fs.FS_MODE_UNFUSED)  # (an op per kernel: 80 MB each)
+    groups = [p.group_info(j) for j in range(p.stats()["num_groups"])]
+    assert [gi["vec_elems"] for gi in groups if gi["num_row_reduces"] > 0] == [4, 4]
+    p.destroy()
