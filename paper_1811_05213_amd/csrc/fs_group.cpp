@@ -532,11 +532,12 @@ struct Scheduler {
     }
     if (col_tiled) {  // RB workgroups per column tile, about `cap` workgroups in all
       s.RB = std::max(1, std::min(s.n_iters, std::max(1, cap / CT)));
-      // Narrow tiles: a workgroup takes the 4 trips whose loads it keeps in flight together, up to 8 where that keeps the fold
-      // at one level of 16 (measured over 19 shapes with 4, 8 and 16 trips: 4 is the fastest or within 3 % of it).
+      // Narrow tiles: a workgroup takes up to 4 trips, whose loads it keeps in flight together, and up to 8 where that keeps the
+      // fold at one level of 16.  Four trips of one workgroup beat two workgroups of two, which have partials to exchange: column
+      // sums f32 [512,1000] 3.1 against 4.6 us, [400,4000] 3.1 against 4.9; sum, max and sum of squares bf16 [512,2000] 7.9
+      // against 9.7; batch normalisation [512,1000] 9.4 against 12.3 us.
       if (narrow_tiles && !(opt.has_hint && opt.hint.max_workgroups > 0)) {
-        // (one alone takes up to 3)
-        const int want = std::max((s.n_iters + 3) / 4, s.n_iters >= 4 ? 2 : 1);
+        const int want = (s.n_iters + 3) / 4;
         if (want <= 32) s.RB = std::min(s.RB, std::min(want, 16));
       }
       s.grid = s.RB * CT;

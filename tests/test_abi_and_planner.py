@@ -974,3 +974,13 @@ def test_row_sums_alone_or_over_large_tensors_keep_16_byte_accesses():
     groups = [p.group_info(j) for j in range(p.stats()["num_groups"])]
     assert [gi["vec_elems"] for gi in groups if gi["num_row_reduces"] > 0] == [4, 4]
     p.destroy()
+
+
+@pytest.mark.parametrize("rows", [100, 385, 512])
+def test_four_trips_of_a_narrow_column_tile_need_no_second_workgroup(rows):
+    # up to four trips of 128 rows: one workgroup per tile of 32 fp32 columns, no partials, no tickets
+    g = Graph()
+    g.set_outputs([g.reduce_col("sum", g.input(rows, 1000))])
+    p = fs.Plan(g)
+    assert p.group_info(0)["grid"] == 32 and p.group_info(0)["scratch_bytes"] == 0 and p.workspace_bytes() == 0
+    p.destroy()

@@ -497,7 +497,7 @@ def test_caller_given_groups():
 
 # ------------------------------------------------------------------ run-time argument errors (nothing is launched)
 def test_run_argument_errors():
-    g, ins, _ = workload(4, 512)
+    g, ins, _ = workload(4, 4096)  # (rows enough for several workgroups per column tile: the plan has partials and tickets)
     plan = fs.Plan(g)
     r = DeviceRun(plan)
     r.set_inputs(ins)
