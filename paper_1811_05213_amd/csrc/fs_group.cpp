@@ -124,7 +124,7 @@ struct Scheduler {
   int ecap = 8, l_min = 1, l_max = 1;
   bool few_long_rows = false, split_rows = false, resident = false, chunked = false, col_tiled = false, narrow_tiles = false, tiled_transpose = false;
   // lanes, vectors, workgroup
-  int L = 64, tt_rows = 64, NVL = 1, CT = 1, NVLC = 0, RESV = 0, WG = 256;
+  int narrow_lanes = 0, L = 64, tt_rows = 64, NVL = 1, CT = 1, NVLC = 0, RESV = 0, WG = 256;
   bool staged_loop = false;
   int fold_width = 0;
 
@@ -241,23 +241,45 @@ struct Scheduler {
     // arrivers of the grid fold read 16 x C floats each.  Column sums of f32: [8192,8192] 58 -> 78 % of peak,
     // [16384,4096] 65 -> 69 %, [4096,16384] 71 -> 78 % (tiles of 256 lanes before), narrower rows unchanged.
     col_tiled = colred && !rowred && !has_transposed && (l_min > 1024 || (l_min > 64 && !has_concat));
-    // Folds of less than 16 MB are bound by latency, above all by the grid-wide fold (~4 us of a 7 us kernel).  Tiles of one
+    // Folds that stream little are bound by latency, above all by the grid-wide fold (~4 us of a 7 us kernel).  Tiles of one
     // 128-byte run let one workgroup, or up to 16 that fold in one level, walk all rows of its columns, and the columns of a
     // tensor fold side by side; several column reductions, and what feeds them, then share a kernel however small it is
     // (worth_fusing).  Whole plans, 256 workgroups and two fold levels -> narrow tiles: column sums + row norms f32 [4765,147]
     // 17.3 -> 8.5 us, [127,1088] 13.4 -> 6.5 us; batch normalisation [1764,512] 21.8 -> 13.6 us, [352,5824] 25.4 -> 11.9 us;
     // LayerNorm backward [318,1145] 17.0 -> 9.7 us.
-    // From there to 128 MB, tiles of 32 lanes for groups that only read one [R,C] tensor: batch normalisation [16384,1024] 56.4 ->
-    // 52.4 us, [2000,4096] 29.9 -> 26.6 us, column sums bf16 [16384,2048] 20.6 -> 14.7 us, f32 [8192,1024] 12.4 -> 9.7 us.  Not for
-    // tall tensors, whose tiles would need many workgroups and the two-level fold again (f32 [65536,500]: 94.8 -> 104.6 us, bf16
-    // [30000,1000]: 15.9 -> 16.6 us), nor where more than one [R,C] tensor streams (bias gradient [8192,2048]: 37.6 -> 42.6 us) or
-    // an [R,1] operand would be read again by every tile.  Beyond, the wide tiles stream as well ([65536,1024]).
-    int row_tensors = 0;  // [R,C] tensors, and [R,1] operands
+    //  - Below 16 MB in all (every tensor the kernel touches counts: a group of 8 inputs streams 8 times what its rows hold).
+    //  - One [R,C] tensor alone: to 128 MB, in tiles of 32 lanes (64 MB where rows are no multiple of a vector and every tile's
+    //    edge shares a line: f32 [500,47169] 18.5 -> 20.9 us, [4096,7681] 24.7 -> 26.0; [4096,3841], 60 MB, 15.8 -> 15.2).
+    //    Column sums f32 [4096,1152] 10.3 -> 7.4 us, [8192,2880] 19.6 -> 17.2, [2000,15712] 23.5 -> 21.6, bf16 [8192,5760] 23.3 ->
+    //    17.5; batch normalisation [16384,1024] 56.4 -> 52.4.  From 16384 rows on a tile needs many workgroups and the two-level
+    //    fold again: 3 % or less on either side for 260 and 512 columns, f32 [24000,1000] 20.1 -> 21.2 us, [65536,500] 94.8 -> 104.6.
+    //  - Several, each below 16 MB: to 64 MB, from 128 to 4096 rows.  Sums of 4 inputs f32 [1000,4000] 20.0 -> 12.6 us, [4096,1000] 21.2 -> 19.8;
+    //    taller tensors leave the device idle on few tiles, larger ones stream better in wide ones ([16000,255], 62 MB, 16.1 -> 20.7;
+    //    8 inputs [16000,100] 14.9 -> 24.6, [4096,1000], 125 MB, 27.2 -> 36.5; bias gradient [8192,2048] 37.6 -> 42.6 us).
+    const bool narrow_form = colred && !rowred && !has_transposed && !has_concat && R > 1;
+    int row_tensors = 0;  // [R,C] tensors, and [R,1] operands, which every tile reads again
     for (const ExtTensor& e : gp->ext_in) row_tensors += e.kind == KIND_FULL || e.kind == KIND_COLV;
     for (const ExtTensor& e : gp->ext_out) row_tensors += e.kind == KIND_FULL;
-    const int64_t bytes = (int64_t)R * C * max_es;
-    narrow_tiles = colred && !rowred && !has_transposed && !has_concat && R > 1 &&
-                   (bytes < (16 << 20) || (bytes < (128 << 20) && R <= 16384 && row_tensors == 1));
+    const uint64_t bytes = gp->min_hbm_bytes;
+    narrow_lanes = 0;
+    if (narrow_form && bytes < (16u << 20)) narrow_lanes = R > 16384 ? 16 : 8;
+    else if (narrow_form && row_tensors == 1 && R <= 16384 && bytes < (C % V ? 64u << 20 : 128u << 20)) narrow_lanes = 32;
+    else if (narrow_form && row_tensors > 1 && R >= 128 && R <= 4096 && (int64_t)R * C * max_es < (16 << 20) && bytes < (64u << 20)) narrow_lanes = 8;
+    if (narrow_lanes > 0) {
+      // Tiles beyond what the device holds at once pay their fixed cost (launch, fold, barriers) in rounds, and rows too few for a
+      // wavefront leave lanes idle: less than two rounds of resident lanes (f32 [16,131072] 6.5 -> 3.4 us, [32,122880] 6.7 -> 4.5,
+      // [64,122880] 8.3 -> 7.6, [128,122880] 12.8 -> 11.3; but [4,524288], two rounds, 4.4 -> 5.3, [32,245760] 8.1 -> 9.0,
+      // [64,245760] 10.6 -> 13.6, [2,1048576], four, 3.7 -> 9.0).  Less than four where 32 lanes a row make workgroups of 256 or 512,
+      // several to a compute unit, one streaming while another folds ([8,983040] 8.3 -> 7.0 us, [16,491520] 8.3 -> 7.4; but
+      // [16,983040], eight, 11.6 -> 12.8, and workgroups of 128, [4,1966080], 7.5 -> 8.6).
+      // Above 16 MB a last round that is more than half empty does not pay either (307 tiles on 256 compute units: f32 [500,39296]
+      // 15.4 -> 16.0 us, bf16 [500,78624] 17.1 -> 19.0; 820: bf16 [300,209696] 23.7 -> 25.5; but 410: f32 [300,52416] 13.0 -> 12.1).
+      const int64_t tiles = (NV + narrow_lanes - 1) / narrow_lanes;
+      const int wg = std::max(64, std::min(1024, narrow_lanes * pow2_ceil(std::min(R, 1024))));
+      const int rounds = narrow_lanes == 32 && (wg == 256 || wg == 512) ? 4 : 2;
+      if (tiles * wg >= rounds * RES || (bytes >= (16u << 20) && tiles > CUS && tiles % CUS > 0 && tiles % CUS < CUS / 2)) narrow_lanes = 0;
+    }
+    narrow_tiles = narrow_lanes > 0;
     col_tiled |= narrow_tiles;
     if (l_min > 1024 && !tileable && !chunked && !col_tiled)
       FS_FAIL(FS_ERR_UNSUPPORTED, "rows of %d columns are too long for one workgroup in a group with %s", C,
@@ -271,7 +293,7 @@ struct Scheduler {
     tiled_transpose = has_transposed && tileable && C >= 16 && R > 1;
     if (split_rows) l_min = 256;
     else if (chunked) l_min = 1024;  // (measured: the largest workgroup keeps the fewest rows in flight, so re-reads hit the caches more often)
-    if (col_tiled) l_min = std::min(narrow_tiles ? ((int64_t)R * C * max_es >= (16 << 20) ? 32 : R > 16384 ? 16 : 8) : 64, l_max);
+    if (col_tiled) l_min = std::min(narrow_tiles ? narrow_lanes : 64, l_max);
     return FS_OK;
   }
 
@@ -377,7 +399,7 @@ struct Scheduler {
   fs_status pick_workgroup() {
     const int64_t total_waves = std::max<int64_t>(1, (int64_t)R * CT * L / 64);
     if (narrow_tiles) {
-      WG = (int)std::max<int64_t>(64, std::min<int64_t>(1024, (int64_t)L * pow2_ceil(std::min(R, 1024))));
+      WG = std::max(64, std::min(1024, L * pow2_ceil(std::min(R, 1024))));
     } else if (col_tiled) {
       WG = std::max(64, L);
       for (int w = 512; w >= 128; w /= 2)

@@ -984,3 +984,31 @@ def test_four_trips_of_a_narrow_column_tile_need_no_second_workgroup(rows):
     p = fs.Plan(g)
     assert p.group_info(0)["grid"] == 32 and p.group_info(0)["scratch_bytes"] == 0 and p.workspace_bytes() == 0
     p.destroy()
+
+
+def _column_sum(rows, cols, inputs=1, dt="f32"):
+    g = Graph()
+    x = None
+    for _ in range(inputs):
+        i = g.input(rows, cols, dt)
+        f = g.unary("convert", i, "f32") if dt != "f32" else i
+        x = f if x is None else g.binary("add", x, f)
+    g.set_outputs([g.reduce_col("sum", x)])
+    return g
+
+
+@pytest.mark.parametrize("rows,cols,inputs,lanes,wide", [
+    (2000, 1000, 1, 8, False), (500, 500, 8, 8, False), (1000, 4000, 4, 8, False),        # below 16 MB in all; several inputs to 64 MB
+    (4096, 1000, 8, 64, True), (16000, 255, 4, 32, True), (16000, 100, 8, 16, True),   # 125 MB in all; too tall
+    (4096, 7680, 1, 32, False), (4096, 7681, 1, 64, True), (4096, 3841, 1, 32, False),   # one tensor: rows of whole vectors to 128 MB, others to 64 MB
+    (16385, 1024, 1, 64, True), (500, 39296, 1, 64, True), (300, 52416, 1, 32, False),  # too tall; 307 tiles and 410 tiles on 256 compute units
+    (2, 1 << 20, 1, 64, True), (4, 1 << 19, 1, 64, True), (16, 1 << 17, 1, 8, False),   # few rows: four and two rounds of resident lanes, less
+    (64, 250000, 1, 64, True), (32, 500000, 1, 64, True), (64, 122880, 1, 32, False), (16, 491520, 1, 32, False), (16, 983040, 1, 64, True),
+])
+def test_which_column_folds_take_narrow_tiles(rows, cols, inputs, lanes, wide):
+    p = fs.Plan(_column_sum(rows, cols, inputs))
+    gi = p.group_info(p.stats()["num_groups"] - 1)
+    assert gi["num_col_reduces"] == 1 and gi["lanes_per_row"] == lanes, gi
+    # a narrow tile holds one vector per lane, a wide one of this many columns several
+    assert (gi["elems_per_lane"] > gi["vec_elems"]) == wide, gi
+    p.destroy()
