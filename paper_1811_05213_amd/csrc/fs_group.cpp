@@ -107,6 +107,8 @@ void add_ext_in(GroupPlan& gp, int node, Kind k, int dtype) {
 // for more wavefronts so that the 256 CUs all get work.
 // -------------------------------------------------------------------------------------------
 namespace {
+constexpr int kNarrowRegs = 96;  // registers a lane of a narrow column tile may hold in rows, accumulators and [1,C] operands
+
 // The decisions of one group's schedule, taken in a fixed order; every step reads what the steps before it decided.
 struct Scheduler {
   const Graph& g;
@@ -124,7 +126,8 @@ struct Scheduler {
   int ecap = 8, l_min = 1, l_max = 1;
   bool few_long_rows = false, split_rows = false, resident = false, chunked = false, col_tiled = false, narrow_tiles = false, tiled_transpose = false;
   // lanes, vectors, workgroup
-  int narrow_lanes = 0, L = 64, tt_rows = 64, NVL = 1, CT = 1, NVLC = 0, RESV = 0, WG = 256;
+  int narrow_lanes = 0, narrow_trip_regs = 0, narrow_regs = 0;  // narrow column tiles: lanes, registers a trip's rows take, and accumulators and [1,C] operands
+  int L = 64, tt_rows = 64, NVL = 1, CT = 1, NVLC = 0, RESV = 0, WG = 256;
   bool staged_loop = false;
   int fold_width = 0;
 
@@ -256,10 +259,18 @@ struct Scheduler {
     //  - Several, each below 16 MB: to 64 MB, from 128 to 4096 rows.  Sums of 4 inputs f32 [1000,4000] 20.0 -> 12.6 us, [4096,1000] 21.2 -> 19.8;
     //    taller tensors leave the device idle on few tiles, larger ones stream better in wide ones ([16000,255], 62 MB, 16.1 -> 20.7;
     //    8 inputs [16000,100] 14.9 -> 24.6, [4096,1000], 125 MB, 27.2 -> 36.5; bias gradient [8192,2048] 37.6 -> 42.6 us).
-    const bool narrow_form = colred && !rowred && !has_transposed && !has_concat && R > 1;
+    // Their 1024-lane workgroups leave a lane 128 registers: 96 for what a trip's rows, the accumulators and the [1,C] operands
+    // take in fp32, the rest for addresses and what is computed.  Sums of 16 bf16 inputs, or 12 of u8, do not fit a single trip.
     int row_tensors = 0;  // [R,C] tensors, and [R,1] operands, which every tile reads again
-    for (const ExtTensor& e : gp->ext_in) row_tensors += e.kind == KIND_FULL || e.kind == KIND_COLV;
+    narrow_trip_regs = 0;
+    narrow_regs = V * (int)gp->col_reduces.size();
+    for (const ExtTensor& e : gp->ext_in) {
+      row_tensors += e.kind == KIND_FULL || e.kind == KIND_COLV;
+      narrow_trip_regs += e.kind == KIND_FULL ? V : e.kind == KIND_COLV ? 1 : 0;
+      narrow_regs += e.kind == KIND_ROWV ? V : 0;
+    }
     for (const ExtTensor& e : gp->ext_out) row_tensors += e.kind == KIND_FULL;
+    const bool narrow_form = opt.narrow_tiles && colred && !rowred && !has_transposed && !has_concat && R > 1 && narrow_trip_regs + narrow_regs <= kNarrowRegs;
     const uint64_t bytes = gp->min_hbm_bytes;
     narrow_lanes = 0;
     if (narrow_form && bytes < (16u << 20)) narrow_lanes = R > 16384 ? 16 : 8;
@@ -568,9 +579,11 @@ struct Scheduler {
     // the bytes in flight, and two row tiles per trip measured 13 % faster (28.1 -> 24.5 us on
     // [65536,512]).  With a row reduction in the body one tile per trip is the faster form.
     s.U = (colred && !rowred && s.grid < s.n_iters && CT == 1) ? 2 : 1;
-    if (narrow_tiles) {  // all loads of a few trips in flight
+    if (narrow_tiles) {  // all loads of a few trips in flight, as far as they fit the registers
+      // (sum of 4 bf16 inputs [2000,512]: 4 trips 9.2 us, 2 trips 6.5; of 8 inputs [1000,4000]: 2 trips 23.6, 1 trip 17.8)
       const int trips = (s.n_iters + s.RB - 1) / s.RB;
       s.U = trips >= 4 ? 4 : trips >= 2 ? 2 : 1;
+      while (s.U > 1 && s.U * narrow_trip_regs + narrow_regs > kNarrowRegs) s.U /= 2;
     }
     if (opt.has_hint && opt.hint.tiles_per_trip >= 1 && opt.hint.tiles_per_trip <= 4) s.U = opt.hint.tiles_per_trip;
     if (has_concat) s.U = 1;

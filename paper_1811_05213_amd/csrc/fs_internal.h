@@ -228,6 +228,7 @@ struct PlanOptions {
   // per lane (or 48 resident ones plus chunks), 1 = 32 resident ones plus chunks, 0 = chunks only.
   // Plan creation steps down while the compiled kernel spills.
   int wide_level = 2;
+  bool narrow_tiles = true;  // column folds may take narrow tiles (plan creation gives them up where the compiled kernel spills)
   int min_waves = 0;  // > 0: the kernel asks the compiler for that many wavefronts per SIMD (occupancy feedback at plan creation)
   bool layered = false;  // group with the layered planner of Section 3.2 instead of the default one
   // set once the groups are final: whether a value leaves a kernel then depends on which kernels compute it themselves

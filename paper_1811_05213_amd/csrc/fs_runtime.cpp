@@ -357,8 +357,8 @@ fs_status fs_plan_create(const fs_graph_desc* desc, fs_plan** out_plan) {
 
   // One translation unit per plan: the building blocks once, then every distinct kernel body.
   // Spill feedback: a kernel whose code object reports scratch memory is planned again with less
-  // register pressure -- rows held beyond 32 elements per lane step down towards chunks, otherwise
-  // the workgroup is halved (the register file is shared by fewer wavefronts) -- and the unit is
+  // register pressure -- rows held beyond 32 elements per lane step down towards chunks, narrow column tiles keep
+  // fewer trips in flight and then become wide ones, otherwise the workgroup is halved (the register file is shared by fewer wavefronts) -- and the unit is
   // compiled again; a few rounds at most.
   // Occupancy feedback: a 1024-lane workgroup is 4 wavefronts per SIMD, so a CU holds two of them
   // only at 64 vector registers or fewer.  A kernel that is up to 16 registers above that is compiled
@@ -424,6 +424,16 @@ fs_status fs_plan_create(const fs_graph_desc* desc, fs_plan** out_plan) {
       bool found = false;
       while (!found && !gp.row_reduces.empty() && (gp.s.E >= 32 || gp.s.resident) && o.wide_level > 0) {
         --o.wide_level;
+        found = analyse_group(g, ordered[gi], plan->group_of, (int)gi, o, &again) == FS_OK &&
+                generate_kernel(g, &again, (int)gi) == FS_OK && again.kernel_name != gp.kernel_name;
+      }
+      // (narrow column tiles: fewer trips in flight, at last the wide form; half a workgroup would need twice the trips)
+      for (int u = gp.s.U / 2; !found && gp.s.narrow_tiles && u >= 0; u = u > 0 ? u / 2 : -1) {
+        o = group_opt[gi];
+        if (!o.has_hint) o.hint = fs_sched_hint{0, 0, 0, 0};
+        o.has_hint = true;
+        o.hint.tiles_per_trip = u > 0 ? u : plan->opt.has_hint ? plan->opt.hint.tiles_per_trip : 0;
+        o.narrow_tiles = u > 0;
         found = analyse_group(g, ordered[gi], plan->group_of, (int)gi, o, &again) == FS_OK &&
                 generate_kernel(g, &again, (int)gi) == FS_OK && again.kernel_name != gp.kernel_name;
       }

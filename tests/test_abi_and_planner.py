@@ -986,14 +986,14 @@ def test_four_trips_of_a_narrow_column_tile_need_no_second_workgroup(rows):
     p.destroy()
 
 
-def _column_sum(rows, cols, inputs=1, dt="f32"):
+def _column_sum(rows, cols, inputs=1, dt="f32", moments=False):
     g = Graph()
     x = None
     for _ in range(inputs):
         i = g.input(rows, cols, dt)
         f = g.unary("convert", i, "f32") if dt != "f32" else i
         x = f if x is None else g.binary("add", x, f)
-    g.set_outputs([g.reduce_col("sum", x)])
+    g.set_outputs([g.reduce_col("sum", x)] + ([g.reduce_col("max", x), g.reduce_col("sum", g.binary("mul", x, x))] if moments else []))
     return g
 
 
@@ -1012,3 +1012,18 @@ def test_which_column_folds_take_narrow_tiles(rows, cols, inputs, lanes, wide):
     # a narrow tile holds one vector per lane, a wide one of this many columns several
     assert (gi["elems_per_lane"] > gi["vec_elems"]) == wide, gi
     p.destroy()
+
+
+@pytest.mark.parametrize("inputs,dt,rows,cols,moments", [(4, "bf16", 2000, 512, False), (4, "bf16", 2000, 512, True), (8, "bf16", 2000, 512, True),
+                                                         (16, "bf16", 2000, 512, True), (8, "f32", 2048, 1024, False), (3, "u8", 4000, 500, True),
+                                                         (16, "u8", 4000, 500, False)])
+def test_column_folds_of_many_inputs_fit_the_registers(inputs, dt, rows, cols, moments, monkeypatch, capfd, tmp_path):
+    # what a trip's rows take decides how many trips a narrow tile keeps in flight, and whether a group takes the form at all:
+    # the first plan compiles without scratch and nothing is planned again
+    monkeypatch.setenv("FS_LOG_PLAN", "1")
+    monkeypatch.setenv("FS_KERNEL_CACHE", str(tmp_path))
+    fs.Plan(_column_sum(rows, cols, inputs, dt, moments)).destroy()
+    log = capfd.readouterr().err
+    assert "planned again" not in log and "kept" not in log
+    scratch = [int(m) for m in re.findall(r"(\d+) bytes of scratch", log)]
+    assert scratch and max(scratch) <= 32, log
