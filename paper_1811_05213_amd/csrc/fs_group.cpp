@@ -123,7 +123,7 @@ struct Scheduler {
   int max_es = 0, V = 4, NV = 0;
   bool has_concat = false, rowred = false, colred = false, has_transposed = false, tileable = false;
   // the form its rows take
-  int ecap = 8, l_min = 1, l_max = 1;
+  int ecap = 8, l_min = 1, l_max = 1, l_hint = 1;  // (l_hint: the fewest lanes per row a hint may ask for)
   bool few_long_rows = false, split_rows = false, resident = false, chunked = false, col_tiled = false, narrow_tiles = false, tiled_transpose = false;
   // lanes, vectors, workgroup
   int narrow_lanes = 0, narrow_trip_regs = 0, narrow_regs = 0;  // narrow column tiles: lanes, registers a trip's rows take, and accumulators and [1,C] operands
@@ -140,6 +140,12 @@ struct Scheduler {
     const int l = pow2_ceil((NV + e / V - 1) / (e / V));
     if (rowred && l >= 2 && e < 32 && ((NV + l / 2 - 1) / (l / 2)) * V * 2 <= e * 3) return l / 2;
     return l;
+  }
+
+  // lanes per row that a hint asks for, 0 when it asks for none or for what the group cannot have
+  int hinted_lanes() const {
+    const int h = opt.has_hint ? opt.hint.lanes_per_row : 0;
+    return h > 0 && (h & (h - 1)) == 0 && h >= l_hint && h <= 1024 ? h : 0;
   }
 
   // element size, vector width, which reductions the group holds
@@ -289,6 +295,10 @@ struct Scheduler {
       const int wg = std::max(64, std::min(1024, narrow_lanes * pow2_ceil(std::min(R, 1024))));
       const int rounds = narrow_lanes == 32 && (wg == 256 || wg == 512) ? 4 : 2;
       if (tiles * wg >= rounds * RES || (bytes >= (16u << 20) && tiles > CUS && tiles % CUS > 0 && tiles % CUS < CUS / 2)) narrow_lanes = 0;
+      // (a tile has a workgroup of its own at least: a hint of fewer blocks is kept by the form over whole rows)
+      l_hint = std::min(8, l_min);
+      const int hinted = hinted_lanes() > 0 ? hinted_lanes() : narrow_lanes;
+      if (opt.has_hint && opt.hint.max_workgroups > 0 && opt.hint.max_workgroups < (NV + hinted - 1) / hinted) narrow_lanes = 0;
     }
     narrow_tiles = narrow_lanes > 0;
     col_tiled |= narrow_tiles;
@@ -304,6 +314,7 @@ struct Scheduler {
     tiled_transpose = has_transposed && tileable && C >= 16 && R > 1;
     if (split_rows) l_min = 256;
     else if (chunked) l_min = 1024;  // (measured: the largest workgroup keeps the fewest rows in flight, so re-reads hit the caches more often)
+    if (!narrow_tiles) l_hint = chunked || col_tiled ? 64 : l_min;
     if (col_tiled) l_min = std::min(narrow_tiles ? narrow_lanes : 64, l_max);
     return FS_OK;
   }
@@ -364,10 +375,7 @@ struct Scheduler {
     const bool col_tiles_anyway = tileable && (int64_t)NV * V > (int64_t)L * ecap;
     while ((int64_t)R * L / 64 < 8 * CUS && L < l_max && !(has_transposed && !rowred) && !chunked && !col_tiled && !col_tiles_anyway) L *= 2;
     if (split_rows) L = 256;
-    if (opt.has_hint && opt.hint.lanes_per_row > 0 && !tiled_transpose && !split_rows) {
-      const int h = opt.hint.lanes_per_row;
-      if ((h & (h - 1)) == 0 && h >= ((chunked || col_tiled) ? 64 : l_min) && h <= 1024) L = h;
-    }
+    if (hinted_lanes() > 0 && !tiled_transpose && !split_rows) L = hinted_lanes();
     return FS_OK;
   }
 
@@ -930,8 +938,11 @@ std::vector<fs_sched_hint> candidate_hints(const GroupPlan& base) {
         if (L == s.L && WG == s.WG && cap == 0) continue;  // the base schedule itself
         out.push_back(fs_sched_hint{L, WG, cap, 0});
       }
+  // narrow column tiles: the other numbers of trips in flight
+  for (int u : {1, 2, 4})
+    if (s.narrow_tiles && u != s.U) out.push_back(fs_sched_hint{s.L, s.WG, 0, u});
   // looping kernels: the other number of row tiles per trip with the base shape
-  if (s.grid < s.n_iters && s.CT == 1) out.push_back(fs_sched_hint{s.L, s.WG, 0, s.U == 1 ? 2 : 1});
+  if (!s.narrow_tiles && s.grid < s.n_iters && s.CT == 1) out.push_back(fs_sched_hint{s.L, s.WG, 0, s.U == 1 ? 2 : 1});
   // row-reduction groups with [1,C] operands staged in LDS: one trip per workgroup against looping
   // workgroups that stage once (32 wavefronts per CU), whichever the base is not
   if (s.stage_rowv && base.col_reduces.empty() && s.CT == 1 && s.L <= 256) {

@@ -1027,3 +1027,38 @@ def test_column_folds_of_many_inputs_fit_the_registers(inputs, dt, rows, cols, m
     assert "planned again" not in log and "kept" not in log
     scratch = [int(m) for m in re.findall(r"(\d+) bytes of scratch", log)]
     assert scratch and max(scratch) <= 32, log
+
+
+def test_hints_on_narrow_column_tiles(tmp_path, monkeypatch):
+    def info(g, **hint):
+        p = fs.Plan(g, hint=hint or None)
+        gi = p.group_info(p.stats()["num_groups"] - 1)
+        p.destroy()
+        return gi
+
+    g = _column_sum(4000, 147)
+    assert info(g)["lanes_per_row"] == 8 and info(g)["grid"] == 5 * 8  # 5 tiles of 32 columns, 8 workgroups each
+    # max_workgroups bounds the blocks, down to the single-block schedule
+    for cap in (1, 2, 4, 5, 7, 39, 1000):
+        assert info(g, max_workgroups=cap)["grid"] <= cap
+    assert info(g, max_workgroups=1)["grid"] == 1 and info(g, max_workgroups=20)["grid"] == 20
+    assert info(g, max_workgroups=3, lanes_per_row=32)["grid"] in (2, 3)  # 2 tiles of 128 columns
+    # lanes_per_row from 8 on, and the workgroup size
+    for lanes in (8, 16, 32, 64, 128):
+        assert info(g, lanes_per_row=lanes)["lanes_per_row"] == lanes
+    assert info(g, lanes_per_row=16, wg_threads=256)["rows_per_iter"] == 16
+    for bad in (3, 4, 2048):
+        assert info(g, lanes_per_row=bad)["lanes_per_row"] == 8
+        assert info(g, lanes_per_row=bad, max_workgroups=3)["grid"] <= 3
+    # the performance library may choose lanes and trips in flight
+    monkeypatch.setenv("FS_PERF_LIBRARY", str(tmp_path / "perflib.tsv"))
+    base = fs.Plan(g)
+    for hint in ({"lanes_per_row": 16, "wg_threads": 1024}, {"lanes_per_row": 8, "wg_threads": 1024, "tiles_per_trip": 2}):
+        other = fs.Plan(g, hint=hint)
+        assert other.group_perf_key(0) != base.group_perf_key(0)
+        (tmp_path / "perflib.tsv").write_text(f"{base.group_perf_key(0)}\t10.0\n{other.group_perf_key(0)}\t5.0\n")
+        chosen = fs.Plan(g)
+        assert chosen.group_perf_key(0) == other.group_perf_key(0)
+        chosen.destroy()
+        other.destroy()
+    base.destroy()

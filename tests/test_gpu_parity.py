@@ -1005,6 +1005,20 @@ def test_small_column_folds_by_narrow_tiles(rows, cols):
                f"batchnorm {rows}x{cols}")
 
 
+@pytest.mark.parametrize("hint", [{"max_workgroups": 1}, {"max_workgroups": 30}, {"lanes_per_row": 16}, {"lanes_per_row": 64, "wg_threads": 256},
+                                  {"lanes_per_row": 8, "wg_threads": 64, "tiles_per_trip": 3}, {"tiles_per_trip": 1}, {"lanes_per_row": 32, "max_workgroups": 7}])
+def test_narrow_column_tiles_under_hints(hint):
+    for rows, cols, dt in ((1030, 577, "f32"), (8300, 100, "bf16"), (129, 65, "bf16")):
+        g = Graph()
+        x, b = g.input(rows, cols, dt), g.input(1, cols)
+        xf = g.unary("convert", x, "f32") if dt == "bf16" else x
+        y = g.binary("add", xf, g.bcast_rowvec(b, rows))
+        g.set_outputs([g.reduce_col("sum", y), g.reduce_col("max", xf), g.reduce_col("sum", g.binary("mul", xf, xf))])
+        v = (0.5 + RNG.standard_normal((rows, cols))).astype(np.float32)
+        ins = [f32_to_bf16_bits(v) if dt == "bf16" else v, RNG.standard_normal((1, cols)).astype(np.float32)]
+        check_all(g, run_graph(g, ins, hint=hint), Reference(g, ins), f"narrow column tiles {dt} {rows}x{cols} {hint}")
+
+
 @pytest.mark.parametrize("rows,cols", [(4097, 17), (333, 64), (70, 130), (1025, 139), (65, 255), (2, 16), (31, 65)])
 def test_narrow_transposes_by_tiles(rows, cols):
     # 2-D tiles down to 16 columns: widths around a tile of 64 or 128 columns, rows around the 32 / 64 of a tile, runs that start at
