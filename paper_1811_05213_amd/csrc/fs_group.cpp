@@ -148,6 +148,10 @@ struct Scheduler {
     return h > 0 && (h & (h - 1)) == 0 && h >= l_hint && h <= 1024 ? h : 0;
   }
 
+  // 2-D transpose tiles keep the shape that measured best whatever a hint asks, but for tensors of up to 256 columns, whose tiles
+  // hardly differ from whole rows: there lanes and workgroup are worth tuning
+  bool tile_hints() const { return C <= 256; }
+
   // element size, vector width, which reductions the group holds
   fs_status measure_group() {
     // the machine: compute units and resident lanes as the device reports them (256 and 524288 on MI355X)
@@ -369,6 +373,7 @@ struct Scheduler {
       // f32 18.5 -> 17.6 us; [9000,130] f32 5.2 -> 3.6 us; 32 columns f32: 19.9 us)
       const auto empty = [&](int lanes) { return (NV + lanes - 1) / lanes * lanes - NV; };
       while (L * V > 64 && empty(L) * 4 >= NV + empty(L) && empty(L / 2) < empty(L)) L /= 2;
+      if (tile_hints() && hinted_lanes() > 0) L = hinted_lanes();
     }
     // small problems: more lanes per row until the device has ~8 wavefronts per CU
     // (a row that will be cut into column tiles anyway is not a small problem)
@@ -478,8 +483,8 @@ struct Scheduler {
       }
     }
     if (chunked) WG = L;  // one row per workgroup
-    if (tiled_transpose) WG = std::max(64, L * std::min(tt_rows, std::max(4, pow2_ceil(R))));
-    if (opt.has_hint && opt.hint.wg_threads > 0 && !chunked && !tiled_transpose) {
+    if (tiled_transpose) WG = std::max(64, std::min(1024, L * std::min(tt_rows, std::max(4, pow2_ceil(std::min(R, 1024))))));
+    if (opt.has_hint && opt.hint.wg_threads > 0 && !chunked && (!tiled_transpose || tile_hints())) {
       const int h = opt.hint.wg_threads;
       if (h % 64 == 0 && h >= L && h <= 1024) WG = h;
     }
@@ -594,7 +599,7 @@ struct Scheduler {
       while (s.U > 1 && s.U * narrow_trip_regs + narrow_regs > kNarrowRegs) s.U /= 2;
     }
     if (opt.has_hint && opt.hint.tiles_per_trip >= 1 && opt.hint.tiles_per_trip <= 4) s.U = opt.hint.tiles_per_trip;
-    if (has_concat) s.U = 1;
+    if (has_concat || tiled_transpose) s.U = 1;
     // two fold levels at most: the smallest fan-in whose square covers the grid (one level for narrow tiles of up to 16 workgroups)
     // (64 workgroups per fold: 16 measured 9 % faster than 8 on column sums of [16384,4096], 44.6 against 48.8 us)
     s.fan_in = s.RB <= 16 && narrow_tiles ? 16 : s.RB <= 32 ? 8 : s.RB <= 256 ? 16 : 32;

@@ -1062,3 +1062,25 @@ def test_hints_on_narrow_column_tiles(tmp_path, monkeypatch):
         chosen.destroy()
         other.destroy()
     base.destroy()
+
+
+def test_hints_on_narrow_transposes():
+    def info(rows, cols, dt="f32", **hint):
+        g = Graph()
+        g.set_outputs([g.transpose(g.input(rows, cols, dt))])
+        p = fs.Plan(g, hint=hint or None)
+        gi = p.group_info(0)
+        p.destroy()
+        return gi
+
+    assert info(4000, 64)["wg_threads"] == 512
+    for wg in (64, 256, 1024):
+        assert info(4000, 64, wg_threads=wg)["wg_threads"] == wg
+    for lanes in (8, 16, 64, 256):
+        gi = info(4000, 64, lanes_per_row=lanes)
+        assert gi["lanes_per_row"] == lanes and lanes <= gi["wg_threads"] <= 1024
+    gi = info(4000, 200, "bf16", lanes_per_row=32, wg_threads=256)
+    assert gi["lanes_per_row"] == 32 and gi["wg_threads"] == 256 and gi["lds_bytes"] <= 65536
+    assert info(4000, 64, max_workgroups=3)["grid"] == 3
+    # wider tensors keep their tiles
+    assert info(4000, 1024, lanes_per_row=64, wg_threads=256) == info(4000, 1024)

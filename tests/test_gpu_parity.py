@@ -1040,6 +1040,18 @@ def test_narrow_transposes_by_tiles(rows, cols):
         both_modes(g, ins, f"narrow transpose {dt} {rows}x{cols}")
 
 
+@pytest.mark.parametrize("hint", [{"wg_threads": 64}, {"wg_threads": 1024}, {"lanes_per_row": 64, "wg_threads": 256}, {"lanes_per_row": 256, "max_workgroups": 5},
+                                  {"lanes_per_row": 32, "wg_threads": 1024, "tiles_per_trip": 2}])
+def test_narrow_transposes_under_hints(hint):
+    from workloads import patterns
+    for rows, cols in ((4097, 17), (333, 64), (1025, 139), (65, 255)):
+        for dt in ("f32", "bf16"):
+            g = patterns.transpose(rows, cols, dt)
+            xs = RNG.standard_normal((rows, cols)).astype(np.float32)
+            ins = [f32_to_bf16_bits(xs) if dt == "bf16" else xs]
+            check_all(g, run_graph(g, ins, hint=hint), Reference(g, ins), f"narrow transpose {dt} {rows}x{cols} {hint}")
+
+
 def test_gpu_matches_the_stored_small_cases():
     # the tiny hand-checkable cases of tests/golden/oracle_small_cases.json (written by the oracle alone), on the GPU
     import json
