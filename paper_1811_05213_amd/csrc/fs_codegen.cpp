@@ -846,7 +846,7 @@ struct Emitter {
     // CW columns are folded together: the whole row, or one column tile
     // (RB, the number of workgroups that fold together, only where something is folded: a kernel without column
     // reductions has the same text, hence the same compiled code, whatever the number of rows)
-    os << "  constexpr int CW = " << (ctile ? "NVL * L * V" : "(C + 3) / 4 * 4") << ", RB = " << (K > 0 || ctile ? s.RB : 1) << ";\n";
+    os << "  constexpr int CW = " << (ctile ? "NVL * L * V" : std::to_string(K > 0 ? s.fold_width : C)) << ", RB = " << (K > 0 || ctile ? s.RB : 1) << ";\n";
     if (ctile) os << "  const int tile = (int)blockIdx.x % CT, rb = (int)blockIdx.x / CT, vbase = tile * (NVL * L);\n";
     else os << "  const int tile = 0, rb = (int)blockIdx.x;\n";
     os << "  (void)tile; (void)rb; (void)CW; (void)RB;\n";
@@ -1232,7 +1232,7 @@ struct Emitter {
 
     // ---- epilogue: finish the column reductions ----
     if (K > 0) {
-      const int CW = ctile ? s.NVL * s.L * s.V : (C + 3) / 4 * 4;
+      const int CW = s.fold_width;
       const int FV = CW % 4 == 0 ? 4 : CW % 2 == 0 ? 2 : 1;
       os << "  {\n    constexpr int FV = " << FV << ";\n    typedef fs_colfold<" << K << ", CW, WG, FV> S;\n    float cv[S::CPT][FV];\n";
       for (int k = 0; k < K; ++k) {

@@ -129,7 +129,6 @@ struct Scheduler {
   int narrow_lanes = 0, narrow_trip_regs = 0, narrow_regs = 0;  // narrow column tiles: lanes, registers a trip's rows take, and accumulators and [1,C] operands
   int L = 64, tt_rows = 64, NVL = 1, CT = 1, NVLC = 0, RESV = 0, WG = 256;
   bool staged_loop = false;
-  int fold_width = 0;
 
   Scheduler(const Graph& g_, const PlanOptions& opt_, GroupPlan* gp_) : g(g_), opt(opt_), gp(gp_), s(gp_->s), R(gp_->R), C(gp_->C) {}
 
@@ -619,7 +618,18 @@ struct Scheduler {
     int fixed = 0, loop_bytes = 0, fold_bytes = 0;
     if (rowred && L > 64) fixed += 2 * s.G * (L / 64) * gp->max_batched_reduces * 4;
     if (split_rows) fixed += 16 + (int)gp->row_reduces.size() * 4;
-    fold_width = col_tiled ? NVL * L * V : (C + 3) / 4 * 4;  // columns one workgroup folds (whole 16-byte chunks)
+    // Columns one workgroup folds: its tile, or the row rounded up to 16-byte chunks, one chunk of every reduction per lane and
+    // round.  Not where that needs another round for less than half of the workgroup: there the row as it is, in the chunks that
+    // divide it (column sums and maxima + row norms f32 [14396,1101] 26.3 us rounded, 23.3 as it is, [10000,2101] 38.8 and 35.8;
+    // with one round or a full last one the rounded row is faster: [14396,1001] 18.7 and 21.5, [12000,1801] 32.7 and 35.1; so it
+    // is with a lane or two in the last one: [12000,1025] 21.7 and 22.9, LayerNorm backward [2500,4099] 50.9 and 58.3).
+    s.fold_width = col_tiled ? NVL * L * V : C;
+    if (!col_tiled && C % 4 != 0) {
+      const int64_t chunks = (int64_t)gp->col_reduces.size() * ((C + 3) / 4);
+      const int last = (int)(chunks % WG);
+      if (chunks <= WG || last < 16 || last >= WG / 2) s.fold_width = (C + 3) / 4 * 4;
+    }
+    const int fold_width = s.fold_width;
     s.fold_piece = fold_width;
     if (colred) {
       // the fold area takes at most half of the budget: wide rows pass through it in pieces
@@ -683,7 +693,7 @@ struct Scheduler {
       gp->part_bytes = s.part_stride_floats * R * 4;
     }
     if (colred) {
-      const size_t kc = gp->col_reduces.size() * (size_t)fold_width;
+      const size_t kc = gp->col_reduces.size() * (size_t)s.fold_width;
       int n = s.RB;
       while (n > 1) {
         s.part_stride_floats += (size_t)n * kc;

@@ -117,6 +117,7 @@ struct Schedule {
   int lds_bytes = 0;    // static LDS of the generated kernel
   int lds_planned = 0;  // ... as planned before code generation (an upper bound of lds_bytes)
   int fan_in = 32;  // column-reduction tree fan-in
+  int fold_width = 0;  // columns a workgroup folds: its column tile, or the row, rounded up to 16-byte chunks where that pays
   int fold_piece = 0;  // columns that pass through the in-workgroup fold area at a time
   bool stage_rowv = false;  // [1,C] inputs are staged once per workgroup in LDS
   // Looping workgroups that stage their [1,C] operands before the loop ask for the first trip's rows before the staging

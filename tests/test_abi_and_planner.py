@@ -1084,3 +1084,13 @@ def test_hints_on_narrow_transposes():
     assert info(4000, 64, max_workgroups=3)["grid"] == 3
     # wider tensors keep their tiles
     assert info(4000, 1024, lanes_per_row=64, wg_threads=256) == info(4000, 1024)
+
+
+@pytest.mark.parametrize("rows,cols,width", [(14396, 1101, 1101), (10000, 2101, 2101), (14396, 1001, 1004), (12000, 1801, 1804), (12000, 1025, 1028), (5000, 1002, 1004)])
+def test_rows_that_column_folds_round_up(rows, cols, width):
+    # a row is folded in 16-byte chunks, a chunk of every reduction per lane and round; not where rounding it up to whole
+    # chunks takes another round for less than half of a workgroup
+    p = fs.Plan(multi_reduce_graph(rows, cols))
+    assert p.stats()["num_launches"] == 1 and p.group_info(0)["num_col_reduces"] == 2
+    assert f"constexpr int CW = {width}, RB = 256" in p.group_source(0)
+    p.destroy()
