@@ -128,6 +128,7 @@ struct Scheduler {
   // lanes, vectors, workgroup
   int narrow_lanes = 0, narrow_trip_regs = 0, narrow_regs = 0;  // narrow column tiles: lanes, registers a trip's rows take, and accumulators and [1,C] operands
   int L = 64, tt_rows = 64, NVL = 1, CT = 1, NVLC = 0, RESV = 0, WG = 256;
+  bool in_pairs = false;  // bf16 rows read two elements at a time (pick_vector_width)
   bool staged_loop = false;
 
   Scheduler(const Graph& g_, const PlanOptions& opt_, GroupPlan* gp_) : g(g_), opt(opt_), gp(gp_), s(gp_->s), R(gp_->R), C(gp_->C) {}
@@ -185,6 +186,34 @@ struct Scheduler {
     NV = (C + V - 1) / V;
     rowred = !gp->row_reduces.empty();
     colred = !gp->col_reduces.empty();
+    return FS_OK;
+  }
+
+  // Vectors that a width does not fill cost arithmetic as well as bytes: a lane computes on what its empty slots repeat.  bf16 rows
+  // with transcendental functions take pairs of elements instead (one 4-byte access each) where that leaves an eighth of the slots
+  // or more out: masked softmax bf16 [4000,577] (1024 slots a row, 640 in pairs; element by element 5.2 us) 6.4 -> 4.7 us,
+  // [6387,289] 5.7 -> 4.5, [16384,577] 11.4 -> 9.9, softmax bf16 [80000,577] 49.7 -> 44.6, [1500,4099] 5.8 -> 4.9.  Not without them
+  // (L2 normalisation [43000,289] 10.2 -> 10.6 us, row sums 8.9 -> 13.1), not with [1,C] operands, whose slices take more accesses too
+  // (LayerNorm+GeLU [4700,577] 5.2 -> 5.7), not for rows of 128 elements and less ([200000,65] 13.8 -> 15.7) or beyond 32
+  // per lane ([1323,33001] 76.2 -> 81.7), and not in fp32 (masked softmax [8004,131] 4.3 -> 4.6 us).
+  fs_status pick_vector_width() {
+    bool heavy = false, rowv = false;
+    for (int m : gp->members) {
+      const int op = g.nodes[m].opcode;
+      heavy |= gp->kind.at(m) == KIND_FULL && (op == FS_EXP || op == FS_LOG || op == FS_TANH || op == FS_SIGMOID || op == FS_GELU_TANH);
+    }
+    for (const ExtTensor& e : gp->ext_in) rowv |= e.kind == KIND_ROWV;
+    if (!heavy || rowv || max_es != 2 || V != 8 || C % V == 0 || !rowred || colred || has_transposed || chunked || CT > 1 || C <= 128 || C > 32768)
+      return FS_OK;
+    const int slots = NVL * L * V;
+    for (int v : {2, V}) {
+      V = v;
+      NV = (C + V - 1) / V;
+      fs_status st;
+      if ((st = pick_row_form()) != FS_OK || (st = pick_lanes()) != FS_OK || (st = pick_vectors()) != FS_OK) return st;
+      in_pairs = V == 2 && !chunked && CT == 1 && NVL * L * V * 8 <= slots * 7;
+      if (in_pairs) break;
+    }
     return FS_OK;
   }
 
@@ -500,6 +529,7 @@ struct Scheduler {
     s.E = s.NVL * V;
     s.WG = WG;
     s.G = WG / L;
+    s.shares_lines = C % V != 0 || in_pairs;
     s.ragged = C % V != 0 || (!resident && (int64_t)CT * NVL * L != NV);
     s.resident = resident;
     s.NVLC = NVLC;
@@ -713,6 +743,7 @@ struct Scheduler {
     if ((st = pick_row_form()) != FS_OK) return st;
     if ((st = pick_lanes()) != FS_OK) return st;
     if ((st = pick_vectors()) != FS_OK) return st;
+    if ((st = pick_vector_width()) != FS_OK) return st;
     if ((st = pick_workgroup()) != FS_OK) return st;
     if ((st = fill_schedule()) != FS_OK) return st;
     if ((st = pick_grid()) != FS_OK) return st;
@@ -923,7 +954,7 @@ fs_status analyse_group(const Graph& g, const std::vector<int>& members, const s
   // from cold memory); masked softmax bf16 [32768,577] 22.5 -> 20.4 us (22.5 -> 22.8 us).  Not for groups that only stream
   // (no difference) or fold columns ([60001,515]: 33.3 -> 35.5 us).
   // So do the narrow tiles of small column folds.
-  if (st == FS_OK && ((gp.C % gp.s.V != 0 && !gp.row_reduces.empty() && gp.col_reduces.empty()) || (gp.s.narrow_tiles && gp.s.L < 32)))
+  if (st == FS_OK && ((gp.s.shares_lines && !gp.row_reduces.empty() && gp.col_reduces.empty()) || (gp.s.narrow_tiles && gp.s.L < 32)))
     for (ExtTensor& e : gp.ext_in) e.streaming = false;
   if (st == FS_OK && gp.s.chunked)  // every stage reads the row again: keep it in the caches
     for (ExtTensor& e : gp.ext_in) e.streaming = false;

@@ -163,6 +163,7 @@ struct Schedule {
   // Column reductions over rows too wide for one workgroup: CT column tiles, each folded by its own
   // RB = grid / CT workgroups (tile = block % CT).  Strides of one tile's scratch in the workspace:
   bool col_tiled = false;
+  bool shares_lines = false;  // rows are no multiple of 16 bytes and are read in vectors all the same: neighbours share cache lines
   bool narrow_tiles = false;  // ... tiles of 8, 16 or 32 lanes with one vector each, a workgroup or a few of them per tile (tensors below 128 MB)
   int RB = 0;
   size_t part_stride_floats = 0;

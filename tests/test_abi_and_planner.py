@@ -1094,3 +1094,18 @@ def test_rows_that_column_folds_round_up(rows, cols, width):
     assert p.stats()["num_launches"] == 1 and p.group_info(0)["num_col_reduces"] == 2
     assert f"constexpr int CW = {width}, RB = 256" in p.group_source(0)
     p.destroy()
+
+
+@pytest.mark.parametrize("rows,cols,vec", [(4000, 577, 2), (16384, 577, 2), (6387, 289, 2), (16384, 289, 8), (4000, 401, 8), (40000, 65, 8), (1500, 4099, 2),
+                                           (4000, 576, 8), (500, 33001, 8)])
+def test_bf16_rows_in_pairs(rows, cols, vec):
+    # rows with exponentials take two elements per access where that leaves an eighth of the slots or more out
+    from workloads import patterns
+    p = fs.Plan(patterns.masked_softmax(rows, cols, "bf16"))
+    gi = p.group_info(0)
+    assert p.stats()["num_launches"] == 1 and gi["vec_elems"] == vec, gi
+    p.destroy()
+    for g in (patterns.masked_softmax(rows, cols, "f32"), layernorm_gelu_graph(rows, cols)):  # not in fp32, nor with [1,C] operands
+        p = fs.Plan(g)
+        assert p.group_info(0)["vec_elems"] != 2, p.group_info(0)
+        p.destroy()

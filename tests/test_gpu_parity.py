@@ -982,6 +982,16 @@ def test_rows_whose_last_vector_overlaps_its_neighbour(rows, cols):
     plan.destroy()
 
 
+@pytest.mark.parametrize("rows,cols", [(8001, 129), (6387, 289), (2049, 577), (4100, 334), (9, 8195), (3, 20001), (2000, 1270)])
+def test_bf16_rows_in_pairs(rows, cols):
+    # two elements per access, an odd last one overlapping its neighbour: exponentials between two row reductions
+    from workloads import patterns
+    g = patterns.masked_softmax(rows, cols, "bf16")
+    x = (8 * RNG.standard_normal((rows, cols))).astype(np.float32)
+    m = np.where(np.arange(cols)[None, :] < RNG.integers((cols + 1) // 2, cols + 1, (rows, 1)), 0.0, -30000.0).astype(np.float32)
+    both_modes(g, [f32_to_bf16_bits(x), f32_to_bf16_bits(m)], f"masked softmax bf16 {rows}x{cols}")
+
+
 @pytest.mark.parametrize("rows,cols", [(2, 31), (127, 33), (129, 64), (513, 65), (1030, 577), (2100, 36), (8300, 100), (17000, 31)])
 def test_small_column_folds_by_narrow_tiles(rows, cols):
     # tiles of 128 bytes: one column past a tile, one row past a workgroup's trip, one / a few / many workgroups per tile, several
