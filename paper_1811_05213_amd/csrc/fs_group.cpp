@@ -370,12 +370,16 @@ struct Scheduler {
     // 107 us, 16 x 2 38 us, 32 x 1 49 us; [200000,161]: 16 x 3 54 us, 32 x 2 45 us; masked softmax bf16 [32768,577]: 32 x 3
     // 22.5 us, 64 x 2 25.7 us).  Runs of whole cache lines (rows of a multiple of 128 bytes, 8 lanes or more) have no such
     // remainder: there the fewest empty slots win (masked softmax bf16 [32768,320]: 16 x 3 12.7 us, 32 x 2 14.9 us).
+    // Three on 32 lanes only while rows of 4-element vectors fit the caches: from 64 MB on 64 x 2 streams better (softmax fp32
+    // [43024,342] 22.9 -> 21.3 us, [82695,317] 39.4 -> 37.2, residual+LayerNorm fp32 [27212,289] 21.3 -> 20.5, masked softmax fp32
+    // [36282,289] 23.5 -> 21.8; below, softmax [20000,289] 9.4 -> 9.5, [5442,289] 4.0 -> 4.5).
     if (rowred && !colred && L > l_min && l_min >= 1) {
       const auto waste = [&](int lanes) { return (int64_t)((NV + lanes - 1) / lanes) * lanes - NV; };
+      const bool streams = V == 4 && gp->min_hbm_bytes >= (64u << 20);
       if (waste(L) * 4 >= NV + waste(L))
         for (int l = L / 2; l >= std::max(l_min, 4); l /= 2) {
           const bool whole_lines = (int64_t)C * max_es % 128 == 0 && l >= 8;
-          if (whole_lines ? waste(l) < waste(L) : (NV + l - 1) / l <= (l >= 32 || (l >= 16 && V >= 8) ? 3 : 2) && waste(l) <= waste(L)) L = l;
+          if (whole_lines ? waste(l) < waste(L) : (NV + l - 1) / l <= (l >= (streams ? 64 : 32) || (l >= 16 && V >= 8) ? 3 : 2) && waste(l) <= waste(L)) L = l;
         }
     }
     if (rowred && !colred && C * max_es <= 32) L = 1;

@@ -1109,3 +1109,11 @@ def test_bf16_rows_in_pairs(rows, cols, vec):
         p = fs.Plan(g)
         assert p.group_info(0)["vec_elems"] != 2, p.group_info(0)
         p.destroy()
+
+
+@pytest.mark.parametrize("rows,cols,lanes", [(20000, 289, 32), (43024, 342, 64), (82695, 317, 64), (43024, 384, 32)])
+def test_odd_rows_that_stream_keep_a_wavefront(rows, cols, lanes):
+    # 72 to 96 vectors a row: 32 lanes of three while the tensors fit the caches, 64 of two beyond (whole cache lines: 32)
+    p = fs.Plan(softmax_graph(rows, cols))
+    assert p.group_info(0)["lanes_per_row"] == lanes
+    p.destroy()
