@@ -24,6 +24,7 @@
 //     paths either; elsewhere the result moves by one rounding, as with the fma contraction.
 #include <cstdlib>
 #include <algorithm>
+#include <cmath>
 #include <cstring>
 #include <functional>
 #include <set>
@@ -123,8 +124,37 @@ struct Emitter {
     return name(src, k) + "[e]";
   }
 
+  // A node that only flips the sign of one operand (a negation, or what the compiler makes one of: x * -1, x / -1, -0 - x):
+  // that operand, else -1.
+  int flipped_operand(int id) const {
+    const fs_node& n = g.nodes[id];
+    auto is_literal = [&](int k, float v) {
+      const int src = source_of(n.in[k]);
+      return g.nodes[src].opcode == FS_CONST && g.nodes[src].attr_f == v && std::signbit(g.nodes[src].attr_f);
+    };
+    if (n.opcode == FS_NEG) return n.in[0];
+    if (n.opcode == FS_MUL && is_literal(1, -1.0f)) return n.in[0];
+    if (n.opcode == FS_MUL && is_literal(0, -1.0f)) return n.in[1];
+    if (n.opcode == FS_DIV && is_literal(1, -1.0f)) return n.in[0];
+    if (n.opcode == FS_SUB && is_literal(0, -0.0f)) return n.in[1];
+    return -1;
+  }
+  // is the value of `id` rounded to bf16, by itself or by a user that does nothing else to it?
+  bool becomes_bf16(int id) const {
+    if (g.nodes[id].dtype == FS_BF16) return true;
+    for (int u : g.users[id]) {
+      const int op = g.nodes[u].opcode;
+      if (op == FS_CONVERT ? g.nodes[u].dtype == FS_BF16 : op == FS_TRANSPOSE || op == FS_BCAST_ROWVEC || op == FS_BCAST_COLVEC || op_is_view(op) ? becomes_bf16(u) : false) return true;
+    }
+    return false;
+  }
+
   std::string expr(int id) {
     const fs_node& n = g.nodes[id];
+    // (the run-time compiler ends the process, "cannot select", on a float negation that two neighbouring conversions to bf16
+    // consume, when packed fp32 instructions are off; on the bits it is an ordinary xor, the same result)
+    const int flipped = flipped_operand(id);
+    if (flipped >= 0 && becomes_bf16(id)) return "fs_neg(" + ref(flipped) + ")";
     auto A = [&]() { return ref(n.in[0]); };
     auto B = [&]() { return ref(n.in[1]); };
     auto Cc = [&]() { return ref(n.in[2]); };

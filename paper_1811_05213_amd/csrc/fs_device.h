@@ -91,6 +91,12 @@ FS_DEV float fs_exp(float x) {
   const float p = __builtin_amdgcn_exp2f(t);
   return __builtin_fmaf(p, r * FS_LN2, p);
 }
+// -x on the bits; the empty statement keeps the compiler from making a float negation of it again
+FS_DEV float fs_neg(float x) {
+  fs_u32 u = __builtin_bit_cast(fs_u32, x) ^ 0x80000000u;
+  asm("" : "+v"(u));
+  return __builtin_bit_cast(float, u);
+}
 FS_DEV float fs_log(float x) { return __builtin_amdgcn_logf(x) * FS_LN2; }
 FS_DEV float fs_rcp(float x) { return __builtin_amdgcn_rcpf(x); }
 FS_DEV float fs_rsqrt(float x) { return __builtin_amdgcn_rsqf(x); }

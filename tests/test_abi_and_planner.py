@@ -1117,3 +1117,34 @@ def test_odd_rows_that_stream_keep_a_wavefront(rows, cols, lanes):
     p = fs.Plan(softmax_graph(rows, cols))
     assert p.group_info(0)["lanes_per_row"] == lanes
     p.destroy()
+
+
+def _sign_flips(rows, cols):
+    """Graphs whose bf16 results are negations: of a loaded value, of a computed one, and what a compiler makes one of."""
+    def graph(f):
+        g = Graph()
+        x = g.input(rows, cols, "bf16")
+        g.set_outputs([f(g, x, g.unary("convert", x, "f32"))])
+        return g
+
+    yield graph(lambda g, x, f: g.unary("neg", x))
+    yield graph(lambda g, x, f: g.unary("convert", g.unary("neg", f), "bf16"))
+    yield graph(lambda g, x, f: g.unary("neg", g.unary("abs", x)))
+    yield graph(lambda g, x, f: g.unary("neg", g.binary("add", x, x)))
+    yield graph(lambda g, x, f: g.unary("convert", g.unary("neg", g.unary("exp", f)), "bf16"))
+    yield graph(lambda g, x, f: g.unary("convert", g.binary("mul", f, g.const(-1.0, rows, cols)), "bf16"))
+    yield graph(lambda g, x, f: g.unary("convert", g.binary("div", f, g.const(-1.0, rows, cols)), "bf16"))
+    yield graph(lambda g, x, f: g.unary("convert", g.binary("sub", g.const(-0.0, rows, cols), f), "bf16"))
+    yield graph(lambda g, x, f: g.transpose(g.unary("neg", x)))
+    yield graph(lambda g, x, f: g.unary("neg", g.transpose(x)))
+
+
+@pytest.mark.parametrize("rows,cols", [(100, 1000), (100, 1001), (50, 37)])
+def test_negated_bf16_results_compile(rows, cols):
+    # the run-time compiler ended the process on these ("cannot select"): plan in a process of its own
+    import subprocess
+    import sys
+    code = ("import sys; sys.path[:0] = [%r, %r]\nimport paper_1811_05213_amd as fs\nfrom test_abi_and_planner import _sign_flips\n"
+            "for g in _sign_flips(%d, %d): fs.Plan(g).destroy()\nprint('planned')" % (ROOT, os.path.join(ROOT, "tests"), rows, cols))
+    r = subprocess.run([sys.executable, "-c", code], capture_output=True, text=True)
+    assert r.returncode == 0 and "planned" in r.stdout, r.stderr[-500:]

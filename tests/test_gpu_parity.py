@@ -1015,6 +1015,17 @@ def test_small_column_folds_by_narrow_tiles(rows, cols):
                f"batchnorm {rows}x{cols}")
 
 
+@pytest.mark.parametrize("rows,cols", [(40, 1000), (33, 1001), (50, 37)])
+def test_negated_bf16_results(rows, cols):
+    from test_abi_and_planner import _sign_flips
+    x = f32_to_bf16_bits(RNG.standard_normal((rows, cols)).astype(np.float32))
+    for k, g in enumerate(_sign_flips(rows, cols)):
+        check_all(g, run_graph(g, [x]), Reference(g, [x]), f"sign flip {k} {rows}x{cols}")
+    x.reshape(-1)[:4] = (0x0000, 0x8000, 0x7F80, 0xFF80)  # zeros and infinities of both signs
+    for g in list(_sign_flips(rows, cols))[:2]:
+        assert np.array_equal(run_graph(g, [x])[0], x ^ 0x8000)
+
+
 @pytest.mark.parametrize("hint", [{"max_workgroups": 1}, {"max_workgroups": 30}, {"lanes_per_row": 16}, {"lanes_per_row": 64, "wg_threads": 256},
                                   {"lanes_per_row": 8, "wg_threads": 64, "tiles_per_trip": 3}, {"tiles_per_trip": 1}, {"lanes_per_row": 32, "max_workgroups": 7}])
 def test_narrow_column_tiles_under_hints(hint):
