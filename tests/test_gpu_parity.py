@@ -1020,6 +1020,8 @@ def test_negated_bf16_results(rows, cols):
     from test_abi_and_planner import _sign_flips
     x = f32_to_bf16_bits(RNG.standard_normal((rows, cols)).astype(np.float32))
     for k, g in enumerate(_sign_flips(rows, cols)):
+        run_graph(g, [x])
+        g = expose_bf16_nodes(g)
         check_all(g, run_graph(g, [x]), Reference(g, [x]), f"sign flip {k} {rows}x{cols}")
     x.reshape(-1)[:4] = (0x0000, 0x8000, 0x7F80, 0xFF80)  # zeros and infinities of both signs
     for g in list(_sign_flips(rows, cols))[:2]:
