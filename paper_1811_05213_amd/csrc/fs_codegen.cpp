@@ -848,7 +848,7 @@ struct Emitter {
     os << "  constexpr int V = " << s.V << ", NVL = " << s.NVL << ", L = " << s.L << ", NV = " << s.NV << ", E = NVL * V, WG = " << s.WG
        << ", G = WG / L, C = " << C << ", CT = " << s.CT << ";\n";
     // (0: all vectors lie inside the row; else 1 + what the last vector overlaps its neighbour by)
-    const int over = s.NV * s.V - C;
+    const int over = (int)((int64_t)s.NV * s.V - C);
     os << "  constexpr int RAGGED = " << (s.ragged ? 1 + over : 0) << ";\n";
     os << "  const int tid = (int)threadIdx.x, lir = tid & (L - 1), rg = tid / L;\n";
     os << "  const long R = a.R;\n";
@@ -1273,7 +1273,7 @@ struct Emitter {
       os << "    if (fs_colred_fold_grid<" << K << ", CW, WG, FV, " << s.fan_in << ", " << kname << "_kinds>(cv, a.part + (long)tile * "
          << s.part_stride_floats << "L, a.tickets + tile * " << s.ticket_stride << ", &lds_flag, (fs_u32)rb, (fs_u32)RB)) {\n";
       os << "      _Pragma(\"unroll\") for (int i = 0; i < S::CPT; ++i) {\n        const int c = tid + i * WG;\n"
-         << "        if (c < S::NCH) {\n          const int k = c / S::CH, col0 = tile * CW + (c % S::CH) * FV;\n";
+         << "        if (c < S::NCH) {\n          const int k = c / S::CH; const fs_col_index<C>::type col0 = (fs_col_index<C>::type)tile * CW + (c % S::CH) * FV;\n";
       for (int k = 0; k < K; ++k) {
         const int m = gp.col_reduces[k];
         const ExtTensor* e = find_out(m);

@@ -197,10 +197,20 @@ template <int DT, int V, bool NT = false, bool UA = false> FS_DEV void fs_store_
 // RAGGED: 0 = every vector index of the slice lies inside a row of NV whole vectors; 1 + D = indices may fall beyond the row,
 // and the last vector overlaps its neighbour by D elements (C = NV*V - D).
 constexpr int fs_overlap(int ragged) { return ragged > 0 ? ragged - 1 : 0; }
-constexpr int fs_cols(int v, int nv, int ragged) { return nv * v - fs_overlap(ragged); }
+constexpr int fs_cols(int v, int nv, int ragged) { return (int)((long)nv * v - fs_overlap(ragged)); }
 // One expression serves both the clamp of vectors beyond the row and the overlapping last vector.
-template <int V, int C> FS_DEV int fs_vec_col(int vi) { return vi * V < C - V ? vi * V : C - V; }
-template <int V, int C> FS_DEV int fs_vec_skip(int vi) { return vi * V < C - V ? 0 : vi * V - (C - V); }
+// (Columns beyond the row stay below 2^31 for rows of up to 2^30; longer ones compare vector indices.)
+constexpr int FS_COLS_INT = 1 << 30;
+template <int V, int C> FS_DEV int fs_vec_col(int vi) {
+  if constexpr (C > FS_COLS_INT) return vi < C / V ? vi * V : C - V;
+  return vi * V < C - V ? vi * V : C - V;
+}
+template <int V, int C> FS_DEV int fs_vec_skip(int vi) {
+  if constexpr (C > FS_COLS_INT) return vi < C / V ? 0 : (vi - C / V) * V + (C % V ? V - C % V : V);
+  return vi * V < C - V ? 0 : vi * V - (C - V);
+}
+template <int C, bool BIG = (C > FS_COLS_INT)> struct fs_col_index { typedef int type; };
+template <int C> struct fs_col_index<C, true> { typedef long type; };
 // column of vector vi, clamped into the row
 template <int V, int NV, int RAGGED> FS_DEV long fs_col_of(int vi) {
   if constexpr (fs_overlap(RAGGED) != 0) return fs_vec_col<V, fs_cols(V, NV, RAGGED)>(vi);
@@ -427,7 +437,7 @@ FS_DEV void fs_store_tile_transposed(const float (&src)[NVL * V], float* lds, vo
   constexpr int WANT = 16 / (int)sizeof(typename fs_elem<DT>::type);
   constexpr int RUN = (G % WANT == 0) ? WANT : (G % 4 == 0) ? 4 : 1;
   constexpr int RPC = G / RUN;  // runs per output row
-  const int col0 = vbase * V;
+  const typename fs_col_index<C>::type col0 = (typename fs_col_index<C>::type)vbase * V;
   for (int i = (int)threadIdx.x; i < TC * RPC; i += WG) {
     const int c = i / RPC, g0 = (i % RPC) * RUN;
     const long r = tile_row0 + g0;

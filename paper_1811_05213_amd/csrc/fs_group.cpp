@@ -17,7 +17,7 @@ int pow2_floor(int x) {
 }
 int pow2_ceil(int x) {
   int p = 1;
-  while (p < x) p <<= 1;
+  while (p < x && p < (1 << 30)) p <<= 1;
   return p;
 }
 
@@ -179,11 +179,11 @@ struct Scheduler {
     // A kernel that holds its whole plan keeps them ([60000,65] fp32 softmax 30.1 -> 8.4 us, [256,1001] 3.5 -> 3.0 us), and
     // so does one that streams 32 MB or more.
     const bool keeps_order = !gp->row_reduces.empty() && gp->exchanges && gp->min_hbm_bytes < kStreamBytes;
-    while (has_concat || narrow_transposed || keeps_order || C * max_es <= 32 ? C % V != 0 : V > C) V /= 2;
+    while (has_concat || narrow_transposed || keeps_order || (int64_t)C * max_es <= 32 ? C % V != 0 : V > C) V /= 2;
     for (int m : gp->members)
       if (g.nodes[m].opcode == FS_CONCAT && g.nodes[m].attr_i == FS_CONCAT_COLS)
         while (g.nodes[g.nodes[m].in[0]].cols % V) V /= 2;
-    NV = (C + V - 1) / V;
+    NV = C / V + (C % V != 0);
     rowred = !gp->row_reduces.empty();
     colred = !gp->col_reduces.empty();
     return FS_OK;
@@ -208,7 +208,7 @@ struct Scheduler {
     const int slots = NVL * L * V;
     for (int v : {2, V}) {
       V = v;
-      NV = (C + V - 1) / V;
+      NV = C / V + (C % V != 0);
       fs_status st;
       if ((st = pick_row_form()) != FS_OK || (st = pick_lanes()) != FS_OK || (st = pick_vectors()) != FS_OK) return st;
       in_pairs = V == 2 && !chunked && CT == 1 && NVL * L * V * 8 <= slots * 7;
@@ -382,7 +382,7 @@ struct Scheduler {
           if (whole_lines ? waste(l) < waste(L) : (NV + l - 1) / l <= (l >= (streams ? 64 : 32) || (l >= 16 && V >= 8) ? 3 : 2) && waste(l) <= waste(L)) L = l;
         }
     }
-    if (rowred && !colred && C * max_es <= 32) L = 1;
+    if (rowred && !colred && (int64_t)C * max_es <= 32) L = 1;
     else if (rowred && !colred && V == 1 && NV >= 4) L = std::min(L, pow2_ceil(NV) / 2);
     // a transposed root leaves as runs of G = WG/L consecutive elements: at least 16 rows per workgroup
     if (has_transposed && !rowred) L = std::min(L, std::max(l_min, 16));

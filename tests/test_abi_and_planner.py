@@ -1148,3 +1148,46 @@ def test_negated_bf16_results_compile(rows, cols):
             "for g in _sign_flips(%d, %d): fs.Plan(g).destroy()\nprint('planned')" % (ROOT, os.path.join(ROOT, "tests"), rows, cols))
     r = subprocess.run([sys.executable, "-c", code], capture_output=True, text=True)
     assert r.returncode == 0 and "planned" in r.stdout, r.stderr[-500:]
+
+
+def test_column_index_of_overlapping_vectors(tmp_path):
+    # fs_vec_col / fs_vec_skip of fs_device.h, compiled for the host, against 64-bit arithmetic: every vector index of small rows,
+    # and those around the end of rows of nearly 2^31 columns, where a column index beyond the row does not fit 32 bits
+    import subprocess
+    text = open(os.path.join(ROOT, "paper_1811_05213_amd", "csrc", "fs_device.h")).read()
+    a, b = text.index("constexpr int fs_overlap"), text.index("// Load the lane's slice of one row tile")
+    (tmp_path / "t.cpp").write_text("#define FS_DEV static inline\n" + text[a:b] + r"""
+#include <cstdio>
+template <int V, int C> int check(long first, long last) {
+  constexpr int NV = C / V + (C % V != 0), RAG = 1 + (int)((long)NV * V - C);
+  static_assert(fs_cols(V, NV, RAG) == C, "columns");
+  int bad = 0;
+  for (long vi = first; vi < last; ++vi) {
+    const long col = vi * V < C - V ? vi * V : C - V, skip = vi * V - col;  // (clamped to the last V columns)
+    bad += fs_vec_col<V, C>((int)vi) != col || fs_vec_skip<V, C>((int)vi) != skip || fs_col_of<V, NV, RAG>((int)vi) != col;
+    for (int k = 0; k < V; ++k) bad += fs_owned<V, NV, RAG>((int)vi, k) != (col + k >= vi * V && vi < NV);
+  }
+  if (bad) printf("V %d C %d: %d wrong\n", V, C, bad);
+  return bad;
+}
+template <int V, int C> int tail() { return check<V, C>(C / V - 3, C / V + 70000 / V) + check<V, C>(0, 3); }
+int main() {
+  return (check<4, 9>(0, 40) + check<4, 1001>(0, 400) + check<8, 17>(0, 40) + check<8, 577>(0, 200) + check<2, 577>(0, 400) + check<16, 33>(0, 9) +
+          tail<4, 1073741825>() + tail<4, 2147483647>() + tail<8, 2147483641>() + tail<2, 2147483647>() + tail<16, 2147483639>()) != 0;
+}
+""")
+    subprocess.run(["g++", "-std=c++17", "-O1", "-fsanitize=undefined", "-fno-sanitize-recover", "-o", str(tmp_path / "t"), str(tmp_path / "t.cpp")], check=True)
+    r = subprocess.run([str(tmp_path / "t")], capture_output=True, text=True)
+    assert r.returncode == 0, r.stdout + r.stderr
+
+
+@pytest.mark.parametrize("cols,dt,vec", [((1 << 29) + 1, "f32", 4), ((1 << 31) - 1, "f32", 4), ((1 << 31) - 5, "bf16", 8), ((1 << 30) + 3, "bf16", 8)])
+def test_rows_of_up_to_two_to_the_31_columns(cols, dt, vec):
+    for op in ("abs", "row", "col"):
+        g = Graph()
+        x = g.input(1 if op != "col" else 2, cols, dt)
+        g.set_outputs([g.unary("abs", x) if op == "abs" else g.reduce_row("max", x) if op == "row" else g.reduce_col("max", x)])
+        p = fs.Plan(g)
+        gi = p.group_info(p.stats()["num_groups"] - 1)
+        assert gi["vec_elems"] == vec and gi["grid"] >= 256, gi
+        p.destroy()
