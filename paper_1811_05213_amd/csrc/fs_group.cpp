@@ -518,7 +518,7 @@ struct Scheduler {
     if (tiled_transpose) WG = std::max(64, std::min(1024, L * std::min(tt_rows, std::max(4, pow2_ceil(std::min(R, 1024))))));
     if (opt.has_hint && opt.hint.wg_threads > 0 && !chunked && (!tiled_transpose || tile_hints())) {
       const int h = opt.hint.wg_threads;
-      if (h % 64 == 0 && h >= L && h <= 1024) WG = h;
+      if (h % 64 == 0 && h % L == 0 && h <= 1024) WG = h;  // (whole rows: lanes left over would share another row group's slots)
     }
     return FS_OK;
   }

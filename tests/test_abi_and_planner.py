@@ -1191,3 +1191,15 @@ def test_rows_of_up_to_two_to_the_31_columns(cols, dt, vec):
         gi = p.group_info(p.stats()["num_groups"] - 1)
         assert gi["vec_elems"] == vec and gi["grid"] >= 256, gi
         p.destroy()
+
+
+@pytest.mark.parametrize("lanes,wg", [(128, 192), (256, 320), (512, 960), (256, 768)])
+def test_hinted_workgroups_hold_whole_rows(lanes, wg):
+    # a workgroup size that is no multiple of the lanes per row would leave lanes without a row group of their own
+    for g in (softmax_graph(300, 1000), multi_reduce_graph(3000, 1000), _column_sum(3000, 1000)):
+        p = fs.Plan(g, hint={"lanes_per_row": lanes, "wg_threads": wg})
+        for j in range(p.stats()["num_groups"]):
+            gi = p.group_info(j)
+            assert gi["wg_threads"] == gi["rows_per_iter"] * gi["lanes_per_row"], gi
+            assert wg % lanes or gi["lanes_per_row"] != lanes or gi["wg_threads"] == wg
+        p.destroy()
