@@ -311,8 +311,15 @@ struct Scheduler {
     const bool narrow_form = opt.narrow_tiles && colred && !rowred && !has_transposed && !has_concat && R > 1 && narrow_trip_regs + narrow_regs <= kNarrowRegs;
     const uint64_t bytes = gp->min_hbm_bytes;
     narrow_lanes = 0;
-    if (narrow_form && bytes < (16u << 20)) narrow_lanes = R > 16384 ? 16 : 8;
-    else if (narrow_form && row_tensors == 1 && R <= 16384 && bytes < (C % V ? 64u << 20 : 128u << 20)) narrow_lanes = 32;
+    // From 16384 rows on tiles of 16 lanes (column sums f32 [65536,38] 9.0 us, 10.1 of 8 lanes; sums + maxima + row norms [40000,38]
+    // 11.7 and 12.7), 8 for one fp32 reduction whose rows they fill exactly (batch normalisation [40000,64] 24.5 -> 21.0 us,
+    // [20000,64] 22.4 -> 18.7, 21.6 as whole rows).  A plain fold of a tensor that no other kernel reads gains nothing from 16
+    // lanes: [30000,100] 8.8 us as whole rows, 9.6 in tiles, [20000,200] 9.2 and 9.6 (after a kernel that read it too, it does:
+    // [40000,100] with row norms 22.8 and 20.6).
+    if (narrow_form && bytes < (16u << 20)) {
+      narrow_lanes = R > 16384 && NV > 8 && !(NV % 8 == 0 && V == 4 && gp->col_reduces.size() == 1) ? 16 : 8;
+      if (narrow_lanes == 16 && V == 4 && gp->members.size() == 1 && gp->reads_alone) narrow_lanes = 0;
+    } else if (narrow_form && row_tensors == 1 && R <= 16384 && bytes < (C % V ? 64u << 20 : 128u << 20)) narrow_lanes = 32;
     else if (narrow_form && row_tensors > 1 && R >= 128 && R <= 4096 && (int64_t)R * C * max_es < (16 << 20) && bytes < (64u << 20)) narrow_lanes = 8;
     if (narrow_lanes > 0) {
       // Tiles beyond what the device holds at once pay their fixed cost (launch, fold, barriers) in rounds, and rows too few for a
@@ -949,7 +956,12 @@ fs_status analyse_group(const Graph& g, const std::vector<int>& members, const s
   for (const ExtTensor& e : gp.ext_in) gp.min_hbm_bytes += (uint64_t)g.nodes[e.node].rows * g.nodes[e.node].cols * dtype_size(e.dtype);
   for (const ExtTensor& e : gp.ext_out) gp.min_hbm_bytes += (uint64_t)g.nodes[e.node].rows * g.nodes[e.node].cols * dtype_size(e.dtype);
   gp.exchanges = false;
-  for (const ExtTensor& e : gp.ext_in) gp.exchanges |= g.nodes[g.root_of[e.node]].opcode != FS_INPUT;
+  gp.reads_alone = true;
+  for (const ExtTensor& e : gp.ext_in) {
+    const int root = g.root_of[e.node];
+    gp.exchanges |= g.nodes[root].opcode != FS_INPUT;
+    gp.reads_alone &= e.kind != KIND_FULL || (g.nodes[root].opcode == FS_INPUT && used_only_here(root));
+  }
   for (const ExtTensor& e : gp.ext_out) gp.exchanges |= !used_only_here(e.node);
 
   const fs_status st = choose_schedule(g, opt, &gp);

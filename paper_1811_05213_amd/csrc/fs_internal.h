@@ -200,6 +200,7 @@ struct GroupPlan {
   size_t ticket_offset = 0;
   int n_tickets = 0;
   uint64_t min_hbm_bytes = 0;
+  bool reads_alone = true; // no other kernel of the plan touches the [R,C] tensors it reads
   bool exchanges = false;  // reads what another kernel of the plan wrote, or writes what another one reads
   // generated kernel
   std::string kernel_name, source;

@@ -1001,6 +1001,7 @@ def _column_sum(rows, cols, inputs=1, dt="f32", moments=False):
     (2000, 1000, 1, 8, False), (500, 500, 8, 8, False), (1000, 4000, 4, 8, False),        # below 16 MB in all; several inputs to 64 MB
     (4096, 1000, 8, 64, True), (16000, 255, 4, 32, True), (16000, 100, 8, 16, True),   # 125 MB in all; too tall
     (4096, 7680, 1, 32, False), (4096, 7681, 1, 64, True), (4096, 3841, 1, 32, False),   # one tensor: rows of whole vectors to 128 MB, others to 64 MB
+    (40000, 64, 1, 8, False), (30000, 100, 1, 16, True),             # tall: rows that tiles of 8 lanes fill, a plain fold over whole rows
     (16385, 1024, 1, 64, True), (500, 39296, 1, 64, True), (300, 52416, 1, 32, False),  # too tall; 307 tiles and 410 tiles on 256 compute units
     (2, 1 << 20, 1, 64, True), (4, 1 << 19, 1, 64, True), (16, 1 << 17, 1, 8, False),   # few rows: four and two rounds of resident lanes, less
     (64, 250000, 1, 64, True), (32, 500000, 1, 64, True), (64, 122880, 1, 32, False), (16, 491520, 1, 32, False), (16, 983040, 1, 64, True),
