@@ -1028,6 +1028,70 @@ def test_negated_bf16_results(rows, cols):
         assert np.array_equal(run_graph(g, [x])[0], x ^ 0x8000)
 
 
+@pytest.mark.parametrize("rows,cols,dt", [(4096, 1153, "f32"), (300, 15713, "f32"), (3000, 3001, "bf16"), (16384, 577, "bf16"), (150, 30003, "f32")])
+def test_medium_column_folds_by_narrow_tiles(rows, cols, dt):
+    # tiles of 32 lanes over 16 to 64 MB whose rows are no multiple of a vector: sums and maxima of one tensor
+    for kind in ("sum", "max"):
+        g = Graph()
+        x = g.input(rows, cols, dt)
+        g.set_outputs([g.reduce_col(kind, g.unary("convert", x, "f32") if dt == "bf16" else x)])
+        plan = fs.Plan(g)
+        assert plan.group_info(0)["lanes_per_row"] == 32 and cols % plan.group_info(0)["vec_elems"]
+        plan.destroy()
+        v = (0.5 + RNG.standard_normal((rows, cols))).astype(np.float32)
+        ins = [f32_to_bf16_bits(v) if dt == "bf16" else v]
+        check_all(g, run_graph(g, ins), Reference(g, ins), f"column {kind} {dt} {rows}x{cols}")
+
+
+@pytest.mark.parametrize("rows,cols,inputs,dt", [(700, 331, 8, "bf16"), (2100, 77, 3, "u8"), (130, 500, 8, "f32"), (515, 129, 4, "u8"), (300, 130, 12, "bf16")])
+def test_column_folds_of_many_inputs(rows, cols, inputs, dt):
+    # from four trips in flight to a single one, and to the wide form where a trip does not fit; a byte mask beside them
+    g = Graph()
+    xs = [g.input(rows, cols, dt) for _ in range(inputs)]
+    m = g.input(rows, cols, "u8")
+    y = None
+    for x in xs:
+        f = g.unary("convert", x, "f32") if dt != "f32" else x
+        y = f if y is None else g.binary("add", y, f)
+    y = g.select(m, y, g.const(0.25, rows, cols))
+    g.set_outputs([g.reduce_col("sum", y), g.reduce_col("max", y)])
+    ins = []
+    for _ in range(inputs):
+        v = RNG.standard_normal((rows, cols)).astype(np.float32)
+        ins.append((v > 0).astype(np.uint8) if dt == "u8" else f32_to_bf16_bits(v) if dt == "bf16" else v)
+    ins.append((RNG.random((rows, cols)) < 0.9).astype(np.uint8))
+    both_modes(g, ins, f"column folds of {inputs} {dt} inputs {rows}x{cols}")
+
+
+@pytest.mark.parametrize("rows,cols", [(130, 1001), (600, 71), (4096, 1153)])
+def test_infinities_and_nan_stay_in_their_columns_and_rows(rows, cols):
+    # values that are not finite beside the columns an overlapping vector repeats and at the edges of column tiles of 32 and 128
+    # columns: every other column and row has the bits it has without them
+    g = Graph()
+    x = g.input(rows, cols)
+    g.set_outputs([g.reduce_col("sum", x), g.reduce_col("max", x), g.reduce_row("sum", x), g.reduce_row("max", x), g.unary("abs", x)])
+    v = RNG.standard_normal((rows, cols)).astype(np.float32)
+    spots = [(5, cols - 5, np.inf), (7, cols - 4, np.nan), (11, cols - 2, -np.inf), (13, cols - 1, np.nan), (17, 31, np.inf), (19, 32, np.nan), (23, 63, -np.inf), (29, 64, np.inf)]
+    spots += [(31, 127, np.nan), (37, 128, np.inf)] if cols > 140 else []
+    bad = v.copy()
+    for r, c, val in spots:
+        v[r, c], bad[r, c] = 0.0, val
+    clean, out = run_graph(g, [v]), run_graph(g, [bad])
+    rs, cs = [r for r, _, _ in spots], [c for _, c, _ in spots]
+    for k in (0, 1):
+        assert np.array_equal(np.delete(out[k], cs, axis=1), np.delete(clean[k], cs, axis=1)), k
+    for k in (2, 3):
+        assert np.array_equal(np.delete(out[k], rs, axis=0), np.delete(clean[k], rs, axis=0)), k
+    assert np.array_equal(out[4], np.abs(bad), equal_nan=True)
+    for r, c, val in spots:  # sums take them over; maxima are IEEE maxNum
+        for got in (out[0][0, c], out[2][r, 0]):
+            assert np.isnan(got) if np.isnan(val) else got == val, (r, c, val, got)
+        if val == np.inf:
+            assert out[1][0, c] == np.inf and out[3][r, 0] == np.inf
+        else:
+            assert out[1][0, c] == np.fmax.reduce(bad[:, c]) and out[3][r, 0] == np.fmax.reduce(bad[r])
+
+
 @pytest.mark.parametrize("hint", [{"max_workgroups": 1}, {"max_workgroups": 30}, {"lanes_per_row": 16}, {"lanes_per_row": 64, "wg_threads": 256},
                                   {"lanes_per_row": 8, "wg_threads": 64, "tiles_per_trip": 3}, {"tiles_per_trip": 1}, {"lanes_per_row": 32, "max_workgroups": 7}])
 def test_narrow_column_tiles_under_hints(hint):
