@@ -172,8 +172,8 @@ typedef struct {
  * scheduler decide).  In the paper's terms (Section 4.1) every group runs a Row
  * schedule with split_dim = 0: `max_workgroups` bounds `blocks`; lanes_per_row
  * says how many lanes cooperate on one row (a power of two, 1..1024, the analogue
- * of reduce_warps in Section 4.4); wg_threads is the workgroup size (multiple of 64,
- * <= 1024).  max_workgroups = 1 gives the always-valid single-block schedule of
+ * of reduce_warps in Section 4.4); wg_threads is the workgroup size (multiple of 64 and of
+ * the group's lanes per row, <= 1024).  max_workgroups = 1 gives the always-valid single-block schedule of
  * Section 4.3.  For a group over a handful of very long rows that are split over
  * workgroups, max_workgroups is the number of row segments in all (lanes_per_row and
  * wg_threads are fixed at 256 there).

@@ -283,8 +283,8 @@ struct Scheduler {
     // [16384,4096] 65 -> 69 %, [4096,16384] 71 -> 78 % (tiles of 256 lanes before), narrower rows unchanged.
     col_tiled = colred && !rowred && !has_transposed && (l_min > 1024 || (l_min > 64 && !has_concat));
     // Folds that stream little are bound by latency, above all by the grid-wide fold (~4 us of a 7 us kernel).  Tiles of one
-    // 128-byte run let one workgroup, or up to 16 that fold in one level, walk all rows of its columns, and the columns of a
-    // tensor fold side by side; several column reductions, and what feeds them, then share a kernel however small it is
+    // 128-byte run let one workgroup, or up to 16 that fold in one level, walk all rows of its columns (beyond 128 trips as many as
+    // fill the device, in two levels), and the columns of a tensor fold side by side; several column reductions, and what feeds them, then share a kernel however small it is
     // (worth_fusing).  Whole plans, 256 workgroups and two fold levels -> narrow tiles: column sums + row norms f32 [4765,147]
     // 17.3 -> 8.5 us, [127,1088] 13.4 -> 6.5 us; batch normalisation [1764,512] 21.8 -> 13.6 us, [352,5824] 25.4 -> 11.9 us;
     // LayerNorm backward [318,1145] 17.0 -> 9.7 us.
@@ -1077,8 +1077,9 @@ bool worth_fusing(const GroupPlan& merged) {
   // one kernel on 8 CUs, 38 us as three kernels that each fill the device; [32, 256K]: 73 -> 37 us;
   // from 64 rows on the single kernel is as fast or faster ([128, 64K]: 20 against 35 us).
   if (merged.members.size() > 1 && merged.s.few_long_rows && !merged.s.split_rows && merged.s.chunked && merged.R <= 32) return false;
-  // Narrow column tiles have no such fold to speak of; what feeds their reductions, and further reductions of the same tensors,
-  // join them at any size.  Not where the reductions are row reductions of transposed tensors: there the other consumers want
+  // Narrow column tiles fold little, or side by side; what feeds their reductions, and further reductions of the same tensors,
+  // join them at any size (column sums, maxima and row norms f32 [421,192] in three kernels 16.1 us, in two 7.2; [20000,64], whose
+  // tiles fold in two levels, 18.5 and 10.7).  Not where the reductions are row reductions of transposed tensors: there the other consumers want
   // the rows in one workgroup (the 200-node DAG: 29.4 us with those kept apart, 30.6 us without).
   bool narrow = merged.s.narrow_tiles;
   for (const auto& f : merged.tflag) narrow &= !f.second;
