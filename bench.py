@@ -4,7 +4,7 @@
     python bench.py [--gpus 1] [--steps K] [--warmup W] [--workload 3] [--no-extras] [--no-cpu] [--copy-sweep | --survey [--filter NAME]]
 
 A step is one fs_plan_run of the whole fused subgraph on one batch of seeded synthetic input
-already resident in HBM.  The headline line is workload 3 of the benchmark spec, the largest of the five
+already resident in HBM.  The headline line is workload 3, the largest of the five
 (20-op elementwise DAG over 4 fp32 [65536,1024] inputs, 1.5 GiB per step); the other four, the two
 backward-pass subgraphs and two row-sweep end points ride along under `other_workloads`, each with
 the same `roofline` block.  `value` is effective HBM GB/s = minimal bytes (every plan input read once
@@ -319,7 +319,7 @@ def main():
     ap.add_argument("--gpus", type=int, default=1)
     ap.add_argument("--steps", type=int, default=400)
     ap.add_argument("--warmup", type=int, default=400, help="untimed launches before the timed ones (repeated until 50 ms have passed: steady clocks)")
-    ap.add_argument("--workload", type=int, default=3, help="BASELINE.json config number (1-5; 6-7 are extra backward-pass subgraphs) for the headline line")
+    ap.add_argument("--workload", type=int, default=3, help="workload number (1-5; 6-7 are extra backward-pass subgraphs) for the headline line")
     ap.add_argument("--no-extras", action="store_true", help="skip the other workloads")
     ap.add_argument("--no-cpu", action="store_true", help="skip the CPU-oracle baseline")
     ap.add_argument("--copy-sweep", action="store_true", help="only sweep the plain-copy launch shapes at the workloads' sizes and print that")
