@@ -660,15 +660,18 @@ struct Scheduler {
     if (rowred && L > 64) fixed += 2 * s.G * (L / 64) * gp->max_batched_reduces * 4;
     if (split_rows) fixed += 16 + (int)gp->row_reduces.size() * 4;
     // Columns one workgroup folds: its tile, or the row rounded up to 16-byte chunks, one chunk of every reduction per lane and
-    // round.  Not where that needs another round for less than half of the workgroup: there the row as it is, in the chunks that
-    // divide it (column sums and maxima + row norms f32 [14396,1101] 26.3 us rounded, 23.3 as it is, [10000,2101] 38.8 and 35.8;
-    // with one round or a full last one the rounded row is faster: [14396,1001] 18.7 and 21.5, [12000,1801] 32.7 and 35.1; so it
-    // is with a lane or two in the last one: [12000,1025] 21.7 and 22.9, LayerNorm backward [2500,4099] 50.9 and 58.3).
+    // round.  Not where that needs another round for less than half of a workgroup of 512 lanes or less that only reads: there the
+    // row as it is, in the chunks that divide it (column sums and maxima + row norms f32 [14396,1101] 26.3 us rounded, 23.3 as it
+    // is, [10000,2101] 38.8 and 35.8).  With one round or a full last one the rounded row is faster ([14396,1001] 18.7 and 21.5,
+    // [12000,1801] 32.7 and 35.1), with a lane or two in the last one ([12000,1025] 21.7 and 22.9), in larger workgroups
+    // ([2500,4501] 30.0 and 35.0), and beside [R,C] outputs (LayerNorm backward [9000,1450] 41.6 and 43.2).
     s.fold_width = col_tiled ? NVL * L * V : C;
     if (!col_tiled && C % 4 != 0) {
       const int64_t chunks = (int64_t)gp->col_reduces.size() * ((C + 3) / 4);
       const int last = (int)(chunks % WG);
-      if (chunks <= WG || last < 16 || last >= WG / 2) s.fold_width = (C + 3) / 4 * 4;
+      bool writes = false;
+      for (const ExtTensor& e : gp->ext_out) writes |= e.kind == KIND_FULL;
+      if (chunks <= WG || last < 16 || last >= WG / 2 || WG > 512 || writes) s.fold_width = (C + 3) / 4 * 4;
     }
     const int fold_width = s.fold_width;
     s.fold_piece = fold_width;

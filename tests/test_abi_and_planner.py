@@ -12,7 +12,7 @@ import pytest
 
 import paper_1811_05213_amd as fs
 from paper_1811_05213_amd import binding
-from workloads import (Graph, elementwise20_graph, layernorm_gelu_graph, min_hbm_bytes, multi_reduce_graph,
+from workloads import (Graph, elementwise20_graph, layernorm_gelu_graph, layernorm_grad_graph, min_hbm_bytes, multi_reduce_graph,
                        random_dag_graph, softmax_graph)
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
@@ -1087,13 +1087,16 @@ def test_hints_on_narrow_transposes():
     assert info(4000, 1024, lanes_per_row=64, wg_threads=256) == info(4000, 1024)
 
 
-@pytest.mark.parametrize("rows,cols,width", [(14396, 1101, 1101), (10000, 2101, 2101), (14396, 1001, 1004), (12000, 1801, 1804), (12000, 1025, 1028), (5000, 1002, 1004)])
+@pytest.mark.parametrize("rows,cols,width", [(14396, 1101, 1101), (10000, 2101, 2101), (14396, 1001, 1004), (12000, 1801, 1804), (12000, 1025, 1028), (5000, 1002, 1004), (2500, 4501, 4504)])
 def test_rows_that_column_folds_round_up(rows, cols, width):
     # a row is folded in 16-byte chunks, a chunk of every reduction per lane and round; not where rounding it up to whole
-    # chunks takes another round for less than half of a workgroup
+    # chunks takes another round for less than half of a workgroup (of 512 lanes or less, without [R,C] outputs)
     p = fs.Plan(multi_reduce_graph(rows, cols))
     assert p.stats()["num_launches"] == 1 and p.group_info(0)["num_col_reduces"] == 2
     assert f"constexpr int CW = {width}, RB = 256" in p.group_source(0)
+    p.destroy()
+    p = fs.Plan(layernorm_grad_graph(9000, 1450))
+    assert "constexpr int CW = 1452, RB = 256" in p.group_source(0)
     p.destroy()
 
 
