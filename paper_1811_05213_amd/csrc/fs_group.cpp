@@ -479,7 +479,12 @@ struct Scheduler {
           WG = w;
           break;
         }
-      if (rowred && L >= 256) WG = std::max(WG, std::min(1024, 4 * L));  // rows across several wavefronts: 16 wavefronts per CU
+      // rows across several wavefronts: 16 wavefronts per CU.  8 where rows that no whole vectors fill leave the kernel too, 20 elements
+      // to a lane or 512 lanes to a row: such kernels are short of registers at 16 (LayerNorm backward [2500,4101] 58.7 -> 51.3 us, [6000,4801] 108.5 ->
+      // 92.5, [4000,6201] 101.5 -> 90.9, [3000,8191] 94.1 -> 89.8; with 16 elements on 256 lanes, [5000,3501], 57.2 against 61.6)
+      bool writes = false;
+      for (const ExtTensor& e : gp->ext_out) writes |= e.kind == KIND_FULL;
+      if (rowred && L >= 256) WG = std::max(WG, C % V != 0 && writes && (NVL * V > 16 || L >= 512) ? 512 : std::min(1024, 4 * L));
     }
     else if (total_waves > 4 * CUS || has_transposed) WG = std::max(256, L);
     else WG = std::max(64, L);

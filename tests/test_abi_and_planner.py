@@ -1207,3 +1207,13 @@ def test_hinted_workgroups_hold_whole_rows(lanes, wg):
             assert gi["wg_threads"] == gi["rows_per_iter"] * gi["lanes_per_row"], gi
             assert wg % lanes or gi["lanes_per_row"] != lanes or gi["wg_threads"] == wg
         p.destroy()
+
+
+@pytest.mark.parametrize("rows,cols,wg", [(2500, 4101, 512), (2500, 4100, 1024), (4000, 6201, 512), (5000, 3501, 1024), (3000, 8192, 1024)])
+def test_workgroups_of_kernels_with_both_reductions(rows, cols, wg):
+    p = fs.Plan(layernorm_grad_graph(rows, cols))
+    assert p.stats()["num_launches"] == 1 and p.group_info(0)["wg_threads"] == wg
+    p.destroy()
+    p = fs.Plan(multi_reduce_graph(rows, cols))  # (nothing of the row's size leaves the kernel)
+    assert p.group_info(0)["wg_threads"] == 1024
+    p.destroy()
