@@ -128,7 +128,7 @@ struct Scheduler {
   // lanes, vectors, workgroup
   int narrow_lanes = 0, narrow_trip_regs = 0, narrow_regs = 0;  // narrow column tiles: lanes, registers a trip's rows take, and accumulators and [1,C] operands
   int L = 64, tt_rows = 64, NVL = 1, CT = 1, NVLC = 0, RESV = 0, WG = 256;
-  bool in_pairs = false;  // bf16 rows read two elements at a time (pick_vector_width)
+  bool in_pairs = false;  // rows are read two elements at a time (pick_vector_width)
   bool staged_loop = false;
 
   Scheduler(const Graph& g_, const PlanOptions& opt_, GroupPlan* gp_) : g(g_), opt(opt_), gp(gp_), s(gp_->s), R(gp_->R), C(gp_->C) {}
@@ -189,13 +189,15 @@ struct Scheduler {
     return FS_OK;
   }
 
-  // Vectors that a width does not fill cost arithmetic as well as bytes: a lane computes on what its empty slots repeat.  bf16 rows
-  // with transcendental functions take pairs of elements instead (one 4-byte access each) where that leaves an eighth of the slots
-  // or more out: masked softmax bf16 [4000,577] (1024 slots a row, 640 in pairs; element by element 5.2 us) 6.4 -> 4.7 us,
-  // [6387,289] 5.7 -> 4.5, [16384,577] 11.4 -> 9.9, softmax bf16 [80000,577] 49.7 -> 44.6, [1500,4099] 5.8 -> 4.9.  Not without them
-  // (L2 normalisation [43000,289] 10.2 -> 10.6 us, row sums 8.9 -> 13.1), not with [1,C] operands, whose slices take more accesses too
-  // (LayerNorm+GeLU [4700,577] 5.2 -> 5.7), not for rows of 128 elements and less ([200000,65] 13.8 -> 15.7) or beyond 32
-  // per lane ([1323,33001] 76.2 -> 81.7), and not in fp32 (masked softmax [8004,131] 4.3 -> 4.6 us).
+  // Vectors that a width does not fill cost arithmetic as well as bytes: a lane computes on what its empty slots repeat.  Rows
+  // with transcendental functions take pairs of elements instead where that leaves an eighth of the slots or more out.
+  // bf16 (a 4-byte access each): masked softmax [4000,577] (1024 slots a row, 640 in pairs; element by element 5.2 us) 6.4 -> 4.7 us,
+  // [6387,289] 5.7 -> 4.5, [16384,577] 11.4 -> 9.9, softmax [80000,577] 49.7 -> 44.6, [1500,4099] 5.8 -> 4.9.
+  // fp32 below 40 MB: masked softmax [1817,577] 5.2 -> 4.7, [476,2201] 5.2 -> 4.7, softmax [694,6225] 8.2 -> 7.2, [682,2305] 4.6 -> 4.3
+  // (at 60 MB [2382,3301] 10.7 -> 11.6, [1263,6225] 11.0 -> 11.7; beyond 8192 columns [604,13001] 11.8 -> 12.4).
+  // Not without such functions (bf16 L2 normalisation [43000,289] 10.2 -> 10.6 us, row sums 8.9 -> 13.1), not with [1,C] operands, whose
+  // slices take more accesses too (LayerNorm+GeLU [4700,577] 5.2 -> 5.7), not for short rows (bf16 [200000,65] 13.8 -> 15.7, fp32
+  // [8004,131] 4.3 -> 4.6) or beyond 32 elements per lane (bf16 [1323,33001] 76.2 -> 81.7).
   fs_status pick_vector_width() {
     bool heavy = false, rowv = false;
     for (int m : gp->members) {
@@ -203,8 +205,8 @@ struct Scheduler {
       heavy |= gp->kind.at(m) == KIND_FULL && (op == FS_EXP || op == FS_LOG || op == FS_TANH || op == FS_SIGMOID || op == FS_GELU_TANH);
     }
     for (const ExtTensor& e : gp->ext_in) rowv |= e.kind == KIND_ROWV;
-    if (!heavy || rowv || max_es != 2 || V != 8 || C % V == 0 || !rowred || colred || has_transposed || chunked || CT > 1 || C <= 128 || C > 32768)
-      return FS_OK;
+    if (!heavy || rowv || V != 16 / max_es || V < 4 || C % V == 0 || !rowred || colred || has_transposed || chunked || CT > 1) return FS_OK;
+    if (max_es == 2 ? C <= 128 || C > 32768 : C <= 256 || C > 8192 || gp->min_hbm_bytes >= (40u << 20)) return FS_OK;
     const int slots = NVL * L * V;
     for (int v : {2, V}) {
       V = v;

@@ -992,6 +992,12 @@ def test_bf16_rows_in_pairs(rows, cols):
     both_modes(g, [f32_to_bf16_bits(x), f32_to_bf16_bits(m)], f"masked softmax bf16 {rows}x{cols}")
 
 
+@pytest.mark.parametrize("rows,cols", [(1817, 577), (694, 6225), (2100, 261), (700, 2305), (1100, 1123)])
+def test_fp32_rows_in_pairs(rows, cols):
+    x = (8 * RNG.standard_normal((rows, cols))).astype(np.float32)
+    both_modes(softmax_graph(rows, cols), [x], f"softmax f32 {rows}x{cols}")
+
+
 @pytest.mark.parametrize("rows,cols", [(2, 31), (127, 33), (129, 64), (513, 65), (1030, 577), (2100, 36), (8300, 100), (17000, 31)])
 def test_small_column_folds_by_narrow_tiles(rows, cols):
     # tiles of 128 bytes: one column past a tile, one row past a workgroup's trip, one / a few / many workgroups per tile, several
