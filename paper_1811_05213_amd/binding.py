@@ -121,7 +121,7 @@ def lib() -> ctypes.CDLL:
         for name in ("fs_plan_create", "fs_plan_destroy", "fs_plan_workspace_bytes", "fs_plan_run",
                      "fs_plan_workspace_init", "fs_plan_stats", "fs_plan_group_info", "fs_plan_node_groups",
                      "fs_plan_group_source", "fs_plan_group_kernel_name", "fs_copy_probe", "fs_plan_tune", "fs_plan_group_perf_key", "fs_plan_node_spans",
-                     "fs_plan_load", "fs_plan_workspace_check", "fs_plan_launched_hbm_bytes", "fs_device_limits"):
+                     "fs_plan_load", "fs_plan_workspace_check", "fs_plan_launched_hbm_bytes", "fs_device_limits", "fs_plan_joined_groups"):
             getattr(L, name).restype = ctypes.c_int
         _lib = L
     return _lib
@@ -233,6 +233,13 @@ class Plan:
         s = ctypes.c_char_p()
         _check(lib().fs_plan_group_source(self._h, group, ctypes.byref(s)))
         return s.value.decode()
+
+    def joined_groups(self) -> List[tuple]:
+        """(first group, number of groups, source) of every run of groups that is launched as one kernel."""
+        out, first, count, s = [], ctypes.c_int32(), ctypes.c_int32(), ctypes.c_char_p()
+        while lib().fs_plan_joined_groups(self._h, len(out), ctypes.byref(first), ctypes.byref(count), ctypes.byref(s)) == 0:
+            out.append((first.value, count.value, s.value.decode()))
+        return out
 
     def group_kernel_name(self, group: int) -> str:
         s = ctypes.c_char_p()

@@ -629,6 +629,186 @@ struct Emitter {
     os << "    }\n  }\n}\n";
   }
 
+  // ---- column reductions joined with what needs their results (GroupPlan::joined) ------------------
+  // One kernel in the place of several groups: batch normalisation as three kernels reads its tensor three times, because a
+  // column result only exists when the whole grid is done.  Here a workgroup keeps its rows of one column tile in registers,
+  // as they came from memory, and the RB workgroups of the tile meet (fs_tile_meet) once per stage of column reductions: the
+  // tensor crosses HBM once, and two launches go.  Values between the inputs and a stage's reductions are computed again by
+  // every stage that needs them.
+  void run_joined(const std::string& kname) {
+    const Schedule& s = gp.s;
+    for (int m : gp.members) in_set[m] = 1;
+    count_uses();
+    int max_level = 0;
+    for (int m : gp.members) max_level = std::max(max_level, gp.level.at(m));
+    for (const ExtTensor& e : gp.ext_in) loc(e.node);
+    for (int m : gp.members) loc(m);
+    const int over = (int)((int64_t)s.NV * s.V - gp.C);
+    const int CW = s.fold_width, FV = 1, NP = (int)(gp.ext_in.size() + gp.ext_out.size());
+    std::vector<std::vector<int>> stage(max_level + 1);  // the column reductions by level
+    for (int m : gp.col_reduces) stage[gp.level.at(m)].push_back(m);
+    while (stage.back().empty()) stage.pop_back();
+    std::map<int, int> slot;  // reduction -> its row in lds_res
+    for (int m : gp.col_reduces) slot.insert({m, (int)slot.size()});
+
+    os << "// joined: work space [R," << gp.C << "], tiles of " << s.L << " lanes, " << s.U << " rows to a lane, " << s.RB << " workgroups of " << s.WG << " per tile\n";
+    os << "struct " << kname << "_args { void* p[" << NP << "]; float* part; fs_u32* tickets; int R; int wait; };\n";
+    for (size_t st = 0; st < stage.size(); ++st) {
+      os << "struct " << kname << "_kinds" << st << " {\n  static FS_DEV float op(int k, float a, float b) { switch (k) {";
+      for (size_t k = 0; k < stage[st].size(); ++k) os << " case " << k << ": return fs_red_op<" << g.nodes[stage[st][k]].attr_i << ">(a, b);";
+      os << " } return a; }\n  static FS_DEV float identity(int k) { switch (k) {";
+      for (size_t k = 0; k < stage[st].size(); ++k) os << " case " << k << ": return fs_red_identity<" << g.nodes[stage[st][k]].attr_i << ">();";
+      os << " } return 0.0f; }\n};\n";
+    }
+    os << "extern \"C\" __global__ void __launch_bounds__(" << s.WG << ") " << kname << "(const " << kname << "_args a) {\n"
+       << "  constexpr int V = " << s.V << ", NVL = 1, L = " << s.L << ", NV = " << s.NV << ", E = V, WG = " << s.WG << ", G = WG / L, C = " << gp.C
+       << ", CT = " << s.CT << ", RB = " << s.RB << ", TR = " << s.U << ", CW = " << CW << ", FV = " << FV << ";\n"
+       << "  constexpr int RAGGED = " << (s.ragged ? 1 + over : 0) << ";\n"
+       << "  const int tid = (int)threadIdx.x, lir = tid & (L - 1), rg = tid / L, tile = (int)blockIdx.x % CT, rb = (int)blockIdx.x / CT, vbase = tile * L;\n"
+       << "  (void)E; (void)NVL; (void)CW;\n"
+       << "  __shared__ float lds_col[(L < 64 ? WG / 64 : G) * CW], lds_res[" << gp.col_reduces.size() << " * CW];\n  __shared__ fs_u32 lds_flag;\n"
+       // (column of the lane's element e inside the tile; what the lane does not own reads any column)
+       << "  const int lcol = lir * V" << (over ? " - fs_vec_skip<V, C>(vbase + lir)" : "") << ";\n";
+    auto raw = [&](const ExtTensor& e) { return "w" + std::to_string(loc(e.node)); };
+    for (const auto* list : {&gp.ext_in, &gp.ext_out})
+      for (const ExtTensor& e : *list)
+        if (e.kind == KIND_FULL)
+          os << "  const __amdgpu_buffer_rsrc_t b" << e.arg << " = fs_make_rsrc(a.p[" << e.arg << "], (fs_u32)a.R * C * " << dtype_size(e.dtype) << "u);\n";
+    // element offsets: of the lane's column, from one row block to the next, from one of the lane's rows to the next
+    os << "  const fs_u32 col = (fs_u32)fs_col_of<V, NV, RAGGED>(vbase + lir);\n  constexpr fs_u32 BLOCK = (fs_u32)G * C, STEP = RB * BLOCK;\n";
+    auto load_rows = [&](const std::string& ind, const std::string& b) {
+      os << ind << "{\n" << ind << "  const fs_u32 o = fs_opaque((fs_u32)" << b << " * BLOCK + (fs_u32)rg * C + col);\n" << ind << "  _Pragma(\"unroll\") for (int t = 0; t < TR; ++t) {\n";
+      for (const ExtTensor& e : gp.ext_in)
+        if (e.kind == KIND_FULL)
+          os << ind << "    fs_load_words<" << e.dtype << ", V, " << (e.streaming ? "true" : "false") << ">(" << raw(e) << "[t], b" << e.arg << ", o + t * STEP);\n";
+      os << ind << "  }\n" << ind << "}\n";
+    };
+    for (const ExtTensor& e : gp.ext_in)
+      if (e.kind == KIND_FULL) os << "  fs_u32 " << raw(e) << "[TR][fs_words<" << e.dtype << ", V>::n];\n";
+    load_rows("  ", "rb");
+    for (const ExtTensor& e : gp.ext_in)
+      if (e.kind == KIND_ROWV)
+        os << "  float " << name(e.node, KIND_ROWV) << "[E];\n  fs_load_row<" << e.dtype << ", " << tmpl_row() << ">(" << name(e.node, KIND_ROWV) << ", a.p[" << e.arg
+           << "], 0, lir, vbase);\n";
+    const std::set<int> reduced(gp.col_reduces.begin(), gp.col_reduces.end());
+    std::set<int> rowv_done;
+    // [1,C] members of a pass: the lane's slice, once
+    auto rowv_members = [&](const std::set<int>& mem) {
+      for (int m : gp.members) {
+        if (!mem.count(m) || folded[m] || gp.kind.at(m) != KIND_ROWV || reduced.count(m) || !rowv_done.insert(m).second) continue;
+        const std::string nm = name(m, KIND_ROWV);
+        os << "  float " << nm << "[E];\n  _Pragma(\"unroll\") for (int e = 0; e < E; ++e) " << nm << "[e] = " << rounded(m, expr(m)) << ";\n";
+        if (const ExtTensor* e = find_out(m))
+          os << "  if (rb == 0 && rg == 0) _Pragma(\"unroll\") for (int e = 0; e < E; ++e)\n    if (fs_owned<V, NV, RAGGED>(vbase + lir, e)) fs_store1<" << e->dtype << ">(a.p[" << e->arg
+             << "], (long)col + e, " << nm << "[e]);\n";
+      }
+    };
+    // one pass over the lane's rows: the [R,C] members the targets need, then `tail` per row
+    auto pass = [&](const std::string& ind, const std::string& b, const std::set<int>& mem, const std::set<int>& ext, auto tail) {
+      os << ind << "const fs_u32 row0 = fs_opaque((fs_u32)" << b << " * G + rg);\n" << ind << "_Pragma(\"unroll\") for (int t = 0; t < TR; ++t) {\n" << ind
+         << "  const bool rok = row0 + t * (RB * G) < (fs_u32)a.R;\n" << ind << "  (void)rok;\n";
+      for (const ExtTensor& e : gp.ext_in)
+        if (e.kind == KIND_FULL && ext.count(e.node))
+          os << ind << "  float " << name(e.node, KIND_FULL) << "[E];\n" << ind << "  fs_unpack_words<" << e.dtype << ", V>(" << name(e.node, KIND_FULL) << ", " << raw(e) << "[t]);\n";
+      for (int m : gp.members)
+        if (mem.count(m) && !folded[m] && gp.kind.at(m) == KIND_FULL)
+          os << ind << "  float " << name(m, KIND_FULL) << "[E];\n" << ind << "  _Pragma(\"unroll\") for (int e = 0; e < E; ++e) " << name(m, KIND_FULL) << "[e] = "
+             << rounded(m, expr(m)) << ";\n";
+      tail(ind + "  ");
+      os << ind << "}\n";
+    };
+    for (size_t st = 0; st < stage.size(); ++st) {
+      const std::vector<int>& red = stage[st];
+      if (red.empty()) continue;
+      const int K = (int)red.size();
+      std::set<int> mem, ext, done;
+      needed_for(red, &mem, &ext, &reduced, &done);
+      rowv_members(mem);
+      const std::string S = "S" + std::to_string(st), cv = "cv" + std::to_string(st);
+      os << "  typedef fs_colfold<" << K << ", CW, WG, FV> " << S << ";\n  float " << cv << "[" << S << "::CPT][FV];\n";
+      auto partial = [&](const std::string& ind, const std::string& b) {  // of row block b, whose rows the lanes hold -> cv
+        for (int m : red)
+          os << ind << "float ca" << loc(m) << "[E];\n" << ind << "_Pragma(\"unroll\") for (int e = 0; e < E; ++e) ca" << loc(m) << "[e] = fs_red_identity<" << g.nodes[m].attr_i << ">();\n";
+        pass(ind, b, mem, ext, [&](const std::string& in) {
+          for (int m : red) {
+            const fs_node& n = g.nodes[m];
+            const std::string ca = "ca" + std::to_string(loc(m));
+            os << in << "_Pragma(\"unroll\") for (int e = 0; e < E; ++e) " << ca << "[e] = rok ? ";
+            if (folded[n.in[0]]) os << "__builtin_fmaf(" << ref(g.nodes[n.in[0]].in[0]) << ", " << ref(g.nodes[n.in[0]].in[1]) << ", " << ca << "[e])";
+            else os << "fs_red_op<" << n.attr_i << ">(" << ca << "[e], " << ref(n.in[0]) << ")";
+            os << " : " << ca << "[e];\n";
+          }
+        });
+        for (int k = 0; k < K; ++k)
+          os << ind << "fs_colred_fold_wg<" << g.nodes[red[k]].attr_i << ", " << k << ", " << K << ", V, 1, L, C, CW, WG, FV, CW, true>(ca" << loc(red[k]) << ", " << cv
+             << ", lds_col, lir, rg, vbase);\n";
+      };
+      os << "  {\n";
+      partial("    ", "rb");
+      os << "  }\n";
+      if (s.RB > 1) {
+        const std::string part = "a.part + (long)tile * " + std::to_string(s.part_stride_floats) + "L + " + std::to_string((size_t)slot.at(red[0]) * CW * s.RB) + "L";
+        os << "  if (fs_tile_meet<" << K << ", CW, WG, FV>(" << cv << ", " << part << ", a.tickets + tile * " << s.ticket_stride << " + " << st << ", &lds_flag, (fs_u32)rb, (fs_u32)RB, a.wait)) {\n"
+           << "    fs_tile_fold<" << K << ", CW, WG, FV, " << kname << "_kinds" << st << ">(" << cv << ", " << part << ", (fs_u32)RB);\n  } else {\n"
+           << "    float tot[" << S << "::CPT][FV];\n    _Pragma(\"unroll 1\") for (int b = 0; b < RB; ++b) {\n";
+        load_rows("      ", "b");
+        partial("      ", "b");
+        os << "      _Pragma(\"unroll\") for (int i = 0; i < " << S << "::CPT; ++i) {\n        const int k = (tid + i * WG) / " << S << "::CH;\n"
+           << "        _Pragma(\"unroll\") for (int f = 0; f < FV; ++f) tot[i][f] = " << kname << "_kinds" << st << "::op(k, b == 0 ? " << kname << "_kinds" << st
+           << "::identity(k) : tot[i][f], " << cv << "[i][f]);\n      }\n    }\n"
+           << "    _Pragma(\"unroll\") for (int i = 0; i < " << S << "::CPT; ++i) _Pragma(\"unroll\") for (int f = 0; f < FV; ++f) " << cv << "[i][f] = tot[i][f];\n";
+        load_rows("    ", "rb");
+        os << "  }\n";
+      }
+      // results: rounded to their dtype, stored by the tile's first workgroup, and through LDS to the lanes' columns
+      os << "  _Pragma(\"unroll\") for (int i = 0; i < " << S << "::CPT; ++i) {\n    const int c = tid + i * WG;\n    if (c < " << S << "::NCH) {\n      const int k = c / " << S
+         << "::CH, c0 = (c % " << S << "::CH) * FV;\n";
+      for (int k = 0; k < K; ++k) {
+        const fs_node& n = g.nodes[red[k]];
+        const std::string v = cv + "[i][f]" + (n.attr_i == FS_RED_MEAN ? " / (float)a.R" : "");
+        os << "      if (k == " << k << ") _Pragma(\"unroll\") for (int f = 0; f < FV; ++f) {\n        const float x = " << rounded(red[k], v) << ";\n        lds_res["
+           << slot.at(red[k]) << " * CW + c0 + f] = x;\n";
+        if (const ExtTensor* e = find_out(red[k]))
+          os << "        if (rb == 0 && (fs_col_index<C>::type)tile * CW + c0 + f < C) fs_store1<" << e->dtype << ">(a.p[" << e->arg << "], (long)tile * CW + c0 + f, x);\n";
+        os << "      }\n";
+      }
+      os << "    }\n  }\n  __syncthreads();\n";
+      for (int m : red)
+        os << "  float " << name(m, KIND_ROWV) << "[E];\n  _Pragma(\"unroll\") for (int e = 0; e < E; ++e) " << name(m, KIND_ROWV) << "[e] = lds_res[" << slot.at(m)
+           << " * CW + (lcol + e > 0 ? lcol + e : 0)];\n";
+    }
+    if (s.RB > 1) os << "  fs_tile_leave(a.tickets + tile * " << s.ticket_stride << ", " << stage.size() + 1 << ", (fs_u32)RB);\n";
+    // what leaves the kernel as an [R,C] tensor, and [1,C] values nothing else needed
+    std::vector<int> roots;
+    for (const ExtTensor& e : gp.ext_out)
+      if (!reduced.count(e.node)) roots.push_back(e.node);
+    if (!roots.empty()) {
+      std::set<int> mem(roots.begin(), roots.end()), ext, done;
+      needed_for(roots, &mem, &ext, &reduced, &done);
+      rowv_members(mem);
+      bool full = false;
+      for (int m : roots) full |= gp.kind.at(m) == KIND_FULL;
+      if (full) {
+        os << "  const fs_u32 out = fs_opaque((fs_u32)rb * BLOCK + (fs_u32)rg * C + col);\n";
+        if (over) os << "  const bool whole = fs_owned<V, NV, RAGGED>(vbase + lir, 0);\n";
+      }
+      if (full)
+        pass("  ", "rb", mem, ext, [&](const std::string& in) {
+          for (const ExtTensor& e : gp.ext_out) {
+            if (e.kind != KIND_FULL) continue;
+            const std::string nt = e.streaming ? "true" : "false", nm = name(e.node, KIND_FULL), dt = std::to_string(e.dtype), b = "b" + std::to_string(e.arg);
+            // (a last vector that overlaps its neighbour leaves the repeated columns alone: their results belong to the tile before)
+            if (over)
+              os << in << "if (whole) fs_store_words<" << dt << ", V, " << nt << ">(" << nm << ", " << b << ", out + t * STEP);\n" << in << "else if (vbase + lir < NV) _Pragma(\"unroll\") for (int e = 0; e < E; ++e)\n"
+                 << in << "  if (fs_owned<V, NV, RAGGED>(vbase + lir, e)) { const float x1[1] = {" << nm << "[e]}; fs_store_words<" << dt << ", 1, " << nt << ">(x1, " << b << ", out + t * STEP + e); }\n";
+            else
+              os << in << (s.ragged ? "if (vbase + lir < NV) " : "") << "fs_store_words<" << dt << ", V, " << nt << ">(" << nm << ", " << b << ", out + t * STEP);\n";
+          }
+        });
+    }
+    os << "}\n";
+  }
+
   // ---- shared-memory planning for rows walked in chunks (Section 5.1) ----------------------------
   // Called on a dry run (no buffers yet), whose passes counted who needs what.
   //   size requirements (5.1.1)  candidates are the values several passes need: [R,C] inputs that more than one pass
@@ -802,6 +982,10 @@ struct Emitter {
   }
 
   void run(const std::string& kname) {
+    if (gp.joined) {
+      run_joined(kname);
+      return;
+    }
     const Schedule& s = gp.s;
     for (int m : gp.members) in_set[m] = 1;
     count_uses();

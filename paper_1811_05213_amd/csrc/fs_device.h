@@ -613,6 +613,74 @@ template <int FV> FS_DEV void fs_store_dev(const float (&src)[FV], __amdgpu_buff
   }
 }
 
+// Vectors of V elements that stay in registers as they came from memory (kernels that join column reductions with what needs
+// their results hold several rows of a tile in a lane): 32-bit words, read and written through a buffer descriptor whose size
+// is the tensor's.  Rows beyond the tensor need no clamp and no branch: they lie beyond the descriptor, where loads give zeros
+// and stores are dropped.  One 32-bit offset per lane serves all rows (pairs of 64-bit addresses of 16 rows cost 32 registers).
+template <int DT, int V> struct fs_words {
+  static constexpr int bytes = V * (int)sizeof(typename fs_elem<DT>::type), n = bytes >= 4 ? bytes / 4 : 1;
+  typedef fs_u32 type[n];
+};
+#define FS_AUX_NT 0x2
+template <int DT, int V, bool NT> FS_DEV void fs_load_words(typename fs_words<DT, V>::type& w, __amdgpu_buffer_rsrc_t r, fs_u32 elem) {
+  constexpr int BYTES = V * (int)sizeof(typename fs_elem<DT>::type), AUX = NT ? FS_AUX_NT : 0;
+  const fs_u32 off = elem * (fs_u32)sizeof(typename fs_elem<DT>::type);
+  if constexpr (BYTES == 16) {
+    const fs_u32x4 u = __builtin_amdgcn_raw_buffer_load_b128(r, off, 0, AUX);
+#pragma unroll
+    for (int k = 0; k < 4; ++k) w[k] = u[k];
+  } else if constexpr (BYTES == 8) {
+    const fs_u32x2 u = __builtin_amdgcn_raw_buffer_load_b64(r, off, 0, AUX);
+    w[0] = u[0], w[1] = u[1];
+  } else if constexpr (BYTES == 4) {
+    w[0] = __builtin_amdgcn_raw_buffer_load_b32(r, off, 0, AUX);
+  } else if constexpr (BYTES == 2) {
+    w[0] = (fs_u16)__builtin_amdgcn_raw_buffer_load_b16(r, off, 0, AUX);
+  } else {
+    w[0] = (fs_u8)__builtin_amdgcn_raw_buffer_load_b8(r, off, 0, AUX);
+  }
+}
+template <int DT, int V> FS_DEV void fs_unpack_words(float (&dst)[V], const typename fs_words<DT, V>::type& w) {
+#pragma unroll
+  for (int k = 0; k < V; ++k) {
+    if constexpr (DT == FS_DT_F32) dst[k] = __builtin_bit_cast(float, w[k]);
+    else if constexpr (DT == FS_DT_BF16) dst[k] = __builtin_bit_cast(float, k % 2 ? w[k / 2] & 0xffff0000u : w[k / 2] << 16);
+    else dst[k] = fs_to_f32<DT>((fs_u8)(w[k / 4] >> (8 * (k % 4))));
+  }
+}
+template <int DT, int V, bool NT> FS_DEV void fs_store_words(const float (&src)[V], __amdgpu_buffer_rsrc_t r, fs_u32 elem) {
+  constexpr int ES = (int)sizeof(typename fs_elem<DT>::type), BYTES = V * ES, AUX = NT ? FS_AUX_NT : 0;
+  const fs_u32 off = elem * (fs_u32)ES;
+  fs_u32 w[fs_words<DT, V>::n] = {};
+#pragma unroll
+  for (int k = 0; k < V; ++k) {
+    if constexpr (DT == FS_DT_F32) w[k] = __builtin_bit_cast(fs_u32, src[k]);
+    else w[k * ES / 4] |= (fs_u32)fs_from_f32<DT>(src[k]) << (8 * (k * ES % 4));
+  }
+  if constexpr (BYTES == 16) {
+    fs_u32x4 u;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) u[k] = w[k];
+    __builtin_amdgcn_raw_buffer_store_b128(u, r, off, 0, AUX);
+  } else if constexpr (BYTES == 8) {
+    fs_u32x2 u;
+    u[0] = w[0], u[1] = w[1];
+    __builtin_amdgcn_raw_buffer_store_b64(u, r, off, 0, AUX);
+  } else if constexpr (BYTES == 4) {
+    __builtin_amdgcn_raw_buffer_store_b32(w[0], r, off, 0, AUX);
+  } else if constexpr (BYTES == 2) {
+    __builtin_amdgcn_raw_buffer_store_b16((fs_u16)w[0], r, off, 0, AUX);
+  } else {
+    __builtin_amdgcn_raw_buffer_store_b8((fs_u8)w[0], r, off, 0, AUX);
+  }
+}
+// an index the compiler does not recognise as the one it computed before (so that a pass over the rows recomputes its offsets
+// instead of keeping those of the pass before in registers)
+FS_DEV fs_u32 fs_opaque(fs_u32 x) {
+  asm("" : "+v"(x));
+  return x;
+}
+
 FS_DEV int fs_lane_id() { return (int)__builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u)); }
 // value of lane (lane ^ mask) of the same wavefront (LDS crossbar, no LDS memory)
 FS_DEV float fs_shfl_xor(float v, int mask) {
@@ -627,7 +695,8 @@ FS_DEV float fs_shfl_xor(float v, int mask) {
 // multiple of 8, or C itself): wide rows need no more LDS than narrow ones, only more barriers.
 // CT columns are in the row, C in the fold (one column tile, or the row rounded up to whole 16-byte chunks: columns beyond the
 // row hold repeated or unwritten values, which fold to something that is not stored).
-template <int KIND, int KIDX, int K, int V, int NVL, int L, int CT, int C, int WG, int FV, int PC, int CPT>
+// FEW: a loop over the LDS rows that keeps eight of them in registers at a time (kernels that hold their rows across the fold).
+template <int KIND, int KIDX, int K, int V, int NVL, int L, int CT, int C, int WG, int FV, int PC, bool FEW = false, int CPT>
 FS_DEV void fs_colred_fold_wg(const float (&acc_in)[NVL * V], float (&vals)[CPT][FV], float* lds /* GL*PC floats */, int lir, int rg, int vbase) {
   typedef fs_colfold<K, C, WG, FV> S;
   static_assert(CPT == S::CPT, "chunks per thread");
@@ -673,6 +742,15 @@ FS_DEV void fs_colred_fold_wg(const float (&acc_in)[NVL * V], float (&vals)[CPT]
       const int c = (int)threadIdx.x + i * WG;
       if (c >= KIDX * S::CH && c < (KIDX + 1) * S::CH) {
         const int col0 = (c - KIDX * S::CH) * FV;
+        if constexpr (FEW) {
+#pragma unroll
+          for (int f = 0; f < FV; ++f) vals[i][f] = lds[col0 + f];
+#pragma unroll 8
+          for (int g = 1; g < GL; ++g)
+#pragma unroll
+            for (int f = 0; f < FV; ++f) vals[i][f] = fs_red_op<KIND>(vals[i][f], lds[g * C + col0 + f]);
+          continue;
+        }
 #pragma unroll
         for (int f = 0; f < FV; ++f) {
           float a = lds[col0 + f];
@@ -797,6 +875,79 @@ FS_DEV bool fs_colred_fold_grid(float (&vals)[CPT][FV], float* part, fs_u32* tic
     n = groups;
   }
   return true;
+}
+
+// ------------------------------------------------------------------------------------------
+// Workgroups of one column tile that meet inside a kernel: each leaves its partial, counts itself in and waits until the others
+// have done so, then all of them fold the partials in index order and go on with the result (a column statistic that every
+// row needs again).  Visibility as in the grid-wide fold: sc1 stores acknowledged before the count, sc1 loads after it.
+// The wait is bounded: a kernel must not depend on workgroups that the device has not started (another stream may hold the
+// compute units).  Where the others have not arrived after `ticks` of the 100 MHz clock the function returns false, and the
+// caller computes their partials itself, from memory, in the same order: the same bits.
+// ------------------------------------------------------------------------------------------
+template <int K, int C, int WG, int FV, int CPT>
+FS_DEV bool fs_tile_meet(const float (&vals)[CPT][FV], float* part, fs_u32* counter, fs_u32* flag, fs_u32 idx, fs_u32 n, int ticks) {
+  typedef fs_colfold<K, C, WG, FV> S;
+  static_assert(CPT == S::CPT, "chunks per thread");
+  constexpr int KC = K * C;
+  const int t = (int)threadIdx.x;
+  const __amdgpu_buffer_rsrc_t mine = fs_make_rsrc(part + (long)idx * KC, KC * 4);
+#pragma unroll
+  for (int i = 0; i < S::CPT; ++i) {
+    const int c = t + i * WG;
+    if (c < S::NCH) fs_store_dev<FV>(vals[i], mine, (fs_u32)c * (FV * 4));
+  }
+  __builtin_amdgcn_s_waitcnt(0);  // this wavefront's partial stores are acknowledged
+  __syncthreads();
+  if (t == 0) {
+    fs_u32 seen = __hip_atomic_fetch_add(counter, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + 1u;
+    if (seen < n) {
+      const unsigned long long t0 = __builtin_amdgcn_s_memrealtime();
+      do {
+        __builtin_amdgcn_s_sleep(1);
+        seen = __hip_atomic_load(counter, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      } while (seen < n && (long long)(__builtin_amdgcn_s_memrealtime() - t0) < (long long)ticks);
+    }
+    *flag = seen >= n ? 1u : 0u;
+  }
+  __syncthreads();
+  return *flag != 0u;
+}
+// ... the fold of the n partials, after fs_tile_meet returned true
+template <int K, int C, int WG, int FV, typename KINDS, int CPT>
+FS_DEV void fs_tile_fold(float (&vals)[CPT][FV], const float* part, fs_u32 n) {
+  typedef fs_colfold<K, C, WG, FV> S;
+  constexpr int KC = K * C, FB = 16;  // loads in flight per chunk
+  const __amdgpu_buffer_rsrc_t all = fs_make_rsrc(part, n * (KC * 4));
+#pragma unroll
+  for (int i = 0; i < S::CPT; ++i) {
+    const int c = (int)threadIdx.x + i * WG;
+    if (c < S::NCH) {
+      const int k = c / S::CH;
+      float a[FV];
+#pragma unroll
+      for (int f = 0; f < FV; ++f) a[f] = KINDS::identity(k);
+      for (fs_u32 jb = 0; jb < n; jb += FB) {
+        float tmp[FB][FV];
+#pragma unroll
+        for (int u = 0; u < FB; ++u) fs_load_dev<FV>(tmp[u], all, ((jb + u) < n ? (jb + u) : (n - 1)) * (KC * 4) + (fs_u32)c * (FV * 4));
+#pragma unroll
+        for (int u = 0; u < FB; ++u)
+#pragma unroll
+          for (int f = 0; f < FV; ++f) a[f] = (jb + u) < n ? KINDS::op(k, a[f], tmp[u][f]) : a[f];
+      }
+#pragma unroll
+      for (int f = 0; f < FV; ++f) vals[i][f] = a[f];
+    }
+  }
+}
+// the last workgroup of a tile to be done with its counters leaves all `count` of them zero (the departures are counted in the last one)
+FS_DEV void fs_tile_leave(fs_u32* counters, int count, fs_u32 n) {
+  if (threadIdx.x == 0) {
+    const fs_u32 old = __hip_atomic_fetch_add(&counters[count - 1], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (old == n - 1)
+      for (int i = 0; i < count; ++i) __hip_atomic_store(&counters[i], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  }
 }
 
 #endif  // FS_DEVICE_H_

@@ -1565,6 +1565,151 @@ void recompute_across_kernels(const Graph& g, const PlanOptions& opt, std::vecto
   *group_of = ci->group_of;
 }
 
+// -------------------------------------------------------------------------------------------
+// Groups joined over their column reductions (GroupPlan::joined).
+// -------------------------------------------------------------------------------------------
+namespace {
+
+// 32-bit registers of rows that a lane may hold, by the workgroup that a compute unit runs: of 256 at 512 lanes.  (Batch
+// normalisation f32 compiles without scratch up to here; where another body does not, plan creation gives the joined kernel up.)
+constexpr int kJoinRegs = 200;
+
+// Lanes of a tile, workgroup, workgroups per tile, rows per lane.  Batch normalisation f32, three kernels -> joined, us:
+//  - 8 lanes, one 128-byte run of f32; 16 where rows are no whole cache lines and tiles share them ([8000,2000] 32.1 of 8 lanes,
+//    28.8 of 16; [12000,500] 24.3, 20.0; [25000,300] 31.6, 25.6; whole lines: [16384,1024] 27.1, 27.3, [1000,8192] 12.5, 13.6).
+//  - One workgroup to a tile of up to 96 KB, which then meets nobody: [600,600] 5.6 us of one, 6.9 of four; [333,777] 5.3, 7.1;
+//    but 128 KB, [1000,1000], 9.6 of one, 7.4 of eight.  Larger tiles: as many as fill the device, each with 16 KB or more of
+//    the tile ([8192,16] 7.2 us of 16, 7.6 of 32, 9.7 of 64) and 32 at most, above 200 KB each 64 ([40000,128], 160 KB,
+//    14.4 us of 32 and 15.2 of 64; [65536,64], 256 KB, 16.3 and 15.3): every workgroup reads all partials of its tile.
+//  - 256 lanes, two workgroups to a compute unit, or 512, one, from 8 MB on, where half as many partials count ([2000,3001]
+//    20.9 and 19.8; [16384,1024] 27.1 either way; [4096,1024] 10.1).
+// [16384,1024] 52 -> 27.1, [2500,8192] 73 -> 30.4, [4096,1024] 19.3 -> 10.1, [65536,16] 23.1 -> 11, [300,64] 10.1 -> 4.7.
+fs_status pick_join_shape(GroupPlan* gp, int dwords_per_row, int max_es) {
+  Schedule& s = gp->s;
+  const int R = gp->R, CUS = device_limits().cus;
+  const int64_t run = (int64_t)s.V * max_es;  // bytes of the widest tensor that a lane takes of a row
+  int L = std::min(8, pow2_ceil(s.NV));
+  const bool alone = (int64_t)R * L * run <= 96 << 10;
+  if (!alone && (int64_t)gp->C * max_es % 128 != 0) L = std::min(16, pow2_ceil(s.NV));
+  int WG = (int64_t)R * gp->C * max_es >= (8 << 20) ? 512 : 256;
+  WG = std::max(64, std::min(WG, L * pow2_ceil(std::min(R, 1024))));
+  const int G = WG / L, CT = (s.NV + L - 1) / L, trips = (R + G - 1) / G;
+  const int64_t tile = (int64_t)R * L * run;
+  int RB = 1;
+  if (!alone) RB = std::max(1, std::min({CUS * 512 / WG / CT, (int)(tile >> 14), tile > 32 * (200 << 10) ? 64 : 32, trips}));
+  const int U = (trips + RB - 1) / RB;
+  s.L = L, s.NVL = 1, s.E = s.V, s.WG = WG, s.G = G, s.CT = CT, s.n_iters = trips, s.RB = (trips + U - 1) / U, s.U = U;
+  s.grid = CT * s.RB;
+  s.fold_width = s.fold_piece = L * s.V;
+  if (U * dwords_per_row > kJoinRegs) FS_FAIL(FS_ERR_UNSUPPORTED, "%d rows to a lane do not fit its registers", U);
+  return FS_OK;
+}
+
+}  // namespace
+
+fs_status join_groups(const Graph& g, const std::vector<GroupPlan>& groups, int first, int count, const PlanOptions& opt, GroupPlan* out) {
+  GroupPlan& gp = *out;
+  gp = GroupPlan();
+  gp.joined = true;
+  std::set<int> members;
+  for (int k = first; k < first + count; ++k) {
+    const GroupPlan& p = groups[k];
+    members.insert(p.members.begin(), p.members.end());
+    gp.R = std::max(gp.R, p.R), gp.C = std::max(gp.C, p.C);
+    for (const auto& t : p.tflag)
+      if (t.second) FS_FAIL(FS_ERR_UNSUPPORTED, "a transposed value");
+  }
+  gp.members.assign(members.begin(), members.end());
+  if (gp.R < 2 || gp.C < 2 || (int)gp.members.size() > kMaxGroupMembers) FS_FAIL(FS_ERR_UNSUPPORTED, "nothing to join");
+  Analyser a(g, gp);
+  for (int m : gp.members) a.in_set[m] = 1;
+  a.R = gp.R, a.C = gp.C;
+  auto read_by_others = [&](int id) {  // from memory, by groups that are not joined here
+    for (int k = 0; k < (int)groups.size(); ++k)
+      if (k < first || k >= first + count)
+        for (const ExtTensor& e : groups[k].ext_in)
+          if (g.root_of[e.node] == id) return true;
+    return false;
+  };
+  int top = 0, max_es = 0, dwords = 0;
+  for (int m : gp.members) {
+    const fs_node& n = g.nodes[m];
+    const bool reduce = n.opcode == FS_REDUCE_COL;
+    const Kind k = a.classify(n.rows, n.cols);
+    if ((k != KIND_FULL && k != KIND_ROWV) || n.opcode == FS_REDUCE_ROW || n.opcode == FS_TRANSPOSE || n.opcode == FS_CONCAT)
+      FS_FAIL(FS_ERR_UNSUPPORTED, "node %d is not elementwise over the columns of [%d,%d]", m, gp.R, gp.C);
+    gp.kind[m] = k;
+    int lvl = 0;
+    for (int i = 0; i < n.num_in; ++i) {
+      Resolved r;
+      if (g.flat_in[m][i] || !a.resolve(n.in[i], reduce ? KIND_FULL : k, false, &r)) FS_FAIL(FS_ERR_UNSUPPORTED, "node %d: operand %d", m, n.in[i]);
+      if (r.literal) continue;
+      if (r.kind != KIND_FULL && r.kind != KIND_ROWV) FS_FAIL(FS_ERR_UNSUPPORTED, "node %d: operand %d", m, n.in[i]);
+      if (a.in_set[r.node]) {
+        lvl = std::max(lvl, gp.level[r.node] + (g.nodes[r.node].opcode == FS_REDUCE_COL ? 1 : 0));
+        continue;
+      }
+      if (a.in_set[g.root_of[r.node]]) FS_FAIL(FS_ERR_UNSUPPORTED, "node %d reads a view of a value of the same kernel", m);
+      for (const ExtTensor& e : gp.ext_in)
+        if (e.node == r.node && e.kind != r.kind) FS_FAIL(FS_ERR_UNSUPPORTED, "node %d is read in two ways", r.node);
+      add_ext_in(gp, r.node, r.kind, g.nodes[r.node].dtype);
+      gp.kind[r.node] = r.kind;
+    }
+    gp.level[m] = lvl;
+    top = std::max(top, lvl);
+    if (reduce) gp.col_reduces.push_back(m);
+    bool leaves = g.output_index[m] >= 0 || read_by_others(m);
+    for (int u : g.users[m]) leaves |= op_is_view(g.nodes[u].opcode);
+    if (!leaves) continue;
+    ExtTensor e;
+    e.node = m, e.kind = k, e.dtype = n.dtype;
+    gp.ext_out.push_back(e);
+  }
+  if (top == 0) FS_FAIL(FS_ERR_UNSUPPORTED, "nothing depends on a column reduction");
+  if ((int)(gp.ext_in.size() + gp.ext_out.size()) > kMaxGroupTensors) FS_FAIL(FS_ERR_UNSUPPORTED, "group touches too many tensors");
+  int arg = 0;
+  for (ExtTensor& e : gp.ext_in) e.arg = arg++;
+  for (ExtTensor& e : gp.ext_out) e.arg = arg++;
+  auto bytes_of = [&](int id) { return (uint64_t)g.nodes[id].rows * g.nodes[id].cols * dtype_size(g.nodes[id].dtype); };
+  for (ExtTensor& e : gp.ext_in) {
+    e.streaming = e.kind == KIND_FULL && bytes_of(e.node) >= (g.nodes[g.root_of[e.node]].opcode == FS_INPUT && !read_by_others(g.root_of[e.node]) ? 2ull << 20 : kStreamBytes);
+    if (e.kind == KIND_FULL) max_es = std::max(max_es, dtype_size(e.dtype));
+    gp.min_hbm_bytes += bytes_of(e.node);
+  }
+  for (ExtTensor& e : gp.ext_out) {
+    e.streaming = e.kind == KIND_FULL && bytes_of(e.node) >= (g.family_output[e.node] >= 0 && !read_by_others(e.node) ? 2ull << 20 : kStreamBytes);
+    if (e.kind == KIND_FULL) max_es = std::max(max_es, dtype_size(e.dtype));
+    gp.min_hbm_bytes += bytes_of(e.node);
+  }
+  if (max_es == 0) FS_FAIL(FS_ERR_UNSUPPORTED, "no [R,C] tensor");
+  Schedule& s = gp.s;
+  s.V = 16 / max_es;
+  while ((int64_t)gp.C * max_es <= 32 ? gp.C % s.V != 0 : s.V > gp.C) s.V /= 2;
+  s.NV = gp.C / s.V + (gp.C % s.V != 0);
+  for (const ExtTensor& e : gp.ext_in)
+    if (e.kind == KIND_FULL) dwords += std::max(1, s.V * dtype_size(e.dtype) / 4);
+  // (32-bit offsets, also of the rows beyond the last one; accesses through a buffer descriptor start at whole words)
+  if ((uint64_t)gp.R * gp.C * max_es > (1ull << 30)) FS_FAIL(FS_ERR_UNSUPPORTED, "tensors too large for the registers of the device");
+  for (const auto* list : {&gp.ext_in, &gp.ext_out})
+    for (const ExtTensor& e : *list)
+      if (e.kind == KIND_FULL && gp.C % s.V != 0 && dtype_size(e.dtype) < 4) FS_FAIL(FS_ERR_UNSUPPORTED, "rows of %d columns of 2 bytes or less start inside a word", gp.C);
+  const fs_status st = pick_join_shape(&gp, std::max(1, dwords), max_es);
+  if (st != FS_OK) return st;
+  s.ragged = gp.C % s.V != 0 || (int64_t)s.CT * s.L != s.NV;
+  s.col_tiled = true;
+  s.lds_bytes = s.lds_planned = ((s.L < 64 ? s.WG / 64 : s.G) + (int)gp.col_reduces.size()) * s.fold_width * 4 + 16;
+  if (s.lds_bytes > opt.lds_budget) FS_FAIL(FS_ERR_LDS_BUDGET, "joined groups need %d bytes of LDS, budget is %d", s.lds_bytes, opt.lds_budget);
+  if (s.RB > 1) {
+    s.part_stride_floats = gp.col_reduces.size() * (size_t)s.fold_width * s.RB;
+    s.ticket_stride = std::max(32, top + 2);  // (a tile's counters share no cache line with another's)
+    gp.n_tickets = s.ticket_stride * s.CT;
+    gp.part_bytes = s.part_stride_floats * s.CT * 4;
+  }
+  gp.wait_ticks = 5000;  // 50 us: several times what the workgroups of the largest tiles need from their start to the last load
+  if (const char* e = getenv("FS_JOIN_WAIT_TICKS")) gp.wait_ticks = atoi(e);
+  return FS_OK;
+}
+
 void work_span(const Graph& g, std::vector<int>* span) {
   PlanOptions opt;
   Former f(g, opt);

@@ -202,6 +202,11 @@ struct GroupPlan {
   uint64_t min_hbm_bytes = 0;
   bool reads_alone = true; // no other kernel of the plan touches the [R,C] tensors it reads
   bool exchanges = false;  // reads what another kernel of the plan wrote, or writes what another one reads
+  // Several groups of the plan in one kernel (join_groups): column reductions and what needs their results, with the rows in
+  // registers between them.  level is then the number of column reductions upstream, s.U the rows a lane holds, s.RB the
+  // workgroups of a tile, which wait for each other for `wait_ticks` of the 100 MHz clock at most.
+  bool joined = false;
+  int wait_ticks = 0;
   // generated kernel
   std::string kernel_name, source;
   std::string perf_key;  // filled on demand by fs_plan_group_perf_key
@@ -256,6 +261,10 @@ fs_status form_groups(const Graph& g, const fs_graph_desc* desc, const PlanOptio
 void recompute_across_kernels(const Graph& g, const PlanOptions& opt, std::vector<int>* group_of,
                               std::vector<std::vector<int>>* groups_in_launch_order, CloneInfo* clones);
 
+// Groups [first, first + count) of a plan as one kernel whose workgroups keep their rows in registers while the column
+// reductions of a tile are folded across workgroups.  FS_ERR_UNSUPPORTED where they are not of that form or do not fit.
+fs_status join_groups(const Graph& g, const std::vector<GroupPlan>& groups, int first, int count, const PlanOptions& opt, GroupPlan* out);
+
 // Work/Span analysis (Section 3.1): span per node, -1 for inlined and dead nodes.
 void work_span(const Graph& g, std::vector<int>* span);
 
@@ -290,6 +299,12 @@ struct fs_plan {
   std::vector<int> group_of;
   fs::CloneInfo clones;               // values computed by more than one kernel (opt.clones points here)
   std::vector<fs::GroupPlan> groups;  // in launch order
+  // runs of groups that fs_plan_run launches as one kernel, in launch order (fs_plan_tune and the introspection see the groups)
+  struct Joined {
+    int first = 0, count = 0;
+    fs::GroupPlan gp;
+  };
+  std::vector<Joined> joined;
   // workspace layout
   std::map<int, size_t> ws_tensor_offset;  // node materialised in the workspace -> byte offset
   size_t ticket_bytes = 0;                 // tickets live at the start of the workspace
@@ -299,7 +314,7 @@ struct fs_plan {
   // per-device loaded code
   struct Loaded {
     std::vector<void*> modules;    // hipModule_t per group
-    std::vector<void*> functions;  // hipFunction_t per group
+    std::vector<void*> functions;  // hipFunction_t per group, then per joined run
   };
   std::mutex mu;
   std::map<int, Loaded> loaded;

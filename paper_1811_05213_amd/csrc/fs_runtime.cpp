@@ -102,14 +102,18 @@ const DeviceLimits& device_limits() {
 }
 
 fs_status compile_kernel(const std::string& source, const std::string& name, std::vector<char>* code) {
-  std::string key_text = source;
+  // (every source starts with the building blocks, most of its text: their part of the two hashes is computed once)
+  static const std::string header = device_header_source();
+  static const uint64_t header_hash[2] = {fnv1a(header), fnv1a(header, 0x9e3779b97f4a7c15ull)};
+  const bool after_header = source.compare(0, header.size(), header) == 0;
+  std::string key_text = after_header ? source.substr(header.size()) : source;
   for (int i = 0; i < kNumCompileOptions; ++i) key_text += kCompileOptions[i];
   int rtc_major = 0, rtc_minor = 0;
   hiprtcVersion(&rtc_major, &rtc_minor);
   key_text += std::to_string(rtc_major) + "." + std::to_string(rtc_minor);
   char key[40];
-  snprintf(key, sizeof(key), "%016llx%016llx", (unsigned long long)fnv1a(key_text),
-           (unsigned long long)fnv1a(key_text, 0x9e3779b97f4a7c15ull));
+  snprintf(key, sizeof(key), "%016llx%016llx", (unsigned long long)(after_header ? fnv1a(key_text, header_hash[0]) : fnv1a(key_text)),
+           (unsigned long long)fnv1a(key_text, after_header ? header_hash[1] : 0x9e3779b97f4a7c15ull));
   const std::string dir = cache_dir();
   const std::string path = dir.empty() ? "" : dir + "/" + key + ".hsaco";
   if (!path.empty() && read_file(path, code)) return FS_OK;
@@ -355,6 +359,19 @@ fs_status fs_plan_create(const fs_graph_desc* desc, fs_plan** out_plan) {
     if (use_library) choose_from_library(g, ordered[gi], plan->group_of, (int)gi, plan->opt, &plan->groups[gi]);
   }
 
+  // Runs of groups that one kernel can take over (the library's own plans only, like the values recomputed across kernels;
+  // not under a hint, which asks for a schedule of each group).  The longest run from each group on.
+  if (plan->opt.mode != FS_MODE_UNFUSED && !plan->opt.layered && !desc->group_of_node && !plan->opt.has_hint)
+    for (int gi = 0; gi + 1 < (int)plan->groups.size(); ++gi)
+      for (int n = (int)plan->groups.size() - gi; n >= 2; --n) {
+        fs_plan::Joined j;
+        j.first = gi, j.count = n;
+        if (join_groups(g, plan->groups, gi, n, plan->opt, &j.gp) != FS_OK || generate_kernel(g, &j.gp, gi) != FS_OK) continue;
+        plan->joined.push_back(std::move(j));
+        gi += n - 1;
+        break;
+      }
+
   // One translation unit per plan: the building blocks once, then every distinct kernel body.
   // Spill feedback: a kernel whose code object reports scratch memory is planned again with less
   // register pressure -- rows held beyond 32 elements per lane step down towards chunks, narrow column tiles keep
@@ -373,6 +390,8 @@ fs_status fs_plan_create(const fs_graph_desc* desc, fs_plan** out_plan) {
     std::set<std::string> seen;
     for (const GroupPlan& gp : plan->groups)
       if (seen.insert(gp.kernel_name).second) tu += "\n" + gp.source;
+    for (const fs_plan::Joined& j : plan->joined)
+      if (seen.insert(j.gp.kernel_name).second) tu += "\n" + j.gp.source;
     st = compile_kernel(tu, "fs_plan", &plan->code);
     if (st != FS_OK) {
       delete plan;
@@ -381,6 +400,19 @@ fs_status fs_plan_create(const fs_graph_desc* desc, fs_plan** out_plan) {
     const std::map<std::string, long> scratch = code_object_kernel_field(plan->code, ".private_segment_fixed_size");
     const std::map<std::string, long> vgprs = code_object_kernel_field(plan->code, ".vgpr_count");
     bool changed = false;
+    for (size_t k = plan->joined.size(); k-- > 0;) {  // (a joined kernel that spills is given up: its groups run as they are)
+      auto it = scratch.find(plan->joined[k].gp.kernel_name);
+      if (getenv("FS_LOG_PLAN")) {
+        auto vg = vgprs.find(plan->joined[k].gp.kernel_name);
+        const Schedule& s = plan->joined[k].gp.s;
+        fprintf(stderr, "fs: groups %d to %d joined, kernel %s: %ld vector registers, %ld bytes of scratch, %d lanes per tile, workgroup %d, %d workgroups per tile, %d rows to a lane, grid %d\n",
+                plan->joined[k].first, plan->joined[k].first + plan->joined[k].count - 1, plan->joined[k].gp.kernel_name.c_str(), vg == vgprs.end() ? -1 : vg->second,
+                it == scratch.end() ? -1 : it->second, s.L, s.WG, s.RB, s.U, s.grid);
+      }
+      if (it == scratch.end() || it->second == 0) continue;
+      plan->joined.erase(plan->joined.begin() + (long)k);
+      changed = true;
+    }
     for (size_t gi = 0; gi < plan->groups.size(); ++gi) {
       GroupPlan& gp = plan->groups[gi];
       auto it = scratch.find(gp.kernel_name);
@@ -467,26 +499,47 @@ fs_status fs_plan_create(const fs_graph_desc* desc, fs_plan** out_plan) {
   }
 
   // workspace: [tickets][tensors crossing group boundaries][column-reduction partials]
-  size_t off = 0;
-  for (GroupPlan& gp : plan->groups) {
-    gp.ticket_offset = off;
-    off += (size_t)gp.n_tickets * 4;
-  }
-  plan->ticket_bytes = align_up(off, 256);
-  off = plan->ticket_bytes;
-  for (GroupPlan& gp : plan->groups)
-    for (const ExtTensor& e : gp.ext_out)
-      // (a value a plan output is a view of is written straight into the caller's buffer)
-      if (g.family_output[e.node] < 0 && !plan->ws_tensor_offset.count(e.node)) {
-        plan->ws_tensor_offset[e.node] = off;
-        off = align_up(off + (size_t)g.nodes[e.node].rows * g.nodes[e.node].cols * dtype_size(e.dtype), 256);
-      }
-  for (GroupPlan& gp : plan->groups)
-    if (gp.part_bytes) {
-      gp.part_offset = off;
-      off = align_up(off + gp.part_bytes, 256);
+  for (;;) {
+    size_t off = 0;
+    for (GroupPlan& gp : plan->groups) {
+      gp.ticket_offset = off;
+      off += (size_t)gp.n_tickets * 4;
     }
-  plan->workspace_bytes = off;
+    for (fs_plan::Joined& j : plan->joined) {
+      off = align_up(off, 128);
+      j.gp.ticket_offset = off;
+      off += (size_t)j.gp.n_tickets * 4;
+    }
+    plan->ticket_bytes = align_up(off, 256);
+    off = plan->ticket_bytes;
+    for (GroupPlan& gp : plan->groups)
+      for (const ExtTensor& e : gp.ext_out)
+        // (a value a plan output is a view of is written straight into the caller's buffer)
+        if (g.family_output[e.node] < 0 && !plan->ws_tensor_offset.count(e.node)) {
+          plan->ws_tensor_offset[e.node] = off;
+          off = align_up(off + (size_t)g.nodes[e.node].rows * g.nodes[e.node].cols * dtype_size(e.dtype), 256);
+        }
+    const size_t parts = off;
+    for (GroupPlan& gp : plan->groups)
+      if (gp.part_bytes) {
+        gp.part_offset = off;
+        off = align_up(off + gp.part_bytes, 256);
+      }
+    // (partials live while their kernel runs, and the kernels of a plan run one after the other: those of joined runs lie over the others)
+    for (fs_plan::Joined& j : plan->joined)
+      if (j.gp.part_bytes) {
+        j.gp.part_offset = parts;
+        off = std::max(off, align_up(parts + j.gp.part_bytes, 256));
+      }
+    plan->workspace_bytes = off;
+    // a plan that runs on the static scratch as separate kernels keeps doing so
+    if (off <= FS_STATIC_SCRATCH_BYTES || plan->joined.empty()) break;
+    size_t extra = 0;
+    for (const fs_plan::Joined& j : plan->joined) extra += align_up((size_t)j.gp.n_tickets * 4 + j.gp.part_bytes, 256) + 512;
+    if (off > FS_STATIC_SCRATCH_BYTES + extra) break;
+    plan->joined.clear();
+    plan->ws_tensor_offset.clear();
+  }
 
   plan->min_hbm_bytes = 0;
   for (int id : g.input_ids) {
@@ -552,12 +605,21 @@ static fs_status load_on_device(fs_plan* plan, int device, fs_plan::Loaded** out
     }
     ld.functions.push_back((void*)fn);
   }
+  for (const fs_plan::Joined& j : plan->joined) {
+    hipFunction_t fn;
+    e = hipModuleGetFunction(&fn, mod, j.gp.kernel_name.c_str());
+    if (e != hipSuccess) {
+      (void)hipModuleUnload(mod);
+      FS_FAIL(FS_ERR_HIP, "hipModuleGetFunction(%s): %s", j.gp.kernel_name.c_str(), hipGetErrorString(e));
+    }
+    ld.functions.push_back((void*)fn);
+  }
   *out = &(plan->loaded[device] = std::move(ld));
   return FS_OK;
 }
 
 namespace fs {
-// kernarg block: { void* p[NP]; float* part; u32* tickets; int R; int n_iters; }
+// kernarg block: { void* p[NP]; float* part; u32* tickets; int R; int n_iters (joined kernels: int wait); }
 hipError_t launch_group(const GroupPlan& gp, void* function, void* const* tensors, void* part, void* tickets, hipStream_t stream) {
   alignas(8) char buf[8 * 48 + 32];
   size_t n = 0;
@@ -569,7 +631,7 @@ hipError_t launch_group(const GroupPlan& gp, void* function, void* const* tensor
   for (size_t k = 0; k < np; ++k) push_ptr(tensors[k]);
   push_ptr(part);
   push_ptr(tickets);
-  const int R = gp.R, iters = gp.s.n_iters;
+  const int R = gp.R, iters = gp.joined ? gp.wait_ticks : gp.s.n_iters;
   memcpy(buf + n, &R, 4);
   memcpy(buf + n + 4, &iters, 4);
   n += 8;
@@ -609,15 +671,19 @@ static fs_status enqueue_groups(const fs_plan* plan, const fs_plan::Loaded* ld, 
     if (g.family_output[root] >= 0) return outputs[g.family_output[root]];
     return ws + plan->ws_tensor_offset.at(root);
   };
+  size_t next_joined = 0;
   for (size_t gi = 0; gi < plan->groups.size(); ++gi) {
-    const GroupPlan& gp = plan->groups[gi];
+    const bool joins = next_joined < plan->joined.size() && plan->joined[next_joined].first == (int)gi;
+    const GroupPlan& gp = joins ? plan->joined[next_joined].gp : plan->groups[gi];
+    void* function = joins ? ld->functions[plan->groups.size() + next_joined] : ld->functions[gi];
     void* tensors[48];
     size_t n = 0;
     for (const ExtTensor& t : gp.ext_in) tensors[n++] = tensor_ptr(t.node);
     for (const ExtTensor& t : gp.ext_out) tensors[n++] = tensor_ptr(t.node);
-    const hipError_t e = launch_group(gp, ld->functions[gi], tensors, gp.part_bytes ? (void*)(ws + gp.part_offset) : nullptr,
+    const hipError_t e = launch_group(gp, function, tensors, gp.part_bytes ? (void*)(ws + gp.part_offset) : nullptr,
                                       gp.n_tickets ? (void*)(ws + gp.ticket_offset) : nullptr, stream);
     if (e != hipSuccess) FS_FAIL(FS_ERR_HIP, "launch of group %zu (%s): %s", gi, gp.kernel_name.c_str(), hipGetErrorString(e));
+    if (joins) gi += (size_t)plan->joined[next_joined++].count - 1;
   }
   return FS_OK;
 }
@@ -666,7 +732,7 @@ fs_status fs_plan_workspace_check(fs_plan* plan, const void* workspace, size_t w
   fs_status st = check_workspace(plan, workspace, workspace_bytes);
   if (st != FS_OK) return st;
   size_t n = 0;
-  for (const GroupPlan& gp : plan->groups) n += (size_t)gp.n_tickets;
+  if (plan->ticket_bytes) n = plan->ticket_bytes / 4;
   if (n == 0) return FS_OK;
   hipError_t e = hipStreamSynchronize((hipStream_t)hip_stream);
   if (e != hipSuccess) FS_FAIL(FS_ERR_HIP, "hipStreamSynchronize: %s", hipGetErrorString(e));
@@ -800,6 +866,16 @@ fs_status fs_plan_group_kernel_name(const fs_plan* plan, int32_t group, const ch
   if (!plan || !out_name) FS_FAIL(FS_ERR_INVALID_ARG, "NULL argument");
   if (group < 0 || group >= (int)plan->groups.size()) FS_FAIL(FS_ERR_INVALID_ARG, "group %d out of range", group);
   *out_name = plan->groups[group].kernel_name.c_str();
+  return FS_OK;
+}
+
+fs_status fs_plan_joined_groups(const fs_plan* plan, int32_t index, int32_t* first_group, int32_t* num_groups, const char** source) {
+  if (!plan) FS_FAIL(FS_ERR_INVALID_ARG, "NULL argument");
+  if (index < 0 || index >= (int)plan->joined.size()) FS_FAIL(FS_ERR_INVALID_ARG, "joined run %d out of range", index);
+  const fs_plan::Joined& j = plan->joined[index];
+  if (first_group) *first_group = j.first;
+  if (num_groups) *num_groups = j.count;
+  if (source) *source = j.gp.source.c_str();
   return FS_OK;
 }
 

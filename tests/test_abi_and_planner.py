@@ -1224,3 +1224,76 @@ def test_workgroups_of_kernels_with_both_reductions(rows, cols, wg):
     p = fs.Plan(multi_reduce_graph(rows, cols))  # (nothing of the row's size leaves the kernel)
     assert p.group_info(0)["wg_threads"] == 1024
     p.destroy()
+
+
+def column_stage_graph(kind, rows, cols, dt):
+    """Column reductions whose results the rows need again: softmax down the columns; two inputs with a mask, intermediates and
+    [1,C] values among the outputs; one stage with a [1,C] input."""
+    g = Graph()
+    x = g.input(rows, cols, dt)
+    z = x if dt == "f32" else g.unary("convert", x, "f32")
+    b = lambda v: g.bcast_rowvec(v, rows)
+    if kind == "softmax":
+        e = g.unary("exp", g.binary("sub", z, b(g.reduce_col("max", z))))
+        y = g.binary("div", e, b(g.reduce_col("sum", e)))
+        g.set_outputs([y if dt == "f32" else g.unary("convert", y, dt)])
+    elif kind == "masked":
+        w, keep = g.input(rows, cols), g.input(rows, cols, "u8")
+        z = g.select(keep, g.binary("mul", z, w), g.const(0.25, rows, cols))
+        mu, lo = g.reduce_col("mean", z), g.reduce_col("min", z)
+        d = g.unary("abs", g.binary("sub", z, b(mu)))
+        mx = g.reduce_col("max", d)
+        one = g.binary("add", mx, g.const(1.0, 1, cols))
+        g.set_outputs([g.binary("div", d, b(one)), z, mx, g.unary("log", one), lo])
+    else:
+        gam = g.input(1, cols)
+        g.set_outputs([g.binary("mul", g.binary("sub", z, b(g.reduce_col("mean", z))), b(gam))])
+    return g
+
+
+def test_groups_joined_over_their_column_reductions():
+    from workloads.patterns import batchnorm
+
+    def joined(g, **kw):
+        p = fs.Plan(g, **kw)
+        out = p.joined_groups(), p.stats()["num_groups"], p.workspace_bytes()
+        p.destroy()
+        return out
+
+    for rows, cols, per_tile in ((16384, 1024, 8), (65536, 64, 64), (1000, 1000, 13), (600, 600, 1), (2, 2, 1)):
+        runs, groups, _ = joined(batchnorm(rows, cols))
+        assert [r[:2] for r in runs] == [(0, 3)] and groups == 3
+        src = runs[0][2]
+        assert f"RB = {per_tile}," in src and src.count("fs_tile_meet<") == (2 if per_tile > 1 else 0)
+        assert src.count("fs_load_words<0, V") == (1 if per_tile == 1 else 5)  # read once (and again where a peer is late)
+    for kind in ("softmax", "masked", "scaled"):
+        for dt in ("f32", "bf16"):
+            runs, groups, _ = joined(column_stage_graph(kind, 500, 96, dt))
+            assert len(runs) == 1 and runs[0][:2] == (0, groups) and groups >= 2
+    # not: tensors beyond the registers of the device, rows of 2-byte elements that start inside a word, a hint, the caller's own
+    # groups, one launch per op, the layered planner, row reductions among the groups
+    g = batchnorm(1000, 1000)
+    p = fs.Plan(g)
+    own = [max(k, 0) for k in p.node_groups()]
+    p.destroy()
+    assert joined(batchnorm(40000, 1024))[0] == [] and joined(column_stage_graph("softmax", 500, 97, "bf16"))[0] == []
+    for kw in ({"hint": {"wg_threads": 256}}, {"group_of_node": own}, {"mode": fs.FS_MODE_UNFUSED}, {"mode": fs.FS_MODE_LAYERED}, {"lds_budget_bytes": 1024}):
+        assert joined(g, **kw)[0] == [], kw
+    assert joined(random_dag_graph())[0] == [] and joined(multi_reduce_graph(1000, 100))[0] == []
+
+
+def test_plans_on_the_static_scratch_stay_there():
+    # a value that passes between two kernels fills the static scratch but for 48 KB: the three kernels of a batch normalisation
+    # fit beside it, the partials of the joined one do not
+    from workloads.patterns import batchnorm
+    g = batchnorm(1000, 1000)
+    p = fs.Plan(g)
+    assert len(p.joined_groups()) == 1
+    p.destroy()
+    x = g.input(2048, 1018)
+    e = g.binary("mul", x, g.bcast_colvec(g.reduce_row("sum", x), 1018))
+    v = g.reshape(e, 1018, 2048)
+    g.set_outputs(list(g.outputs) + [g.reduce_row("sum", v)])
+    p = fs.Plan(g)
+    assert p.joined_groups() == [] and 8 << 20 >= p.workspace_bytes() > (8 << 20) - (48 << 10)
+    p.destroy()

@@ -1268,3 +1268,57 @@ def test_views_of_nd_tensors_and_concats():
     c = g.concat(g.unary("tanh", ia), g.reshape(ib, 64, 48))
     g.set_outputs([g.reduce_row("sum", c), g.unary("sigmoid", c)])
     both_modes(g, [RNG.standard_normal((64, 48)).astype(np.float32), RNG.standard_normal((32, 96)).astype(np.float32)], "concat of computed + view")
+
+
+# ------------------------------------------------------------------ groups joined over their column reductions
+@pytest.mark.parametrize("kind,rows,cols,dt", [
+    ("softmax", 2, 2, "f32"), ("softmax", 3, 5, "f32"), ("softmax", 767, 96, "f32"), ("softmax", 770, 96, "f32"),  # one workgroup a tile, several
+    ("softmax", 1003, 101, "f32"), ("softmax", 5000, 33, "f32"), ("softmax", 3000, 64, "bf16"), ("softmax", 70000, 8, "bf16"),
+    ("masked", 300, 77, "f32"), ("masked", 2100, 260, "bf16"), ("masked", 4097, 129, "f32"), ("scaled", 33, 1000, "f32"), ("scaled", 9000, 257, "f32"),
+    ("scaled", 3000, 1600, "f32"), ("scaled", 2049, 640, "bf16")])
+def test_joined_groups(kind, rows, cols, dt, monkeypatch):
+    from test_abi_and_planner import column_stage_graph
+    g = column_stage_graph(kind, rows, cols, dt)
+    ins = []
+    for i in g.input_ids():
+        n = g.nodes[i]
+        a = RNG.standard_normal((n.rows, n.cols)).astype(np.float32)
+        ins.append((RNG.random((n.rows, n.cols)) < 0.8).astype(np.uint8) if n.dtype == "u8" else f32_to_bf16_bits(a) if n.dtype == "bf16" else a)
+    p = fs.Plan(g)
+    assert len(p.joined_groups()) == 1
+    p.destroy()
+    _, out, _ = both_modes(g, ins, f"{kind} {rows}x{cols} {dt}")
+    # a workgroup that does not wait for the others computes their partials itself: the same bits
+    monkeypatch.setenv("FS_JOIN_WAIT_TICKS", "0")
+    for a, b in zip(out, run_graph(g, ins)):
+        np.testing.assert_array_equal(a.view(np.uint8), b.view(np.uint8))
+
+
+def test_joined_groups_repeat_and_replay():
+    # counters return to zero after every run; runs agree bit for bit, eagerly and from a graph
+    import torch
+    from workloads.patterns import batchnorm
+    rows, cols = 3000, 200
+    g = batchnorm(rows, cols)
+    p = fs.Plan(g)
+    assert "fs_tile_meet<" in p.joined_groups()[0][2]
+    r = DeviceRun(p)
+    r.set_inputs([RNG.standard_normal((rows, cols)).astype(np.float32), RNG.standard_normal((1, cols)).astype(np.float32), RNG.standard_normal((1, cols)).astype(np.float32)])
+    p.load()
+    r.launch()
+    first = r.results()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        r.launch()
+    for k in range(40):
+        for o in r.outputs:
+            o.fill_(7)
+        if k % 2:
+            graph.replay()
+        else:
+            r.launch()
+        for a, b in zip(first, r.results()):
+            np.testing.assert_array_equal(a, b)
+    p.workspace_check(r.workspace.data_ptr(), r.ws_bytes)
+    del graph
+    p.destroy()
