@@ -216,6 +216,36 @@ struct Emitter {
     return "fs_round<" + std::to_string(n.dtype) + ">(" + e + ")";
   }
 
+  // The per-row value ([R,1], computed by this kernel) that [R,C] member `m` divides by, where the division may go through its
+  // reciprocal (fs_div_row): not on a predicate path, which sees the IEEE division itself.  Else -1.
+  int row_divisor(int m) const {
+    const fs_node& n = g.nodes[m];
+    if (n.opcode != FS_DIV || g.exact[m] || gp.kind.at(m) != KIND_FULL || g.nodes[n.in[1]].opcode == FS_CONST) return -1;
+    const int s = source_of(n.in[1]);
+    return in_set[s] && !folded[s] && gp.kind.at(s) == KIND_COLV ? s : -1;
+  }
+  // ... what it needs beside a per-row value that has just been computed
+  void emit_reciprocal(int s, std::ostringstream& to, const std::string& ind) {
+    for (int m : gp.members)
+      if (row_divisor(m) == s) {
+        const std::string nm = name(s, KIND_COLV), k = std::to_string(loc(s));
+        to << ind << "const float i" << k << " = fs_div(1.0f, " << nm << ");\n" << ind << "const bool o" << k << " = fs_reciprocal_overflows(" << nm << ");\n";
+        return;
+      }
+  }
+  // the elements of [R,C] member `m` (declared already), inside the loop `loop`
+  void emit_elements(int m, const std::string& ind, const std::string& loop, const std::string& value) {
+    const std::string nm = name(m, KIND_FULL);
+    const int s = row_divisor(m);
+    if (s < 0) {
+      os << ind << loop << nm << "[e] = " << value << ";\n";
+      return;
+    }
+    const std::string k = std::to_string(loc(s)), a = ref(g.nodes[m].in[0]), sn = name(s, KIND_COLV);
+    os << ind << loop << nm << "[e] = " << rounded(m, "fs_div_row(" + a + ", " + sn + ", i" + k + ")") << ";\n"
+       << ind << "if (__builtin_expect(o" << k << ", false)) " << loop << nm << "[e] = " << value << ";\n";
+  }
+
   static std::string tmpl_row() { return "V, NVL, L, NV, RAGGED"; }
 
   // The last stage of a row-reduction body (everything after the last exchange: normalise, scale,
@@ -381,6 +411,7 @@ struct Emitter {
       const fs_node& bn = g.nodes[b];
       const std::string q = "q" + std::to_string(loc(b));
       os << ind << "const float " << name(b, KIND_COLV) << " = " << rounded(b, bn.attr_i == FS_RED_MEAN ? q + " / (float)C" : q) << ";\n";
+      emit_reciprocal(b, os, ind);
       if (const ExtTensor* e = find_out(b)) emit_store(*e, ind);
     }
   }
@@ -442,9 +473,12 @@ struct Emitter {
       if (!mem.count(m) || folded[m]) continue;
       const fs_node& n = g.nodes[m];
       const Kind k = gp.kind.at(m);
-      if (!is_alias(m))
-        os << "      float " << name(m, k) << "[E];\n      _Pragma(\"unroll\") for (int e = 0; e < E; ++e) " << name(m, k) << "[e] = "
-           << (n.opcode == FS_TRANSPOSE ? ref(n.in[0]) : rounded(m, expr(m))) << ";\n";
+      if (!is_alias(m)) {
+        os << "      float " << name(m, k) << "[E];\n";
+        if (k == KIND_FULL && n.opcode != FS_TRANSPOSE) emit_elements(m, "      ", "_Pragma(\"unroll\") for (int e = 0; e < E; ++e) ", rounded(m, expr(m)));
+        else
+          os << "      _Pragma(\"unroll\") for (int e = 0; e < E; ++e) " << name(m, k) << "[e] = " << (n.opcode == FS_TRANSPOSE ? ref(n.in[0]) : rounded(m, expr(m))) << ";\n";
+      }
       if (staged(m) && !stage_written.count(m))  // its first pass: the slot takes it over (from whatever it dominates)
         os << "      if (ch < STAGE_CHUNKS) fs_stage_row_chunk<" << n.dtype << ", V, NVL, L>(" << stage_chunk(m) << ", " << name(m, k) << ", lir);\n";
       if (!store_outputs) continue;
@@ -544,6 +578,7 @@ struct Emitter {
       for (int m : gp.members) {
         if (gp.level.at(m) != lvl || gp.kind.at(m) != KIND_COLV || is_rr(m) || folded[m]) continue;
         os << "    const float " << name(m, KIND_COLV) << " = " << rounded(m, expr(m)) << ";\n";
+        emit_reciprocal(m, os, "    ");
         if (const ExtTensor* e = find_out(m))
           os << "    if (lir == 0) fs_store1<" << e->dtype << ">(a.p[" << e->arg << "], row, " << name(m, KIND_COLV) << ");\n";
       }
@@ -1131,6 +1166,29 @@ struct Emitter {
         }
     }
     if (stage_before_loop) emit_staging("  ");
+    // the next row of every [R,C] input on its way (Schedule::ahead)
+    auto emit_ask = [&](const std::string& ind, const std::string& row0) {
+      int k = 0;
+      for (const ExtTensor& e : gp.ext_in) {
+        if (e.kind != KIND_FULL) continue;
+        const std::string nt = e.streaming ? "true" : "false", ua = over ? "true" : "false", p = "a.p[" + std::to_string(e.arg) + "]";
+        os << ind << "fs_row_ask<" << e.dtype << ", V, L, JL, " << ua << ", " << nt << ">(lds_ahead + " << k++ << " * (JL * L * 16), " << p << ", " << row0 << ", lir);\n";
+        if (s.ahead_lds < s.NVL)
+          os << ind << "_Pragma(\"unroll\") for (int j = JL; j < NVL; ++j) n" << loc(e.node) << "[j - JL] = fs_load_raw<" << e.dtype << ", V, " << nt << ", " << ua << ">(" << p << ", " << row0
+             << " + fs_col_of<V, NV, RAGGED>(j * L + lir));\n";
+      }
+    };
+    if (s.ahead) {
+      int n_full = 0;
+      for (const ExtTensor& e : gp.ext_in)
+        if (e.kind == KIND_FULL) {
+          ++n_full;
+          if (s.ahead_lds < s.NVL) os << "  typename fs_vec<typename fs_elem<" << e.dtype << ">::type, V>::type n" << loc(e.node) << "[" << s.NVL - s.ahead_lds << "];\n";
+        }
+      os << "  constexpr int JL = " << s.ahead_lds << ";\n  __shared__ __attribute__((aligned(16))) fs_u8 lds_ahead[" << n_full << " * JL * L * 16];\n";
+      emit_ask("  ", "(long)blockIdx.x * C");
+      os << "  fs_wait_vm<0>();\n";
+    }
     for (int k = 0; k < K; ++k) {
       const int m = gp.col_reduces[k];
       os << "  float ca" << loc(m) << "[E];\n  _Pragma(\"unroll\") for (int e = 0; e < E; ++e) ca" << loc(m) << "[e] = fs_red_identity<"
@@ -1177,6 +1235,9 @@ struct Emitter {
     } else {
       os << "  for (int it0 = (int)blockIdx.x * " << U << "; it0 < a.n_iters; it0 += (int)gridDim.x * " << U << ") {\n";
     }
+    int n_asked = 0;
+    // (a row's column offsets are computed again for every row: kept across the loop they would take registers)
+    if (s.ahead) os << "    const int lir = (int)fs_opaque((fs_u32)tid) & (L - 1);\n";
     for (int u = 0; u < U && UN == 1; ++u) {
       const std::string x = U == 1 ? "" : "_" + std::to_string(u);
       if (U > 1) os << "    const int it" << x << " = it0 + " << u << ";\n";
@@ -1202,10 +1263,19 @@ struct Emitter {
         os << "    const long unit = (long)it * G + rg;\n    const long row = unit / CT;\n    const int vbase = (int)(unit % CT) * (NVL * L);\n";
       }
       // rows beyond R are clamped for loads (never predicated) and masked at stores / accumulations
-      os << "    const bool rok" << x << " = row" << x << " < R;\n    const long row_ld" << x << " = rok" << x << " ? row" << x
-         << " : R - 1;\n    const long row0" << x << " = row_ld" << x << " * C;\n    (void)row0" << x << "; (void)vbase" << x << ";\n";
+      if (s.ahead)  // (one row to a trip: all of them lie inside the tensor, and the stores need no branch)
+        os << "    constexpr bool rok = true;\n    const long row_ld = row, row0 = row_ld * C;\n    (void)rok; (void)row_ld; (void)row0; (void)vbase;\n";
+      else
+        os << "    const bool rok" << x << " = row" << x << " < R;\n    const long row_ld" << x << " = rok" << x << " ? row" << x
+           << " : R - 1;\n    const long row0" << x << " = row_ld" << x << " * C;\n    (void)row0" << x << "; (void)vbase" << x << ";\n";
       for (const ExtTensor& e : gp.ext_in) {
-        if (e.kind == KIND_FULL && rotate) {
+        if (e.kind == KIND_FULL && s.ahead) {
+          os << "    float " << name(e.node, KIND_FULL) << "[E];\n    fs_row_take<" << e.dtype << ", V, NVL, L, JL>(" << name(e.node, KIND_FULL) << ", lds_ahead + " << n_asked++
+             << " * (JL * L * 16), lir);\n";
+          if (s.ahead_lds < s.NVL)
+            os << "    _Pragma(\"unroll\") for (int j = JL; j < NVL; ++j) _Pragma(\"unroll\") for (int k = 0; k < V; ++k) " << name(e.node, KIND_FULL) << "[j * V + k] = fs_to_f32<" << e.dtype
+               << ">(n" << loc(e.node) << "[j - JL][k]);\n";
+        } else if (e.kind == KIND_FULL && rotate) {
           // (already in registers: requested before the loop or at the end of the previous trip)
         } else if (e.kind == KIND_FULL) {
           os << "    float " << name(e.node, KIND_FULL) << x << "[E];\n";
@@ -1224,6 +1294,12 @@ struct Emitter {
         os << "    float " << name(m, KIND_FULL) << "[E];\n    fs_load_row_concat<" << cn.dtype << ", " << tmpl_row() << ", " << cn.attr_i << ", " << split
            << "L, " << g.nodes[cn.in[1]].cols << "L>(" << name(m, KIND_FULL) << ", a.p[" << ea.arg << "], a.p[" << eb.arg << "], row_ld, lir, vbase);\n";
       }
+    }
+    if (s.ahead) {
+      // (the LDS reads are done before the next row may overwrite what they read)
+      os << "    fs_wait_lds();\n    if (it + (int)gridDim.x < a.n_iters) {\n      const long next0 = ((long)it + (int)gridDim.x) * C;\n";
+      emit_ask("      ", "next0");
+      os << "    }\n";
     }
     // Inside the loop body every per-column value is made available right before its first use,
     // one tensor at a time (a [1,C] operand costs E registers from its load to its last use; three
@@ -1369,7 +1445,7 @@ struct Emitter {
           os << "    {\n      const fs_xwave<" << KB << ", " << WPR << "> xw{lds_rr + (parity * G + rg) * " << WPR * KB
              << ", lir >> 6, (tid & 63) == 0};\n";
           for (size_t k = 0; k < batch.size(); ++k) os << "      xw.put(" << k << ", q" << loc(batch[k]) << ");\n";
-          os << "      fs_lds_barrier();\n";
+          os << "      fs_lds_barrier" << (s.ahead ? "_ahead" : "") << "();\n";
           for (size_t k = 0; k < batch.size(); ++k)
             os << "      q" << loc(batch[k]) << " = xw.get<" << g.nodes[batch[k]].attr_i << ">(" << k << ");\n";
           os << "      parity ^= 1;\n    }\n";
@@ -1378,6 +1454,7 @@ struct Emitter {
           const fs_node& bn = g.nodes[b];
           const std::string q = "q" + std::to_string(loc(b));
           os << "    const float " << name(b, KIND_COLV) << " = " << rounded(b, bn.attr_i == FS_RED_MEAN ? q + " / (float)C" : q) << ";\n";
+          emit_reciprocal(b, os, "    ");
           if (const ExtTensor* e = find_out(b)) emit_store(*e, "    ");
         }
         continue;
@@ -1410,9 +1487,11 @@ struct Emitter {
       const Kind k = gp.kind.at(m);
       if (k == KIND_COLV) {
         (strip ? pre : os) << "    const float " << name(m, k) << " = " << rounded(m, expr(m)) << ";\n";
+        emit_reciprocal(m, strip ? pre : os, "    ");
       } else {
         declare(name(m, k), "    ");
-        os << "    " << eloop() << name(m, k) << "[e] = " << rounded(m, expr(m)) << ";\n";
+        if (k == KIND_FULL) emit_elements(m, "    ", eloop(), rounded(m, expr(m)));
+        else os << "    " << eloop() << name(m, k) << "[e] = " << rounded(m, expr(m)) << ";\n";
       }
       if (const ExtTensor* e = find_out(m)) emit_store(*e, "    ");
     }
@@ -1441,6 +1520,13 @@ struct Emitter {
           os << "      fs_load_row<" << e.dtype << ", " << tmpl_row() << ", " << (e.streaming ? "true" : "false") << ">(" << name(e.node, KIND_FULL)
              << ", a.p[" << e.arg << "], rnl * C, lir, 0);\n";
       os << "    }\n";
+    }
+    if (s.ahead) {
+      // what was asked for is older than the stores that every lane has made of this row: it has arrived when no more than those are outstanding
+      int stores = 0;
+      for (const ExtTensor& e : gp.ext_out)
+        if (e.kind == KIND_FULL) stores += (int)(C / ((int64_t)s.L * s.V));
+      os << "    fs_wait_vm<" << std::min(stores, 63) << ">();\n";
     }
     os << "  }\n";
 

@@ -102,6 +102,17 @@ FS_DEV float fs_rcp(float x) { return __builtin_amdgcn_rcpf(x); }
 FS_DEV float fs_rsqrt(float x) { return __builtin_amdgcn_rsqf(x); }
 FS_DEV float fs_sqrt(float x) { return __builtin_sqrtf(x); }
 FS_DEV float fs_div(float a, float b) { return a / b; }
+// Division of a row's elements by one value of the row.  With r = 1 / s, computed once, x * r is at most 1.5 ulp off and one
+// residual step, q + (x - q s) r, makes it the correctly rounded quotient (Markstein's division theorem; the same bits as the
+// division in 2e8 random pairs; denormal quotients within 1.3 of their spacings): five instructions in the place of eleven, one of
+// them a reciprocal.  A quotient that is zero, infinite or no number is what the product says.  Divisors whose reciprocal overflows (below 2^-128, but not zero)
+// take the general division.
+FS_DEV bool fs_reciprocal_overflows(float s) { return __builtin_fabsf(s) < 0x1p-128f && s != 0.0f; }
+FS_DEV float fs_div_row(float x, float s, float r) {
+  const float q = x * r;
+  const float c = __builtin_fmaf(__builtin_fmaf(-q, s, x), r, q);
+  return __builtin_amdgcn_classf(q, 0x198 /* normal or denormal, of either sign */) ? c : q;
+}
 FS_DEV float fs_max(float a, float b) { return __builtin_fmaxf(a, b); }
 FS_DEV float fs_min(float a, float b) { return __builtin_fminf(a, b); }
 
@@ -301,6 +312,48 @@ template <int DT, int V, int NVL, int L> FS_DEV void fs_load_row_chunk_lds(float
 #pragma unroll
   for (int j = 0; j < NVL; ++j) fs_load_vec<DT, V>(&dst[j * V], lds_chunk, (long)(j * L + lir) * V);
 }
+
+// The next row on its way while a row is worked on: its first JL vectors go from memory to LDS without passing registers, the rest
+// waits in registers of their own.  A wavefront reads back what it asked for itself, 64 lanes x 16 bytes that follow each other, so
+// only its own counter of outstanding accesses orders the two; the compiler does not see that dependence, the waits are spelled out
+// (fs_wait_vm).  All JL vectors lie inside the row.  Rows that start inside a vector (UA) are asked for in 4-byte pieces.
+#define FS_LDS_BYTES(p) ((__attribute__((address_space(3))) void*)(p))
+#define FS_GLOBAL_BYTES(p) ((const __attribute__((address_space(1))) void*)(p))
+template <int DT, int V, int L, int JL, bool UA, bool NT> FS_DEV void fs_row_ask(fs_u8* lds, const void* base, long row_elem0, int lir) {
+  typedef typename fs_elem<DT>::type T;
+  static_assert(V * sizeof(T) == 16 && L % 64 == 0 && (!UA || sizeof(T) == 4), "16 bytes to a lane");
+  const int wave = __builtin_amdgcn_readfirstlane(lir >> 6);
+#pragma unroll
+  for (int j = 0; j < JL; ++j) {
+    fs_u8* const to = lds + (j * (L / 64) + wave) * 1024;
+    if constexpr (UA) {
+      const T* const from = static_cast<const T*>(base) + row_elem0 + (j * L + wave * 64) * V + (lir & 63);
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        if constexpr (NT) __builtin_amdgcn_global_load_lds(FS_GLOBAL_BYTES(from + q * 64), FS_LDS_BYTES(to + q * 256), 4, 0, 2);
+        else __builtin_amdgcn_global_load_lds(FS_GLOBAL_BYTES(from + q * 64), FS_LDS_BYTES(to + q * 256), 4, 0, 0);
+      }
+    } else {
+      const T* const from = static_cast<const T*>(base) + row_elem0 + (long)(j * L + lir) * V;
+      if constexpr (NT) __builtin_amdgcn_global_load_lds(FS_GLOBAL_BYTES(from), FS_LDS_BYTES(to), 16, 0, 2);
+      else __builtin_amdgcn_global_load_lds(FS_GLOBAL_BYTES(from), FS_LDS_BYTES(to), 16, 0, 0);
+    }
+  }
+}
+template <int DT, int V, int NVL, int L, int JL> FS_DEV void fs_row_take(float (&dst)[NVL * V], const fs_u8* lds, int lir) {
+  const int wave = lir >> 6;
+#pragma unroll
+  for (int j = 0; j < JL; ++j) fs_load_vec<DT, V>(&dst[j * V], lds + (j * (L / 64) + wave) * 1024, (long)(lir & 63) * V);
+}
+// waits until at most N of this wavefront's accesses to global memory are outstanding (they complete in order)
+template <int N> FS_DEV void fs_wait_vm() {
+  asm volatile("" : : : "memory");
+  __builtin_amdgcn_s_waitcnt((N & 15) | 0xf70 | (N >> 4) << 14);
+  asm volatile("" : : : "memory");
+}
+FS_DEV void fs_wait_lds() { asm volatile("s_waitcnt lgkmcnt(0)" : : : "memory"); }
+// fs_lds_barrier where a row is on its way to LDS: a fence would wait for it
+FS_DEV void fs_lds_barrier_ahead() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" : : : "memory"); }
 
 // Transposing store of the lane's slice of row `row` of a [R,C] value into a [C,R] tensor.
 template <int DT, int V, int NVL, int L, int NV, int RAGGED>
@@ -677,7 +730,7 @@ template <int DT, int V, bool NT> FS_DEV void fs_store_words(const float (&src)[
 // an index the compiler does not recognise as the one it computed before (so that a pass over the rows recomputes its offsets
 // instead of keeping those of the pass before in registers)
 FS_DEV fs_u32 fs_opaque(fs_u32 x) {
-  asm("" : "+v"(x));
+  asm volatile("" : "+v"(x));
   return x;
 }
 

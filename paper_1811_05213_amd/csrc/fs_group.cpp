@@ -612,6 +612,27 @@ struct Scheduler {
         if (e.kind == KIND_FULL) full_bytes += dtype_size(e.dtype);
       if (rowv_bytes * 2 >= full_bytes * 3) cap = std::max(CUS, (int)(RES / 2 / WG));
     }
+    // Rows that fill a compute unit's registers, one workgroup to a unit: loads, arithmetic and stores of a row would follow each
+    // other.  One workgroup per unit stays instead and asks for its next row, mostly through LDS, before it works on a row (loads
+    // asked for after the stores wait for them: 14-20 % slower).  softmax fp32 [1024,65536] 110.8 -> 103.8 us, [2048,50000] 159.2 -> 155.8,
+    // [2048,32768] 97.9 -> 94.3, [300,65000] 43.6 -> 39.8, [400,50000] 38.2 -> 31.6; a copy in such rows takes 144 us for the second.
+    // Below 32 elements per lane two workgroups share a unit, which is better ([4096,20000] 108.8 against 115.0).  Rows that start
+    // inside a vector cross to LDS in 4-byte pieces, which eats the gain ([2048,33001] 104.7 against 106.3) but for a few rows
+    // ([400,50001] 37.6 -> 31.0).
+    int row_inputs = 0;
+    bool whole_lanes = true;
+    for (const ExtTensor& e : gp->ext_in) {
+      row_inputs += e.kind == KIND_FULL ? 1 : e.kind == KIND_ROWV ? 2 : 0;
+      whole_lanes &= e.kind != KIND_FULL || V * dtype_size(e.dtype) == 16;
+    }
+    s.ahead = opt.ahead && rowred && !colred && !chunked && !resident && !has_transposed && !has_concat && CT == 1 && s.G == 1 && WG == 1024 && s.E >= 32 && row_inputs == 1 &&
+              whole_lanes && (C % V == 0 ? R > CUS : max_es == 4 && R > CUS && R <= 2 * CUS);
+    if (s.ahead) {
+      const int lds = opt.lds_budget_given ? opt.lds_budget : device_limits().lds_per_workgroup;
+      s.ahead_lds = std::min(C / (L * V), (lds - 2048) / (L * 16));
+      s.ahead = s.ahead_lds >= 1 && NVL - s.ahead_lds <= 8;
+      if (s.ahead) cap = CUS;
+    }
     if (opt.has_hint && opt.hint.max_workgroups > 0) cap = opt.hint.max_workgroups;
     cap = std::min(cap, (int)(0x7fffffff / WG));  // a launch holds fewer than 2^31 lanes: beyond that the workgroups loop
     s.grid = std::max(1, std::min(s.n_iters, cap));
@@ -718,6 +739,7 @@ struct Scheduler {
     // (one 1024-lane workgroup per compute unit runs such a kernel, so it may take all a workgroup is allowed
     // unless the caller set a budget); code generation decides which inputs are worth it.
     s.stage_avail = 0;
+    if (s.ahead) s.lds_bytes = s.lds_planned = lds + s.ahead_lds * L * 16;  // (a workgroup has its compute unit to itself, like those below)
     if (chunked && !split_rows) {
       const int cap = opt.lds_budget_given ? opt.lds_budget : device_limits().lds_per_workgroup;
       s.stage_avail = std::max(0, cap - lds - 512);
@@ -962,6 +984,9 @@ fs_status analyse_group(const Graph& g, const std::vector<int>& members, const s
     e.streaming = e.kind == KIND_FULL && !e.transposed && bytes_of(e) >= (once ? kStreamOnceBytes : kStreamBytes);
   }
 
+  int min_es = 4;
+  for (const ExtTensor& e : gp.ext_in)
+    if (e.kind == KIND_FULL) min_es = std::min(min_es, dtype_size(e.dtype));
   gp.min_hbm_bytes = 0;
   for (const ExtTensor& e : gp.ext_in) gp.min_hbm_bytes += (uint64_t)g.nodes[e.node].rows * g.nodes[e.node].cols * dtype_size(e.dtype);
   for (const ExtTensor& e : gp.ext_out) gp.min_hbm_bytes += (uint64_t)g.nodes[e.node].rows * g.nodes[e.node].cols * dtype_size(e.dtype);
@@ -980,7 +1005,11 @@ fs_status analyse_group(const Graph& g, const std::vector<int>& members, const s
   // from cold memory); masked softmax bf16 [32768,577] 22.5 -> 20.4 us (22.5 -> 22.8 us).  Not for groups that only stream
   // (no difference) or fold columns ([60001,515]: 33.3 -> 35.5 us).
   // So do the narrow tiles of small column folds.
-  if (st == FS_OK && ((gp.s.shares_lines && !gp.row_reduces.empty() && gp.col_reduces.empty()) || (gp.s.narrow_tiles && gp.s.L < 32)))
+  // Nor where a row has one such line among 32 or more and the tensors are far beyond the caches (masked softmax f32 [4096,8191]
+  // 73.0 -> 68.2 us, softmax [9000,7001] 88.7 -> 83.6, residual+LayerNorm [3000,10001] 92.0 -> 90.4; but at 100 MB LayerNorm+GeLU
+  // [4000,6001] 25.8 -> 27.4).
+  const bool long_rows = (int64_t)C * min_es >= 4096 && gp.min_hbm_bytes >= (128ull << 20);
+  if (st == FS_OK && ((gp.s.shares_lines && !gp.row_reduces.empty() && gp.col_reduces.empty() && !long_rows) || (gp.s.narrow_tiles && gp.s.L < 32)))
     for (ExtTensor& e : gp.ext_in) e.streaming = false;
   if (st == FS_OK && gp.s.chunked)  // every stage reads the row again: keep it in the caches
     for (ExtTensor& e : gp.ext_in) e.streaming = false;

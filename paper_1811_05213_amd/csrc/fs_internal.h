@@ -124,6 +124,10 @@ struct Schedule {
   // and for the next trip's at the end of a trip (the same registers: the rows are dead by then), so the first memory
   // round trip overlaps the staging.  Rows of one wavefront and a handful of trips only.
   bool rotate_loop = false;
+  // One row to a workgroup, and workgroups that stay for many rows: the next row is asked for while a row is worked on, its first
+  // ahead_lds vectors per lane and tensor to LDS, the rest to registers.
+  bool ahead = false;
+  int ahead_lds = 0;
   bool tile_transpose = false;  // transposed roots leave through a padded LDS tile
   // Reduction-free groups with transposed roots over wide rows: 2-D tiles.  A workgroup owns G
   // consecutive rows of one column tile of NVL*L*V columns (unit = column tile fastest), so both
@@ -237,6 +241,7 @@ struct PlanOptions {
   // Plan creation steps down while the compiled kernel spills.
   int wide_level = 2;
   bool narrow_tiles = true;  // column folds may take narrow tiles (plan creation gives them up where the compiled kernel spills)
+  bool ahead = true;  // long rows may be asked for one ahead (given up where the compiled kernel spills)
   int min_waves = 0;  // > 0: the kernel asks the compiler for that many wavefronts per SIMD (occupancy feedback at plan creation)
   bool layered = false;  // group with the layered planner of Section 3.2 instead of the default one
   // set once the groups are final: whether a value leaves a kernel then depends on which kernels compute it themselves

@@ -432,7 +432,7 @@ fs_status fs_plan_create(const fs_graph_desc* desc, fs_plan** out_plan) {
       // run-time compiler compiled before in the same process; hundreds of bytes are what ruins a kernel)
       if (it == scratch.end() || it->second <= 128) {
         auto vg = vgprs.find(gp.kernel_name);
-        if (!waves_tried[gi] && gp.s.WG == 1024 && vg != vgprs.end() && vg->second > 64 && vg->second <= 80 && (it == scratch.end() || it->second == 0)) {
+        if (!waves_tried[gi] && gp.s.WG == 1024 && !gp.s.ahead && vg != vgprs.end() && vg->second > 64 && vg->second <= 80 && (it == scratch.end() || it->second == 0)) {
           waves_tried[gi] = 1;
           PlanOptions o = group_opt[gi];
           o.min_waves = 8;
@@ -454,6 +454,10 @@ fs_status fs_plan_create(const fs_graph_desc* desc, fs_plan** out_plan) {
       PlanOptions o = group_opt[gi];
       GroupPlan again;
       bool found = false;
+      if (gp.s.ahead) {
+        o.ahead = false;
+        found = analyse_group(g, ordered[gi], plan->group_of, (int)gi, o, &again) == FS_OK && generate_kernel(g, &again, (int)gi) == FS_OK;
+      }
       while (!found && !gp.row_reduces.empty() && (gp.s.E >= 32 || gp.s.resident) && o.wide_level > 0) {
         --o.wide_level;
         found = analyse_group(g, ordered[gi], plan->group_of, (int)gi, o, &again) == FS_OK &&

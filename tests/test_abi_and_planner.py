@@ -1297,3 +1297,49 @@ def test_plans_on_the_static_scratch_stay_there():
     p = fs.Plan(g)
     assert p.joined_groups() == [] and 8 << 20 >= p.workspace_bytes() > (8 << 20) - (48 << 10)
     p.destroy()
+
+
+def test_division_through_the_reciprocal(tmp_path):
+    # fs_div_row of fs_device.h, compiled for the host, against the division itself
+    import subprocess
+    text = open(os.path.join(ROOT, "paper_1811_05213_amd", "csrc", "fs_device.h")).read()
+    a, b = text.index("FS_DEV bool fs_reciprocal_overflows"), text.index("FS_DEV float fs_max(")
+    (tmp_path / "t.cpp").write_text("#include <cmath>\n#define FS_DEV static inline\nstatic bool normal(float q) { return std::isfinite(q) && q != 0; }\n#define __builtin_amdgcn_classf(q, m) normal(q)\n" +
+                                    text[a:b] + r"""
+#include <cstdio>
+#include <cstring>
+#include <cstdint>
+static float f(uint32_t u) { float x; memcpy(&x, &u, 4); return x; }
+int main() {
+  uint64_t seed = 12345, bad = 0;
+  for (long i = 0; i < 20000000; ++i) {
+    seed = seed * 6364136223846793005ull + 1442695040888963407ull;
+    const uint32_t u = (uint32_t)(seed >> 32), v = (uint32_t)(seed >> 11);
+    const float x = f((u & 0x807fffff) | ((64 + (seed & 63)) << 23)), s = f((v & 0x807fffff) | ((100 + (seed >> 6 & 63)) << 23));
+    bad += fs_div_row(x, s, 1.0f / s) != x / s;
+  }
+  const float v[] = {0.f, -0.f, 1.f, -3.f, INFINITY, -INFINITY, NAN, 1e38f, 3.4e38f, 1e30f, 1e-30f};
+  for (float x : v)
+    for (float s : v) {
+      const float d = fs_reciprocal_overflows(s) ? x / s : fs_div_row(x, s, 1.0f / s), t = x / s;
+      // (denormal quotients: 1.3 of their spacings at most)
+      bad += !(std::isnan(d) ? std::isnan(t) : (d == t || (std::fpclassify(t) == FP_SUBNORMAL && std::fabs(d - t) < 0x1.8p-148f)) && std::signbit(d) == std::signbit(t));
+    }
+  return printf("%llu differ\n", (unsigned long long)bad), bad != 0;
+}
+""")
+    subprocess.run(["g++", "-std=c++17", "-O2", "-mfma", "-ffp-contract=off", "-o", str(tmp_path / "t"), str(tmp_path / "t.cpp")], check=True)
+    r = subprocess.run([str(tmp_path / "t")], capture_output=True, text=True)
+    assert r.returncode == 0, r.stdout
+
+
+@pytest.mark.parametrize("rows,cols,ahead", [(257, 32768, 1), (256, 32768, 0), (1024, 65536, 1), (4096, 28672, 0), (2048, 50000, 1), (2048, 50001, 0), (512, 50001, 1), (40, 65536, 0)])
+def test_which_long_rows_are_asked_for_ahead(rows, cols, ahead):
+    p = fs.Plan(softmax_graph(rows, cols))
+    gi = p.group_info(0)
+    assert ("fs_row_ask<" in p.group_source(0)) == bool(ahead)
+    assert gi["grid"] == (256 if ahead else rows) and gi["lds_bytes"] <= 163840
+    p.destroy()
+    p = fs.Plan(softmax_graph(rows, cols), lds_budget_bytes=65536)  # a caller's budget binds
+    assert p.group_info(0)["lds_bytes"] <= 65536
+    p.destroy()

@@ -1322,3 +1322,52 @@ def test_joined_groups_repeat_and_replay():
     p.workspace_check(r.workspace.data_ptr(), r.ws_bytes)
     del graph
     p.destroy()
+
+
+# ------------------------------------------------------------------ division by a per-row value; long rows asked for ahead
+def test_division_by_row_values():
+    # the quotients of fs_div_row against IEEE division: divisors of every magnitude, zero, infinite, denormal, NaN
+    divisors = np.array([1.0, 3.0, 1e-45, 1e-39, 2.9e-39, 1.2e-38, 1e-20, 7e20, 1.7e38, 3.4e38, np.inf, 0.0, -0.0, -7.0, -1e-40, np.nan], np.float32)
+    for cols in (64, 4097):
+        x = (RNG.standard_normal((len(divisors), cols)) * 10.0 ** RNG.integers(-30, 30, (len(divisors), cols))).astype(np.float32)
+        x[:, :6] = [0.0, -0.0, np.inf, -np.inf, np.nan, 1e-42]
+        d = np.full((len(divisors), cols), -np.inf, np.float32)
+        d[:, 5] = divisors
+        g = Graph()
+        a, b = g.input(*x.shape), g.input(*x.shape)
+        s = g.reduce_row("max", b)
+        g.set_outputs([g.binary("div", a, g.bcast_colvec(s, cols)), s])
+        y, m = run_graph(g, [x, d])
+        with np.errstate(all="ignore"):
+            ref = x / m
+        np.testing.assert_array_equal(np.isnan(y), np.isnan(ref))
+        normal = np.abs(ref) >= np.finfo(np.float32).tiny
+        np.testing.assert_array_equal(y[normal], ref[normal])
+        rest = ~normal & ~np.isnan(ref)  # zeros, and denormals that are 1.3 of their spacings off at most
+        assert np.all(np.abs(y[rest].astype(np.float64) - ref[rest]) <= 2.1e-45) and np.all(np.signbit(y[rest]) == np.signbit(ref[rest]))
+
+
+@pytest.mark.parametrize("rows,cols,dt", [(257, 32768, "f32"), (300, 28676, "f32"), (520, 40000, "f32"), (300, 65533, "f32"), (259, 50001, "f32"),
+                                          (300, 65536, "bf16"), (260, 32768, "bf16"), (513, 57344, "f32")])
+def test_long_rows_asked_for_ahead(rows, cols, dt):
+    g = Graph()
+    x, t = g.input(rows, cols, dt), g.input(rows, 1)
+    z = g.binary("mul", x if dt == "f32" else g.unary("convert", x, "f32"), g.bcast_colvec(t, cols))
+    m = g.reduce_row("max", z)
+    e = g.unary("exp", g.binary("sub", z, g.bcast_colvec(m, cols)))
+    y = g.binary("div", e, g.bcast_colvec(g.reduce_row("sum", e), cols))
+    g.set_outputs([y, m] if dt == "f32" else [g.unary("convert", y, dt), m, g.unary("convert", g.unary("abs", z), dt)])
+    a = RNG.standard_normal((rows, cols)).astype(np.float32)
+    ins = [a if dt == "f32" else f32_to_bf16_bits(a), RNG.uniform(0.5, 2, (rows, 1)).astype(np.float32)]
+    p = fs.Plan(g)
+    assert p.stats()["num_launches"] == 1 and "fs_row_ask<" in p.group_source(0)
+    r = DeviceRun(p)
+    r.set_inputs(ins)
+    r.launch()
+    first = r.results()
+    check_all(g, first, Reference(g, ins), f"rows ahead {rows}x{cols} {dt}")
+    for _ in range(5):
+        r.launch()
+        for u, v in zip(first, r.results()):
+            np.testing.assert_array_equal(u, v)
+    p.destroy()
