@@ -701,7 +701,7 @@ struct Emitter {
        << "  constexpr int RAGGED = " << (s.ragged ? 1 + over : 0) << ";\n"
        << "  const int tid = (int)threadIdx.x, lir = tid & (L - 1), rg = tid / L, tile = (int)blockIdx.x % CT, rb = (int)blockIdx.x / CT, vbase = tile * L;\n"
        << "  (void)E; (void)NVL; (void)CW;\n"
-       << "  __shared__ float lds_col[(L < 64 ? WG / 64 : G) * CW], lds_res[" << gp.col_reduces.size() << " * CW];\n  __shared__ fs_u32 lds_flag;\n"
+       << "  __shared__ float lds_col[(L < 64 ? WG / 64 : G) * CW], lds_res[" << gp.col_reduces.size() << " * CW]" << (s.RB > 1 ? ", lds_fold[WG]" : "") << ";\n  __shared__ fs_u32 lds_flag;\n"
        // (column of the lane's element e inside the tile; what the lane does not own reads any column)
        << "  const int lcol = lir * V" << (over ? " - fs_vec_skip<V, C>(vbase + lir)" : "") << ";\n";
     auto raw = [&](const ExtTensor& e) { return "w" + std::to_string(loc(e.node)); };
@@ -762,16 +762,22 @@ struct Emitter {
       const std::string S = "S" + std::to_string(st), cv = "cv" + std::to_string(st);
       os << "  typedef fs_colfold<" << K << ", CW, WG, FV> " << S << ";\n  float " << cv << "[" << S << "::CPT][FV];\n";
       auto partial = [&](const std::string& ind, const std::string& b) {  // of row block b, whose rows the lanes hold -> cv
-        for (int m : red)
-          os << ind << "float ca" << loc(m) << "[E];\n" << ind << "_Pragma(\"unroll\") for (int e = 0; e < E; ++e) ca" << loc(m) << "[e] = fs_red_identity<" << g.nodes[m].attr_i << ">();\n";
+        // (sums of many rows in blocks of eight: a float that eats fifty terms one after the other loses two bits more)
+        auto blocks = [&](int m) { return s.U > 8 && (g.nodes[m].attr_i == FS_RED_SUM || g.nodes[m].attr_i == FS_RED_MEAN); };
+        for (int m : red) {
+          const std::string id = "fs_red_identity<" + std::to_string(g.nodes[m].attr_i) + ">()", ca = "ca" + std::to_string(loc(m));
+          os << ind << "float " << ca << "[E]" << (blocks(m) ? ", " + ca + "_b[E]" : "") << ";\n" << ind << "_Pragma(\"unroll\") for (int e = 0; e < E; ++e) " << ca << "[e] = "
+             << (blocks(m) ? ca + "_b[e] = " : "") << id << ";\n";
+        }
         pass(ind, b, mem, ext, [&](const std::string& in) {
           for (int m : red) {
             const fs_node& n = g.nodes[m];
-            const std::string ca = "ca" + std::to_string(loc(m));
+            const std::string sum = "ca" + std::to_string(loc(m)), ca = sum + (blocks(m) ? "_b" : "");
             os << in << "_Pragma(\"unroll\") for (int e = 0; e < E; ++e) " << ca << "[e] = rok ? ";
             if (folded[n.in[0]]) os << "__builtin_fmaf(" << ref(g.nodes[n.in[0]].in[0]) << ", " << ref(g.nodes[n.in[0]].in[1]) << ", " << ca << "[e])";
             else os << "fs_red_op<" << n.attr_i << ">(" << ca << "[e], " << ref(n.in[0]) << ")";
             os << " : " << ca << "[e];\n";
+            if (blocks(m)) os << in << "if (t % 8 == 7 || t == TR - 1) _Pragma(\"unroll\") for (int e = 0; e < E; ++e) " << sum << "[e] += " << ca << "[e], " << ca << "[e] = 0.0f;\n";
           }
         });
         for (int k = 0; k < K; ++k)
@@ -784,14 +790,15 @@ struct Emitter {
       if (s.RB > 1) {
         const std::string part = "a.part + (long)tile * " + std::to_string(s.part_stride_floats) + "L + " + std::to_string((size_t)slot.at(red[0]) * CW * s.RB) + "L";
         os << "  if (fs_tile_meet<" << K << ", CW, WG, FV>(" << cv << ", " << part << ", a.tickets + tile * " << s.ticket_stride << " + " << st << ", &lds_flag, (fs_u32)rb, (fs_u32)RB, a.wait)) {\n"
-           << "    fs_tile_fold<" << K << ", CW, WG, FV, " << kname << "_kinds" << st << ">(" << cv << ", " << part << ", (fs_u32)RB);\n  } else {\n"
-           << "    float tot[" << S << "::CPT][FV];\n    _Pragma(\"unroll 1\") for (int b = 0; b < RB; ++b) {\n";
+           << "    fs_tile_fold<" << K << ", CW, WG, RB, " << kname << "_kinds" << st << ">(" << cv << ", " << part << ", lds_fold);\n  } else {\n"
+           << "    typedef fs_tile_slices<" << K << ", CW, WG, RB> Q;\n    float tot[" << S << "::CPT], slice[" << S << "::CPT];\n    _Pragma(\"unroll 1\") for (int b = 0; b < RB; ++b) {\n";
         load_rows("      ", "b");
         partial("      ", "b");
+        const std::string kinds = kname + "_kinds" + std::to_string(st);
         os << "      _Pragma(\"unroll\") for (int i = 0; i < " << S << "::CPT; ++i) {\n        const int k = (tid + i * WG) / " << S << "::CH;\n"
-           << "        _Pragma(\"unroll\") for (int f = 0; f < FV; ++f) tot[i][f] = " << kname << "_kinds" << st << "::op(k, b == 0 ? " << kname << "_kinds" << st
-           << "::identity(k) : tot[i][f], " << cv << "[i][f]);\n      }\n    }\n"
-           << "    _Pragma(\"unroll\") for (int i = 0; i < " << S << "::CPT; ++i) _Pragma(\"unroll\") for (int f = 0; f < FV; ++f) " << cv << "[i][f] = tot[i][f];\n";
+           << "        if (b % Q::PS == 0) {\n          tot[i] = b == 0 ? " << kinds << "::identity(k) : " << kinds << "::op(k, tot[i], slice[i]);\n          slice[i] = " << kinds << "::identity(k);\n        }\n"
+           << "        slice[i] = " << kinds << "::op(k, slice[i], " << cv << "[i][0]);\n      }\n    }\n"
+           << "    _Pragma(\"unroll\") for (int i = 0; i < " << S << "::CPT; ++i) " << cv << "[i][0] = " << kinds << "::op((tid + i * WG) / " << S << "::CH, tot[i], slice[i]);\n";
         load_rows("    ", "rb");
         os << "  }\n";
       }
@@ -812,7 +819,7 @@ struct Emitter {
         os << "  float " << name(m, KIND_ROWV) << "[E];\n  _Pragma(\"unroll\") for (int e = 0; e < E; ++e) " << name(m, KIND_ROWV) << "[e] = lds_res[" << slot.at(m)
            << " * CW + (lcol + e > 0 ? lcol + e : 0)];\n";
     }
-    if (s.RB > 1) os << "  fs_tile_leave(a.tickets + tile * " << s.ticket_stride << ", " << stage.size() + 1 << ", (fs_u32)RB);\n";
+    if (s.RB > 1) os << "  const fs_u32 left = fs_tile_leave(a.tickets + tile * " << s.ticket_stride << ", " << stage.size() + 1 << ");\n";
     // what leaves the kernel as an [R,C] tensor, and [1,C] values nothing else needed
     std::vector<int> roots;
     for (const ExtTensor& e : gp.ext_out)
@@ -841,6 +848,7 @@ struct Emitter {
           }
         });
     }
+    if (s.RB > 1) os << "  fs_tile_clear(left, a.tickets + tile * " << s.ticket_stride << ", " << stage.size() + 1 << ", (fs_u32)RB);\n";
     os << "}\n";
   }
 

@@ -1603,29 +1603,39 @@ namespace {
 // normalisation f32 compiles without scratch up to here; where another body does not, plan creation gives the joined kernel up.)
 constexpr int kJoinRegs = 200;
 
-// Lanes of a tile, workgroup, workgroups per tile, rows per lane.  Batch normalisation f32, three kernels -> joined, us:
-//  - 8 lanes, one 128-byte run of f32; 16 where rows are no whole cache lines and tiles share them ([8000,2000] 32.1 of 8 lanes,
-//    28.8 of 16; [12000,500] 24.3, 20.0; [25000,300] 31.6, 25.6; whole lines: [16384,1024] 27.1, 27.3, [1000,8192] 12.5, 13.6).
+// Lanes of a tile, workgroup, workgroups per tile, rows per lane.  Batch normalisation f32, us:
+//  - 8 lanes, one 128-byte run of f32, where rows are whole cache lines ([16384,1024] 27.0, 27.2 of 16 lanes, 27.8 of 32;
+//    [1000,8192] 12.5, 13.6 of 16) and in narrow rows ([30000,33] 12.3 of 8, 13.5 of 16; [5000,48] 7.2, 7.7); elsewhere tiles share
+//    the lines at their edges: 16 lanes below 8 MB ([3000,200] 8.5 of 8, 8.4 of 16; [1000,1000] 7.5, 7.2, 7.7 of 32), 32 above ([8000,2000] 32.1 of
+//    8, 28.8 of 16; [2000,3001] 25.7, 19.8, 16.5 of 32; [25000,300] 31.5, 25.8, 24.4; [65536,99] 33.9, 29.3, 26.7).
 //  - One workgroup to a tile of up to 96 KB, which then meets nobody: [600,600] 5.6 us of one, 6.9 of four; [333,777] 5.3, 7.1;
-//    but 128 KB, [1000,1000], 9.6 of one, 7.4 of eight.  Larger tiles: as many as fill the device, each with 16 KB or more of
-//    the tile ([8192,16] 7.2 us of 16, 7.6 of 32, 9.7 of 64) and 32 at most, above 200 KB each 64 ([40000,128], 160 KB,
-//    14.4 us of 32 and 15.2 of 64; [65536,64], 256 KB, 16.3 and 15.3): every workgroup reads all partials of its tile.
+//    but 128 KB, [1000,1000], 9.6 of one, 7.4 of eight.  Tiles of half the width where that makes them small enough and the tensor
+//    is below 2 MB ([1500,100] 5.5, 6.5 of 8 lanes; above, 64-byte runs cost more, [1000,1000] 7.9).
+//  - Larger tiles: as many workgroups as fill the device, each with 16 KB or more of the tile ([8192,16] 7.2 us of 16, 7.6 of 32,
+//    9.7 of 64), 32 at most, up to 128 where each would have more than 200 KB ([40000,128], 160 KB, 13.9 of 32, 14.0 of 64;
+//    [65536,64], 256 KB, 16.0 and 13.9; [65536,99] on tiles of 32 lanes 26.7 of 128, 29.6 of 256): the counts of a tile queue up.
 //  - 256 lanes, two workgroups to a compute unit, or 512, one, from 8 MB on, where half as many partials count ([2000,3001]
-//    20.9 and 19.8; [16384,1024] 27.1 either way; [4096,1024] 10.1).
-// [16384,1024] 52 -> 27.1, [2500,8192] 73 -> 30.4, [4096,1024] 19.3 -> 10.1, [65536,16] 23.1 -> 11, [300,64] 10.1 -> 4.7.
+//    16.9 and 16.5; [16384,1024] 27.4 and 27.0; [4096,1024] 10.2 either way).
+// Three kernels before: [16384,1024] 52, [2500,8192] 73, [4096,1024] 19.3, [65536,99] 29.9, [2000,3001] 27.2, [300,64] 10.1 (joined 4.7).
 fs_status pick_join_shape(GroupPlan* gp, int dwords_per_row, int max_es) {
   Schedule& s = gp->s;
   const int R = gp->R, CUS = device_limits().cus;
-  const int64_t run = (int64_t)s.V * max_es;  // bytes of the widest tensor that a lane takes of a row
-  int L = std::min(8, pow2_ceil(s.NV));
-  const bool alone = (int64_t)R * L * run <= 96 << 10;
-  if (!alone && (int64_t)gp->C * max_es % 128 != 0) L = std::min(16, pow2_ceil(s.NV));
-  int WG = (int64_t)R * gp->C * max_es >= (8 << 20) ? 512 : 256;
+  const int64_t run = (int64_t)s.V * max_es, row = (int64_t)gp->C * max_es, bytes = R * row;  // of the widest tensor: what a lane takes of a row, a row, all
+  auto tile_bytes = [&](int lanes) { return R * std::min(lanes, pow2_ceil(s.NV)) * run; };
+  int L = 8;
+  const bool half = tile_bytes(8) > 96 << 10 && tile_bytes(4) <= 96 << 10 && bytes <= 2 << 20, alone = half || tile_bytes(8) <= 96 << 10;
+  if (half) L = 4;
+  else if (!alone && row % 128 != 0 && s.NV > 16) L = bytes >= 8 << 20 ? 32 : 16;
+  L = std::min(L, pow2_ceil(s.NV));
+  int WG = bytes >= 8 << 20 ? 512 : 256;
   WG = std::max(64, std::min(WG, L * pow2_ceil(std::min(R, 1024))));
   const int G = WG / L, CT = (s.NV + L - 1) / L, trips = (R + G - 1) / G;
-  const int64_t tile = (int64_t)R * L * run;
   int RB = 1;
-  if (!alone) RB = std::max(1, std::min({CUS * 512 / WG / CT, (int)(tile >> 14), tile > 32 * (200 << 10) ? 64 : 32, trips}));
+  if (!alone) {
+    int most = 32;
+    while (most < 128 && tile_bytes(L) / most > 200 << 10) most *= 2;
+    RB = std::max(1, std::min({CUS * 512 / WG / CT, (int)std::min<int64_t>(tile_bytes(L) >> 14, 1024), most, trips}));
+  }
   const int U = (trips + RB - 1) / RB;
   s.L = L, s.NVL = 1, s.E = s.V, s.WG = WG, s.G = G, s.CT = CT, s.n_iters = trips, s.RB = (trips + U - 1) / U, s.U = U;
   s.grid = CT * s.RB;
@@ -1726,7 +1736,7 @@ fs_status join_groups(const Graph& g, const std::vector<GroupPlan>& groups, int 
   if (st != FS_OK) return st;
   s.ragged = gp.C % s.V != 0 || (int64_t)s.CT * s.L != s.NV;
   s.col_tiled = true;
-  s.lds_bytes = s.lds_planned = ((s.L < 64 ? s.WG / 64 : s.G) + (int)gp.col_reduces.size()) * s.fold_width * 4 + 16;
+  s.lds_bytes = s.lds_planned = ((s.L < 64 ? s.WG / 64 : s.G) + (int)gp.col_reduces.size()) * s.fold_width * 4 + (s.RB > 1 ? s.WG * 4 : 0) + 16;
   if (s.lds_bytes > opt.lds_budget) FS_FAIL(FS_ERR_LDS_BUDGET, "joined groups need %d bytes of LDS, budget is %d", s.lds_bytes, opt.lds_budget);
   if (s.RB > 1) {
     s.part_stride_floats = gp.col_reduces.size() * (size_t)s.fold_width * s.RB;

@@ -1275,7 +1275,7 @@ def test_views_of_nd_tensors_and_concats():
     ("softmax", 2, 2, "f32"), ("softmax", 3, 5, "f32"), ("softmax", 767, 96, "f32"), ("softmax", 770, 96, "f32"),  # one workgroup a tile, several
     ("softmax", 1003, 101, "f32"), ("softmax", 5000, 33, "f32"), ("softmax", 3000, 64, "bf16"), ("softmax", 70000, 8, "bf16"),
     ("masked", 300, 77, "f32"), ("masked", 2100, 260, "bf16"), ("masked", 4097, 129, "f32"), ("scaled", 33, 1000, "f32"), ("scaled", 9000, 257, "f32"),
-    ("scaled", 3000, 1600, "f32"), ("scaled", 2049, 640, "bf16")])
+    ("scaled", 3000, 1600, "f32"), ("scaled", 2049, 640, "bf16"), ("softmax", 1500, 100, "f32"), ("softmax", 23000, 99, "f32"), ("masked", 25000, 99, "f32")])
 def test_joined_groups(kind, rows, cols, dt, monkeypatch):
     from test_abi_and_planner import column_stage_graph
     g = column_stage_graph(kind, rows, cols, dt)
