@@ -990,6 +990,11 @@ fs_status analyse_group(const Graph& g, const std::vector<int>& members, const s
   gp.min_hbm_bytes = 0;
   for (const ExtTensor& e : gp.ext_in) gp.min_hbm_bytes += (uint64_t)g.nodes[e.node].rows * g.nodes[e.node].cols * dtype_size(e.dtype);
   for (const ExtTensor& e : gp.ext_out) gp.min_hbm_bytes += (uint64_t)g.nodes[e.node].rows * g.nodes[e.node].cols * dtype_size(e.dtype);
+  // (an [R,C] value that another kernel reads is as a rule computed again there in the end: no reason to fold beside row reductions;
+  // column sums and row norms f32 [3440,1000]: 17.5 us with one of two folds in the kernel of the norms, 11.4 apart in one launch)
+  gp.fold_bytes = gp.min_hbm_bytes;
+  for (const ExtTensor& e : gp.ext_out)
+    if (e.kind == KIND_FULL && g.family_output[e.node] < 0) gp.fold_bytes -= bytes_of(e);
   gp.exchanges = false;
   gp.reads_alone = true;
   for (const ExtTensor& e : gp.ext_in) {
@@ -1122,7 +1127,7 @@ bool worth_fusing(const GroupPlan& merged) {
   // the rows in one workgroup (the 200-node DAG: 29.4 us with those kept apart, 30.6 us without).
   bool narrow = merged.s.narrow_tiles;
   for (const auto& f : merged.tflag) narrow &= !f.second;
-  return merged.col_reduces.empty() || merged.members.size() == 1 || merged.s.grid == 1 || narrow || merged.min_hbm_bytes >= kFoldWorthBytes;
+  return merged.col_reduces.empty() || merged.members.size() == 1 || merged.s.grid == 1 || narrow || (merged.row_reduces.empty() ? merged.min_hbm_bytes : merged.fold_bytes) >= kFoldWorthBytes;
 }
 
 struct Former {
@@ -1663,6 +1668,9 @@ fs_status join_groups(const Graph& g, const std::vector<GroupPlan>& groups, int 
   Analyser a(g, gp);
   for (int m : gp.members) a.in_set[m] = 1;
   a.R = gp.R, a.C = gp.C;
+  bool folds = false;
+  for (int m : gp.members) folds |= g.nodes[m].opcode == FS_REDUCE_COL;
+  if (!folds) FS_FAIL(FS_ERR_UNSUPPORTED, "no column reduction");
   auto read_by_others = [&](int id) {  // from memory, by groups that are not joined here
     for (int k = 0; k < (int)groups.size(); ++k)
       if (k < first || k >= first + count)
@@ -1747,6 +1755,238 @@ fs_status join_groups(const Graph& g, const std::vector<GroupPlan>& groups, int 
   gp.wait_ticks = 5000;  // 50 us: several times what the workgroups of the largest tiles need from their start to the last load
   if (const char* e = getenv("FS_JOIN_WAIT_TICKS")) gp.wait_ticks = atoi(e);
   return FS_OK;
+}
+
+// -------------------------------------------------------------------------------------------
+// Groups that share a launch (Composite).
+// -------------------------------------------------------------------------------------------
+namespace {
+
+struct Composer {
+  const Graph& g;
+  const std::vector<GroupPlan>& groups;
+  const std::vector<int>& group_of;
+  const PlanOptions& opt;
+  std::map<int, int> stored_by;            // tensor in memory -> the group that stores it
+  std::vector<std::set<int>> deps;         // groups whose results a group reads
+  static constexpr uint64_t kSmall = 32ull << 20;  // bytes of a group whose launch, not its traffic, is what it costs (above, nothing was left to gain)
+  static constexpr int kMaxTracks = 4, kMaxLds = 65536;
+
+  Composer(const Graph& g_, const std::vector<GroupPlan>& groups_, const std::vector<int>& group_of_, const PlanOptions& o)
+      : g(g_), groups(groups_), group_of(group_of_), opt(o), deps(groups_.size()) {
+    for (size_t k = 0; k < groups.size(); ++k)
+      for (const ExtTensor& e : groups[k].ext_out) stored_by[e.node] = (int)k;
+    for (size_t k = 0; k < groups.size(); ++k)
+      for (const ExtTensor& e : groups[k].ext_in) {
+        auto it = stored_by.find(g.root_of[e.node]);
+        if (it != stored_by.end() && it->second != (int)k) deps[k].insert(it->second);
+      }
+  }
+
+  bool small(int k) const {
+    const GroupPlan& p = groups[k];
+    return !p.s.chunked && !p.s.split_rows && !p.s.resident && (p.s.U == 1 || !p.col_reduces.empty()) && !p.s.ahead && p.min_hbm_bytes <= kSmall;
+  }
+
+  // does workgroup b of `to` read of `from` only what workgroup b wrote, when both take the same rows?
+  bool row_local(int from, int to) const {
+    const GroupPlan &a = groups[from], &b = groups[to];
+    if (a.R != b.R || !a.col_reduces.empty() || !b.col_reduces.empty()) return false;
+    for (const ExtTensor& e : b.ext_in) {
+      auto it = stored_by.find(g.root_of[e.node]);
+      if (it == stored_by.end() || it->second != from) continue;
+      if (it->first != e.node || (e.kind != KIND_COLV && e.kind != KIND_FULL)) return false;
+      for (const ExtTensor& w : a.ext_out)
+        if (w.node == e.node && (w.kind != e.kind || w.transposed || (e.kind == KIND_FULL && a.C != b.C))) return false;
+    }
+    return true;
+  }
+
+  // group k with L lanes a row (0: its own) and WG lanes a workgroup, one trip to a workgroup
+  bool plan(int k, int L, int WG, GroupPlan* out) const {
+    if (!groups[k].col_reduces.empty()) {  // as it is: partials and counters are laid out for it
+      *out = groups[k];
+      return L <= 0 && out->s.WG == WG;
+    }
+    const Schedule& was = groups[k].s;
+    if (L <= 0) L = was.L;
+    if (L == was.L && WG == was.WG && was.min_waves == 0) {
+      *out = groups[k];
+    } else {
+      PlanOptions o = opt;
+      o.hint = fs_sched_hint{L, WG, 0, 0};
+      o.has_hint = true;
+      if (analyse_group(g, groups[k].members, group_of, k, o, out) != FS_OK) return false;
+    }
+    const Schedule& s = out->s;
+    return s.WG == WG && s.L == L && s.V == was.V && s.grid == s.n_iters && s.U == 1 && !s.chunked && !s.resident && !s.split_rows && !s.ahead && s.tile_transpose >= was.tile_transpose;
+  }
+
+  // plans for all tracks with a common workgroup; false where they do not agree or do not fit
+  bool fit(Composite* c) const {
+    // the largest workgroup among them, or that of a column fold, whose partials are laid out for it
+    c->WG = 0;
+    bool folds = false;
+    for (const auto& t : c->tracks)
+      for (int k : t) {
+        const bool f = !groups[k].col_reduces.empty();
+        if (f > folds || (f == folds && groups[k].s.WG > c->WG)) c->WG = groups[k].s.WG;
+        folds |= f;
+      }
+    c->plans.assign(c->tracks.size(), {});
+    c->blocks.assign(c->tracks.size(), 0);
+    int pointers = 0, lds = 0, parts = 0;
+    for (size_t t = 0; t < c->tracks.size(); ++t) {
+      int L = 0;
+      for (int k : c->tracks[t]) L = std::max(L, groups[k].s.L);
+      for (int k : c->tracks[t]) {
+        GroupPlan p;
+        if (!plan(k, c->tracks[t].size() > 1 ? L : 0, c->WG, &p)) return false;
+        if (c->blocks[t] != 0 && p.s.grid != c->blocks[t]) return false;
+        c->blocks[t] = p.s.grid;
+        pointers += (int)(p.ext_in.size() + p.ext_out.size());
+        lds += p.s.lds_bytes;
+        c->plans[t].push_back(std::move(p));
+        ++parts;
+      }
+    }
+    return pointers <= kMaxCompositePointers && parts <= kMaxCompositeGroups && lds <= std::min(kMaxLds, opt.lds_budget);
+  }
+};
+
+void replace_all(std::string* s, const std::string& from, const std::string& to) {
+  for (size_t p = 0; (p = s->find(from, p)) != std::string::npos; p += to.size()) s->replace(p, from.size(), to);
+}
+
+// the kernels of a composite become functions of one kernel
+bool generate_composite(const Graph& g, Composite* c) {
+  for (size_t t = 0; t < c->tracks.size(); ++t)
+    for (size_t k = 0; k < c->plans[t].size(); ++k)
+      if (c->plans[t][k].source.empty() && generate_kernel(g, &c->plans[t][k], c->tracks[t][k]) != FS_OK) return false;
+  std::string text, body;
+  std::set<std::string> seen;
+  int total = 0;
+  std::string args;
+  for (size_t t = 0; t < c->tracks.size(); ++t) {
+    body += std::string("  ") + (t + 1 < c->tracks.size() ? "if (block < " + std::to_string(c->blocks[t]) + ") {\n" : "{\n");
+    for (size_t k = 0; k < c->plans[t].size(); ++k) {
+      const GroupPlan& p = c->plans[t][k];
+      const std::string field = "g" + std::to_string(total++), n = p.kernel_name;
+      if (seen.insert(n).second) {
+        std::string src = p.source;
+        const size_t a = src.find("extern \"C\" __global__"), b = src.find("{\n", a);
+        src.replace(a, b - a, "FS_DEV void " + n + "_rows(const " + n + "_args& a, const int fs_block, const int fs_blocks) ");
+        replace_all(&src, "struct " + n + "_args", "struct " + n + "_part_args");
+        replace_all(&src, "const " + n + "_args&", "const " + n + "_part_args&");
+        replace_all(&src, n + "_kinds", n + "_part_kinds");
+        replace_all(&src, "blockIdx.x", "fs_block");
+        replace_all(&src, "gridDim.x", "fs_blocks");
+        text += src;
+      }
+      args += "  " + n + "_part_args " + field + ";\n";
+      // (what a workgroup wrote before the barrier it reads after it: the vector cache of a compute unit writes through)
+      if (k > 0) body += "    __syncthreads();\n";
+      body += "    " + n + "_rows(a." + field + ", block, " + std::to_string(c->blocks[t]) + ");\n";
+    }
+    body += "    return;\n  }\n";
+    if (t + 1 < c->tracks.size()) body += "  block -= " + std::to_string(c->blocks[t]) + ";\n";
+  }
+  uint64_t h = 1469598103934665603ull;
+  for (unsigned char ch : text + body) h = (h ^ ch) * 1099511628211ull;
+  char nm[64];
+  snprintf(nm, sizeof(nm), "fs_c_%016llx", (unsigned long long)h);
+  c->kernel_name = nm;
+  std::string head = "// one launch:";
+  for (size_t t = 0; t < c->tracks.size(); ++t) {
+    head += t ? " | groups" : " groups";
+    for (int k : c->tracks[t]) head += " " + std::to_string(k);
+    head += " on " + std::to_string(c->blocks[t]) + " workgroups";
+  }
+  c->source = head + "\n" + text + "struct " + c->kernel_name + "_args {\n" + args + "};\nextern \"C\" __global__ void __launch_bounds__(" + std::to_string(c->WG) + ") " + c->kernel_name + "(const " +
+              c->kernel_name + "_args a) {\n  int block = (int)blockIdx.x;\n" + body + "}\n";
+  return true;
+}
+
+}  // namespace
+
+// Launch-bound groups cost what a launch costs, whatever they move: a kernel that loads a row, computes and stores little takes
+// 2.6-3 us.  A chain of groups over the same rows, of which each reads only what the same rows of the others wrote, runs as one
+// kernel: a workgroup takes its rows through all of them, with a barrier in between.  Chains and single groups that do not depend
+// on each other run side by side on workgroups of their own.
+void compose_groups(const Graph& g, const std::vector<GroupPlan>& groups, const std::vector<int>& group_of, const std::vector<std::pair<int, int>>& joined,
+                    const PlanOptions& opt, bool may_share, std::vector<Composite>* composites, std::vector<LaunchItem>* launches) {
+  composites->clear();
+  launches->clear();
+  Composer c(g, groups, group_of, opt);
+  const int n = (int)groups.size();
+  // the launches in order, as tracks of groups (a joined run is one that nothing joins)
+  struct Item {
+    Composite comp;
+    int joined = -1;
+    std::set<int> holds;
+  };
+  std::vector<Item> items;
+  for (int k = 0; k < n; ++k) {
+    Item it;
+    for (size_t j = 0; j < joined.size(); ++j)
+      if (joined[j].first == k) it.joined = (int)j;
+    const int last = it.joined >= 0 ? k + joined[it.joined].second - 1 : k;
+    for (int m = k; m <= last; ++m) it.holds.insert(m);
+    if (it.joined < 0) it.comp.tracks = {{k}};
+    items.push_back(it);
+    k = last;
+  }
+  auto open = [&](const Item& it) { return may_share && it.joined < 0 && c.small(*it.holds.begin()); };
+  auto ready = [&](const std::set<int>& holds, size_t before, const std::set<int>& besides) {  // everything they read is launched before, or in `besides` or `holds`
+    std::set<int> done(besides);
+    done.insert(holds.begin(), holds.end());
+    for (size_t i = 0; i < before; ++i) done.insert(items[i].holds.begin(), items[i].holds.end());
+    for (int k : holds)
+      for (int d : c.deps[k])
+        if (!done.count(d)) return false;
+    return true;
+  };
+  auto take = [&](size_t into, size_t from, const Composite& comp) {
+    items[into].comp = comp;
+    items[into].holds.insert(items[from].holds.begin(), items[from].holds.end());
+    items.erase(items.begin() + (long)from);
+  };
+  for (int pass = 0; pass < 2; ++pass)  // chains first, then what runs beside them
+    for (size_t i = 0; i < items.size(); ++i) {
+      if (!open(items[i])) continue;
+      for (size_t j = i + 1; j < items.size();) {
+        bool ok = open(items[j]) && (pass == 1 || items[j].comp.tracks.size() + items[j].comp.tracks[0].size() == 2);
+        Composite trial = items[i].comp;
+        if (ok && pass == 0) {  // at the end of the chain: of its groups it reads rows only, everything else is there already
+          const int k = *items[j].holds.begin();
+          bool reads = false;
+          for (int d : c.deps[k])
+            if (items[i].holds.count(d)) reads = true, ok &= c.row_local(d, k);
+          ok &= reads && ready(items[j].holds, i, items[i].holds);
+          if (ok) trial.tracks[0].push_back(k);
+        } else if (ok) {
+          ok = ready(items[j].holds, i, std::set<int>()) && trial.tracks.size() < Composer::kMaxTracks && items[j].comp.tracks.size() == 1;
+          if (ok) trial.tracks.push_back(items[j].comp.tracks[0]);
+        }
+        if (ok && c.fit(&trial)) take(i, j, trial);
+        else ++j;
+      }
+    }
+  for (const Item& it : items) {
+    LaunchItem l;
+    if (it.joined >= 0) l.kind = LaunchItem::JOINED, l.index = it.joined;
+    else if (it.holds.size() == 1) l.kind = LaunchItem::GROUP, l.index = *it.holds.begin();
+    else {
+      l.kind = LaunchItem::COMPOSITE, l.index = (int)composites->size();
+      composites->push_back(it.comp);
+      if (!generate_composite(g, &composites->back())) {  // (its groups one by one, in their order)
+        composites->pop_back();
+        for (int k : it.holds) launches->push_back({LaunchItem::GROUP, k});
+        continue;
+      }
+    }
+    launches->push_back(l);
+  }
 }
 
 void work_span(const Graph& g, std::vector<int>* span) {

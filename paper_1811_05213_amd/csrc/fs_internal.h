@@ -204,6 +204,7 @@ struct GroupPlan {
   size_t ticket_offset = 0;
   int n_tickets = 0;
   uint64_t min_hbm_bytes = 0;
+  uint64_t fold_bytes = 0; // ... without the [R,C] values that only other kernels of the plan read
   bool reads_alone = true; // no other kernel of the plan touches the [R,C] tensors it reads
   bool exchanges = false;  // reads what another kernel of the plan wrote, or writes what another one reads
   // Several groups of the plan in one kernel (join_groups): column reductions and what needs their results, with the rows in
@@ -270,6 +271,25 @@ void recompute_across_kernels(const Graph& g, const PlanOptions& opt, std::vecto
 // reductions of a tile are folded across workgroups.  FS_ERR_UNSUPPORTED where they are not of that form or do not fit.
 fs_status join_groups(const Graph& g, const std::vector<GroupPlan>& groups, int first, int count, const PlanOptions& opt, GroupPlan* out);
 
+// Small groups of a plan that share one launch: tracks that run side by side on workgroups of their own, each a chain of groups
+// that a workgroup runs one after the other on its rows.
+constexpr int kMaxCompositePointers = 192, kMaxCompositeGroups = 24;  // in the argument block of one launch
+struct Composite {
+  std::vector<std::vector<int>> tracks;         // groups, by their place in the plan
+  std::vector<std::vector<GroupPlan>> plans;    // ... planned for the common workgroup size, a chain also for common lanes per row
+  std::vector<int> blocks;                      // workgroups per track
+  int WG = 0;
+  std::string kernel_name, source;
+};
+// One launch of fs_plan_run: a group, a joined run or a composite.
+struct LaunchItem {
+  enum Kind { GROUP, JOINED, COMPOSITE } kind = GROUP;
+  int index = 0;
+};
+// Decides which groups share launches (none unless may_share), and the order of all of them.  joined: first group and number of groups of the joined runs.
+void compose_groups(const Graph& g, const std::vector<GroupPlan>& groups, const std::vector<int>& group_of, const std::vector<std::pair<int, int>>& joined,
+                    const PlanOptions& opt, bool may_share, std::vector<Composite>* composites, std::vector<LaunchItem>* launches);
+
 // Work/Span analysis (Section 3.1): span per node, -1 for inlined and dead nodes.
 void work_span(const Graph& g, std::vector<int>* span);
 
@@ -310,6 +330,8 @@ struct fs_plan {
     fs::GroupPlan gp;
   };
   std::vector<Joined> joined;
+  std::vector<fs::Composite> composites;  // groups that share a launch
+  std::vector<fs::LaunchItem> launches;   // what fs_plan_run enqueues
   // workspace layout
   std::map<int, size_t> ws_tensor_offset;  // node materialised in the workspace -> byte offset
   size_t ticket_bytes = 0;                 // tickets live at the start of the workspace
@@ -319,7 +341,7 @@ struct fs_plan {
   // per-device loaded code
   struct Loaded {
     std::vector<void*> modules;    // hipModule_t per group
-    std::vector<void*> functions;  // hipFunction_t per group, then per joined run
+    std::vector<void*> functions;  // hipFunction_t per group, then per joined run, then per composite
   };
   std::mutex mu;
   std::map<int, Loaded> loaded;

@@ -363,7 +363,7 @@ fs_status fs_plan_create(const fs_graph_desc* desc, fs_plan** out_plan) {
   // not under a hint, which asks for a schedule of each group).  The longest run from each group on.
   if (plan->opt.mode != FS_MODE_UNFUSED && !plan->opt.layered && !desc->group_of_node && !plan->opt.has_hint)
     for (int gi = 0; gi + 1 < (int)plan->groups.size(); ++gi)
-      for (int n = (int)plan->groups.size() - gi; n >= 2; --n) {
+      for (int n = (int)plan->groups.size() - gi; n >= 2 && !plan->groups[gi].col_reduces.empty(); --n) {
         fs_plan::Joined j;
         j.first = gi, j.count = n;
         if (join_groups(g, plan->groups, gi, n, plan->opt, &j.gp) != FS_OK || generate_kernel(g, &j.gp, gi) != FS_OK) continue;
@@ -371,6 +371,15 @@ fs_status fs_plan_create(const fs_graph_desc* desc, fs_plan** out_plan) {
         gi += n - 1;
         break;
       }
+
+  bool may_compose = plan->opt.mode != FS_MODE_UNFUSED && !plan->opt.layered && !desc->group_of_node && !plan->opt.has_hint;
+
+  auto compose = [&]() {
+    std::vector<std::pair<int, int>> runs;
+    for (const fs_plan::Joined& j : plan->joined) runs.push_back({j.first, j.count});
+    compose_groups(g, plan->groups, plan->group_of, runs, plan->opt, may_compose, &plan->composites, &plan->launches);
+  };
+  compose();
 
   // One translation unit per plan: the building blocks once, then every distinct kernel body.
   // Spill feedback: a kernel whose code object reports scratch memory is planned again with less
@@ -392,6 +401,8 @@ fs_status fs_plan_create(const fs_graph_desc* desc, fs_plan** out_plan) {
       if (seen.insert(gp.kernel_name).second) tu += "\n" + gp.source;
     for (const fs_plan::Joined& j : plan->joined)
       if (seen.insert(j.gp.kernel_name).second) tu += "\n" + j.gp.source;
+    for (const Composite& c : plan->composites)
+      if (seen.insert(c.kernel_name).second) tu += "\n" + c.source;
     st = compile_kernel(tu, "fs_plan", &plan->code);
     if (st != FS_OK) {
       delete plan;
@@ -489,6 +500,16 @@ fs_status fs_plan_create(const fs_graph_desc* desc, fs_plan** out_plan) {
       gp = again;
       changed = true;
     }
+    for (const Composite& c : plan->composites) {  // (one that spills: its groups are launched one by one)
+      auto it = scratch.find(c.kernel_name);
+      if (getenv("FS_LOG_PLAN")) {
+        auto vg = vgprs.find(c.kernel_name);
+        fprintf(stderr, "fs: composite %s: %ld vector registers, %ld bytes of scratch, workgroup %d\n", c.kernel_name.c_str(), vg == vgprs.end() ? -1 : vg->second,
+                it == scratch.end() ? -1 : it->second, c.WG);
+      }
+      if (it != scratch.end() && it->second > 0) may_compose = false, changed = true;
+    }
+    if (changed) compose();
     if (!changed) {
       if (getenv("FS_LOG_PLAN"))
         for (size_t gi = 0; gi < plan->groups.size(); ++gi) {
@@ -543,6 +564,9 @@ fs_status fs_plan_create(const fs_graph_desc* desc, fs_plan** out_plan) {
     if (off > FS_STATIC_SCRATCH_BYTES + extra) break;
     plan->joined.clear();
     plan->ws_tensor_offset.clear();
+    plan->launches.clear();  // (their groups one by one; the kernels of composites stay as they are)
+    plan->composites.clear();
+    for (int k = 0; k < (int)plan->groups.size(); ++k) plan->launches.push_back({LaunchItem::GROUP, k});
   }
 
   plan->min_hbm_bytes = 0;
@@ -609,12 +633,15 @@ static fs_status load_on_device(fs_plan* plan, int device, fs_plan::Loaded** out
     }
     ld.functions.push_back((void*)fn);
   }
-  for (const fs_plan::Joined& j : plan->joined) {
+  std::vector<const char*> more;
+  for (const fs_plan::Joined& j : plan->joined) more.push_back(j.gp.kernel_name.c_str());
+  for (const Composite& c : plan->composites) more.push_back(c.kernel_name.c_str());
+  for (const char* name : more) {
     hipFunction_t fn;
-    e = hipModuleGetFunction(&fn, mod, j.gp.kernel_name.c_str());
+    e = hipModuleGetFunction(&fn, mod, name);
     if (e != hipSuccess) {
       (void)hipModuleUnload(mod);
-      FS_FAIL(FS_ERR_HIP, "hipModuleGetFunction(%s): %s", j.gp.kernel_name.c_str(), hipGetErrorString(e));
+      FS_FAIL(FS_ERR_HIP, "hipModuleGetFunction(%s): %s", name, hipGetErrorString(e));
     }
     ld.functions.push_back((void*)fn);
   }
@@ -624,22 +651,18 @@ static fs_status load_on_device(fs_plan* plan, int device, fs_plan::Loaded** out
 
 namespace fs {
 // kernarg block: { void* p[NP]; float* part; u32* tickets; int R; int n_iters (joined kernels: int wait); }
-hipError_t launch_group(const GroupPlan& gp, void* function, void* const* tensors, void* part, void* tickets, hipStream_t stream) {
-  alignas(8) char buf[8 * 48 + 32];
-  size_t n = 0;
-  auto push_ptr = [&](void* p) {
-    memcpy(buf + n, &p, 8);
-    n += 8;
-  };
+size_t put_arguments(const GroupPlan& gp, void* const* tensors, void* part, void* tickets, char* buf) {
   const size_t np = gp.ext_in.size() + gp.ext_out.size();
-  for (size_t k = 0; k < np; ++k) push_ptr(tensors[k]);
-  push_ptr(part);
-  push_ptr(tickets);
-  const int R = gp.R, iters = gp.joined ? gp.wait_ticks : gp.s.n_iters;
-  memcpy(buf + n, &R, 4);
-  memcpy(buf + n + 4, &iters, 4);
-  n += 8;
-  size_t size = n;
+  memcpy(buf, tensors, 8 * np);
+  memcpy(buf + 8 * np, &part, 8);
+  memcpy(buf + 8 * np + 8, &tickets, 8);
+  const int32_t tail[2] = {gp.R, gp.joined ? gp.wait_ticks : gp.s.n_iters};
+  memcpy(buf + 8 * np + 16, tail, 8);
+  return 8 * np + 24;
+}
+hipError_t launch_group(const GroupPlan& gp, void* function, void* const* tensors, void* part, void* tickets, hipStream_t stream) {
+  alignas(8) char buf[8 * kMaxGroupTensors + 24];
+  size_t size = put_arguments(gp, tensors, part, tickets, buf);
   void* config[] = {HIP_LAUNCH_PARAM_BUFFER_POINTER, buf, HIP_LAUNCH_PARAM_BUFFER_SIZE, &size, HIP_LAUNCH_PARAM_END};
   return hipModuleLaunchKernel((hipFunction_t)function, (unsigned)gp.s.grid, 1, 1, (unsigned)gp.s.WG, 1, 1, 0, stream, nullptr, config);
 }
@@ -675,19 +698,39 @@ static fs_status enqueue_groups(const fs_plan* plan, const fs_plan::Loaded* ld, 
     if (g.family_output[root] >= 0) return outputs[g.family_output[root]];
     return ws + plan->ws_tensor_offset.at(root);
   };
-  size_t next_joined = 0;
-  for (size_t gi = 0; gi < plan->groups.size(); ++gi) {
-    const bool joins = next_joined < plan->joined.size() && plan->joined[next_joined].first == (int)gi;
-    const GroupPlan& gp = joins ? plan->joined[next_joined].gp : plan->groups[gi];
-    void* function = joins ? ld->functions[plan->groups.size() + next_joined] : ld->functions[gi];
-    void* tensors[48];
+  // tensors of one group, and its argument block
+  auto fill = [&](const GroupPlan& gp, void** tensors) {
     size_t n = 0;
     for (const ExtTensor& t : gp.ext_in) tensors[n++] = tensor_ptr(t.node);
     for (const ExtTensor& t : gp.ext_out) tensors[n++] = tensor_ptr(t.node);
-    const hipError_t e = launch_group(gp, function, tensors, gp.part_bytes ? (void*)(ws + gp.part_offset) : nullptr,
-                                      gp.n_tickets ? (void*)(ws + gp.ticket_offset) : nullptr, stream);
-    if (e != hipSuccess) FS_FAIL(FS_ERR_HIP, "launch of group %zu (%s): %s", gi, gp.kernel_name.c_str(), hipGetErrorString(e));
-    if (joins) gi += (size_t)plan->joined[next_joined++].count - 1;
+  };
+  for (const LaunchItem& l : plan->launches) {
+    void* tensors[kMaxGroupTensors];
+    hipError_t e;
+    if (l.kind == LaunchItem::COMPOSITE) {
+      const Composite& c = plan->composites[l.index];
+      alignas(8) char buf[8 * kMaxCompositePointers + 24 * kMaxCompositeGroups];
+      size_t size = 0;
+      unsigned grid = 0;
+      for (size_t t = 0; t < c.plans.size(); ++t) {
+        grid += (unsigned)c.blocks[t];
+        for (size_t k = 0; k < c.plans[t].size(); ++k) {
+          const GroupPlan& own = plan->groups[c.tracks[t][k]];  // (whose partials and tickets are laid out)
+          fill(c.plans[t][k], tensors);
+          size += put_arguments(c.plans[t][k], tensors, own.part_bytes ? (void*)(ws + own.part_offset) : nullptr, own.n_tickets ? (void*)(ws + own.ticket_offset) : nullptr, buf + size);
+        }
+      }
+      void* config[] = {HIP_LAUNCH_PARAM_BUFFER_POINTER, buf, HIP_LAUNCH_PARAM_BUFFER_SIZE, &size, HIP_LAUNCH_PARAM_END};
+      void* function = ld->functions[plan->groups.size() + plan->joined.size() + l.index];
+      e = hipModuleLaunchKernel((hipFunction_t)function, grid, 1, 1, (unsigned)c.WG, 1, 1, 0, stream, nullptr, config);
+    } else {
+      const bool joins = l.kind == LaunchItem::JOINED;
+      const GroupPlan& gp = joins ? plan->joined[l.index].gp : plan->groups[l.index];
+      fill(gp, tensors);
+      e = launch_group(gp, ld->functions[joins ? plan->groups.size() + l.index : l.index], tensors, gp.part_bytes ? (void*)(ws + gp.part_offset) : nullptr,
+                       gp.n_tickets ? (void*)(ws + gp.ticket_offset) : nullptr, stream);
+    }
+    if (e != hipSuccess) FS_FAIL(FS_ERR_HIP, "launch %zu of %zu: %s", (size_t)(&l - plan->launches.data()), plan->launches.size(), hipGetErrorString(e));
   }
   return FS_OK;
 }
@@ -875,11 +918,22 @@ fs_status fs_plan_group_kernel_name(const fs_plan* plan, int32_t group, const ch
 
 fs_status fs_plan_joined_groups(const fs_plan* plan, int32_t index, int32_t* first_group, int32_t* num_groups, const char** source) {
   if (!plan) FS_FAIL(FS_ERR_INVALID_ARG, "NULL argument");
-  if (index < 0 || index >= (int)plan->joined.size()) FS_FAIL(FS_ERR_INVALID_ARG, "joined run %d out of range", index);
-  const fs_plan::Joined& j = plan->joined[index];
-  if (first_group) *first_group = j.first;
-  if (num_groups) *num_groups = j.count;
-  if (source) *source = j.gp.source.c_str();
+  const int nj = plan ? (int)plan->joined.size() : 0;
+  if (index < 0 || index >= nj + (int)plan->composites.size()) FS_FAIL(FS_ERR_INVALID_ARG, "shared launch %d out of range", index);
+  if (index < nj) {
+    const fs_plan::Joined& j = plan->joined[index];
+    if (first_group) *first_group = j.first;
+    if (num_groups) *num_groups = j.count;
+    if (source) *source = j.gp.source.c_str();
+    return FS_OK;
+  }
+  const Composite& c = plan->composites[index - nj];
+  int first = c.tracks[0][0], count = 0;
+  for (const auto& t : c.tracks)
+    for (int k : t) first = std::min(first, k), ++count;
+  if (first_group) *first_group = first;
+  if (num_groups) *num_groups = count;
+  if (source) *source = c.source.c_str();
   return FS_OK;
 }
 

@@ -1279,7 +1279,7 @@ def test_groups_joined_over_their_column_reductions():
     assert joined(batchnorm(40000, 1024))[0] == [] and joined(column_stage_graph("softmax", 500, 97, "bf16"))[0] == []
     for kw in ({"hint": {"wg_threads": 256}}, {"group_of_node": own}, {"mode": fs.FS_MODE_UNFUSED}, {"mode": fs.FS_MODE_LAYERED}, {"lds_budget_bytes": 1024}):
         assert joined(g, **kw)[0] == [], kw
-    assert joined(random_dag_graph())[0] == [] and joined(multi_reduce_graph(1000, 100))[0] == []
+    assert joined(multi_reduce_graph(65536, 100))[0] == []
 
 
 def test_plans_on_the_static_scratch_stay_there():
@@ -1343,3 +1343,53 @@ def test_which_long_rows_are_asked_for_ahead(rows, cols, ahead):
     p = fs.Plan(softmax_graph(rows, cols), lds_budget_bytes=65536)  # a caller's budget binds
     assert p.group_info(0)["lds_bytes"] <= 65536
     p.destroy()
+
+
+def test_groups_that_share_a_launch():
+    def shared(g, **kw):
+        p = fs.Plan(g, **kw)
+        out = [s.split("\n")[0] for _, _, s in p.joined_groups()], p.stats()
+        p.destroy()
+        return out
+
+    # a chain over the same rows ([512, 128], [512, 64], [512, 256], [R,1] values in between), two groups that do not depend on each other
+    lines, st = shared(random_dag_graph())
+    assert lines == ["// one launch: groups 2 3 4 on 128 workgroups", "// one launch: groups 5 on 128 workgroups | groups 6 on 32 workgroups"]
+    assert st["num_groups"] == st["num_launches"] == 7
+    # row norms beside the column folds of the same tensor; the fold keeps its workgroup
+    lines, _ = shared(multi_reduce_graph(421, 192))
+    assert lines == ["// one launch: groups 0 on 27 workgroups | groups 1 on 6 workgroups"]
+    lines, _ = shared(multi_reduce_graph(3440, 1000))
+    assert len(lines) == 1 and lines[0].count("|") == 2
+    # not: groups beyond 32 MB, a hint, the caller's own groups, one launch per op, the layered planner, a group alone
+    p = fs.Plan(multi_reduce_graph(421, 192))
+    own = [max(k, 0) for k in p.node_groups()]
+    p.destroy()
+    for kw in ({"hint": {"tiles_per_trip": 1}}, {"group_of_node": own}, {"mode": fs.FS_MODE_UNFUSED}, {"mode": fs.FS_MODE_LAYERED}):
+        assert shared(multi_reduce_graph(421, 192), **kw)[0] == [], kw
+    assert shared(softmax_graph(256, 1024))[0] == [] and shared(softmax_graph(2, 1 << 22))[0] == []
+
+
+def test_chains_read_rows_only():
+    # b reads a column result of a, a value in the other orientation, or rows of another tensor shape: not in one chain
+    rows, cols = 256, 192
+    for kind in ("rows", "column", "transposed"):
+        g = Graph()
+        x, w = g.input(rows, cols), g.input(rows, 2 * cols)
+        s = g.reduce_row("sum", g.unary("tanh", x))
+        if kind == "rows":
+            y = g.binary("mul", w, g.bcast_colvec(s, 2 * cols))
+        elif kind == "column":
+            y = g.binary("mul", w, g.bcast_rowvec(g.reduce_col("max", w), rows))
+        else:
+            y = g.transpose(g.binary("mul", w, g.bcast_colvec(s, 2 * cols)))
+            y = g.binary("sub", y, g.bcast_colvec(g.reduce_row("max", y), rows))
+        g.set_outputs([y, s])
+        p = fs.Plan(g)
+        chains = [src.split("\n")[0] for _, _, src in p.joined_groups() if "one launch" in src]
+        if kind == "rows" and p.stats()["num_groups"] == 2:
+            assert chains and "groups 0 1 on" in chains[0]
+        for line in chains:
+            for part in line.split("|"):
+                assert kind == "rows" or len(part.replace("// one launch:", "").split(" on ")[0].split()) == 2, line
+        p.destroy()

@@ -1371,3 +1371,51 @@ def test_long_rows_asked_for_ahead(rows, cols, dt):
         for u, v in zip(first, r.results()):
             np.testing.assert_array_equal(u, v)
     p.destroy()
+
+
+# ------------------------------------------------------------------ groups that share a launch
+@pytest.mark.parametrize("rows,ks", [(512, (64, 128, 256)), (100, (25, 50, 100)), (333, (50, 100, 200)), (48, (8, 16, 32)), (70, (96, 192, 384)), (2047, (32, 64, 128)),
+                                     (1024, (96, 192, 384))])
+def test_chains_and_groups_side_by_side(rows, ks):
+    # the same kernels one by one (a hint that changes no schedule keeps the groups apart): the same bits, on every run
+    g = random_dag_graph(rows=rows, ks=ks)
+    ins = random_dag_inputs(g)
+    p = fs.Plan(g)
+    assert any("one launch" in src for _, _, src in p.joined_groups())
+    r = DeviceRun(p)
+    r.set_inputs(ins)
+    q = fs.Plan(g, hint={"tiles_per_trip": 1})
+    assert not q.joined_groups() and q.stats()["num_groups"] == p.stats()["num_groups"]
+    alone = DeviceRun(q)
+    alone.set_inputs(ins)
+    alone.launch()
+    ref = alone.results()
+    for _ in range(10):
+        for o in r.outputs:
+            o.fill_(3)
+        r.workspace[p.workspace_bytes() // 2:].fill_(0x7f)  # (what passes between groups is written before it is read)
+        r.launch()
+        for a, b in zip(ref, r.results()):
+            np.testing.assert_array_equal(a.view(np.uint32), b.view(np.uint32))
+    p.destroy()
+    q.destroy()
+
+
+@pytest.mark.parametrize("rows,cols", [(421, 192), (265, 64), (4765, 147), (3440, 1000), (20000, 64), (1000, 2001)])
+def test_column_folds_beside_row_norms(rows, cols):
+    g, ins = multi_reduce_graph(rows, cols), multi_reduce_inputs(rows, cols)
+    p = fs.Plan(g)
+    assert len(p.joined_groups()) == 1
+    r = DeviceRun(p)
+    r.set_inputs(ins)
+    ref = Reference(g, ins)
+    first = None
+    for _ in range(5):
+        r.launch()
+        out = r.results()
+        first = first or out
+        for a, b in zip(first, out):
+            np.testing.assert_array_equal(a.view(np.uint32), b.view(np.uint32))
+    check_all(g, first, ref, f"multi_reduce {rows}x{cols}")
+    p.workspace_check(r.workspace.data_ptr(), r.ws_bytes)
+    p.destroy()
