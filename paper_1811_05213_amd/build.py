@@ -1,4 +1,4 @@
-"""Builds libfs.so (the C-ABI library) in-tree with hipcc for gfx950.
+"""Builds libfs.so (the C-ABI library) and _launch.so (the launch path of runner.py) in-tree with hipcc for gfx950.
 
     python -m paper_1811_05213_amd.build
 
@@ -10,11 +10,13 @@ from __future__ import annotations
 import os
 import subprocess
 import sys
+import sysconfig
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 ROOT = os.path.dirname(HERE)
 LIB = os.path.join(HERE, "libfs.so")
+LAUNCH = os.path.join(HERE, "_launch.so")
 SOURCES = ["fs_graph.cpp", "fs_group.cpp", "fs_codegen.cpp", "fs_runtime.cpp", "fs_perflib.cpp", "fs_probe.hip", "fs_device_src.cpp"]
 HIP_FLAGS = ["--offload-arch=gfx950", "-O2", "-std=c++17", "-fPIC", "-ffp-contract=off",
              "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops", "-Wall", "-Wno-unused-function"]
@@ -63,6 +65,8 @@ def build(verbose: bool = False) -> str:
         raise RuntimeError("hipcc failed")
     cmd = [hipcc, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", LIB] + objs + ["-lhiprtc", "-ldl"]
     subprocess.run(cmd, check=True)
+    # the Python module of the launch path: host code only
+    subprocess.run([hipcc, "-xc++", "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-I" + sysconfig.get_paths()["include"], os.path.join(CSRC, "fs_pylaunch.cpp"), "-o", LAUNCH], check=True)
     return LIB
 
 

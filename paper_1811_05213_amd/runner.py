@@ -6,12 +6,18 @@ uint16 arrays of raw bits, u8 tensors are uint8 arrays.
 """
 from __future__ import annotations
 
+import ctypes
 from typing import List, Sequence
 
 import numpy as np
 import torch
 
-from .binding import Plan
+from .binding import Plan, _check, lib
+
+try:
+    from . import _launch
+except ImportError:  # not built yet: planning needs no launch path
+    _launch = None
 
 _NP_DT = {"f32": np.float32, "bf16": np.uint16, "u8": np.uint8}
 _TORCH_DT = {"f32": torch.float32, "bf16": torch.int16, "u8": torch.uint8}
@@ -39,7 +45,10 @@ class DeviceRun:
     def __init__(self, plan: Plan, device: str = "cuda:0"):
         if not torch.cuda.is_available():
             raise RuntimeError("no GPU: the stitched kernels only run on a MI355X")
+        if _launch is None:
+            raise FileNotFoundError("_launch.so is missing: run `python -m paper_1811_05213_amd.build` first")
         self.plan = plan
+        self._run = ctypes.cast(lib().fs_plan_run, ctypes.c_void_p).value
         self.device = torch.device(device)
         self._device_index = self.device.index if self.device.index is not None else torch.cuda.current_device()
         g = plan.graph
@@ -61,10 +70,12 @@ class DeviceRun:
 
     def launch(self) -> None:
         # The raw handle of the device's current stream: building a torch.cuda.Stream object for it costs 2.0 us a call, this
-        # 0.08 us (a launch of softmax f32 [256,1024]: 6.8 -> 4.4 us of host time, where the kernel itself takes 3 us).
-        stream = _raw_stream(self._device_index)
-        ins, outs = self.plan.pointer_tables([t.data_ptr() for t in self.inputs], [t.data_ptr() for t in self.outputs])
-        self.plan.run_tables(ins, outs, self.workspace.data_ptr() if self.ws_bytes else 0, self.ws_bytes, stream)
+        # 0.08 us.  Addresses and the call itself in C (softmax f32 [256,1024]: 4.0 -> 2.9 us of host time, of which the runtime's
+        # launch takes 2.65; the kernel itself takes 3 us).
+        status = _launch.launch(self._run, self.plan._h.value or 0, self.inputs, self.outputs, self.workspace if self.ws_bytes else None, self.ws_bytes,
+                                _raw_stream(self._device_index))
+        if status != 0:
+            _check(status)
 
     def tune(self, reps: int = 0) -> dict:
         """fs_plan_tune on this run's buffers: fills the performance library for the plan's groups."""

@@ -1393,3 +1393,31 @@ def test_chains_read_rows_only():
             for part in line.split("|"):
                 assert kind == "rows" or len(part.replace("// one launch:", "").split(" on ")[0].split()) == 2, line
         p.destroy()
+
+
+def test_launch_module(built_lib):
+    # addresses of tensors to fs_plan_run's two tables, in order; its status comes back; what is no tensor raises
+    import torch
+    from paper_1811_05213_amd import _launch
+    seen = []
+    proto = ctypes.CFUNCTYPE(ctypes.c_int, ctypes.c_void_p, ctypes.POINTER(ctypes.c_void_p), ctypes.POINTER(ctypes.c_void_p), ctypes.c_void_p, ctypes.c_size_t, ctypes.c_void_p)
+
+    @proto
+    def run(plan, ins, outs, ws, nbytes, stream):
+        seen.append((plan, [ins[k] for k in range(n)], [outs[k] for k in range(2)], ws, nbytes, stream))
+        return 7
+
+    fn = ctypes.cast(run, ctypes.c_void_p).value
+    outs, ws = [torch.zeros(3), torch.zeros(5)], torch.zeros(64)
+    for n in (0, 1, 3, 90):  # (more tensors than the table on the stack holds)
+        ins = [torch.zeros(2) for _ in range(n)]
+        assert _launch.launch(fn, 5, ins, tuple(outs), ws, 256, 9) == 7
+        assert seen[-1] == (5, [t.data_ptr() for t in ins], [t.data_ptr() for t in outs], ws.data_ptr(), 256, 9)
+        assert _launch.launch(fn, 5, ins, outs, None, 0, 0) == 7 and seen[-1][3:] == (None, 0, None)
+    calls = len(seen)
+    for bad in ((fn, 5, [None], outs, None, 0, 0), (fn, 5, 3, outs, None, 0, 0), (fn, 5, [], [1.5], None, 0, 0), (0, 5, [], outs, None, 0, 0), (fn, 5, [], outs, None, -1, 0), (fn, 5)):
+        with pytest.raises((AttributeError, TypeError, ValueError, OverflowError)):
+            _launch.launch(*bad)
+    assert len(seen) == calls
+    real = ctypes.cast(built_lib.fs_plan_run, ctypes.c_void_p).value
+    assert _launch.launch(real, 0, [], outs, None, 0, 0) == 1 and b"plan is NULL" in built_lib.fs_last_error()
