@@ -1235,13 +1235,13 @@ struct Former {
             for (const ExtTensor& y : plan[a].ext_in) share_full |= x.node == y.node && y.kind == KIND_FULL;
           const bool small = plan[a].min_hbm_bytes + plan[b].min_hbm_bytes <= kFootprintThreshold;
           if (!share_full && !small) continue;
+          auto seen = refused.find({a, b});
+          if (seen != refused.end() && seen->second == std::make_pair(version[a], version[b])) continue;
           // a path a -> c -> ... -> b through a third group would become a cycle
           bool cycle = false;
           for (int c : successors((int)a)) cycle |= c != (int)b && reaches(c, (int)b);
           for (int c : successors((int)b)) cycle |= c != (int)a && reaches(c, (int)a);
           if (cycle) continue;
-          auto seen = refused.find({a, b});
-          if (seen != refused.end() && seen->second == std::make_pair(version[a], version[b])) continue;
           std::vector<int> merged = members[a];
           merged.insert(merged.end(), members[b].begin(), members[b].end());
           if (analyse_group(g, merged, group_of, (int)a, opt, &merged_plan) != FS_OK || !worth_fusing(merged_plan)) {

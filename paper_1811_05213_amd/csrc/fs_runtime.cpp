@@ -394,133 +394,138 @@ fs_status fs_plan_create(const fs_graph_desc* desc, fs_plan** out_plan) {
   std::vector<PlanOptions> group_opt(plan->groups.size(), plan->opt);
   std::vector<GroupPlan> before_waves(plan->groups.size());  // the plan to return to when forcing the occupancy spills
   std::vector<char> waves_tried(plan->groups.size(), 0);
-  for (int round = 0;; ++round) {
-    std::string tu = device_header_source();
-    std::set<std::string> seen;
-    for (const GroupPlan& gp : plan->groups)
-      if (seen.insert(gp.kernel_name).second) tu += "\n" + gp.source;
-    for (const fs_plan::Joined& j : plan->joined)
-      if (seen.insert(j.gp.kernel_name).second) tu += "\n" + j.gp.source;
-    for (const Composite& c : plan->composites)
-      if (seen.insert(c.kernel_name).second) tu += "\n" + c.source;
-    st = compile_kernel(tu, "fs_plan", &plan->code);
-    if (st != FS_OK) {
-      delete plan;
-      return st;
-    }
-    const std::map<std::string, long> scratch = code_object_kernel_field(plan->code, ".private_segment_fixed_size");
-    const std::map<std::string, long> vgprs = code_object_kernel_field(plan->code, ".vgpr_count");
-    bool changed = false;
-    for (size_t k = plan->joined.size(); k-- > 0;) {  // (a joined kernel that spills is given up: its groups run as they are)
-      auto it = scratch.find(plan->joined[k].gp.kernel_name);
-      if (getenv("FS_LOG_PLAN")) {
-        auto vg = vgprs.find(plan->joined[k].gp.kernel_name);
-        const Schedule& s = plan->joined[k].gp.s;
-        fprintf(stderr, "fs: groups %d to %d joined, kernel %s: %ld vector registers, %ld bytes of scratch, %d lanes per tile, workgroup %d, %d workgroups per tile, %d rows to a lane, grid %d\n",
-                plan->joined[k].first, plan->joined[k].first + plan->joined[k].count - 1, plan->joined[k].gp.kernel_name.c_str(), vg == vgprs.end() ? -1 : vg->second,
-                it == scratch.end() ? -1 : it->second, s.L, s.WG, s.RB, s.U, s.grid);
-      }
-      if (it == scratch.end() || it->second == 0) continue;
-      plan->joined.erase(plan->joined.begin() + (long)k);
-      changed = true;
-    }
-    for (size_t gi = 0; gi < plan->groups.size(); ++gi) {
-      GroupPlan& gp = plan->groups[gi];
-      auto it = scratch.find(gp.kernel_name);
-      if (gp.s.min_waves > 0) {  // a forced occupancy must come (nearly) for free: at most 8 spilled registers
-        if (it != scratch.end() && it->second > 32) {
-          if (getenv("FS_LOG_PLAN"))
-            fprintf(stderr, "fs: group %zu kernel %s spills %ld bytes at %d wavefronts per SIMD: back to the plain form\n", gi,
-                    gp.kernel_name.c_str(), it->second, gp.s.min_waves);
-          gp = before_waves[gi];
-          group_opt[gi].min_waves = 0;
-          changed = true;
+  auto settle = [&]() -> fs_status {
+    for (int round = 0;; ++round) {
+      std::string tu = device_header_source();
+      std::set<std::string> seen;
+      // (groups that another launch takes over stay out: fs_plan_tune compiles them when it measures them)
+      for (const LaunchItem& l : plan->launches)
+        if (l.kind == LaunchItem::GROUP && seen.insert(plan->groups[l.index].kernel_name).second) tu += "\n" + plan->groups[l.index].source;
+      for (const fs_plan::Joined& j : plan->joined)
+        if (seen.insert(j.gp.kernel_name).second) tu += "\n" + j.gp.source;
+      for (const Composite& c : plan->composites)
+        if (seen.insert(c.kernel_name).second) tu += "\n" + c.source;
+      st = compile_kernel(tu, "fs_plan", &plan->code);
+      if (st != FS_OK) return st;
+      const std::map<std::string, long> scratch = code_object_kernel_field(plan->code, ".private_segment_fixed_size");
+      const std::map<std::string, long> vgprs = code_object_kernel_field(plan->code, ".vgpr_count");
+      bool changed = false;
+      for (size_t k = plan->joined.size(); k-- > 0;) {  // (a joined kernel that spills is given up: its groups run as they are)
+        auto it = scratch.find(plan->joined[k].gp.kernel_name);
+        if (getenv("FS_LOG_PLAN")) {
+          auto vg = vgprs.find(plan->joined[k].gp.kernel_name);
+          const Schedule& s = plan->joined[k].gp.s;
+          fprintf(stderr, "fs: groups %d to %d joined, kernel %s: %ld vector registers, %ld bytes of scratch, %d lanes per tile, workgroup %d, %d workgroups per tile, %d rows to a lane, grid %d\n",
+                  plan->joined[k].first, plan->joined[k].first + plan->joined[k].count - 1, plan->joined[k].gp.kernel_name.c_str(), vg == vgprs.end() ? -1 : vg->second,
+                  it == scratch.end() ? -1 : it->second, s.L, s.WG, s.RB, s.U, s.grid);
         }
-        continue;
+        if (it == scratch.end() || it->second == 0) continue;
+        plan->joined.erase(plan->joined.begin() + (long)k);
+        changed = true;
       }
-      if (round >= 4) continue;  // (only returns to the plain form are still taken: the loop ends)
-      // (a few spilled registers cost nothing measurable, and whether a borderline kernel gets them varies with what the
-      // run-time compiler compiled before in the same process; hundreds of bytes are what ruins a kernel)
-      if (it == scratch.end() || it->second <= 128) {
-        auto vg = vgprs.find(gp.kernel_name);
-        if (!waves_tried[gi] && gp.s.WG == 1024 && !gp.s.ahead && vg != vgprs.end() && vg->second > 64 && vg->second <= 80 && (it == scratch.end() || it->second == 0)) {
-          waves_tried[gi] = 1;
-          PlanOptions o = group_opt[gi];
-          o.min_waves = 8;
-          GroupPlan again;
-          if (analyse_group(g, ordered[gi], plan->group_of, (int)gi, o, &again) == FS_OK && generate_kernel(g, &again, (int)gi) == FS_OK &&
-              again.kernel_name != gp.kernel_name) {
+      for (size_t gi = 0; gi < plan->groups.size(); ++gi) {
+        GroupPlan& gp = plan->groups[gi];
+        auto it = scratch.find(gp.kernel_name);
+        if (gp.s.min_waves > 0) {  // a forced occupancy must come (nearly) for free: at most 8 spilled registers
+          if (it != scratch.end() && it->second > 32) {
             if (getenv("FS_LOG_PLAN"))
-              fprintf(stderr, "fs: group %zu kernel %s uses %ld registers with 1024-lane workgroups: trying 8 wavefronts per SIMD\n", gi,
-                      gp.kernel_name.c_str(), vg->second);
-            before_waves[gi] = gp;
-            group_opt[gi] = o;
-            gp = again;
+              fprintf(stderr, "fs: group %zu kernel %s spills %ld bytes at %d wavefronts per SIMD: back to the plain form\n", gi,
+                      gp.kernel_name.c_str(), it->second, gp.s.min_waves);
+            gp = before_waves[gi];
+            group_opt[gi].min_waves = 0;
             changed = true;
           }
+          continue;
         }
-        continue;
-      }
-      // the next milder plan that actually differs from the current one
-      PlanOptions o = group_opt[gi];
-      GroupPlan again;
-      bool found = false;
-      if (gp.s.ahead) {
-        o.ahead = false;
-        found = analyse_group(g, ordered[gi], plan->group_of, (int)gi, o, &again) == FS_OK && generate_kernel(g, &again, (int)gi) == FS_OK;
-      }
-      while (!found && !gp.row_reduces.empty() && (gp.s.E >= 32 || gp.s.resident) && o.wide_level > 0) {
-        --o.wide_level;
-        found = analyse_group(g, ordered[gi], plan->group_of, (int)gi, o, &again) == FS_OK &&
-                generate_kernel(g, &again, (int)gi) == FS_OK && again.kernel_name != gp.kernel_name;
-      }
-      // (narrow column tiles: fewer trips in flight, at last the wide form; half a workgroup would need twice the trips)
-      for (int u = gp.s.U / 2; !found && gp.s.narrow_tiles && u >= 0; u = u > 0 ? u / 2 : -1) {
-        o = group_opt[gi];
-        if (!o.has_hint) o.hint = fs_sched_hint{0, 0, 0, 0};
-        o.has_hint = true;
-        o.hint.tiles_per_trip = u > 0 ? u : plan->opt.has_hint ? plan->opt.hint.tiles_per_trip : 0;
-        o.narrow_tiles = u > 0;
-        found = analyse_group(g, ordered[gi], plan->group_of, (int)gi, o, &again) == FS_OK &&
-                generate_kernel(g, &again, (int)gi) == FS_OK && again.kernel_name != gp.kernel_name;
-      }
-      if (!found && gp.s.WG >= 2 * std::max(64, gp.s.L) && !gp.s.chunked && !gp.s.tiled_transpose) {
-        o = group_opt[gi];
-        if (!o.has_hint) o.hint = fs_sched_hint{0, 0, 0, 0};
-        o.has_hint = true;
-        o.hint.wg_threads = gp.s.WG / 2;
-        found = analyse_group(g, ordered[gi], plan->group_of, (int)gi, o, &again) == FS_OK &&
-                generate_kernel(g, &again, (int)gi) == FS_OK && again.kernel_name != gp.kernel_name;
-      }
-      if (getenv("FS_LOG_PLAN"))
-        fprintf(stderr, "fs: group %zu kernel %s spills %ld bytes (%d lanes/row, %d elements/lane, workgroup %d): %s\n", gi, gp.kernel_name.c_str(),
-                it->second, gp.s.L, gp.s.E, gp.s.WG, found ? "planned again" : "kept");
-      if (!found) continue;
-      group_opt[gi] = o;
-      gp = again;
-      changed = true;
-    }
-    for (const Composite& c : plan->composites) {  // (one that spills: its groups are launched one by one)
-      auto it = scratch.find(c.kernel_name);
-      if (getenv("FS_LOG_PLAN")) {
-        auto vg = vgprs.find(c.kernel_name);
-        fprintf(stderr, "fs: composite %s: %ld vector registers, %ld bytes of scratch, workgroup %d\n", c.kernel_name.c_str(), vg == vgprs.end() ? -1 : vg->second,
-                it == scratch.end() ? -1 : it->second, c.WG);
-      }
-      if (it != scratch.end() && it->second > 0) may_compose = false, changed = true;
-    }
-    if (changed) compose();
-    if (!changed) {
-      if (getenv("FS_LOG_PLAN"))
-        for (size_t gi = 0; gi < plan->groups.size(); ++gi) {
-          const GroupPlan& gp = plan->groups[gi];
+        if (round >= 4) continue;  // (only returns to the plain form are still taken: the loop ends)
+        // (a few spilled registers cost nothing measurable, and whether a borderline kernel gets them varies with what the
+        // run-time compiler compiled before in the same process; hundreds of bytes are what ruins a kernel)
+        if (it == scratch.end() || it->second <= 128) {
           auto vg = vgprs.find(gp.kernel_name);
-          auto sc = scratch.find(gp.kernel_name);
-          fprintf(stderr, "fs: group %zu kernel %s: %ld vector registers, %ld bytes of scratch, workgroup %d, grid %d\n", gi, gp.kernel_name.c_str(),
-                  vg == vgprs.end() ? -1 : vg->second, sc == scratch.end() ? -1 : sc->second, gp.s.WG, gp.s.grid);
+          if (!waves_tried[gi] && gp.s.WG == 1024 && !gp.s.ahead && vg != vgprs.end() && vg->second > 64 && vg->second <= 80 && (it == scratch.end() || it->second == 0)) {
+            waves_tried[gi] = 1;
+            PlanOptions o = group_opt[gi];
+            o.min_waves = 8;
+            GroupPlan again;
+            if (analyse_group(g, ordered[gi], plan->group_of, (int)gi, o, &again) == FS_OK && generate_kernel(g, &again, (int)gi) == FS_OK &&
+                again.kernel_name != gp.kernel_name) {
+              if (getenv("FS_LOG_PLAN"))
+                fprintf(stderr, "fs: group %zu kernel %s uses %ld registers with 1024-lane workgroups: trying 8 wavefronts per SIMD\n", gi,
+                        gp.kernel_name.c_str(), vg->second);
+              before_waves[gi] = gp;
+              group_opt[gi] = o;
+              gp = again;
+              changed = true;
+            }
+          }
+          continue;
         }
-      break;
+        // the next milder plan that actually differs from the current one
+        PlanOptions o = group_opt[gi];
+        GroupPlan again;
+        bool found = false;
+        if (gp.s.ahead) {
+          o.ahead = false;
+          found = analyse_group(g, ordered[gi], plan->group_of, (int)gi, o, &again) == FS_OK && generate_kernel(g, &again, (int)gi) == FS_OK;
+        }
+        while (!found && !gp.row_reduces.empty() && (gp.s.E >= 32 || gp.s.resident) && o.wide_level > 0) {
+          --o.wide_level;
+          found = analyse_group(g, ordered[gi], plan->group_of, (int)gi, o, &again) == FS_OK &&
+                  generate_kernel(g, &again, (int)gi) == FS_OK && again.kernel_name != gp.kernel_name;
+        }
+        // (narrow column tiles: fewer trips in flight, at last the wide form; half a workgroup would need twice the trips)
+        for (int u = gp.s.U / 2; !found && gp.s.narrow_tiles && u >= 0; u = u > 0 ? u / 2 : -1) {
+          o = group_opt[gi];
+          if (!o.has_hint) o.hint = fs_sched_hint{0, 0, 0, 0};
+          o.has_hint = true;
+          o.hint.tiles_per_trip = u > 0 ? u : plan->opt.has_hint ? plan->opt.hint.tiles_per_trip : 0;
+          o.narrow_tiles = u > 0;
+          found = analyse_group(g, ordered[gi], plan->group_of, (int)gi, o, &again) == FS_OK &&
+                  generate_kernel(g, &again, (int)gi) == FS_OK && again.kernel_name != gp.kernel_name;
+        }
+        if (!found && gp.s.WG >= 2 * std::max(64, gp.s.L) && !gp.s.chunked && !gp.s.tiled_transpose) {
+          o = group_opt[gi];
+          if (!o.has_hint) o.hint = fs_sched_hint{0, 0, 0, 0};
+          o.has_hint = true;
+          o.hint.wg_threads = gp.s.WG / 2;
+          found = analyse_group(g, ordered[gi], plan->group_of, (int)gi, o, &again) == FS_OK &&
+                  generate_kernel(g, &again, (int)gi) == FS_OK && again.kernel_name != gp.kernel_name;
+        }
+        if (getenv("FS_LOG_PLAN"))
+          fprintf(stderr, "fs: group %zu kernel %s spills %ld bytes (%d lanes/row, %d elements/lane, workgroup %d): %s\n", gi, gp.kernel_name.c_str(),
+                  it->second, gp.s.L, gp.s.E, gp.s.WG, found ? "planned again" : "kept");
+        if (!found) continue;
+        group_opt[gi] = o;
+        gp = again;
+        changed = true;
+      }
+      for (const Composite& c : plan->composites) {  // (one that spills: its groups are launched one by one)
+        auto it = scratch.find(c.kernel_name);
+        if (getenv("FS_LOG_PLAN")) {
+          auto vg = vgprs.find(c.kernel_name);
+          fprintf(stderr, "fs: composite %s: %ld vector registers, %ld bytes of scratch, workgroup %d\n", c.kernel_name.c_str(), vg == vgprs.end() ? -1 : vg->second,
+                  it == scratch.end() ? -1 : it->second, c.WG);
+        }
+        if (it != scratch.end() && it->second > 0) may_compose = false, changed = true;
+      }
+      if (changed) compose();
+      if (!changed) {
+        if (getenv("FS_LOG_PLAN"))
+          for (size_t gi = 0; gi < plan->groups.size(); ++gi) {
+            const GroupPlan& gp = plan->groups[gi];
+            auto vg = vgprs.find(gp.kernel_name);
+            auto sc = scratch.find(gp.kernel_name);
+            fprintf(stderr, "fs: group %zu kernel %s: %ld vector registers, %ld bytes of scratch, workgroup %d, grid %d\n", gi, gp.kernel_name.c_str(),
+                    vg == vgprs.end() ? -1 : vg->second, sc == scratch.end() ? -1 : sc->second, gp.s.WG, gp.s.grid);
+          }
+        break;
+      }
     }
+    return FS_OK;
+  };
+  if ((st = settle()) != FS_OK) {
+    delete plan;
+    return st;
   }
 
   // workspace: [tickets][tensors crossing group boundaries][column-reduction partials]
@@ -564,9 +569,12 @@ fs_status fs_plan_create(const fs_graph_desc* desc, fs_plan** out_plan) {
     if (off > FS_STATIC_SCRATCH_BYTES + extra) break;
     plan->joined.clear();
     plan->ws_tensor_offset.clear();
-    plan->launches.clear();  // (their groups one by one; the kernels of composites stay as they are)
-    plan->composites.clear();
-    for (int k = 0; k < (int)plan->groups.size(); ++k) plan->launches.push_back({LaunchItem::GROUP, k});
+    may_compose = false;
+    compose();
+    if ((st = settle()) != FS_OK) {
+      delete plan;
+      return st;
+    }
   }
 
   plan->min_hbm_bytes = 0;
@@ -624,20 +632,17 @@ static fs_status load_on_device(fs_plan* plan, int device, fs_plan::Loaded** out
   if (e != hipSuccess) FS_FAIL(FS_ERR_HIP, "hipModuleLoadData: %s", hipGetErrorString(e));
   fs_plan::Loaded ld;
   ld.modules.push_back((void*)mod);
-  for (const GroupPlan& gp : plan->groups) {
-    hipFunction_t fn;
-    e = hipModuleGetFunction(&fn, mod, gp.kernel_name.c_str());
-    if (e != hipSuccess) {
-      (void)hipModuleUnload(mod);
-      FS_FAIL(FS_ERR_HIP, "hipModuleGetFunction(%s): %s", gp.kernel_name.c_str(), hipGetErrorString(e));
+  std::vector<const char*> names(plan->groups.size(), nullptr);  // (groups without a launch of their own have no kernel here)
+  for (const LaunchItem& l : plan->launches)
+    if (l.kind == LaunchItem::GROUP) names[l.index] = plan->groups[l.index].kernel_name.c_str();
+  for (const fs_plan::Joined& j : plan->joined) names.push_back(j.gp.kernel_name.c_str());
+  for (const Composite& c : plan->composites) names.push_back(c.kernel_name.c_str());
+  for (const char* name : names) {
+    hipFunction_t fn = nullptr;
+    if (!name) {
+      ld.functions.push_back(nullptr);
+      continue;
     }
-    ld.functions.push_back((void*)fn);
-  }
-  std::vector<const char*> more;
-  for (const fs_plan::Joined& j : plan->joined) more.push_back(j.gp.kernel_name.c_str());
-  for (const Composite& c : plan->composites) more.push_back(c.kernel_name.c_str());
-  for (const char* name : more) {
-    hipFunction_t fn;
     e = hipModuleGetFunction(&fn, mod, name);
     if (e != hipSuccess) {
       (void)hipModuleUnload(mod);
@@ -955,10 +960,12 @@ struct TuneScratch {  // everything fs_plan_tune allocates, released on every ex
   void* flush = nullptr;
   void* scratch = nullptr;
   hipModule_t module = nullptr;
+  std::vector<hipModule_t> groups;  // kernels of groups that have no launch of their own
   std::vector<hipEvent_t> events;
   ~TuneScratch() {
     (void)hipDeviceSynchronize();  // nothing below may still be in use by a launch
     if (module) (void)hipModuleUnload(module);
+    for (hipModule_t m : groups) (void)hipModuleUnload(m);
     if (scratch) (void)hipFree(scratch);
     if (flush) (void)hipFree(flush);
     for (hipEvent_t e : events) (void)hipEventDestroy(e);
@@ -1018,6 +1025,18 @@ fs_status fs_plan_tune(fs_plan* plan, const void* const* inputs, void* const* ou
     void* base_part = base.part_bytes ? (void*)(ws + base.part_offset) : nullptr;
     void* base_tickets = base.n_tickets ? (void*)(ws + base.ticket_offset) : nullptr;
 
+    void* base_fn = ld->functions[gi];
+    if (!base_fn) {
+      std::vector<char> code;
+      st = compile_kernel(std::string(device_header_source()) + "\n" + base.source, base.kernel_name, &code);
+      if (st != FS_OK) return st;
+      hipModule_t mod;
+      FS_HIP(hipModuleLoadData(&mod, code.data()));
+      res.groups.push_back(mod);
+      hipFunction_t f;
+      FS_HIP(hipModuleGetFunction(&f, mod, base.kernel_name.c_str()));
+      base_fn = (void*)f;
+    }
     // the current schedule first, then its neighbourhood (distinct kernels only)
     std::vector<GroupPlan> cands;
     cands.push_back(base);
@@ -1045,7 +1064,7 @@ fs_status fs_plan_tune(fs_plan* plan, const void* const* inputs, void* const* ou
       if (perflib_lookup(key, &us)) {
         ++rep.hits;
       } else {
-        void* fn = ld->functions[gi];
+        void* fn = base_fn;
         void* part = base_part;
         void* tickets = base_tickets;
         if (k > 0) {
@@ -1115,7 +1134,7 @@ fs_status fs_plan_tune(fs_plan* plan, const void* const* inputs, void* const* ou
     if (best_us < cur_us) ++rep.improvable;
     ++rep.groups;
     // leave this group's results as a normal run would, for the groups that follow
-    FS_HIP(launch_group(base, ld->functions[gi], tensors, base_part, base_tickets, stream));
+    FS_HIP(launch_group(base, base_fn, tensors, base_part, base_tickets, stream));
   }
   FS_HIP(hipStreamSynchronize(stream));
 #undef FS_HIP
