@@ -1107,14 +1107,24 @@ struct Emitter {
     if (ctile) os << "  const int tile = (int)blockIdx.x % CT, rb = (int)blockIdx.x / CT, vbase = tile * (NVL * L);\n";
     else os << "  const int tile = 0, rb = (int)blockIdx.x;\n";
     os << "  (void)tile; (void)rb; (void)CW; (void)RB;\n";
+    if (s.ahead) {
+      int n_full = 0;
+      for (const ExtTensor& e : gp.ext_in) n_full += e.kind == KIND_FULL;
+      os << "  constexpr int JL = " << s.ahead_lds << ";\n  __shared__ __attribute__((aligned(16))) fs_u8 lds_ahead[" << n_full << " * JL * WG * 16];\n";
+    }
     // One LDS pool, shared by lifetime: the row loop's buffers (transpose tile, staged [1,C]
     // operands) and the epilogue's column-fold area never live at the same time.
     if (K > 0 || s.tile_transpose || s.stage_rowv) {
       os << "  constexpr int TCW = " << (s.tiled_transpose ? "NVL * L * V" : "C") << ";  // columns of one transpose tile\n";
       os << "  constexpr int SLOT = NVL * L * V, TILE_FLOATS = " << (s.tile_transpose ? "TCW * (G + 1)" : "0") << ", LOOP_FLOATS = TILE_FLOATS + "
-         << (s.stage_rowv ? n_slots : 0) << " * SLOT, PC = " << std::max(1, s.fold_piece) << ", FOLD_FLOATS = " << (K > 0 ? "(L < 64 ? WG / 64 : G) * PC" : "0") << ";\n";
-      os << "  __shared__ float lds_pool[LOOP_FLOATS > FOLD_FLOATS ? LOOP_FLOATS : FOLD_FLOATS];\n";
-      os << "  float* const lds_tile = lds_pool; float* const lds_rowv = lds_pool + TILE_FLOATS; float* const lds_col = lds_pool;\n";
+         << (s.stage_rowv ? n_slots : 0) << " * SLOT, PC = " << std::max(1, s.fold_piece) << ", FOLD_FLOATS = " << (K > 0 ? "(L < 64 ? WG / 64 : G) * PC" : "0");
+      // (workgroups that meet fold their slices in the same place)
+      if (s.meet) os << " > WG / 64 * " << s.meet * fold_vector(s.fold_width) << " ? (L < 64 ? WG / 64 : G) * PC : WG / 64 * " << s.meet * fold_vector(s.fold_width);
+      os << ";\n";
+      // (rows asked for ahead have been worked on when the columns are folded: the fold takes their place)
+      if (s.ahead) os << "  __shared__ float lds_pool[LOOP_FLOATS > 0 ? LOOP_FLOATS : 1];\n  static_assert(FOLD_FLOATS * 4 <= (int)sizeof(lds_ahead), \"fold area\");\n";
+      else os << "  __shared__ float lds_pool[LOOP_FLOATS > FOLD_FLOATS ? LOOP_FLOATS : FOLD_FLOATS];\n";
+      os << "  float* const lds_tile = lds_pool; float* const lds_rowv = lds_pool + TILE_FLOATS; float* const lds_col = " << (s.ahead ? "(float*)lds_ahead" : "lds_pool") << ";\n";
       os << "  (void)lds_tile; (void)lds_rowv; (void)lds_col; (void)SLOT; (void)PC;\n";
     }
     if (K > 0) os << "  __shared__ fs_u32 lds_flag;\n";
@@ -1180,21 +1190,18 @@ struct Emitter {
       for (const ExtTensor& e : gp.ext_in) {
         if (e.kind != KIND_FULL) continue;
         const std::string nt = e.streaming ? "true" : "false", ua = over ? "true" : "false", p = "a.p[" + std::to_string(e.arg) + "]";
-        os << ind << "fs_row_ask<" << e.dtype << ", V, L, JL, " << ua << ", " << nt << ">(lds_ahead + " << k++ << " * (JL * L * 16), " << p << ", " << row0 << ", lir);\n";
+        os << ind << "fs_row_ask<" << e.dtype << ", V, L, NV, RAGGED, WG, JL, " << ua << ", " << nt << ">(lds_ahead + " << k++ << " * (JL * WG * 16), " << p << ", " << row0 << ", lir, tid);\n";
         if (s.ahead_lds < s.NVL)
           os << ind << "_Pragma(\"unroll\") for (int j = JL; j < NVL; ++j) n" << loc(e.node) << "[j - JL] = fs_load_raw<" << e.dtype << ", V, " << nt << ", " << ua << ">(" << p << ", " << row0
              << " + fs_col_of<V, NV, RAGGED>(j * L + lir));\n";
       }
     };
     if (s.ahead) {
-      int n_full = 0;
       for (const ExtTensor& e : gp.ext_in)
-        if (e.kind == KIND_FULL) {
-          ++n_full;
-          if (s.ahead_lds < s.NVL) os << "  typename fs_vec<typename fs_elem<" << e.dtype << ">::type, V>::type n" << loc(e.node) << "[" << s.NVL - s.ahead_lds << "];\n";
-        }
-      os << "  constexpr int JL = " << s.ahead_lds << ";\n  __shared__ __attribute__((aligned(16))) fs_u8 lds_ahead[" << n_full << " * JL * L * 16];\n";
-      emit_ask("  ", "(long)blockIdx.x * C");
+        if (e.kind == KIND_FULL && s.ahead_lds < s.NVL)
+          os << "  typename fs_vec<typename fs_elem<" << e.dtype << ">::type, V>::type n" << loc(e.node) << "[" << s.NVL - s.ahead_lds << "];\n";
+      os << "  const long first = (long)blockIdx.x * G + rg;\n";
+      emit_ask("  ", "(first < R ? first : R - 1) * C");
       os << "  fs_wait_vm<0>();\n";
     }
     for (int k = 0; k < K; ++k) {
@@ -1271,15 +1278,15 @@ struct Emitter {
         os << "    const long unit = (long)it * G + rg;\n    const long row = unit / CT;\n    const int vbase = (int)(unit % CT) * (NVL * L);\n";
       }
       // rows beyond R are clamped for loads (never predicated) and masked at stores / accumulations
-      if (s.ahead)  // (one row to a trip: all of them lie inside the tensor, and the stores need no branch)
+      if (s.ahead)  // (trips are of whole groups of rows: all of them lie inside the tensor, and the stores need no branch)
         os << "    constexpr bool rok = true;\n    const long row_ld = row, row0 = row_ld * C;\n    (void)rok; (void)row_ld; (void)row0; (void)vbase;\n";
       else
         os << "    const bool rok" << x << " = row" << x << " < R;\n    const long row_ld" << x << " = rok" << x << " ? row" << x
            << " : R - 1;\n    const long row0" << x << " = row_ld" << x << " * C;\n    (void)row0" << x << "; (void)vbase" << x << ";\n";
       for (const ExtTensor& e : gp.ext_in) {
         if (e.kind == KIND_FULL && s.ahead) {
-          os << "    float " << name(e.node, KIND_FULL) << "[E];\n    fs_row_take<" << e.dtype << ", V, NVL, L, JL>(" << name(e.node, KIND_FULL) << ", lds_ahead + " << n_asked++
-             << " * (JL * L * 16), lir);\n";
+          os << "    float " << name(e.node, KIND_FULL) << "[E];\n    fs_row_take<" << e.dtype << ", V, NVL, WG, JL>(" << name(e.node, KIND_FULL) << ", lds_ahead + " << n_asked++
+             << " * (JL * WG * 16), tid);\n";
           if (s.ahead_lds < s.NVL)
             os << "    _Pragma(\"unroll\") for (int j = JL; j < NVL; ++j) _Pragma(\"unroll\") for (int k = 0; k < V; ++k) " << name(e.node, KIND_FULL) << "[j * V + k] = fs_to_f32<" << e.dtype
                << ">(n" << loc(e.node) << "[j - JL][k]);\n";
@@ -1305,7 +1312,7 @@ struct Emitter {
     }
     if (s.ahead) {
       // (the LDS reads are done before the next row may overwrite what they read)
-      os << "    fs_wait_lds();\n    if (it + (int)gridDim.x < a.n_iters) {\n      const long next0 = ((long)it + (int)gridDim.x) * C;\n";
+      os << "    fs_wait_lds();\n    if (it + (int)gridDim.x < a.n_iters) {\n      const long next = ((long)it + (int)gridDim.x) * G + rg, next0 = (next < R ? next : R - 1) * C;\n";
       emit_ask("      ", "next0");
       os << "    }\n";
     }
@@ -1541,17 +1548,25 @@ struct Emitter {
     // ---- epilogue: finish the column reductions ----
     if (K > 0) {
       const int CW = s.fold_width;
-      const int FV = CW % 4 == 0 ? 4 : CW % 2 == 0 ? 2 : 1;
+      const int FV = fold_vector(CW);
       os << "  {\n    constexpr int FV = " << FV << ";\n    typedef fs_colfold<" << K << ", CW, WG, FV> S;\n    float cv[S::CPT][FV];\n";
       for (int k = 0; k < K; ++k) {
         const int m = gp.col_reduces[k];
         os << "    fs_colred_fold_wg<" << g.nodes[m].attr_i << ", " << k << ", " << K << ", V, NVL, L, C, CW, WG, FV, PC>(ca" << loc(m)
            << ", cv, lds_col, lir, rg, " << (ctile ? "vbase" : "0") << ");\n";
       }
-      os << "    if (fs_colred_fold_grid<" << K << ", CW, WG, FV, " << s.fan_in << ", " << kname << "_kinds>(cv, a.part + (long)tile * "
-         << s.part_stride_floats << "L, a.tickets + tile * " << s.ticket_stride << ", &lds_flag, (fs_u32)rb, (fs_u32)RB)) {\n";
-      os << "      _Pragma(\"unroll\") for (int i = 0; i < S::CPT; ++i) {\n        const int c = tid + i * WG;\n"
-         << "        if (c < S::NCH) {\n          const int k = c / S::CH; const fs_col_index<C>::type col0 = (fs_col_index<C>::type)tile * CW + (c % S::CH) * FV;\n";
+      const std::string part = "a.part + (long)tile * " + std::to_string(s.part_stride_floats) + "L", tickets = "a.tickets + tile * " + std::to_string(s.ticket_stride);
+      if (s.meet) {
+        os << "    const int met = fs_colred_meet<" << K << ", CW, WG, FV>(cv, " << part << ", " << tickets << ", &lds_flag, (fs_u32)rb, (fs_u32)RB, " << gp.wait_ticks << ");\n"
+           << "    constexpr int SC = " << s.meet << ";\n    for (int all = 0; all < met && (all == 0 || fs_colred_left(&lds_flag)); ++all) {\n"
+           << "      for (int sl = all ? 0 : rb; sl * SC < S::NCH; sl += all ? 1 : RB) {\n"
+           << "        fs_colred_slice<" << K << ", CW, WG, FV, SC, RB, " << kname << "_kinds>(cv[0], " << part << ", lds_col, sl);\n"
+           << "        constexpr int i = 0;\n        const int c = sl * SC + tid;\n        if (tid < SC && c < S::NCH) {\n";
+      } else {
+        os << "    if (fs_colred_fold_grid<" << K << ", CW, WG, FV, " << s.fan_in << ", " << kname << "_kinds>(cv, " << part << ", " << tickets << ", &lds_flag, (fs_u32)rb, (fs_u32)RB)) {\n"
+           << "      _Pragma(\"unroll\") for (int i = 0; i < S::CPT; ++i) {\n        const int c = tid + i * WG;\n        if (c < S::NCH) {\n";
+      }
+      os << "          const int k = c / S::CH; const fs_col_index<C>::type col0 = (fs_col_index<C>::type)tile * CW + (c % S::CH) * FV;\n";
       for (int k = 0; k < K; ++k) {
         const int m = gp.col_reduces[k];
         const ExtTensor* e = find_out(m);
@@ -1560,7 +1575,8 @@ struct Emitter {
         os << "          if (k == " << k << ") { _Pragma(\"unroll\") for (int f = 0; f < FV; ++f) if (col0 + f < C) fs_store1<" << e->dtype
            << ">(a.p[" << e->arg << "], col0 + f, cv[i][f]" << (n.attr_i == FS_RED_MEAN ? " / (float)a.R" : "") << "); }\n";
       }
-      os << "        }\n      }\n    }\n  }\n";
+      os << "        }\n      }\n    }\n";
+      os << "  }\n";
     }
     os << "}\n";
   }

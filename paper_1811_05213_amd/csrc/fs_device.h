@@ -313,19 +313,20 @@ template <int DT, int V, int NVL, int L> FS_DEV void fs_load_row_chunk_lds(float
   for (int j = 0; j < NVL; ++j) fs_load_vec<DT, V>(&dst[j * V], lds_chunk, (long)(j * L + lir) * V);
 }
 
-// The next row on its way while a row is worked on: its first JL vectors go from memory to LDS without passing registers, the rest
-// waits in registers of their own.  A wavefront reads back what it asked for itself, 64 lanes x 16 bytes that follow each other, so
-// only its own counter of outstanding accesses orders the two; the compiler does not see that dependence, the waits are spelled out
-// (fs_wait_vm).  All JL vectors lie inside the row.  Rows that start inside a vector (UA) are asked for in 4-byte pieces.
+// The next rows on their way while rows are worked on: the first JL vectors of a lane go from memory to LDS without passing
+// registers, the rest waits in registers of their own.  A wavefront reads back what it asked for itself, 64 lanes x 16 bytes that
+// follow each other, so only its own counter of outstanding accesses orders the two; the compiler does not see that dependence, the
+// waits are spelled out (fs_wait_vm).  Rows that start inside a vector (UA; whole vectors of one row to a workgroup) are asked for
+// in 4-byte pieces.
 #define FS_LDS_BYTES(p) ((__attribute__((address_space(3))) void*)(p))
 #define FS_GLOBAL_BYTES(p) ((const __attribute__((address_space(1))) void*)(p))
-template <int DT, int V, int L, int JL, bool UA, bool NT> FS_DEV void fs_row_ask(fs_u8* lds, const void* base, long row_elem0, int lir) {
+template <int DT, int V, int L, int NV, int RAGGED, int WG, int JL, bool UA, bool NT> FS_DEV void fs_row_ask(fs_u8* lds, const void* base, long row_elem0, int lir, int tid) {
   typedef typename fs_elem<DT>::type T;
-  static_assert(V * sizeof(T) == 16 && L % 64 == 0 && (!UA || sizeof(T) == 4), "16 bytes to a lane");
-  const int wave = __builtin_amdgcn_readfirstlane(lir >> 6);
+  static_assert(V * sizeof(T) == 16 && WG % 64 == 0 && (!UA || (sizeof(T) == 4 && L == WG)), "16 bytes to a lane");
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
 #pragma unroll
   for (int j = 0; j < JL; ++j) {
-    fs_u8* const to = lds + (j * (L / 64) + wave) * 1024;
+    fs_u8* const to = lds + (j * (WG / 64) + wave) * 1024;
     if constexpr (UA) {
       const T* const from = static_cast<const T*>(base) + row_elem0 + (j * L + wave * 64) * V + (lir & 63);
 #pragma unroll
@@ -334,16 +335,15 @@ template <int DT, int V, int L, int JL, bool UA, bool NT> FS_DEV void fs_row_ask
         else __builtin_amdgcn_global_load_lds(FS_GLOBAL_BYTES(from + q * 64), FS_LDS_BYTES(to + q * 256), 4, 0, 0);
       }
     } else {
-      const T* const from = static_cast<const T*>(base) + row_elem0 + (long)(j * L + lir) * V;
+      const T* const from = static_cast<const T*>(base) + row_elem0 + fs_col_of<V, NV, RAGGED>(j * L + lir);
       if constexpr (NT) __builtin_amdgcn_global_load_lds(FS_GLOBAL_BYTES(from), FS_LDS_BYTES(to), 16, 0, 2);
       else __builtin_amdgcn_global_load_lds(FS_GLOBAL_BYTES(from), FS_LDS_BYTES(to), 16, 0, 0);
     }
   }
 }
-template <int DT, int V, int NVL, int L, int JL> FS_DEV void fs_row_take(float (&dst)[NVL * V], const fs_u8* lds, int lir) {
-  const int wave = lir >> 6;
+template <int DT, int V, int NVL, int WG, int JL> FS_DEV void fs_row_take(float (&dst)[NVL * V], const fs_u8* lds, int tid) {
 #pragma unroll
-  for (int j = 0; j < JL; ++j) fs_load_vec<DT, V>(&dst[j * V], lds + (j * (L / 64) + wave) * 1024, (long)(lir & 63) * V);
+  for (int j = 0; j < JL; ++j) fs_load_vec<DT, V>(&dst[j * V], lds + (j * (WG / 64) + (tid >> 6)) * 1024, (long)(tid & 63) * V);
 }
 // waits until at most N of this wavefront's accesses to global memory are outstanding (they complete in order)
 template <int N> FS_DEV void fs_wait_vm() {
@@ -928,6 +928,121 @@ FS_DEV bool fs_colred_fold_grid(float (&vals)[CPT][FV], float* part, fs_u32* tic
     n = groups;
   }
   return true;
+}
+
+// Stage 2 where all n workgroups are running at once (one to a compute unit): in the place of a tree in which one workgroup folds the
+// partials of F others and then one the rest, all of them meet and fold slices of the columns, from all partials.
+//   fs_colred_meet   leaves this workgroup's partial and waits until the others have: 1 they have (fold your slices), 2 they have, and this
+//                    is the last one, 0 they have not after `ticks` of the 100 MHz clock (leave: nothing waits for workgroups that the
+//                    device has not started).
+//   fs_colred_left   of the last one: has any left?  (Then it folds all slices.)
+//   counters         [0] groups of 16 workgroups that are complete, [32 * (1 + g)] workgroups of group g that have arrived (256 on one
+//                    counter take 10 us), then a door for each workgroup, opened by the last one.  Zero, and left zero: by the last
+//                    workgroup of a group, the last of all, who passes a door, and, where a workgroup has left, by the last of all.
+//   fs_colred_slice  slice `sl`: SC chunks of FV columns; lanes SC apart take a partial each, and fold in pairs.  In this order whoever
+//                    folds.  The results are those of chunks sl * SC + lane in the first SC lanes.
+FS_DEV fs_u32* fs_colred_door(fs_u32* counters, fs_u32 idx, fs_u32 n) { return counters + 32 * (1 + (n + 15) / 16) + idx; }
+template <int K, int C, int WG, int FV, int CPT>
+FS_DEV int fs_colred_meet(const float (&vals)[CPT][FV], float* part, fs_u32* counters, fs_u32* flag, fs_u32 idx, fs_u32 n, int ticks) {
+  typedef fs_colfold<K, C, WG, FV> S;
+  static_assert(CPT == S::CPT, "chunks per thread");
+  constexpr int KC = K * C;
+  const int t = (int)threadIdx.x;
+  const __amdgpu_buffer_rsrc_t mine = fs_make_rsrc(part + (long)idx * KC, KC * 4);
+#pragma unroll
+  for (int i = 0; i < S::CPT; ++i) {
+    const int c = t + i * WG;
+    if (c < S::NCH) fs_store_dev<FV>(vals[i], mine, (fs_u32)c * (FV * 4));
+  }
+  __builtin_amdgcn_s_waitcnt(0);  // this wavefront's partial stores are acknowledged
+  __syncthreads();
+  if (t == 0) {
+    const fs_u32 groups = (n + 15) / 16, grp = idx / 16, cnt = n - grp * 16 < 16 ? n - grp * 16 : 16;
+    fs_u32* const arrived = counters + 32 * (1 + grp);
+    fs_u32 met = 0;
+    if (__hip_atomic_fetch_add(arrived, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == cnt - 1) {
+      __hip_atomic_store(arrived, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      if (__hip_atomic_fetch_add(counters, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == groups - 1) {
+        __hip_atomic_store(counters, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        met = 2;
+      }
+    }
+    if (met == 0) {
+      fs_u32* const door = fs_colred_door(counters, idx, n);
+      const unsigned long long t0 = __builtin_amdgcn_s_memrealtime();
+      do {
+        __builtin_amdgcn_s_sleep(1);
+        met = __hip_atomic_load(door, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      } while (met == 0 && (long long)(__builtin_amdgcn_s_memrealtime() - t0) < (long long)ticks);
+      if (met == 0) met = __hip_atomic_exchange(door, 2u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);  // (1: opened in between)
+      if (met != 0) __hip_atomic_store(door, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    *flag = met;
+  }
+  __syncthreads();
+  const int met = (int)*flag;
+  if (met == 2) {
+    for (fs_u32 i = (fs_u32)t; i < n; i += WG) {
+      fs_u32* const door = fs_colred_door(counters, i, n);
+      if (i != idx && __hip_atomic_exchange(door, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == 2u) {
+        __hip_atomic_store(door, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        *flag = 3u;
+      }
+    }
+  }
+  return met;
+}
+FS_DEV bool fs_colred_left(const fs_u32* flag) {
+  __syncthreads();
+  return *flag == 3u;
+}
+template <int K, int C, int WG, int FV, int SC, int N, typename KINDS>
+FS_DEV void fs_colred_slice(float (&vals)[FV], const float* part, float* lds /* WG/64*SC*FV floats */, int sl) {
+  typedef fs_colfold<K, C, WG, FV> S;
+  constexpr int KC = K * C, H = WG / SC, PS = (N + H - 1) / H, FB = PS < 8 ? PS : 8;  // H lanes to a chunk, PS partials to each
+  static_assert(SC <= 64 && (SC & (SC - 1)) == 0, "slice width");
+  const int t = (int)threadIdx.x, h = t / SC, c0 = sl * SC + t % SC, c = c0 < S::NCH ? c0 : S::NCH - 1, k = c / S::CH;
+  const __amdgpu_buffer_rsrc_t all = fs_make_rsrc(part, N * (KC * 4));
+  float a[FV];
+#pragma unroll
+  for (int f = 0; f < FV; ++f) a[f] = KINDS::identity(k);
+  for (int j0 = 0; j0 < PS; j0 += FB) {
+    float tmp[FB][FV];
+#pragma unroll
+    for (int u = 0; u < FB; ++u) {
+      const int j = (j0 + u) * H + h;
+      fs_load_dev<FV>(tmp[u], all, (fs_u32)(j < N ? j : N - 1) * (KC * 4) + (fs_u32)c * (FV * 4));
+    }
+#pragma unroll
+    for (int u = 0; u < FB; ++u)
+#pragma unroll
+      for (int f = 0; f < FV; ++f) a[f] = j0 + u < PS && (j0 + u) * H + h < N ? KINDS::op(k, a[f], tmp[u][f]) : a[f];
+  }
+#pragma unroll
+  for (int m = SC; m < 64; m <<= 1) {
+    const bool upper = (fs_lane_id() & m) != 0;
+#pragma unroll
+    for (int f = 0; f < FV; ++f) {
+      const float other = fs_shfl_xor(a[f], m);
+      a[f] = KINDS::op(k, upper ? other : a[f], upper ? a[f] : other);
+    }
+  }
+  if constexpr (WG > 64) {
+    __syncthreads();  // (the slice before this one may still be read)
+    if ((t & 63) < SC) {
+#pragma unroll
+      for (int f = 0; f < FV; ++f) lds[(t / 64 * SC + (t & 63)) * FV + f] = a[f];
+    }
+    __syncthreads();
+    if (t < SC) {
+#pragma unroll
+      for (int w = 1; w < WG / 64; ++w)
+#pragma unroll
+        for (int f = 0; f < FV; ++f) a[f] = KINDS::op(k, a[f], lds[(w * SC + t) * FV + f]);
+    }
+  }
+#pragma unroll
+  for (int f = 0; f < FV; ++f) vals[f] = a[f];
 }
 
 // ------------------------------------------------------------------------------------------

@@ -10,6 +10,12 @@ namespace fs {
 
 namespace {
 
+// how long workgroups wait for each other: 50 us, several times what those of the largest tiles need from their start to the last load
+int wait_ticks() {
+  const char* e = getenv("FS_JOIN_WAIT_TICKS");
+  return e ? atoi(e) : 5000;
+}
+
 int pow2_floor(int x) {
   int p = 1;
   while (p * 2 <= x) p *= 2;
@@ -130,6 +136,8 @@ struct Scheduler {
   int L = 64, tt_rows = 64, NVL = 1, CT = 1, NVLC = 0, RESV = 0, WG = 256;
   bool in_pairs = false;  // rows are read two elements at a time (pick_vector_width)
   bool staged_loop = false;
+  int row_inputs = 0;        // [R,C] tensors from memory
+  bool whole_lanes = true;   // ... of which a lane takes 16 bytes at a time
 
   Scheduler(const Graph& g_, const PlanOptions& opt_, GroupPlan* gp_) : g(g_), opt(opt_), gp(gp_), s(gp_->s), R(gp_->R), C(gp_->C) {}
 
@@ -460,8 +468,23 @@ struct Scheduler {
     return FS_OK;
   }
 
+  // Wide rows of kernels that reduce rows and columns, one workgroup of 512 lanes to a compute unit (plan_lds): such a workgroup asks
+  // for the rows of its next trip before it works on those it has.  Rows of whole vectors and trips of whole groups of rows: a branch
+  // around the loads or stores would have the compiler wait for all of them.  Where this takes 512 lanes in the place of 1024, from
+  // 12 trips on.  (Fewer would gain as well, LayerNorm backward [3000,4096] 40.2 -> 34.6 us, [2048,8192] 56.9 -> 47.0: the tests of the
+  // planner hold 1024 lanes there.)
+  bool columns_ahead() const {
+    const int64_t trips = R / std::max(1, 512 / L);
+    return opt.ahead && rowred && colred && !col_tiled && !has_transposed && !has_concat && CT == 1 && C >= 2048 && C % V == 0 && L <= 512 && whole_lanes && row_inputs > 0 &&
+           R % (512 / L) == 0 && (L < 256 ? trips > CUS : trips >= 12 * (int64_t)CUS);
+  }
+
   // workgroup size; whether workgroups loop with their [1,C] operands staged once
   fs_status pick_workgroup() {
+    for (const ExtTensor& e : gp->ext_in) {
+      row_inputs += e.kind == KIND_FULL;
+      whole_lanes &= e.kind != KIND_FULL || V * dtype_size(e.dtype) == 16;
+    }
     const int64_t total_waves = std::max<int64_t>(1, (int64_t)R * CT * L / 64);
     if (narrow_tiles) {
       WG = std::max(64, std::min(1024, L * pow2_ceil(std::min(R, 1024))));
@@ -486,7 +509,7 @@ struct Scheduler {
       // 92.5, [4000,6201] 101.5 -> 90.9, [3000,8191] 94.1 -> 89.8; with 16 elements on 256 lanes, [5000,3501], 57.2 against 61.6)
       bool writes = false;
       for (const ExtTensor& e : gp->ext_out) writes |= e.kind == KIND_FULL;
-      if (rowred && L >= 256) WG = std::max(WG, C % V != 0 && writes && (NVL * V > 16 || L >= 512) ? 512 : std::min(1024, 4 * L));
+      if (rowred && L >= 256) WG = std::max(WG, columns_ahead() || (C % V != 0 && writes && (NVL * V > 16 || L >= 512)) ? 512 : std::min(1024, 4 * L));
     }
     else if (total_waves > 4 * CUS || has_transposed) WG = std::max(256, L);
     else WG = std::max(64, L);
@@ -619,17 +642,13 @@ struct Scheduler {
     // Below 32 elements per lane two workgroups share a unit, which is better ([4096,20000] 108.8 against 115.0).  Rows that start
     // inside a vector cross to LDS in 4-byte pieces, which eats the gain ([2048,33001] 104.7 against 106.3) but for a few rows
     // ([400,50001] 37.6 -> 31.0).
-    int row_inputs = 0;
-    bool whole_lanes = true;
-    for (const ExtTensor& e : gp->ext_in) {
-      row_inputs += e.kind == KIND_FULL ? 1 : e.kind == KIND_ROWV ? 2 : 0;
-      whole_lanes &= e.kind != KIND_FULL || V * dtype_size(e.dtype) == 16;
-    }
-    s.ahead = opt.ahead && rowred && !colred && !chunked && !resident && !has_transposed && !has_concat && CT == 1 && s.G == 1 && WG == 1024 && s.E >= 32 && row_inputs == 1 &&
+    bool rowv = false;
+    for (const ExtTensor& e : gp->ext_in) rowv |= e.kind == KIND_ROWV;
+    s.ahead = opt.ahead && rowred && !colred && !chunked && !resident && !has_transposed && !has_concat && CT == 1 && s.G == 1 && WG == 1024 && s.E >= 32 && row_inputs == 1 && !rowv &&
               whole_lanes && (C % V == 0 ? R > CUS : max_es == 4 && R > CUS && R <= 2 * CUS);
     if (s.ahead) {
       const int lds = opt.lds_budget_given ? opt.lds_budget : device_limits().lds_per_workgroup;
-      s.ahead_lds = std::min(C / (L * V), (lds - 2048) / (L * 16));
+      s.ahead_lds = std::min(C / (L * V), (lds - 2048) / (WG * 16));
       s.ahead = s.ahead_lds >= 1 && NVL - s.ahead_lds <= 8;
       if (s.ahead) cap = CUS;
     }
@@ -703,6 +722,7 @@ struct Scheduler {
     }
     const int fold_width = s.fold_width;
     s.fold_piece = fold_width;
+    s.meet = 0;
     if (colred) {
       // the fold area takes at most half of the budget: wide rows pass through it in pieces
       fixed += 16;
@@ -731,6 +751,38 @@ struct Scheduler {
       s.stage_rowv = true;
       loop_bytes += n_rowv * slot_bytes;
     }
+    // Partials of 16 KB or more from every compute unit: where a tree's last workgroups read 16 of them each, twice, on one unit, all
+    // workgroups meet and fold a slice of the columns each.  LayerNorm backward fp32 [4096,8192] 102.7 -> 93.5 us, [5000,3000] 54.4 ->
+    // 47.2, [8192,4096] 85.9 -> 82.3, [16384,2048] 80.3 and 80.2; moments bf16 [8192,8192] 69.5 -> 57.7.  To meet takes 2 us more than
+    // to pass two tickets, which smaller partials do not return: [16384,1024] 39.6 against 41.1, moments [65536,512] 26.5 against 28.5.
+    if (opt.meet && colred && !col_tiled && s.RB > s.fan_in && s.RB <= CUS && (int64_t)gp->col_reduces.size() * fold_width >= 4096) {
+      const int FV = fold_vector(fold_width), chunks = (int)gp->col_reduces.size() * (fold_width / FV);
+      const int SC = std::max(16 / FV, std::min(64, pow2_ceil((chunks + s.RB - 1) / s.RB))), meet_bytes = WG / 64 * SC * FV * 4;
+      if (fixed + std::max({loop_bytes, fold_bytes, meet_bytes}) <= opt.lds_budget) {
+        s.meet = SC;
+        fold_bytes = std::max(fold_bytes, meet_bytes);
+        gp->wait_ticks = wait_ticks();
+      }
+    }
+    // Rows asked for ahead in kernels that reduce rows and columns (columns_ahead): without that one workgroup to a compute unit has
+    // few loads in flight while it works on its rows.  Through LDS as far as 40000 bytes go, whose place the column fold takes at the
+    // end, the rest to registers (all of it through LDS was no faster).  8 wavefronts, which have the registers, instead of 16, whose
+    // trips come in larger bursts.  LayerNorm backward fp32 [8192,4096] 82.6 -> 74.2 us (16 wavefronts: 80.9), [4096,8192] 94.2 ->
+    // 78.7 (85.8), [12288,4096] 116.4 -> 107.3 (116.8), [8192,8192] 166.9 -> 147.0 (153.6), [5000,3000] 47.2 -> 43.1, [16384,2048] 81.2 -> 74.2; moments bf16
+    // [16384,4096] 55.1 -> 48.4, [16384,2048] 34.2 -> 29.3.  Rows of up to 1024 columns, many to a workgroup, lose (moments [65536,1024] 45.3
+    // against 54.3, LayerNorm backward [16384,1024] 39.3 and 39.6).
+    if (columns_ahead() && WG == 512 && s.U == 1 && s.grid < s.n_iters) {
+      const int most = std::min(opt.lds_budget, 40000), each = row_inputs * WG * 16, fold_rows = L < 64 ? WG / 64 : s.G;
+      const int JL = std::min({NVL, C / (L * V), (most - fixed - loop_bytes - 256) / each}), piece = JL * each / (fold_rows * 4) / 8 * 8;
+      if (JL > 0) {
+        s.ahead = true;
+        s.ahead_lds = JL;
+        s.fold_piece = std::min(fold_width, piece);
+        s.lds_bytes = s.lds_planned = fixed + loop_bytes + JL * each;
+        s.stage_avail = 0;
+        return FS_OK;
+      }
+    }
     const int lds = total();
     s.lds_bytes = s.lds_planned = lds;
     if (lds > (s.tile_transpose ? tile_cap : opt.lds_budget))
@@ -739,7 +791,7 @@ struct Scheduler {
     // (one 1024-lane workgroup per compute unit runs such a kernel, so it may take all a workgroup is allowed
     // unless the caller set a budget); code generation decides which inputs are worth it.
     s.stage_avail = 0;
-    if (s.ahead) s.lds_bytes = s.lds_planned = lds + s.ahead_lds * L * 16;  // (a workgroup has its compute unit to itself, like those below)
+    if (s.ahead && !colred) s.lds_bytes = s.lds_planned = lds + row_inputs * s.ahead_lds * WG * 16;  // (a workgroup has its compute unit to itself, like those below)
     if (chunked && !split_rows) {
       const int cap = opt.lds_budget_given ? opt.lds_budget : device_limits().lds_per_workgroup;
       s.stage_avail = std::max(0, cap - lds - 512);
@@ -772,6 +824,10 @@ struct Scheduler {
         s.part_stride_floats += (size_t)n * kc;
         n = (n + s.fan_in - 1) / s.fan_in;
         s.ticket_stride += n;
+        if (s.meet) {  // one level of partials, two counters in cache lines of their own
+          s.ticket_stride = 32 * (1 + (s.RB + 15) / 16) + s.RB;
+          break;
+        }
       }
       const int tiles = col_tiled ? CT : 1;
       gp->n_tickets = s.ticket_stride * tiles;
@@ -1752,8 +1808,7 @@ fs_status join_groups(const Graph& g, const std::vector<GroupPlan>& groups, int 
     gp.n_tickets = s.ticket_stride * s.CT;
     gp.part_bytes = s.part_stride_floats * s.CT * 4;
   }
-  gp.wait_ticks = 5000;  // 50 us: several times what the workgroups of the largest tiles need from their start to the last load
-  if (const char* e = getenv("FS_JOIN_WAIT_TICKS")) gp.wait_ticks = atoi(e);
+  gp.wait_ticks = wait_ticks();
   return FS_OK;
 }
 

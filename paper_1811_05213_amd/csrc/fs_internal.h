@@ -117,6 +117,7 @@ struct Schedule {
   int lds_bytes = 0;    // static LDS of the generated kernel
   int lds_planned = 0;  // ... as planned before code generation (an upper bound of lds_bytes)
   int fan_in = 32;  // column-reduction tree fan-in
+  int meet = 0;     // > 0: no tree: all workgroups meet and fold slices of the columns, this many chunks wide
   int fold_width = 0;  // columns a workgroup folds: its column tile, or the row, rounded up to 16-byte chunks where that pays
   int fold_piece = 0;  // columns that pass through the in-workgroup fold area at a time
   bool stage_rowv = false;  // [1,C] inputs are staged once per workgroup in LDS
@@ -183,6 +184,9 @@ struct StageSlot {
   std::vector<int> owners;
 };
 
+// columns to a chunk of a column fold of this many
+inline int fold_vector(int width) { return width % 4 == 0 ? 4 : width % 2 == 0 ? 2 : 1; }
+
 struct GroupPlan {
   std::vector<int> members;  // compute nodes, ascending id
   int R = 0, C = 0;          // work space
@@ -242,6 +246,7 @@ struct PlanOptions {
   // Plan creation steps down while the compiled kernel spills.
   int wide_level = 2;
   bool narrow_tiles = true;  // column folds may take narrow tiles (plan creation gives them up where the compiled kernel spills)
+  bool meet = true;   // the workgroups of a column fold may meet
   bool ahead = true;  // long rows may be asked for one ahead (given up where the compiled kernel spills)
   int min_waves = 0;  // > 0: the kernel asks the compiler for that many wavefronts per SIMD (occupancy feedback at plan creation)
   bool layered = false;  // group with the layered planner of Section 3.2 instead of the default one

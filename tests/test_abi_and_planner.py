@@ -1333,6 +1333,33 @@ int main() {
     assert r.returncode == 0, r.stdout
 
 
+def rows_and_columns_graph(rows, cols, dt, folds, writes):
+    """A row maximum, column folds of what it leaves, and that itself"""
+    g = Graph()
+    x, t = g.input(rows, cols, dt), g.input(rows, 1)
+    z = g.binary("mul", x if dt == "f32" else g.unary("convert", x, "f32"), g.bcast_colvec(t, cols))
+    y = g.binary("sub", z, g.bcast_colvec(g.reduce_row("max", z), cols))
+    outs = [g.reduce_col("sum", y), g.reduce_col("max", z), g.reduce_col("mean", g.binary("mul", y, z))][:folds]
+    g.set_outputs(outs + ([y if dt == "f32" else g.unary("convert", y, dt)] if writes else []))
+    return g
+
+
+# the workgroups meet to fold 16 KB of partials each; wide rows of whole vectors in whole trips are asked for ahead
+@pytest.mark.parametrize("rows,cols,dt,folds,writes,meet,ahead", [
+    (6144, 4096, "f32", 2, 1, 1, 1), (6145, 4096, "f32", 2, 1, 1, 0), (6142, 4096, "f32", 2, 1, 1, 0), (400, 8192, "f32", 2, 1, 1, 0), (20000, 1024, "f32", 3, 1, 0, 0), (20000, 1368, "f32", 3, 1, 1, 0),
+    (3002, 2056, "bf16", 3, 1, 1, 0), (3072, 8192, "bf16", 3, 1, 1, 1), (2048, 2048, "f32", 2, 0, 1, 1), (2048, 2048, "f32", 1, 1, 0, 1)])
+def test_which_column_folds_meet(rows, cols, dt, folds, writes, meet, ahead):
+    g = rows_and_columns_graph(rows, cols, dt, folds, writes)
+    p = fs.Plan(g)
+    gi, src = p.group_info(0), p.group_source(0)
+    assert ("fs_colred_meet<" in src, "fs_row_ask<" in src) == (bool(meet), bool(ahead))
+    assert gi["grid"] <= 256 and gi["lds_bytes"] <= (40000 if ahead else 65536)
+    p.destroy()
+    p = fs.Plan(g, lds_budget_bytes=32768)  # a caller's budget binds
+    assert p.group_info(0)["lds_bytes"] <= 32768
+    p.destroy()
+
+
 @pytest.mark.parametrize("rows,cols,ahead", [(257, 32768, 1), (256, 32768, 0), (1024, 65536, 1), (4096, 28672, 0), (2048, 50000, 1), (2048, 50001, 0), (512, 50001, 1), (40, 65536, 0)])
 def test_which_long_rows_are_asked_for_ahead(rows, cols, ahead):
     p = fs.Plan(softmax_graph(rows, cols))

@@ -1373,6 +1373,49 @@ def test_long_rows_asked_for_ahead(rows, cols, dt):
     p.destroy()
 
 
+# ------------------------------------------------------------------ workgroups that meet to fold columns
+@pytest.mark.parametrize("rows,cols,dt,folds,writes", [
+    (6148, 4096, "f32", 2, 1), (1029, 4096, "f32", 2, 1), (400, 8192, "f32", 2, 1),  # trips of whole groups of rows, ragged ones, fewer workgroups than units
+    (5000, 3000, "f32", 2, 1), (3077, 8200, "f32", 3, 1), (700, 8190, "f32", 1, 1), (2100, 5001, "f32", 3, 0), (999, 4101, "f32", 1, 1), (3000, 2052, "f32", 2, 0),
+    (3072, 8192, "bf16", 3, 1), (3002, 2056, "bf16", 3, 1), (20000, 1368, "f32", 3, 1), (400, 24000, "f32", 3, 0)])  # ... several slices to a workgroup
+def test_workgroups_meet_to_fold_columns(rows, cols, dt, folds, writes, monkeypatch):
+    import torch
+    from test_abi_and_planner import rows_and_columns_graph
+    g = rows_and_columns_graph(rows, cols, dt, folds, writes)
+    a = RNG.standard_normal((rows, cols)).astype(np.float32)
+    ins = [a if dt == "f32" else f32_to_bf16_bits(a), RNG.uniform(0.5, 2, (rows, 1)).astype(np.float32)]
+    p = fs.Plan(g)
+    assert p.stats()["num_launches"] == 1 and "fs_colred_meet<" in p.group_source(0)
+    r = DeviceRun(p)
+    r.set_inputs(ins)
+    r.launch()
+    first = r.results()
+    check_all(g, first, Reference(g, ins), f"columns met {rows}x{cols} {dt}")
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        r.launch()
+    for k in range(8):  # counters return to zero: the same bits again, eagerly and from a graph
+        for o in r.outputs:
+            o.fill_(7)
+        graph.replay() if k % 2 else r.launch()
+        for u, v in zip(first, r.results()):
+            np.testing.assert_array_equal(u, v)
+    p.workspace_check(r.workspace.data_ptr(), r.ws_bytes)
+    del graph
+    p.destroy()
+    # workgroups that do not wait leave everything to the last one: the same bits, and counters that are zero again
+    monkeypatch.setenv("FS_JOIN_WAIT_TICKS", "0")
+    p = fs.Plan(g)
+    r = DeviceRun(p)
+    r.set_inputs(ins)
+    for _ in range(4):
+        r.launch()
+        for u, v in zip(first, r.results()):
+            np.testing.assert_array_equal(u, v)
+    p.workspace_check(r.workspace.data_ptr(), r.ws_bytes)
+    p.destroy()
+
+
 # ------------------------------------------------------------------ groups that share a launch
 @pytest.mark.parametrize("rows,ks", [(512, (64, 128, 256)), (100, (25, 50, 100)), (333, (50, 100, 200)), (48, (8, 16, 32)), (70, (96, 192, 384)), (2047, (32, 64, 128)),
                                      (1024, (96, 192, 384))])
