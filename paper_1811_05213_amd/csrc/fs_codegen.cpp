@@ -297,8 +297,10 @@ struct Emitter {
     if (e.kind == KIND_FULL)
       os << indent << vec_fn("fs_store_row") << "<" << e.dtype << ", " << tmpl_row() << ", " << (e.streaming ? "true" : "false") << ">(" << nm
          << ", a.p[" << e.arg << "], row0, lir, vbase, rok" << vec_arg() << ");\n";
-    else if (e.kind == KIND_COLV)
+    else if (e.kind == KIND_COLV) {
+      if (gp.leaves.count(e.node)) (strip ? pre : os) << indent << "x." << gp.leaves.at(e.node) << " = " << nm << ";\n";
       (strip ? pre : os) << indent << "if (rok && lir == 0 && vbase == 0) fs_store1<" << e.dtype << ">(a.p[" << e.arg << "], row, " << nm << ");\n";
+    }
   }
 
   // the [1,C] tensor from memory behind operand `o`, or -1
@@ -1069,17 +1071,32 @@ struct Emitter {
         os << " case " << k << ": return fs_red_identity<" << g.nodes[folded_across[k]].attr_i << ">();";
       os << " } return 0.0f; }\n};\n";
     }
+    const int over = (int)((int64_t)s.NV * s.V - C);
+    auto constants = [&]() {
+      os << "  constexpr int V = " << s.V << ", NVL = " << s.NVL << ", L = " << s.L << ", NV = " << s.NV << ", E = NVL * V, WG = " << s.WG
+         << ", G = WG / L, C = " << C << ", CT = " << s.CT << ";\n";
+      // (0: all vectors lie inside the row; else 1 + what the last vector overlaps its neighbour by)
+      os << "  constexpr int RAGGED = " << (s.ragged ? 1 + over : 0) << ";\n";
+      os << "  const int tid = (int)threadIdx.x, lir = tid & (L - 1), rg = tid / L;\n";
+      os << "  const long R = a.R;\n";
+      os << "  (void)lir; (void)rg; (void)R; (void)C; (void)G; (void)CT;\n";
+    };
+    if (!gp.asked.empty()) {
+      os << "template <class X> FS_DEV void " << kname << "_ask(const " << kname << "_args& a, const int fs_block, X& x) {\n";
+      constants();
+      os << "  const long row = (long)fs_block * G + rg, row_ld = row < R ? row : R - 1;\n  (void)row_ld;\n";
+      for (const ExtTensor& e : gp.ext_in) {
+        if (!gp.asked.count(e.node)) continue;
+        const std::string to = "x." + gp.comes.at(e.node), p = "a.p[" + std::to_string(e.arg) + "]";
+        if (e.kind == KIND_COLV) os << "  " << to << " = fs_load1<" << e.dtype << ">(" << p << ", row_ld);\n";
+        else os << "  fs_load_row<" << e.dtype << ", " << tmpl_row() << ">(" << to << ", " << p << ", " << (e.kind == KIND_FULL ? "row_ld * C" : "0") << ", lir, 0);\n";
+      }
+      os << "}\n";
+    }
     os << "extern \"C\" __global__ void __launch_bounds__(" << s.WG << ") ";
     if (s.min_waves > 0) os << "__attribute__((amdgpu_waves_per_eu(" << s.min_waves << "))) ";
     os << kname << "(const " << kname << "_args a) {\n";
-    os << "  constexpr int V = " << s.V << ", NVL = " << s.NVL << ", L = " << s.L << ", NV = " << s.NV << ", E = NVL * V, WG = " << s.WG
-       << ", G = WG / L, C = " << C << ", CT = " << s.CT << ";\n";
-    // (0: all vectors lie inside the row; else 1 + what the last vector overlaps its neighbour by)
-    const int over = (int)((int64_t)s.NV * s.V - C);
-    os << "  constexpr int RAGGED = " << (s.ragged ? 1 + over : 0) << ";\n";
-    os << "  const int tid = (int)threadIdx.x, lir = tid & (L - 1), rg = tid / L;\n";
-    os << "  const long R = a.R;\n";
-    os << "  (void)lir; (void)rg; (void)R; (void)C; (void)G; (void)CT;\n";
+    constants();
     if (xwave) os << "  __shared__ float lds_rr[2 * G * " << WPR << " * " << KB << "];\n  int parity = 0;\n";
     if (s.chunked) {
       os << "  constexpr int NVLC = " << s.NVLC << ", RESV = " << s.RESV << ";\n  constexpr int RAGC = " << (s.ragged_chunks ? 1 + over : 0)
@@ -1284,7 +1301,11 @@ struct Emitter {
         os << "    const bool rok" << x << " = row" << x << " < R;\n    const long row_ld" << x << " = rok" << x << " ? row" << x
            << " : R - 1;\n    const long row0" << x << " = row_ld" << x << " * C;\n    (void)row0" << x << "; (void)vbase" << x << ";\n";
       for (const ExtTensor& e : gp.ext_in) {
-        if (e.kind == KIND_FULL && s.ahead) {
+        if (gp.comes.count(e.node) && e.kind == KIND_FULL) {
+          os << "    float " << name(e.node, KIND_FULL) << "[E];\n    " << eloop() << name(e.node, KIND_FULL) << "[e] = x." << gp.comes.at(e.node) << "[e];\n";
+        } else if (gp.comes.count(e.node) && e.kind == KIND_COLV) {
+          os << "    const float " << name(e.node, KIND_COLV) << " = x." << gp.comes.at(e.node) << ";\n";
+        } else if (e.kind == KIND_FULL && s.ahead) {
           os << "    float " << name(e.node, KIND_FULL) << "[E];\n    fs_row_take<" << e.dtype << ", V, NVL, WG, JL>(" << name(e.node, KIND_FULL) << ", lds_ahead + " << n_asked++
              << " * (JL * WG * 16), tid);\n";
           if (s.ahead_lds < s.NVL)
@@ -1331,7 +1352,9 @@ struct Emitter {
         for (const ExtTensor& e : gp.ext_in) {
           if (e.kind != KIND_ROWV || e.node != src) continue;
           declare(nm, "    ");
-          if (s.stage_rowv)
+          if (gp.comes.count(src) && !strip)
+            os << "    " << eloop() << nm << "[e] = x." << gp.comes.at(src) << "[e];\n";
+          else if (s.stage_rowv)
             os << "    " << vec_fn("fs_read_staged") << "<" << tmpl_row() << ">(" << nm << ", lds_rowv + " << slot_of_ext.at(src) << " * SLOT, lir"
                << vec_arg() << ");\n";
           else

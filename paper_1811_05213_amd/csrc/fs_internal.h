@@ -188,6 +188,11 @@ struct StageSlot {
 inline int fold_vector(int width) { return width % 4 == 0 ? 4 : width % 2 == 0 ? 2 : 1; }
 
 struct GroupPlan {
+  // Groups of a Composite's chain: per-row results that leave in x.<name>, besides memory, for the groups after; what comes in
+  // x.<name> instead of from memory: those, and tensors that were asked for before the first group's work.
+  std::map<int, std::string> leaves, comes;
+  std::set<int> asked;
+  bool linked = false;  // nothing else of theirs is read: no barrier
   std::vector<int> members;  // compute nodes, ascending id
   int R = 0, C = 0;          // work space
   std::map<int, Kind> kind;  // members and external tensors -> kind

@@ -1333,6 +1333,18 @@ int main() {
     assert r.returncode == 0, r.stdout
 
 
+@pytest.mark.parametrize("rows,ks", [(512, (64, 128, 256)), (333, (50, 100, 200)), (48, (8, 16, 32)), (1024, (96, 192, 384))])
+def test_chains_pass_row_results_in_registers(rows, ks):
+    # no group of the chain reads what another has stored: no barrier, and what they read of others is asked for first
+    p = fs.Plan(random_dag_graph(rows=rows, ks=ks))
+    chains = [src for _, _, src in p.joined_groups() if "_ask(" in src]
+    assert chains
+    for src in chains:
+        body = src[src.index('extern "C" __global__'):]
+        assert "__syncthreads" not in body and body.index("_ask(a.g1") < body.index("_rows(a.g0")
+    p.destroy()
+
+
 def rows_and_columns_graph(rows, cols, dt, folds, writes):
     """A row maximum, column folds of what it leaves, and that itself"""
     g = Graph()
