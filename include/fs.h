@@ -260,8 +260,8 @@ fs_status fs_plan_workspace_bytes(const fs_plan* plan, size_t* bytes);
 fs_status fs_plan_load(fs_plan* plan);
 
 /*
- * fs_plan_run: execute the fusion plan - ONE kernel launch per fused computation, or per run of
- * them that is joined (fs_plan_joined_groups) (Section 1: the
+ * fs_plan_run: execute the fusion plan - ONE kernel launch per fused computation, or per set of
+ * them that runs as one kernel (fs_plan_joined_groups) (Section 1: the
  * ops of a fused computation are composed inside a single kernel, by thread composition in
  * registers and by block composition through on-chip memory; Section 2.2: the stitched kernel) -
  * enqueued in dependence order on `hip_stream` (a hipStream_t; NULL = the null stream) of the
@@ -318,7 +318,7 @@ fs_status fs_plan_workspace_check(fs_plan* plan, const void* workspace, size_t w
 
 /*
  * fs_plan_stats: plan-level figures for the metric.  num_groups = fused computations;
- * num_launches = kernel launches per run, one per group (groups that run joined, see
+ * num_launches = kernel launches per run, one per group (groups that run as one kernel, see
  * fs_plan_joined_groups, are counted as the launches they replace).  Their
  * ratio between a stitched and an unfused plan of the same DAG is the paper's fusion ratio
  * (Section 6.3: kernels after fusion / kernels of the baseline).  min_hbm_bytes = every plan
@@ -363,11 +363,13 @@ fs_status fs_plan_group_source(const fs_plan* plan, int32_t group, const char** 
 fs_status fs_plan_group_kernel_name(const fs_plan* plan, int32_t group, const char** out_name);
 
 /*
- * fs_plan_joined_groups: the index-th run of consecutive groups that fs_plan_run launches as ONE kernel: column reductions
- * and the groups that need their results, where the rows of a column tile fit the registers of the device between them
- * (Section 5.2's block composition, across the workgroups of a tile).  *first_group and *num_groups name the groups, *source
- * is the kernel's source; any of them may be NULL.  FS_ERR_INVALID_ARG when the plan has no such run.  The other calls about
- * groups, fs_plan_stats and fs_plan_tune describe and measure the groups themselves.
+ * fs_plan_joined_groups: the index-th set of groups that fs_plan_run launches as ONE kernel.  First the runs of consecutive groups
+ * that are joined over their column reductions: these and the groups that need their results, where the rows of a column tile fit
+ * the registers of the device between them (Section 5.2's block composition, across the workgroups of a tile).  Then small groups that
+ * share a launch, whose kernels are functions of one: chains over the same rows, and independent groups side by side (its first line
+ * names them; they need not be consecutive).  *first_group is the first of them and *num_groups their number, *source is the
+ * kernel's source; any of them may be NULL.  FS_ERR_INVALID_ARG when there is no such set.  The other calls about groups, fs_plan_stats
+ * and fs_plan_tune describe and measure the groups themselves.
  */
 fs_status fs_plan_joined_groups(const fs_plan* plan, int32_t index, int32_t* first_group, int32_t* num_groups, const char** source);
 

@@ -824,7 +824,7 @@ struct Scheduler {
         s.part_stride_floats += (size_t)n * kc;
         n = (n + s.fan_in - 1) / s.fan_in;
         s.ticket_stride += n;
-        if (s.meet) {  // one level of partials, two counters in cache lines of their own
+        if (s.meet) {  // one level of partials; counters in cache lines of their own, and the doors
           s.ticket_stride = 32 * (1 + (s.RB + 15) / 16) + s.RB;
           break;
         }
@@ -1065,10 +1065,9 @@ fs_status analyse_group(const Graph& g, const std::vector<int>& members, const s
   // loads there.  LayerNorm+GeLU bf16 [30001,1021]: 24.5 -> 22.1 us right after the kernel that wrote the input (28.3 -> 28.7 us
   // from cold memory); masked softmax bf16 [32768,577] 22.5 -> 20.4 us (22.5 -> 22.8 us).  Not for groups that only stream
   // (no difference) or fold columns ([60001,515]: 33.3 -> 35.5 us).
-  // So do the narrow tiles of small column folds.
   // Nor where a row has one such line among 32 or more and the tensors are far beyond the caches (masked softmax f32 [4096,8191]
   // 73.0 -> 68.2 us, softmax [9000,7001] 88.7 -> 83.6, residual+LayerNorm [3000,10001] 92.0 -> 90.4; but at 100 MB LayerNorm+GeLU
-  // [4000,6001] 25.8 -> 27.4).
+  // [4000,6001] 25.8 -> 27.4).  The narrow tiles of small column folds read with ordinary loads too.
   const bool long_rows = (int64_t)C * min_es >= 4096 && gp.min_hbm_bytes >= (128ull << 20);
   if (st == FS_OK && ((gp.s.shares_lines && !gp.row_reduces.empty() && gp.col_reduces.empty() && !long_rows) || (gp.s.narrow_tiles && gp.s.L < 32)))
     for (ExtTensor& e : gp.ext_in) e.streaming = false;
