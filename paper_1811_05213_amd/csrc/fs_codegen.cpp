@@ -1263,7 +1263,7 @@ struct Emitter {
     } else if (ctile) {
       os << "  for (int it = rb; it < a.n_iters; it += RB) {\n";
     } else if (U == 1) {
-      os << "  for (int it = (int)blockIdx.x; it < a.n_iters; it += (int)gridDim.x) {\n";
+      os << "  for (int it = " << (s.xcd_rows ? "fs_xcd_place<" + std::to_string(s.xcd_rows) + ">((int)blockIdx.x, (int)gridDim.x)" : "(int)blockIdx.x") << "; it < a.n_iters; it += (int)gridDim.x) {\n";
     } else {
       os << "  for (int it0 = (int)blockIdx.x * " << U << "; it0 < a.n_iters; it0 += (int)gridDim.x * " << U << ") {\n";
     }

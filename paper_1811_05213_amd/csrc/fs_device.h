@@ -355,6 +355,13 @@ FS_DEV void fs_wait_lds() { asm volatile("s_waitcnt lgkmcnt(0)" : : : "memory");
 // fs_lds_barrier where a row is on its way to LDS: a fence would wait for it
 FS_DEV void fs_lds_barrier_ahead() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" : : : "memory"); }
 
+// Workgroups go to the 8 XCDs in turn.  Workgroup b of n takes this place among the rows, so that M neighbours run on one XCD: the lines that
+// they share, at the ends of their rows or in a transposed tensor, meet in its L2.
+template <int M> FS_DEV int fs_xcd_place(int b, int n) {
+  const int r = b % (8 * M), first = b - r;
+  return first + 8 * M <= n ? first + r % 8 * M + r / 8 : b;
+}
+
 // Transposing store of the lane's slice of row `row` of a [R,C] value into a [C,R] tensor.
 template <int DT, int V, int NVL, int L, int NV, int RAGGED>
 FS_DEV void fs_store_row_transposed(const float (&src)[NVL * V], void* base, long R, long row, int lir, int vbase, bool rok) {

@@ -690,6 +690,18 @@ struct Scheduler {
     // two fold levels at most: the smallest fan-in whose square covers the grid (one level for narrow tiles of up to 16 workgroups)
     // (64 workgroups per fold: 16 measured 9 % faster than 8 on column sums of [16384,4096], 44.6 against 48.8 us)
     s.fan_in = s.RB <= 16 && narrow_tiles ? 16 : s.RB <= 32 ? 8 : s.RB <= 256 ? 16 : 32;
+    // One-trip grids whose workgroups share cache lines with their neighbours: in a transposed tensor, into which a workgroup writes a few rows
+    // of a line (8 workgroups of 4 fp32 rows fill one), and at the ends of rows that are no whole lines.  Placed in turn on the XCDs, each of two
+    // L2s moves such a line; now 8 or 16 neighbours run on one XCD.  Random DAGs of 200 ops [512,256] 21.4 -> 20.4 us, [700,384] 36.0 -> 31.4, [1500,256]
+    // 31.2 -> 27.6 (4: 28.0, 16: 28.1); masked softmax bf16 [16384,577] 10.5 -> 10.2, [32768,129] 7.6 -> 6.9, softmax fp32 [2048,50001] 164.8 -> 160.2 (4 and 8:
+    // 162.1), elementwise of 6 tensors [16384,1001] 67.8 -> 66.2, LayerNorm+GeLU bf16 [8000,1021] 7.5 -> 7.1.  Rows of whole lines have nothing to gain
+    // ([16384,1024] 64.3 and 64.3; an eighth of all rows to an XCD, which meets the same channels, 67.9).
+    if (!has_concat && !tiled_transpose && !colred && !chunked && CT == 1 && s.U == 1 && s.grid == s.n_iters) {
+      bool shared = false;
+      for (const auto* list : {&gp->ext_in, &gp->ext_out})
+        for (const ExtTensor& e : *list) shared |= e.kind == KIND_FULL && !e.transposed && (int64_t)s.G * C * dtype_size(e.dtype) % 128 != 0;
+      s.xcd_rows = has_transposed ? 8 : shared ? 16 : 0;
+    }
     return FS_OK;
   }
 
@@ -1975,10 +1987,13 @@ bool generate_composite(const Graph& g, Composite* c) {
   for (size_t t = 0; t < c->tracks.size(); ++t) {
     body += std::string("  ") + (t + 1 < c->tracks.size() ? "if (block < " + std::to_string(c->blocks[t]) + ") {\n" : "{\n");
     const bool passes = !fields[t].empty();
+    int xcd_rows = 0;
+    for (const GroupPlan& p : c->plans[t]) xcd_rows = xcd_rows == 0 || p.s.xcd_rows == 0 ? std::max(xcd_rows, p.s.xcd_rows) : std::min(xcd_rows, p.s.xcd_rows);
+    const std::string place = xcd_rows ? "fs_xcd_place<" + std::to_string(xcd_rows) + ">(block, " + std::to_string(c->blocks[t]) + ")" : "block";
     if (passes) {
       body += "    struct {" + fields[t] + " } x;\n";
       for (size_t k = 1; k < c->plans[t].size(); ++k)
-        if (!c->plans[t][k].asked.empty()) body += "    " + c->plans[t][k].kernel_name + "_ask(a.g" + std::to_string(total + (int)k) + ", block, x);\n";
+        if (!c->plans[t][k].asked.empty()) body += "    " + c->plans[t][k].kernel_name + "_ask(a.g" + std::to_string(total + (int)k) + ", " + place + ", x);\n";
     }
     for (size_t k = 0; k < c->plans[t].size(); ++k) {
       const GroupPlan& p = c->plans[t][k];
@@ -1990,6 +2005,7 @@ bool generate_composite(const Graph& g, Composite* c) {
         replace_all(&src, "struct " + n + "_args", "struct " + n + "_part_args");
         replace_all(&src, "const " + n + "_args&", "const " + n + "_part_args&");
         replace_all(&src, n + "_kinds", n + "_part_kinds");
+        if (p.s.xcd_rows) replace_all(&src, "fs_xcd_place<" + std::to_string(p.s.xcd_rows) + ">((int)blockIdx.x, (int)gridDim.x)", "fs_block");
         replace_all(&src, "blockIdx.x", "fs_block");
         replace_all(&src, "gridDim.x", "fs_blocks");
         text += src;
@@ -1997,7 +2013,7 @@ bool generate_composite(const Graph& g, Composite* c) {
       args += "  " + n + "_part_args " + field + ";\n";
       // (what a workgroup wrote before the barrier it reads after it: the vector cache of a compute unit writes through)
       if (k > 0 && !p.linked) body += "    __syncthreads();\n";
-      body += "    " + n + "_rows(a." + field + ", block, " + std::to_string(c->blocks[t]) + (passes ? ", x" : "") + ");\n";
+      body += "    " + n + "_rows(a." + field + ", " + place + ", " + std::to_string(c->blocks[t]) + (passes ? ", x" : "") + ");\n";
     }
     body += "    return;\n  }\n";
     if (t + 1 < c->tracks.size()) body += "  block -= " + std::to_string(c->blocks[t]) + ";\n";

@@ -129,6 +129,7 @@ struct Schedule {
   // ahead_lds vectors per lane and tensor to LDS, the rest to registers.
   bool ahead = false;
   int ahead_lds = 0;
+  int xcd_rows = 0;  // > 0: this many workgroups of one XCD take neighbouring rows
   bool tile_transpose = false;  // transposed roots leave through a padded LDS tile
   // Reduction-free groups with transposed roots over wide rows: 2-D tiles.  A workgroup owns G
   // consecutive rows of one column tile of NVL*L*V columns (unit = column tile fastest), so both

@@ -1345,6 +1345,38 @@ def test_chains_pass_row_results_in_registers(rows, ks):
     p.destroy()
 
 
+@pytest.mark.parametrize("rows,cols,m", [(2048, 50001, 16), (16384, 1001, 16), (16384, 1024, 0), (300, 4099, 16), (65536, 32, 0), (2048, 50000, 0)])
+def test_which_rows_are_placed_by_xcd(rows, cols, m):
+    p = fs.Plan(softmax_graph(rows, cols))
+    assert ("fs_xcd_place<%d>" % m in p.group_source(0)) == (m > 0) and ("fs_xcd_place<" in p.group_source(0)) == (m > 0)
+    p.destroy()
+
+
+def test_places_by_xcd_are_a_permutation(tmp_path):
+    import subprocess
+    header = open(os.path.join(ROOT, "paper_1811_05213_amd", "csrc", "fs_device.h")).read()
+    f = header[header.index("template <int M> FS_DEV int fs_xcd_place"):]
+    (tmp_path / "t.cpp").write_text("#include <vector>\n#define FS_DEV\n" + f[:f.index("\n}\n") + 3] + """
+template <int M> int bad(int n) {
+  std::vector<int> seen(n);
+  int wrong = 0;
+  for (int b = 0; b < n; ++b) {
+    const int p = fs_xcd_place<M>(b, n);
+    wrong += p < 0 || p >= n || seen[p]++;
+    wrong += b + 8 < n && b % (8 * M) + 8 < 8 * M && b - b % (8 * M) + 8 * M <= n && fs_xcd_place<M>(b + 8, n) != p + 1;  // the next workgroup of an XCD
+  }
+  return wrong;
+}
+int main() {
+  int wrong = 0;
+  for (int n = 1; n < 700; ++n) wrong += bad<8>(n) + bad<16>(n);
+  return wrong != 0;
+}
+""")
+    subprocess.run(["g++", "-std=c++17", "-O1", "-o", str(tmp_path / "t"), str(tmp_path / "t.cpp")], check=True)
+    assert subprocess.run([str(tmp_path / "t")]).returncode == 0
+
+
 def rows_and_columns_graph(rows, cols, dt, folds, writes):
     """A row maximum, column folds of what it leaves, and that itself"""
     g = Graph()

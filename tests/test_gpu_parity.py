@@ -1416,6 +1416,20 @@ def test_workgroups_meet_to_fold_columns(rows, cols, dt, folds, writes, monkeypa
     p.destroy()
 
 
+# ------------------------------------------------------------------ neighbouring rows on one XCD
+@pytest.mark.parametrize("rows", [127, 128, 129, 600])
+@pytest.mark.parametrize("transposed", [0, 1])
+def test_rows_placed_by_xcd(rows, transposed):
+    g = Graph()
+    x = g.input(rows, 4099)
+    y = g.binary("sub", x, g.bcast_colvec(g.reduce_row("max", x), 4099))
+    g.set_outputs([g.transpose(y) if transposed else y, g.reduce_row("sum", y)])
+    p = fs.Plan(g)
+    assert any("fs_xcd_place<" in p.group_source(k) for k in range(p.stats()["num_groups"]))
+    p.destroy()
+    both_modes(g, [RNG.standard_normal((rows, 4099)).astype(np.float32)], f"rows by XCD {rows} {transposed}")
+
+
 # ------------------------------------------------------------------ groups that share a launch
 @pytest.mark.parametrize("rows,ks", [(512, (64, 128, 256)), (100, (25, 50, 100)), (333, (50, 100, 200)), (48, (8, 16, 32)), (70, (96, 192, 384)), (2047, (32, 64, 128)),
                                      (1024, (96, 192, 384))])
