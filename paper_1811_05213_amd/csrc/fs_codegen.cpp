@@ -303,6 +303,10 @@ struct Emitter {
     }
   }
 
+  std::string workgroup_place() const {
+    return gp.s.xcd_rows ? "fs_xcd_place<" + std::to_string(gp.s.xcd_rows) + ">((int)blockIdx.x, (int)gridDim.x)" : "(int)blockIdx.x";
+  }
+
   // the [1,C] tensor from memory behind operand `o`, or -1
   int ext_rowv_of(int o) const {
     if (g.nodes[o].opcode == FS_CONST) return -1;
@@ -701,7 +705,7 @@ struct Emitter {
        << "  constexpr int V = " << s.V << ", NVL = 1, L = " << s.L << ", NV = " << s.NV << ", E = V, WG = " << s.WG << ", G = WG / L, C = " << gp.C
        << ", CT = " << s.CT << ", RB = " << s.RB << ", TR = " << s.U << ", CW = " << CW << ", FV = " << FV << ";\n"
        << "  constexpr int RAGGED = " << (s.ragged ? 1 + over : 0) << ";\n"
-       << "  const int tid = (int)threadIdx.x, lir = tid & (L - 1), rg = tid / L, tile = (int)blockIdx.x % CT, rb = (int)blockIdx.x / CT, vbase = tile * L;\n"
+       << "  const int tid = (int)threadIdx.x, lir = tid & (L - 1), rg = tid / L, place = " << workgroup_place() << ", tile = place % CT, rb = place / CT, vbase = tile * L;\n"
        << "  (void)E; (void)NVL; (void)CW;\n"
        << "  __shared__ float lds_col[(L < 64 ? WG / 64 : G) * CW], lds_res[" << gp.col_reduces.size() << " * CW]" << (s.RB > 1 ? ", lds_fold[WG]" : "") << ";\n  __shared__ fs_u32 lds_flag;\n"
        // (column of the lane's element e inside the tile; what the lane does not own reads any column)
@@ -1121,7 +1125,7 @@ struct Emitter {
     // (RB, the number of workgroups that fold together, only where something is folded: a kernel without column
     // reductions has the same text, hence the same compiled code, whatever the number of rows)
     os << "  constexpr int CW = " << (ctile ? "NVL * L * V" : std::to_string(K > 0 ? s.fold_width : C)) << ", RB = " << (K > 0 || ctile ? s.RB : 1) << ";\n";
-    if (ctile) os << "  const int tile = (int)blockIdx.x % CT, rb = (int)blockIdx.x / CT, vbase = tile * (NVL * L);\n";
+    if (ctile) os << "  const int place = " << workgroup_place() << ", tile = place % CT, rb = place / CT, vbase = tile * (NVL * L);\n";
     else os << "  const int tile = 0, rb = (int)blockIdx.x;\n";
     os << "  (void)tile; (void)rb; (void)CW; (void)RB;\n";
     if (s.ahead) {
@@ -1263,7 +1267,7 @@ struct Emitter {
     } else if (ctile) {
       os << "  for (int it = rb; it < a.n_iters; it += RB) {\n";
     } else if (U == 1) {
-      os << "  for (int it = " << (s.xcd_rows ? "fs_xcd_place<" + std::to_string(s.xcd_rows) + ">((int)blockIdx.x, (int)gridDim.x)" : "(int)blockIdx.x") << "; it < a.n_iters; it += (int)gridDim.x) {\n";
+      os << "  for (int it = " << workgroup_place() << "; it < a.n_iters; it += (int)gridDim.x) {\n";
     } else {
       os << "  for (int it0 = (int)blockIdx.x * " << U << "; it0 < a.n_iters; it0 += (int)gridDim.x * " << U << ") {\n";
     }

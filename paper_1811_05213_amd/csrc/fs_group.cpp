@@ -10,6 +10,17 @@ namespace fs {
 
 namespace {
 
+// Do column tiles, which are walked tile by tile, share cache lines with their neighbours at most rows?  8 neighbours then run on one XCD.  Batch
+// normalisation fp32 [16384,1001] 41.0 -> 38.0 us, [8192,2001] 40.6 -> 36.5, [1000,4001] 12.6 -> 11.7, [30000,517] 42.2 -> 41.2; column sums beside row norms
+// [1500,2001] 12.5 -> 10.8, [3440,1000] 11.3 -> 10.4.  Not for rows of whole lines ([16384,1024] 26.8 against 29.0), nor for a few tiles or
+// workgroups, which part the rows instead ([56203,143] 31.7 against 33.4).
+bool tiles_share_lines(const GroupPlan& gp) {
+  bool shared = false;
+  for (const auto* list : {&gp.ext_in, &gp.ext_out})
+    for (const ExtTensor& e : *list) shared |= e.kind == KIND_FULL && (int64_t)gp.C * dtype_size(e.dtype) % 128 != 0;
+  return shared && gp.s.CT >= 5 && gp.s.grid >= 64;
+}
+
 // how long workgroups wait for each other: 50 us, several times what those of the largest tiles need from their start to the last load
 int wait_ticks() {
   const char* e = getenv("FS_JOIN_WAIT_TICKS");
@@ -674,6 +685,7 @@ struct Scheduler {
         if (want <= 32) s.RB = std::min(s.RB, std::min(want, 16));
       }
       s.grid = s.RB * CT;
+      if (tiles_share_lines(*gp)) s.xcd_rows = 8;
     }
     // Looping kernels that only fold columns have almost no arithmetic per trip: their rate is set by
     // the bytes in flight, and two row tiles per trip measured 13 % faster (28.1 -> 24.5 us on
@@ -1820,6 +1832,7 @@ fs_status join_groups(const Graph& g, const std::vector<GroupPlan>& groups, int 
     gp.part_bytes = s.part_stride_floats * s.CT * 4;
   }
   gp.wait_ticks = wait_ticks();
+  if (s.WG >= 512 && tiles_share_lines(gp)) s.xcd_rows = 8;  // (smaller tensors: [4096,333] 10.0 against 10.2, [2000,1002] 10.4 against 10.6)
   return FS_OK;
 }
 

@@ -1430,6 +1430,17 @@ def test_rows_placed_by_xcd(rows, transposed):
     both_modes(g, [RNG.standard_normal((rows, 4099)).astype(np.float32)], f"rows by XCD {rows} {transposed}")
 
 
+@pytest.mark.parametrize("rows,cols", [(9000, 517), (3000, 777), (1000, 4001)])
+def test_column_tiles_placed_by_xcd(rows, cols):
+    from workloads.patterns import batchnorm
+    ins = [RNG.standard_normal(shape).astype(np.float32) for shape in ((rows, cols), (1, cols), (1, cols))]
+    for g, k in ((batchnorm(rows, cols), 1), (multi_reduce_graph(rows, cols), None)):
+        p = fs.Plan(g)
+        assert any("fs_xcd_place<" in src for _, _, src in p.joined_groups()) or k is None
+        p.destroy()
+        both_modes(g, ins if k else ins[:1], f"column tiles by XCD {rows}x{cols}")
+
+
 # ------------------------------------------------------------------ groups that share a launch
 @pytest.mark.parametrize("rows,ks", [(512, (64, 128, 256)), (100, (25, 50, 100)), (333, (50, 100, 200)), (48, (8, 16, 32)), (70, (96, 192, 384)), (2047, (32, 64, 128)),
                                      (1024, (96, 192, 384))])
