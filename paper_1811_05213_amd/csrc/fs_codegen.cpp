@@ -1088,7 +1088,7 @@ struct Emitter {
     if (!gp.asked.empty()) {
       os << "template <class X> FS_DEV void " << kname << "_ask(const " << kname << "_args& a, const int fs_block, X& x) {\n";
       constants();
-      os << "  const long row = (long)fs_block * G + rg, row_ld = row < R ? row : R - 1;\n  (void)row_ld;\n";
+      os << "  static_assert(CT == 1, \"whole rows\");\n  const long row = (long)fs_block * G + rg, row_ld = row < R ? row : R - 1;\n  (void)row_ld;\n";
       for (const ExtTensor& e : gp.ext_in) {
         if (!gp.asked.count(e.node)) continue;
         const std::string to = "x." + gp.comes.at(e.node), p = "a.p[" + std::to_string(e.arg) + "]";

@@ -1920,7 +1920,10 @@ struct Composer {
       for (int k : c->tracks[t]) L = std::max(L, groups[k].s.L);
       for (int k : c->tracks[t]) {
         GroupPlan p;
-        if (!plan(k, c->tracks[t].size() > 1 ? L : 0, c->WG, &p)) return false;
+        const bool chain = c->tracks[t].size() > 1;
+        if (!plan(k, chain ? L : 0, c->WG, &p)) return false;
+        // (a workgroup of column tiles has part of its rows: what the next group reads of them others have written)
+        if (chain && (p.s.CT > 1 || p.s.col_tiled || p.s.tiled_transpose)) return false;
         if (c->blocks[t] != 0 && p.s.grid != c->blocks[t]) return false;
         c->blocks[t] = p.s.grid;
         pointers += (int)(p.ext_in.size() + p.ext_out.size());

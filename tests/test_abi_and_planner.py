@@ -1492,3 +1492,24 @@ def test_launch_module(built_lib):
     assert len(seen) == calls
     real = ctypes.cast(built_lib.fs_plan_run, ctypes.c_void_p).value
     assert _launch.launch(real, 0, [], outs, None, 0, 0) == 1 and b"plan is NULL" in built_lib.fs_last_error()
+
+
+def wide_chain_graph(rows, cols, other):
+    """Two groups over the same rows whose rows are wide enough for column tiles; the second needs a row value of the first."""
+    g = Graph()
+    t, x, w = g.input(rows, 1), g.input(rows, cols), g.input(rows, other)
+    s = g.unary("exp", g.unary("tanh", t))
+    g.set_outputs([g.binary("mul", x, g.bcast_colvec(s, cols)), g.binary("add", w, g.bcast_colvec(s, other)), s])
+    return g
+
+
+@pytest.mark.parametrize("rows,cols,other", [(64, 4096, 3000), (256, 4096, 3000), (1000, 4096, 3000), (64, 3000, 4096), (100, 2100, 2080)])
+def test_column_tiles_form_no_chain(rows, cols, other):
+    # a workgroup of a kernel that cuts its rows into column tiles has part of a row: the next group cannot go on with that
+    p = fs.Plan(wide_chain_graph(rows, cols, other))
+    for _, _, src in p.joined_groups():
+        for track in src.split("\n")[0].replace("// one launch:", "").split("|"):
+            chain = [int(k) for k in track.split(" on ")[0].split()[1:]]
+            tiles = [int(p.group_source(k).split("CT = ")[1].split(";")[0]) for k in chain]
+            assert len(chain) == 1 or set(tiles) == {1}, (track, tiles)
+    p.destroy()

@@ -1469,6 +1469,13 @@ def test_chains_and_groups_side_by_side(rows, ks):
     q.destroy()
 
 
+@pytest.mark.parametrize("rows,cols,other", [(64, 4096, 3000), (256, 4096, 3000), (1000, 4096, 3000), (100, 2100, 2080)])
+def test_row_values_of_groups_on_column_tiles(rows, cols, other):
+    from test_abi_and_planner import wide_chain_graph
+    g = wide_chain_graph(rows, cols, other)
+    both_modes(g, [RNG.standard_normal((rows, n)).astype(np.float32) for n in (1, cols, other)], f"row values beside tiles {rows}x{cols}, {other}")
+
+
 @pytest.mark.parametrize("rows,cols", [(421, 192), (265, 64), (4765, 147), (3440, 1000), (20000, 64), (1000, 2001)])
 def test_column_folds_beside_row_norms(rows, cols):
     g, ins = multi_reduce_graph(rows, cols), multi_reduce_inputs(rows, cols)
