@@ -689,8 +689,11 @@ struct Emitter {
     std::vector<std::vector<int>> stage(max_level + 1);  // the column reductions by level
     for (int m : gp.col_reduces) stage[gp.level.at(m)].push_back(m);
     while (stage.back().empty()) stage.pop_back();
-    std::map<int, int> slot;  // reduction -> its row in lds_res
-    for (int m : gp.col_reduces) slot.insert({m, (int)slot.size()});
+    // reduction -> its row in lds_res, and its place among the partials of a tile: stage by stage, so that a stage's partials follow
+    // each other and no stage writes over those of another, which slower workgroups may still have to fold
+    std::map<int, int> slot;
+    for (const std::vector<int>& st : stage)
+      for (int m : st) slot.insert({m, (int)slot.size()});
 
     os << "// joined: work space [R," << gp.C << "], tiles of " << s.L << " lanes, " << s.U << " rows to a lane, " << s.RB << " workgroups of " << s.WG << " per tile\n";
     os << "struct " << kname << "_args { void* p[" << NP << "]; float* part; fs_u32* tickets; int R; int wait; };\n";

@@ -1513,3 +1513,38 @@ def test_column_tiles_form_no_chain(rows, cols, other):
             tiles = [int(p.group_source(k).split("CT = ")[1].split(";")[0]) for k in chain]
             assert len(chain) == 1 or set(tiles) == {1}, (track, tiles)
     p.destroy()
+
+
+def interleaved_stages_graph(rows, cols, three=False):
+    """Column reductions whose ids and stages (how many of them are upstream) are not in the same order."""
+    g = Graph()
+    x, y = g.input(rows, cols), g.input(rows, cols)
+    b = lambda v: g.bcast_rowvec(v, rows)
+    m = g.reduce_col("max", x)
+    e = g.unary("exp", g.binary("sub", x, b(m)))
+    s = g.reduce_col("sum", e)
+    q = g.binary("div", e, b(s))
+    u = g.reduce_col("max", q) if three else s
+    t = g.reduce_col("mean", y)
+    v = g.reduce_col("sum", g.binary("mul", g.binary("sub", y, b(t)), y))
+    w = g.reduce_col("min", y)
+    g.set_outputs([g.binary("mul", g.binary("add", q, b(t)), b(g.binary("add", v, w)))] + ([u] if three else []))
+    return g
+
+
+@pytest.mark.parametrize("rows,cols,three", [(4096, 512, 0), (2048, 1024, 1), (3000, 200, 0), (16384, 512, 1)])
+def test_partials_of_the_stages_of_a_joined_kernel_lie_apart(rows, cols, three):
+    import re
+    p = fs.Plan(interleaved_stages_graph(rows, cols, three))
+    (first, count, src), = p.joined_groups()
+    assert count == p.stats()["num_groups"]
+    columns = int(re.search(r"tiles of (\d+) lanes", src).group(1)) * int(re.search(r"constexpr int V = (\d+)", src).group(1))
+    workgroups = int(re.search(r"RB = (\d+),", src).group(1))
+    meets = [tuple(map(int, m)) for m in re.findall(r"fs_tile_meet<(\d+), CW, WG, FV>\(\w+, a\.part \+ \(long\)tile \* (\d+)L \+ (\d+)L", src)]
+    assert len(meets) == (3 if three else 2) and workgroups > 1
+    end = 0
+    for k, stride, offset in meets:
+        assert offset >= end
+        end = offset + k * columns * workgroups
+        assert end <= stride
+    p.destroy()

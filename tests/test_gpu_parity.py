@@ -1294,6 +1294,24 @@ def test_joined_groups(kind, rows, cols, dt, monkeypatch):
         np.testing.assert_array_equal(a.view(np.uint8), b.view(np.uint8))
 
 
+@pytest.mark.parametrize("rows,cols,three", [(2048, 1024, 0), (3000, 200, 1), (9000, 517, 1)])
+def test_joined_groups_whose_stages_interleave(rows, cols, three):
+    from test_abi_and_planner import interleaved_stages_graph
+    g = interleaved_stages_graph(rows, cols, three)
+    # (the second input away from zero: the mean of centred values is what is left of sums sqrt(rows) times its size)
+    ins = [(RNG.standard_normal((rows, cols)) + shift).astype(np.float32) for shift in (0, 6)]
+    p = fs.Plan(g)
+    assert len(p.joined_groups()) == 1
+    r = DeviceRun(p)
+    r.set_inputs(ins)
+    _, first, _ = both_modes(g, ins, f"interleaved stages {rows}x{cols}")
+    for _ in range(20):
+        r.launch()
+        for a, b in zip(first, r.results()):
+            np.testing.assert_array_equal(a.view(np.uint32), b.view(np.uint32))
+    p.destroy()
+
+
 def test_joined_groups_repeat_and_replay():
     # counters return to zero after every run; runs agree bit for bit, eagerly and from a graph
     import torch
