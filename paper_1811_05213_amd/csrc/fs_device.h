@@ -989,11 +989,12 @@ FS_DEV int fs_colred_meet(const float (&vals)[CPT][FV], float* part, fs_u32* cou
   __syncthreads();
   const int met = (int)*flag;
   if (met == 2) {
+    __syncthreads();  // (every wavefront has read the flag before one writes it again)
     for (fs_u32 i = (fs_u32)t; i < n; i += WG) {
       fs_u32* const door = fs_colred_door(counters, i, n);
       if (i != idx && __hip_atomic_exchange(door, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == 2u) {
         __hip_atomic_store(door, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        *flag = 3u;
+        __hip_atomic_store(flag, 3u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
       }
     }
   }

@@ -83,3 +83,18 @@ def test_host_planner_under_address_and_ub_sanitizers(workdir):
     r = subprocess.run([exe] + files, env=ENV, capture_output=True, text=True, timeout=900)
     assert r.returncode == 0, (r.stdout[-3000:], r.stderr[-4000:])
     assert r.stdout.count("status 0") >= 3 * len(files), r.stdout   # every plan is planned in the three modes
+
+
+def test_meeting_workgroups_under_thread_sanitizer(workdir):
+    # the workgroups of a column fold that meet, some of which leave: every access to a workgroup's flag is ordered by a barrier,
+    # its lanes agree, and the counters are zero again
+    text = open(os.path.join(ROOT, "paper_1811_05213_amd", "csrc", "fs_device.h")).read()
+    a = text.index("FS_DEV fs_u32* fs_colred_door")
+    b = text.index("template <int K, int C, int WG, int FV, int SC, int N, typename KINDS>", a)
+    with open(os.path.join(workdir, "meet.inc"), "w") as f:
+        f.write(text[a:b])
+    exe = os.path.join(workdir, "meet_san")
+    subprocess.run(["g++", "-std=c++17", "-O1", "-g", "-fsanitize=thread", "-pthread", "-Wno-unknown-pragmas", "-I" + workdir, os.path.join(SAN, "meet_san_main.cpp"),
+                    "-o", exe], check=True)
+    r = subprocess.run([exe], env=dict(os.environ, LD_PRELOAD="", TSAN_OPTIONS="halt_on_error=1"), capture_output=True, text=True, timeout=100)
+    assert r.returncode == 0 and r.stdout == "0 wrong\n", (r.stdout, r.stderr[:4000])
