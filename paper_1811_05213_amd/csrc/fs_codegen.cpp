@@ -216,36 +216,6 @@ struct Emitter {
     return "fs_round<" + std::to_string(n.dtype) + ">(" + e + ")";
   }
 
-  // The per-row value ([R,1], computed by this kernel) that [R,C] member `m` divides by, where the division may go through its
-  // reciprocal (fs_div_row): not on a predicate path, which sees the IEEE division itself.  Else -1.
-  int row_divisor(int m) const {
-    const fs_node& n = g.nodes[m];
-    if (n.opcode != FS_DIV || g.exact[m] || gp.kind.at(m) != KIND_FULL || g.nodes[n.in[1]].opcode == FS_CONST) return -1;
-    const int s = source_of(n.in[1]);
-    return in_set[s] && !folded[s] && gp.kind.at(s) == KIND_COLV ? s : -1;
-  }
-  // ... what it needs beside a per-row value that has just been computed
-  void emit_reciprocal(int s, std::ostringstream& to, const std::string& ind) {
-    for (int m : gp.members)
-      if (row_divisor(m) == s) {
-        const std::string nm = name(s, KIND_COLV), k = std::to_string(loc(s));
-        to << ind << "const float i" << k << " = fs_div(1.0f, " << nm << ");\n" << ind << "const bool o" << k << " = fs_reciprocal_overflows(" << nm << ");\n";
-        return;
-      }
-  }
-  // the elements of [R,C] member `m` (declared already), inside the loop `loop`
-  void emit_elements(int m, const std::string& ind, const std::string& loop, const std::string& value) {
-    const std::string nm = name(m, KIND_FULL);
-    const int s = row_divisor(m);
-    if (s < 0) {
-      os << ind << loop << nm << "[e] = " << value << ";\n";
-      return;
-    }
-    const std::string k = std::to_string(loc(s)), a = ref(g.nodes[m].in[0]), sn = name(s, KIND_COLV);
-    os << ind << loop << nm << "[e] = " << rounded(m, "fs_div_row(" + a + ", " + sn + ", i" + k + ")") << ";\n"
-       << ind << "if (__builtin_expect(o" << k << ", false)) " << loop << nm << "[e] = " << value << ";\n";
-  }
-
   static std::string tmpl_row() { return "V, NVL, L, NV, RAGGED"; }
 
   // The last stage of a row-reduction body (everything after the last exchange: normalise, scale,
@@ -417,7 +387,6 @@ struct Emitter {
       const fs_node& bn = g.nodes[b];
       const std::string q = "q" + std::to_string(loc(b));
       os << ind << "const float " << name(b, KIND_COLV) << " = " << rounded(b, bn.attr_i == FS_RED_MEAN ? q + " / (float)C" : q) << ";\n";
-      emit_reciprocal(b, os, ind);
       if (const ExtTensor* e = find_out(b)) emit_store(*e, ind);
     }
   }
@@ -481,9 +450,7 @@ struct Emitter {
       const Kind k = gp.kind.at(m);
       if (!is_alias(m)) {
         os << "      float " << name(m, k) << "[E];\n";
-        if (k == KIND_FULL && n.opcode != FS_TRANSPOSE) emit_elements(m, "      ", "_Pragma(\"unroll\") for (int e = 0; e < E; ++e) ", rounded(m, expr(m)));
-        else
-          os << "      _Pragma(\"unroll\") for (int e = 0; e < E; ++e) " << name(m, k) << "[e] = " << (n.opcode == FS_TRANSPOSE ? ref(n.in[0]) : rounded(m, expr(m))) << ";\n";
+        os << "      _Pragma(\"unroll\") for (int e = 0; e < E; ++e) " << name(m, k) << "[e] = " << (n.opcode == FS_TRANSPOSE ? ref(n.in[0]) : rounded(m, expr(m))) << ";\n";
       }
       if (staged(m) && !stage_written.count(m))  // its first pass: the slot takes it over (from whatever it dominates)
         os << "      if (ch < STAGE_CHUNKS) fs_stage_row_chunk<" << n.dtype << ", V, NVL, L>(" << stage_chunk(m) << ", " << name(m, k) << ", lir);\n";
@@ -584,7 +551,6 @@ struct Emitter {
       for (int m : gp.members) {
         if (gp.level.at(m) != lvl || gp.kind.at(m) != KIND_COLV || is_rr(m) || folded[m]) continue;
         os << "    const float " << name(m, KIND_COLV) << " = " << rounded(m, expr(m)) << ";\n";
-        emit_reciprocal(m, os, "    ");
         if (const ExtTensor* e = find_out(m))
           os << "    if (lir == 0) fs_store1<" << e->dtype << ">(a.p[" << e->arg << "], row, " << name(m, KIND_COLV) << ");\n";
       }
@@ -1499,7 +1465,6 @@ struct Emitter {
           const fs_node& bn = g.nodes[b];
           const std::string q = "q" + std::to_string(loc(b));
           os << "    const float " << name(b, KIND_COLV) << " = " << rounded(b, bn.attr_i == FS_RED_MEAN ? q + " / (float)C" : q) << ";\n";
-          emit_reciprocal(b, os, "    ");
           if (const ExtTensor* e = find_out(b)) emit_store(*e, "    ");
         }
         continue;
@@ -1532,11 +1497,9 @@ struct Emitter {
       const Kind k = gp.kind.at(m);
       if (k == KIND_COLV) {
         (strip ? pre : os) << "    const float " << name(m, k) << " = " << rounded(m, expr(m)) << ";\n";
-        emit_reciprocal(m, strip ? pre : os, "    ");
       } else {
         declare(name(m, k), "    ");
-        if (k == KIND_FULL) emit_elements(m, "    ", eloop(), rounded(m, expr(m)));
-        else os << "    " << eloop() << name(m, k) << "[e] = " << rounded(m, expr(m)) << ";\n";
+        os << "    " << eloop() << name(m, k) << "[e] = " << rounded(m, expr(m)) << ";\n";
       }
       if (const ExtTensor* e = find_out(m)) emit_store(*e, "    ");
     }

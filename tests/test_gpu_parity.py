@@ -1344,25 +1344,28 @@ def test_joined_groups_repeat_and_replay():
 
 # ------------------------------------------------------------------ division by a per-row value; long rows asked for ahead
 def test_division_by_row_values():
-    # the quotients of fs_div_row against IEEE division: divisors of every magnitude, zero, infinite, denormal, NaN
-    divisors = np.array([1.0, 3.0, 1e-45, 1e-39, 2.9e-39, 1.2e-38, 1e-20, 7e20, 1.7e38, 3.4e38, np.inf, 0.0, -0.0, -7.0, -1e-40, np.nan], np.float32)
-    for cols in (64, 4097):
-        x = (RNG.standard_normal((len(divisors), cols)) * 10.0 ** RNG.integers(-30, 30, (len(divisors), cols))).astype(np.float32)
-        x[:, :6] = [0.0, -0.0, np.inf, -np.inf, np.nan, 1e-42]
-        d = np.full((len(divisors), cols), -np.inf, np.float32)
-        d[:, 5] = divisors
-        g = Graph()
-        a, b = g.input(*x.shape), g.input(*x.shape)
-        s = g.reduce_row("max", b)
-        g.set_outputs([g.binary("div", a, g.bcast_colvec(s, cols)), s])
-        y, m = run_graph(g, [x, d])
-        with np.errstate(all="ignore"):
-            ref = x / m
-        np.testing.assert_array_equal(np.isnan(y), np.isnan(ref))
-        normal = np.abs(ref) >= np.finfo(np.float32).tiny
-        np.testing.assert_array_equal(y[normal], ref[normal])
-        rest = ~normal & ~np.isnan(ref)  # zeros, and denormals that are 1.3 of their spacings off at most
-        assert np.all(np.abs(y[rest].astype(np.float64) - ref[rest]) <= 2.1e-45) and np.all(np.signbit(y[rest]) == np.signbit(ref[rest]))
+    # the quotients are those of IEEE division, bit for bit: divisors of every magnitude, next to where the reciprocal overflows, zero,
+    # infinite, NaN; dividends of every magnitude, among them probabilities that are almost nothing
+    divisors = np.array([1.0, 3.0, 1e-45, 1e-39, 2.9e-39, 2.0 ** -128, 1.0000001 * 2.0 ** -128, 0.9999999 * 2.0 ** -128, -2.0 ** -128, 1.2e-38, 1e-20, 2.0 ** -24, 1e-3, 977.0, 2.0 ** 24,
+                         7e20, 1.7e38, 3.4e38, np.inf, 0.0, -0.0, -7.0, -1e-40, np.nan, 0.97450274], np.float32)
+    for cols in (64, 577, 4097):
+        for scale in (30, 3):
+            x = (RNG.standard_normal((len(divisors), cols)) * 10.0 ** RNG.integers(-scale, scale, (len(divisors), cols))).astype(np.float32)
+            x[:, :3] = [0.0, -0.0, np.float32(np.exp(-81.0)) if scale == 30 else 1.5]
+            if scale == 30:
+                x[:, 3:12] = [np.inf, -np.inf, np.nan, 1e-42, 3.3155697e38, 2.0 ** -100, 2.0 ** -126, 1e-3, np.exp(-76.0)]
+            d = np.full((len(divisors), cols), -np.inf, np.float32)
+            d[:, 5] = divisors
+            g = Graph()
+            a, b = g.input(*x.shape), g.input(*x.shape)
+            s = g.reduce_row("max", b)
+            g.set_outputs([g.binary("div", a, g.bcast_colvec(s, cols)), s])
+            y, m = run_graph(g, [x, d])
+            with np.errstate(all="ignore"):
+                ref = x / m
+            np.testing.assert_array_equal(np.isnan(y), np.isnan(ref))
+            there = ~np.isnan(ref)
+            np.testing.assert_array_equal(y[there].view(np.uint32), ref[there].view(np.uint32))
 
 
 @pytest.mark.parametrize("rows,cols,dt", [(257, 32768, "f32"), (300, 28676, "f32"), (520, 40000, "f32"), (300, 65533, "f32"), (259, 50001, "f32"),
