@@ -2045,8 +2045,9 @@ bool generate_composite(const Graph& g, Composite* c) {
     for (int k : c->tracks[t]) head += " " + std::to_string(k);
     head += " on " + std::to_string(c->blocks[t]) + " workgroups";
   }
-  c->source = head + "\n" + text + "struct " + c->kernel_name + "_args {\n" + args + "};\nextern \"C\" __global__ void __launch_bounds__(" + std::to_string(c->WG) + ") " + c->kernel_name + "(const " +
-              c->kernel_name + "_args a) {\n  int block = (int)blockIdx.x;\n" + body + "}\n";
+  // (in a namespace: another composite of the plan may hold the same group's functions)
+  c->source = head + "\nnamespace " + c->kernel_name + "_parts {\n" + text + "struct " + c->kernel_name + "_args {\n" + args + "};\nextern \"C\" __global__ void __launch_bounds__(" + std::to_string(c->WG) + ") " + c->kernel_name + "(const " +
+              c->kernel_name + "_args a) {\n  int block = (int)blockIdx.x;\n" + body + "}\n}\n";
   return true;
 }
 

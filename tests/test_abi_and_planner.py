@@ -1526,3 +1526,25 @@ def test_partials_of_the_stages_of_a_joined_kernel_lie_apart(rows, cols, three):
         end = offset + k * columns * workgroups
         assert end <= stride
     p.destroy()
+
+
+def repeated_group_graph(rows, a, b, c):
+    """Two launches of groups side by side; one group of the first and one of the second have the same kernel."""
+    g = Graph()
+    top = lambda v, t, n: g.reduce_row("max", g.binary("mul", v, g.bcast_colvec(t, n)))
+    p, q, p2, q2, t = g.input(a, rows), g.input(b, rows), g.input(a, rows), g.input(c, rows), g.input(rows, 1)
+    v, w = g.transpose(g.unary("tanh", p)), g.transpose(g.unary("tanh", q))
+    k, m = top(v, t, a), top(w, t, b)
+    r = g.reshape(g.binary("mul", k, m), 1, rows)  # the launches after it wait for those before
+    v2, w2 = (g.transpose(g.binary("mul", x, g.bcast_rowvec(r, n))) for x, n in ((p2, a), (q2, c)))
+    g.set_outputs([k, m, v, w, v2, w2, top(v2, t, a), top(w2, t, c)])
+    return g
+
+
+@pytest.mark.parametrize("rows,a,b,c", [(4096, 900, 800, 700), (4096, 1000, 600, 1024), (3000, 900, 1000, 1024)])
+def test_the_same_group_in_two_shared_launches(rows, a, b, c):
+    p = fs.Plan(repeated_group_graph(rows, a, b, c))
+    names = [p.group_kernel_name(k) for k in range(p.stats()["num_groups"])]
+    shared = [src for _, _, src in p.joined_groups()]
+    assert any(sum(n + "_rows(const" in src for src in shared) > 1 for n in names)
+    p.destroy()

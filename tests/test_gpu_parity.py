@@ -1497,6 +1497,12 @@ def test_row_values_of_groups_on_column_tiles(rows, cols, other):
     both_modes(g, [RNG.standard_normal((rows, n)).astype(np.float32) for n in (1, cols, other)], f"row values beside tiles {rows}x{cols}, {other}")
 
 
+def test_the_same_group_in_two_shared_launches():
+    from test_abi_and_planner import repeated_group_graph
+    g = repeated_group_graph(3000, 900, 1000, 1024)
+    both_modes(g, [RNG.standard_normal((g.nodes[i].rows, g.nodes[i].cols)).astype(np.float32) for i in g.input_ids()], "one group in two launches")
+
+
 @pytest.mark.parametrize("rows,cols", [(421, 192), (265, 64), (4765, 147), (3440, 1000), (20000, 64), (1000, 2001)])
 def test_column_folds_beside_row_norms(rows, cols):
     g, ins = multi_reduce_graph(rows, cols), multi_reduce_inputs(rows, cols)
