@@ -2000,9 +2000,10 @@ bool generate_composite(const Graph& g, Composite* c) {
   std::set<std::string> seen;
   int total = 0;
   std::string args;
+  bool passes = false;  // (one form for all tracks: a group's functions are defined once, whichever tracks it is in)
+  for (const std::string& f : fields) passes |= !f.empty();
   for (size_t t = 0; t < c->tracks.size(); ++t) {
     body += std::string("  ") + (t + 1 < c->tracks.size() ? "if (block < " + std::to_string(c->blocks[t]) + ") {\n" : "{\n");
-    const bool passes = !fields[t].empty();
     int xcd_rows = 0;
     for (const GroupPlan& p : c->plans[t]) xcd_rows = xcd_rows == 0 || p.s.xcd_rows == 0 ? std::max(xcd_rows, p.s.xcd_rows) : std::min(xcd_rows, p.s.xcd_rows);
     const std::string place = xcd_rows ? "fs_xcd_place<" + std::to_string(xcd_rows) + ">(block, " + std::to_string(c->blocks[t]) + ")" : "block";

@@ -1548,3 +1548,25 @@ def test_the_same_group_in_two_shared_launches(rows, a, b, c):
     shared = [src for _, _, src in p.joined_groups()]
     assert any(sum(n + "_rows(const" in src for src in shared) > 1 for n in names)
     p.destroy()
+
+
+def passing_and_plain_graph(rows, a, b, c):
+    """A chain that passes a row value in registers and holds a group that takes no part in that, and the same group beside it."""
+    g = Graph()
+    top = lambda v, t: g.reduce_row("max", g.binary("mul", v, g.bcast_colvec(t, g.nodes[v].cols)))
+    x, w, u, z = g.input(rows, 200), g.input(rows, b), g.input(rows, a), g.input(rows, c)
+    v, t = g.input(rows, b), g.input(rows, 1, "bf16")
+    s = g.reduce_row("sum", g.unary("tanh", x))
+    h = g.unary("convert", g.unary("exp", g.unary("tanh", g.unary("exp", s))), "bf16")
+    f32 = lambda x: g.unary("convert", x, "f32")
+    g.set_outputs([top(w, f32(h)), top(u, f32(h)), top(v, f32(t)), top(z, s), s, h])
+    return g
+
+
+@pytest.mark.parametrize("rows,a,b,c", [(4096, 600, 800, 300), (4096, 900, 1024, 512)])
+def test_the_same_group_in_a_chain_that_passes_values_and_beside_it(rows, a, b, c):
+    p = fs.Plan(passing_and_plain_graph(rows, a, b, c))
+    names = [p.group_kernel_name(k) for k in range(p.stats()["num_groups"])]
+    assert len(set(names)) < len(names)
+    assert any("X& x" in src and src.count(n + "_rows(a.") == 2 for _, _, src in p.joined_groups() for n in names)
+    p.destroy()

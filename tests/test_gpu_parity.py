@@ -1503,6 +1503,13 @@ def test_the_same_group_in_two_shared_launches():
     both_modes(g, [RNG.standard_normal((g.nodes[i].rows, g.nodes[i].cols)).astype(np.float32) for i in g.input_ids()], "one group in two launches")
 
 
+def test_the_same_group_in_a_chain_that_passes_values_and_beside_it():
+    from test_abi_and_planner import passing_and_plain_graph
+    g = passing_and_plain_graph(4096, 600, 800, 300)
+    ins = [(0.01 * RNG.standard_normal((g.nodes[i].rows, g.nodes[i].cols))).astype(np.float32) for i in g.input_ids()]
+    both_modes(g, [f32_to_bf16_bits(a) if g.nodes[i].dtype == "bf16" else a for a, i in zip(ins, g.input_ids())], "one group in and beside a chain")
+
+
 @pytest.mark.parametrize("rows,cols", [(421, 192), (265, 64), (4765, 147), (3440, 1000), (20000, 64), (1000, 2001)])
 def test_column_folds_beside_row_norms(rows, cols):
     g, ins = multi_reduce_graph(rows, cols), multi_reduce_inputs(rows, cols)
