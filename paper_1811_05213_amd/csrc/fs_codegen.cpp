@@ -696,6 +696,7 @@ struct Emitter {
     for (const ExtTensor& e : gp.ext_in)
       if (e.kind == KIND_FULL) os << "  fs_u32 " << raw(e) << "[TR][fs_words<" << e.dtype << ", V>::n];\n";
     load_rows("  ", "rb");
+    if (s.RB > 1) os << "  int next, late = 0;  // late: 31 once others were (no more waiting for them)\n  fs_u32 *const counters = a.tickets + tile * " << s.ticket_stride << ", *const bits = counters + " << join_counters((int)stage.size()) << ";\n";
     for (const ExtTensor& e : gp.ext_in)
       if (e.kind == KIND_ROWV)
         os << "  float " << name(e.node, KIND_ROWV) << "[E];\n  fs_load_row<" << e.dtype << ", " << tmpl_row() << ">(" << name(e.node, KIND_ROWV) << ", a.p[" << e.arg
@@ -763,19 +764,20 @@ struct Emitter {
       partial("    ", "rb");
       os << "  }\n";
       if (s.RB > 1) {
+        // (what is missing in a loop of its own: in a loop with the own rows, the compiler waits for all of them before it works on the first one, [1000,1000] 7.4 -> 7.7 us)
         const std::string part = "a.part + (long)tile * " + std::to_string(s.part_stride_floats) + "L + " + std::to_string((size_t)slot.at(red[0]) * CW * s.RB) + "L";
-        os << "  if (fs_tile_meet<" << K << ", CW, WG, FV>(" << cv << ", " << part << ", a.tickets + tile * " << s.ticket_stride << " + " << st << ", &lds_flag, (fs_u32)rb, (fs_u32)RB, a.wait)) {\n"
-           << "    fs_tile_fold<" << K << ", CW, WG, RB, " << kname << "_kinds" << st << ">(" << cv << ", " << part << ", lds_fold);\n  } else {\n"
-           << "    typedef fs_tile_slices<" << K << ", CW, WG, RB> Q;\n    float tot[" << S << "::CPT], slice[" << S << "::CPT];\n    _Pragma(\"unroll 1\") for (int b = 0; b < RB; ++b) {\n";
+        auto meet = [&](const std::string& ind, const std::string& b) {
+          os << ind << "fs_tile_put<" << K << ", CW, WG, FV>(" << cv << ", " << part << ", " << b << ");\n" << ind << "next = fs_tile_" << (b == "rb" ? "meet" : "next") << "<RB>(counters + "
+             << st << ", bits + " << st * 2 * ((s.RB + 31) / 32) << ", &lds_flag, " << b << (b == "rb" ? ", a.wait >> late" : "") << ");\n";
+        };
+        meet("  ", "rb");
+        os << "  if (next >= 0) {\n    late = 31;\n    do {\n      const int b = next;\n";
         load_rows("      ", "b");
         partial("      ", "b");
-        const std::string kinds = kname + "_kinds" + std::to_string(st);
-        os << "      _Pragma(\"unroll\") for (int i = 0; i < " << S << "::CPT; ++i) {\n        const int k = (tid + i * WG) / " << S << "::CH;\n"
-           << "        if (b % Q::PS == 0) {\n          tot[i] = b == 0 ? " << kinds << "::identity(k) : " << kinds << "::op(k, tot[i], slice[i]);\n          slice[i] = " << kinds << "::identity(k);\n        }\n"
-           << "        slice[i] = " << kinds << "::op(k, slice[i], " << cv << "[i][0]);\n      }\n    }\n"
-           << "    _Pragma(\"unroll\") for (int i = 0; i < " << S << "::CPT; ++i) " << cv << "[i][0] = " << kinds << "::op((tid + i * WG) / " << S << "::CH, tot[i], slice[i]);\n";
+        meet("      ", "b");
+        os << "    } while (next >= 0);\n";
         load_rows("    ", "rb");
-        os << "  }\n";
+        os << "  }\n  fs_tile_fold<" << K << ", CW, WG, RB, " << kname << "_kinds" << st << ">(" << cv << ", " << part << ", lds_fold);\n";
       }
       // results: rounded to their dtype, stored by the tile's first workgroup, and through LDS to the lanes' columns
       os << "  _Pragma(\"unroll\") for (int i = 0; i < " << S << "::CPT; ++i) {\n    const int c = tid + i * WG;\n    if (c < " << S << "::NCH) {\n      const int k = c / " << S
@@ -794,7 +796,7 @@ struct Emitter {
         os << "  float " << name(m, KIND_ROWV) << "[E];\n  _Pragma(\"unroll\") for (int e = 0; e < E; ++e) " << name(m, KIND_ROWV) << "[e] = lds_res[" << slot.at(m)
            << " * CW + (lcol + e > 0 ? lcol + e : 0)];\n";
     }
-    if (s.RB > 1) os << "  const fs_u32 left = fs_tile_leave(a.tickets + tile * " << s.ticket_stride << ", " << stage.size() + 1 << ");\n";
+    if (s.RB > 1) os << "  const fs_u32 left = fs_tile_leave(counters, " << stage.size() + 1 << ");\n";
     // what leaves the kernel as an [R,C] tensor, and [1,C] values nothing else needed
     std::vector<int> roots;
     for (const ExtTensor& e : gp.ext_out)
@@ -823,7 +825,7 @@ struct Emitter {
           }
         });
     }
-    if (s.RB > 1) os << "  fs_tile_clear(left, a.tickets + tile * " << s.ticket_stride << ", " << stage.size() + 1 << ", (fs_u32)RB);\n";
+    if (s.RB > 1) os << "  fs_tile_clear(left, counters, " << stage.size() + 1 << ", bits, " << stage.size() * 2 * ((s.RB + 31) / 32) << ", (fs_u32)RB);\n";
     os << "}\n";
   }
 

@@ -1045,45 +1045,76 @@ FS_DEV void fs_colred_slice(float (&vals)[FV], const float* part, float* lds /* 
 }
 
 // ------------------------------------------------------------------------------------------
-// Workgroups of one column tile that meet inside a kernel: each leaves its partial, counts itself in and waits until the others
-// have done so, then all of them fold the partials in the same order and go on with the result (a column statistic that every
-// row needs again).  Visibility as in the grid-wide fold: sc1 stores acknowledged before the count, sc1 loads after it.  (A flag per
-// workgroup that all the others read in the place of one counter: batch normalisation fp32 [4096,1024] 10.1 -> 10.7 us, [65536,64]
-// 13.9 -> 14.9.)  The wait is bounded: a kernel must not depend on workgroups that the device has not started (another stream may
-// hold the compute units).  Where the others have not arrived after `ticks` of the 100 MHz clock the function returns false, and
-// the caller computes their partials itself, from memory, in the same order: the same bits.
+// Workgroups of one column tile that meet inside a kernel: each leaves its partial (fs_tile_put) and waits until all N are there
+// (fs_tile_meet), then all of them fold the partials in the same order and go on with the result (a column statistic that every
+// row needs again).  Visibility as in the grid-wide fold: sc1 stores acknowledged before the bit is set, sc1 loads after it.  (A flag per
+// workgroup in a word of its own that all the others read: batch normalisation fp32 [4096,1024] 10.1 -> 10.7 us, [65536,64] 13.9 -> 14.9.)
+// A kernel must not depend on workgroups that the device has not started (another stream may hold the compute units): after `ticks` of
+// the 100 MHz clock a waiting workgroup claims a partial that is missing, computes it from memory and puts it in its place, and so on
+// until all are there: the missing rows are read once more, shared among those who wait.  A workgroup that starts late puts the same bits
+// to the same place.  Every wait ends: what is missing a running workgroup has claimed, or the next one who waits claims it.
+//   counter  workgroups whose own partial is there, and kTileLate once one has waited in vain: from then on each sets the bit of what it has put
+//   bits     a bit for each partial that is there, then one for each that is claimed.  All zero before and after the kernel.  (Bits that all
+//            set and read from the start, in the place of the count: [65536,99] 26.7 -> 34.4 us, [1000,1000] 7.4 -> 7.9)
+//   result   -1: all are there; else the partial to compute, after which fs_tile_next tells what comes then
 // ------------------------------------------------------------------------------------------
 template <int K, int C, int WG, int FV, int CPT>
-FS_DEV bool fs_tile_meet(const float (&vals)[CPT][FV], float* part, fs_u32* counter, fs_u32* flag, fs_u32 idx, fs_u32 n, int ticks) {
+FS_DEV void fs_tile_put(const float (&vals)[CPT][FV], float* part, int idx) {
   typedef fs_colfold<K, C, WG, FV> S;
   static_assert(CPT == S::CPT, "chunks per thread");
   constexpr int KC = K * C;
-  const int t = (int)threadIdx.x;
   const __amdgpu_buffer_rsrc_t mine = fs_make_rsrc(part + (long)idx * KC, KC * 4);
 #pragma unroll
   for (int i = 0; i < S::CPT; ++i) {
-    const int c = t + i * WG;
+    const int c = (int)threadIdx.x + i * WG;
     if (c < S::NCH) fs_store_dev<FV>(vals[i], mine, (fs_u32)c * (FV * 4));
   }
   __builtin_amdgcn_s_waitcnt(0);  // this wavefront's partial stores are acknowledged
   __syncthreads();
-  if (t == 0) {
+}
+constexpr fs_u32 kTileLate = 1u << 30;
+template <int N> FS_DEV fs_u32 fs_tile_missing(fs_u32* counter, fs_u32* bits, int idx) {  // (one lane; one more than the partial to compute)
+  constexpr int W = (N + 31) / 32;
+  (void)__hip_atomic_fetch_or(&bits[idx / 32], 1u << (idx & 31), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  for (;;) {
+    __builtin_amdgcn_s_sleep(8);  // (those who wait for the count see that it is late, and set their bits)
+    if ((__hip_atomic_load(counter, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) & (kTileLate - 1)) == (fs_u32)N) return 0;
+    bool all = true;
+    for (int w = 0; w < W; ++w) {
+      const fs_u32 missing = (N - w * 32 >= 32 ? ~0u : (1u << (N - w * 32)) - 1) & ~__hip_atomic_load(&bits[w], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      if (missing == 0) continue;
+      all = false;
+      const fs_u32 open = missing & ~__hip_atomic_load(&bits[W + w], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT), after = open & (~0u << (idx & 31));
+      const fs_u32 from = after ? after : open, bit = from & (~from + 1);  // (workgroups start at different places)
+      if (bit && !(__hip_atomic_fetch_or(&bits[W + w], bit, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) & bit)) return 1 + (fs_u32)(w * 32 + __builtin_ctz(bit));
+    }
+    if (all) return 0;
+  }
+}
+template <int N> FS_DEV int fs_tile_meet(fs_u32* counter, fs_u32* bits, fs_u32* flag, int idx, int ticks) {
+  if (threadIdx.x == 0) {
     fs_u32 seen = __hip_atomic_fetch_add(counter, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + 1u;
-    if (seen < n) {
+    if (seen < (fs_u32)N) {
       const unsigned long long t0 = __builtin_amdgcn_s_memrealtime();
       do {
         __builtin_amdgcn_s_sleep(1);
         seen = __hip_atomic_load(counter, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      } while (seen < n && (long long)(__builtin_amdgcn_s_memrealtime() - t0) < (long long)ticks);
+      } while (seen < (fs_u32)N && (long long)(__builtin_amdgcn_s_memrealtime() - t0) < (long long)ticks);
+      if (seen < (fs_u32)N) seen = __hip_atomic_fetch_or(counter, kTileLate, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) | kTileLate;
     }
-    *flag = seen >= n ? 1u : 0u;
+    *flag = seen > (fs_u32)N ? fs_tile_missing<N>(counter, bits, idx) : 0;
   }
   __syncthreads();
-  return *flag != 0u;
+  return __builtin_amdgcn_readfirstlane((int)*flag) - 1;
 }
-// ... the fold of the N partials, after fs_tile_meet returned true.  Where the chunks leave lanes of the workgroup idle, H slices of
+template <int N> FS_DEV int fs_tile_next(fs_u32* counter, fs_u32* bits, fs_u32* flag, int idx) {
+  if (threadIdx.x == 0) *flag = fs_tile_missing<N>(counter, bits, idx);
+  __syncthreads();
+  return __builtin_amdgcn_readfirstlane((int)*flag) - 1;
+}
+// ... the fold of the N partials, once they are there.  Where the chunks leave lanes of the workgroup idle, H slices of
 // PS partials are folded side by side and then, through LDS (WG floats), each other: one round of loads instead of one for every
-// sixteen partials.  Always in this order (fs_tile_slices), whoever folds.
+// sixteen partials.
 template <int K, int C, int WG, int N> struct fs_tile_slices {
   static constexpr int NCH = K * C, H0 = NCH < WG ? WG / NCH : 1, H = H0 < N ? H0 : N;
   static constexpr int PS = (N + H - 1) / H;
@@ -1125,14 +1156,16 @@ FS_DEV void fs_tile_fold(float (&vals)[CPT][1], const float* part, float* lds) {
     }
   }
 }
-// A workgroup that has met its tile's others for the last time says so in the last of the tile's counters, and the last one to say
-// it leaves all of them zero.  (In two halves: the answer of the first is on its way while the results leave.)
+// A workgroup that has met its tile's others for the last time says so in the last of the tile's `count` counters, and the last one to say
+// it leaves all of them, and the bits, zero.  (In two halves: the answer of the first is on its way while the results leave.)
 FS_DEV fs_u32 fs_tile_leave(fs_u32* counters, int count) {
   return threadIdx.x == 0 ? __hip_atomic_fetch_add(&counters[count - 1], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0u;
 }
-FS_DEV void fs_tile_clear(fs_u32 before, fs_u32* counters, int count, fs_u32 n) {
-  if (threadIdx.x == 0 && before == n - 1)
+FS_DEV void fs_tile_clear(fs_u32 before, fs_u32* counters, int count, fs_u32* bits, int words, fs_u32 n) {
+  if (threadIdx.x == 0 && before == n - 1) {
     for (int i = 0; i < count; ++i) __hip_atomic_store(&counters[i], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    for (int i = 0; i < words; ++i) __hip_atomic_store(&bits[i], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  }
 }
 
 #endif  // FS_DEVICE_H_

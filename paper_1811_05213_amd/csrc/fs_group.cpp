@@ -21,7 +21,8 @@ bool tiles_share_lines(const GroupPlan& gp) {
   return shared && gp.s.CT >= 5 && gp.s.grid >= 64;
 }
 
-// how long workgroups wait for each other: 50 us, several times what those of the largest tiles need from their start to the last load
+// how long workgroups wait for each other before they do each other's work (joined kernels) or leave the rest to the last one (column folds):
+// 50 us, several times what those of the largest tiles need from their start to the last load
 int wait_ticks() {
   const char* e = getenv("FS_JOIN_WAIT_TICKS");
   return e ? atoi(e) : 5000;
@@ -1827,7 +1828,8 @@ fs_status join_groups(const Graph& g, const std::vector<GroupPlan>& groups, int 
   if (s.lds_bytes > opt.lds_budget) FS_FAIL(FS_ERR_LDS_BUDGET, "joined groups need %d bytes of LDS, budget is %d", s.lds_bytes, opt.lds_budget);
   if (s.RB > 1) {
     s.part_stride_floats = gp.col_reduces.size() * (size_t)s.fold_width * s.RB;
-    s.ticket_stride = std::max(32, top + 2);  // (a tile's counters share no cache line with another's)
+    // (a tile's counters share no cache line with another's; top: the last stage there can be)
+    s.ticket_stride = join_counters(top + 1) + ((top + 1) * 2 * ((s.RB + 31) / 32) + 31) / 32 * 32;
     gp.n_tickets = s.ticket_stride * s.CT;
     gp.part_bytes = s.part_stride_floats * s.CT * 4;
   }

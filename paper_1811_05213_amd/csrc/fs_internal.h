@@ -188,6 +188,9 @@ struct StageSlot {
 // columns to a chunk of a column fold of this many
 inline int fold_vector(int width) { return width % 4 == 0 ? 4 : width % 2 == 0 ? 2 : 1; }
 
+// what the counters of a tile's stages, and of the workgroups that leave it, take in a joined kernel: whole cache lines (the bits of its partials follow)
+inline int join_counters(int stages) { return (stages + 1 + 31) / 32 * 32; }
+
 struct GroupPlan {
   // Groups of a Composite's chain: per-row results that leave in x.<name>, besides memory, for the groups after; what comes in
   // x.<name> instead of from memory: those, and tensors that were asked for before the first group's work.
@@ -219,7 +222,7 @@ struct GroupPlan {
   bool exchanges = false;  // reads what another kernel of the plan wrote, or writes what another one reads
   // Several groups of the plan in one kernel (join_groups): column reductions and what needs their results, with the rows in
   // registers between them.  level is then the number of column reductions upstream, s.U the rows a lane holds, s.RB the
-  // workgroups of a tile, which wait for each other for `wait_ticks` of the 100 MHz clock at most.
+  // workgroups of a tile, which wait for each other for `wait_ticks` of the 100 MHz clock before they do each other's work.
   bool joined = false;
   int wait_ticks = 0;
   // generated kernel

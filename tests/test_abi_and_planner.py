@@ -1518,7 +1518,7 @@ def test_partials_of_the_stages_of_a_joined_kernel_lie_apart(rows, cols, three):
     assert count == p.stats()["num_groups"]
     columns = int(re.search(r"tiles of (\d+) lanes", src).group(1)) * int(re.search(r"constexpr int V = (\d+)", src).group(1))
     workgroups = int(re.search(r"RB = (\d+),", src).group(1))
-    meets = [tuple(map(int, m)) for m in re.findall(r"fs_tile_meet<(\d+), CW, WG, FV>\(\w+, a\.part \+ \(long\)tile \* (\d+)L \+ (\d+)L", src)]
+    meets = [tuple(map(int, m)) for m in dict.fromkeys(re.findall(r"fs_tile_put<(\d+), CW, WG, FV>\(\w+, a\.part \+ \(long\)tile \* (\d+)L \+ (\d+)L", src))]
     assert len(meets) == (3 if three else 2) and workgroups > 1
     end = 0
     for k, stride, offset in meets:

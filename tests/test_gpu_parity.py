@@ -1288,7 +1288,7 @@ def test_joined_groups(kind, rows, cols, dt, monkeypatch):
     assert len(p.joined_groups()) == 1
     p.destroy()
     _, out, _ = both_modes(g, ins, f"{kind} {rows}x{cols} {dt}")
-    # a workgroup that does not wait for the others computes their partials itself: the same bits
+    # workgroups that do not wait for the others compute what is missing: the same bits
     monkeypatch.setenv("FS_JOIN_WAIT_TICKS", "0")
     for a, b in zip(out, run_graph(g, ins)):
         np.testing.assert_array_equal(a.view(np.uint8), b.view(np.uint8))
@@ -1340,6 +1340,39 @@ def test_joined_groups_repeat_and_replay():
     p.workspace_check(r.workspace.data_ptr(), r.ws_bytes)
     del graph
     p.destroy()
+
+
+@pytest.mark.parametrize("rows,cols", [(65536, 64), (16384, 1024), (3000, 200)])
+def test_joined_groups_beside_work_of_another_stream(rows, cols):
+    # workgroups that start late, because another stream's hold the compute units: the same bits, and counters that return to zero
+    import torch
+    from workloads.patterns import batchnorm
+    g = batchnorm(rows, cols)
+    p = fs.Plan(g)
+    assert "fs_tile_meet<" in p.joined_groups()[0][2]
+    r = DeviceRun(p)
+    r.set_inputs([RNG.standard_normal((g.nodes[i].rows, g.nodes[i].cols)).astype(np.float32) for i in g.input_ids()])
+    p.load()
+    r.launch()
+    first = r.results()
+    q = fs.Plan(softmax_graph(512, 40000))
+    other = DeviceRun(q)
+    other.set_inputs([RNG.standard_normal((512, 40000)).astype(np.float32)])
+    q.load()
+    mine, theirs = torch.cuda.Stream(), torch.cuda.Stream()
+    torch.cuda.synchronize()
+    for _ in range(20):
+        with torch.cuda.stream(theirs):
+            for _ in range(3):
+                other.launch()
+        with torch.cuda.stream(mine):
+            r.launch()
+        torch.cuda.synchronize()
+        for a, b in zip(first, r.results()):
+            np.testing.assert_array_equal(a.view(np.uint32), b.view(np.uint32))
+    p.workspace_check(r.workspace.data_ptr(), r.ws_bytes)
+    p.destroy()
+    q.destroy()
 
 
 # ------------------------------------------------------------------ division by a per-row value; long rows asked for ahead

@@ -86,13 +86,14 @@ def test_host_planner_under_address_and_ub_sanitizers(workdir):
 
 
 def test_meeting_workgroups_under_thread_sanitizer(workdir):
-    # the workgroups of a column fold that meet, some of which leave: every access to a workgroup's flag is ordered by a barrier,
-    # its lanes agree, and the counters are zero again
+    # the workgroups of a column fold that meet, some of which leave, and those of a tile, some of which start late: every access to a
+    # workgroup's flag is ordered by a barrier, its lanes agree, every wait ends, and the counters are as they should be
     text = open(os.path.join(ROOT, "paper_1811_05213_amd", "csrc", "fs_device.h")).read()
-    a = text.index("FS_DEV fs_u32* fs_colred_door")
-    b = text.index("template <int K, int C, int WG, int FV, int SC, int N, typename KINDS>", a)
     with open(os.path.join(workdir, "meet.inc"), "w") as f:
-        f.write(text[a:b])
+        for begin, end in (("FS_DEV fs_u32* fs_colred_door", "template <int K, int C, int WG, int FV, int SC, int N, typename KINDS>"),
+                           ("template <int K, int C, int WG, int FV, int CPT>\nFS_DEV void fs_tile_put", "// ... the fold of the N partials")):
+            a = text.index(begin)
+            f.write(text[a:text.index(end, a)])
     exe = os.path.join(workdir, "meet_san")
     subprocess.run(["g++", "-std=c++17", "-O1", "-g", "-fsanitize=thread", "-pthread", "-Wno-unknown-pragmas", "-I" + workdir, os.path.join(SAN, "meet_san_main.cpp"),
                     "-o", exe], check=True)
