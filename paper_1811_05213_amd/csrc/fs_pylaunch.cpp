@@ -51,12 +51,15 @@ PyObject* launch(PyObject*, PyObject* const* args, Py_ssize_t nargs) {
     void* few[64];
     std::vector<void*> many;
     void** table = few;
-    if (ni + no + 1 > 64) {
-      many.resize((size_t)(ni + no + 1));
+    if (ni + no + 2 > 64) {
+      many.resize((size_t)(ni + no + 2));
       table = many.data();
     }
+    // (each list ends with NULL, which fs_plan_run refuses where the plan has more tensors than were given)
+    void** const out_table = table + ni + 1;
+    table[ni] = out_table[no] = nullptr;
     void* workspace = nullptr;
-    bool ok = addresses(ins, table, ni) && addresses(outs, table + ni, no);
+    bool ok = addresses(ins, table, ni) && addresses(outs, out_table, no);
     if (ok && args[4] != Py_None) {
       PyObject* p = PyObject_CallMethodNoArgs(args[4], g_data_ptr);
       workspace = p ? PyLong_AsVoidPtr(p) : nullptr;
@@ -66,7 +69,7 @@ PyObject* launch(PyObject*, PyObject* const* args, Py_ssize_t nargs) {
     if (ok) {
       int status;
       Py_BEGIN_ALLOW_THREADS
-      status = run(plan, table, table + ni, workspace, workspace_bytes, stream);
+      status = run(plan, table, out_table, workspace, workspace_bytes, stream);
       Py_END_ALLOW_THREADS
       result = PyLong_FromLong(status);
     }

@@ -1570,3 +1570,18 @@ def test_the_same_group_in_a_chain_that_passes_values_and_beside_it(rows, a, b, 
     assert len(set(names)) < len(names)
     assert any("X& x" in src and src.count(n + "_rows(a.") == 2 for _, _, src in p.joined_groups() for n in names)
     p.destroy()
+
+
+def test_launch_with_too_few_tensors(built_lib):
+    # a plan that has more tensors than were given is refused, whatever lies behind the last one
+    import torch
+    from paper_1811_05213_amd import _launch
+    g = Graph()
+    a, b, c = (g.input(8, 8) for _ in range(3))
+    g.set_outputs([g.binary("add", g.binary("add", a, b), c), g.unary("tanh", a)])
+    p = fs.Plan(g)
+    real = ctypes.cast(built_lib.fs_plan_run, ctypes.c_void_p).value
+    ins, outs = [torch.zeros(64) for _ in range(3)], [torch.zeros(64) for _ in range(2)]
+    for i, o, what in ((0, 2, b"inputs[0] is NULL"), (2, 2, b"inputs[2] is NULL"), (3, 0, b"outputs[0] is NULL"), (3, 1, b"outputs[1] is NULL")):
+        assert _launch.launch(real, p._h.value, ins[:i], outs[:o], None, 0, 0) == 1 and what in built_lib.fs_last_error(), (i, o, built_lib.fs_last_error())
+    p.destroy()
