@@ -8,7 +8,6 @@
 #include <Python.h>
 
 #include <cstddef>
-#include <vector>
 
 namespace {
 
@@ -49,11 +48,15 @@ PyObject* launch(PyObject*, PyObject* const* args, Py_ssize_t nargs) {
   if (outs) {
     const Py_ssize_t ni = PySequence_Fast_GET_SIZE(ins), no = PySequence_Fast_GET_SIZE(outs);
     void* few[64];
-    std::vector<void*> many;
+    void** many = nullptr;  // (no exception may leave a C entry: no std::vector)
     void** table = few;
     if (ni + no + 2 > 64) {
-      many.resize((size_t)(ni + no + 2));
-      table = many.data();
+      table = many = static_cast<void**>(PyMem_Malloc(sizeof(void*) * (size_t)(ni + no + 2)));
+      if (!many) {
+        Py_DECREF(outs);
+        Py_DECREF(ins);
+        return PyErr_NoMemory();
+      }
     }
     // (each list ends with NULL, which fs_plan_run refuses where the plan has more tensors than were given)
     void** const out_table = table + ni + 1;
@@ -73,6 +76,7 @@ PyObject* launch(PyObject*, PyObject* const* args, Py_ssize_t nargs) {
       Py_END_ALLOW_THREADS
       result = PyLong_FromLong(status);
     }
+    PyMem_Free(many);
   }
   Py_XDECREF(outs);
   Py_XDECREF(ins);
