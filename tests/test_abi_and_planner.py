@@ -1585,3 +1585,30 @@ def test_launch_with_too_few_tensors(built_lib):
     for i, o, what in ((0, 2, b"inputs[0] is NULL"), (2, 2, b"inputs[2] is NULL"), (3, 0, b"outputs[0] is NULL"), (3, 1, b"outputs[1] is NULL")):
         assert _launch.launch(real, p._h.value, ins[:i], outs[:o], None, 0, 0) == 1 and what in built_lib.fs_last_error(), (i, o, built_lib.fs_last_error())
     p.destroy()
+
+
+def test_launch_without_the_launch_module(built_lib, monkeypatch):
+    # the same addresses, workspace and stream reach fs_plan_run
+    import torch
+    from paper_1811_05213_amd import runner
+    seen = []
+    proto = ctypes.CFUNCTYPE(ctypes.c_int, ctypes.c_void_p, ctypes.POINTER(ctypes.c_void_p), ctypes.POINTER(ctypes.c_void_p), ctypes.c_void_p, ctypes.c_size_t, ctypes.c_void_p)
+    run = proto(lambda plan, ins, outs, ws, nbytes, stream: seen.append((plan, ins[0], ins[1], outs[0], ws, nbytes, stream)) or 0)
+    p = fs.Plan(softmax_graph(8, 8))
+    r = object.__new__(runner.DeviceRun)
+    r.plan, r._device_index, r.ws_bytes = p, 0, 256
+    r.inputs, r.outputs, r.workspace = [torch.zeros(3), torch.zeros(5)], [torch.zeros(7)], torch.zeros(64)
+    r._run = ctypes.cast(run, ctypes.c_void_p).value
+    monkeypatch.setattr(runner, "_raw_stream", lambda index: 12)
+    monkeypatch.setattr(p, "_run", run)
+    r.launch()
+    monkeypatch.setattr(runner, "_launch", None)
+    r.launch()
+    assert seen[0] == seen[1] == (p._h.value, *(t.data_ptr() for t in (*r.inputs, *r.outputs, r.workspace)), 256, 12)
+    p.destroy()
+    monkeypatch.setattr(torch.cuda, "is_available", lambda: True)  # (no longer stopped for want of the module)
+    monkeypatch.setattr(torch, "empty", lambda *a, **k: (_ for _ in ()).throw(MemoryError("the device's buffers")))
+    q = fs.Plan(softmax_graph(8, 8))
+    with pytest.raises(MemoryError, match="the device's buffers"):
+        runner.DeviceRun(q)
+    q.destroy()
