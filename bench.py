@@ -22,6 +22,7 @@ from __future__ import annotations
 import argparse
 import json
 import os
+import re
 import statistics
 import sys
 import time
@@ -189,6 +190,19 @@ def measured_traffic(workload_name):
     return None
 
 
+def launched_kernels(plan):
+    """Names of the kernels a run of the plan launches, in no particular order: a set of groups that runs as one kernel has one."""
+    alone, names = set(range(plan.stats()["num_groups"])), []
+    for first, count, src in plan.joined_groups():
+        line = src.split("\n")[0]
+        if line.startswith("// one launch:"):  # "// one launch: groups 2 3 4 on 128 workgroups | groups 5 on 32 workgroups"
+            alone -= {int(k) for track in line.split(":")[1].split("|") for k in track.split(" on ")[0].split()[1:]}
+        else:
+            alone -= set(range(first, first + count))
+        names.append(re.search(r'extern "C" __global__ .*?(fs_\w+)\(const', src).group(1))
+    return names + [plan.group_kernel_name(k) for k in sorted(alone)]
+
+
 def measure_workload(cfg, steps, warmup, with_unfused=True, rows=None, graph_leg=False):
     import torch
     from paper_1811_05213_amd import Plan, FS_MODE_UNFUSED, FS_MODE_LAYERED
@@ -203,7 +217,9 @@ def measure_workload(cfg, steps, warmup, with_unfused=True, rows=None, graph_leg
         runs = build_sets(plan, g, ins, "cuda:0", target if mode == 0 or st["launched_hbm_bytes"] < 2 ** 31 else 0)
         res = time_plan(runs, steps if mode == 0 else max(5, steps // 4), warmup if mode == 0 else max(2, warmup // 4))
         hot = time_plan(runs[:1], max(5, steps // 4), 2, min_warm_ms=0.0)
-        res.update({"ms_hot": hot["ms_median"], "launches": st["num_launches"], "launched_hbm_bytes": st["launched_hbm_bytes"],
+        kernels = launched_kernels(plan)
+        # (launched_hbm_bytes: of the groups by themselves; those that run as one kernel may read less)
+        res.update({"ms_hot": hot["ms_median"], "launches": len(kernels), "launched_hbm_bytes": st["launched_hbm_bytes"],
                     "buffer_sets": len(runs)})
         out[label] = res
         if mode == 0:
@@ -213,10 +229,10 @@ def measure_workload(cfg, steps, warmup, with_unfused=True, rows=None, graph_leg
             out["gbs"] = st["min_hbm_bytes"] / ms / 1e6
             out["frac_of_peak"] = out["gbs"] / HBM_PEAK_GBS
             out["groups"] = [plan.group_info(i) for i in range(min(st["num_groups"], 4))]
-            out["kernels"] = [plan.group_kernel_name(i) for i in range(st["num_groups"])]
+            out["kernels"] = kernels
             # the roofline of the step: algorithmic bytes of the plan over the measured time of its launches
             out["roofline"] = {"bound": "hbm", "achieved": out["gbs"], "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": out["frac_of_peak"],
-                               "traffic": measured_traffic(name), "kernel": plan.group_kernel_name(0) if st["num_groups"] == 1 else out["kernels"],
+                               "traffic": measured_traffic(name), "kernel": kernels[0] if len(kernels) == 1 else kernels,
                                "algorithmic_bytes_per_launch": st["min_hbm_bytes"], "avg_launch_us": ms * 1e3,
                                "median_us": res["ms_median"] * 1e3, "min_us": res["ms_min"] * 1e3, "p90_us": res["ms_p90"] * 1e3,
                                "frac_at_median": st["min_hbm_bytes"] / res["ms_median"] / 1e6 / HBM_PEAK_GBS}
@@ -232,7 +248,7 @@ def measure_workload(cfg, steps, warmup, with_unfused=True, rows=None, graph_leg
         plan = Plan(g, mode=FS_MODE_LAYERED)
         runs = build_sets(plan, g, ins, "cuda:0", target)
         res = time_plan(runs, steps, warmup)
-        out["layered_planner"] = {"ms": res["ms"], "ms_median": res["ms_median"], "launches": plan.stats()["num_launches"],
+        out["layered_planner"] = {"ms": res["ms"], "ms_median": res["ms_median"], "launches": len(launched_kernels(plan)),
                                   "launched_hbm_bytes": plan.stats()["launched_hbm_bytes"]}
         del runs
         plan.destroy()
@@ -307,7 +323,7 @@ def survey(steps, name_filter):
             res = time_plan(runs, 400, 40)
         gbs = min_hbm_bytes(g) / res["ms_median"] / 1e6
         print("%-30s %9d x %-9d %2d  %5d %3d %5d %7d %6d | %9.1f %9.1f %7.0f %6.1f" % (
-            name, r, c, plan.stats()["num_launches"], gi["lanes_per_row"], gi["elems_per_lane"], gi["wg_threads"], gi["grid"],
+            name, r, c, len(launched_kernels(plan)), gi["lanes_per_row"], gi["elems_per_lane"], gi["wg_threads"], gi["grid"],
             gi["lds_bytes"], res["ms"] * 1e3, res["ms_median"] * 1e3, gbs, gbs / 80.0), flush=True)
         del runs
         plan.destroy()

@@ -35,6 +35,10 @@
  *                          scratch bytes of every kernel it ends up with
  *   FS_DUMP_FAILED_SOURCE  file that receives the generated source when its
  *                          compilation fails
+ *   FS_JOIN_WAIT_TICKS     read by plan creation: how long, in ticks of 10 ns, workgroups
+ *                          of a kernel wait for each other before they do each other's
+ *                          work or leave it to the last one (default 5000; 0: not at
+ *                          all).  Results are the same bits; it is there for tests
  */
 #ifndef FS_H_
 #define FS_H_
@@ -318,8 +322,9 @@ fs_status fs_plan_workspace_check(fs_plan* plan, const void* workspace, size_t w
 
 /*
  * fs_plan_stats: plan-level figures for the metric.  num_groups = fused computations;
- * num_launches = kernel launches per run, one per group (groups that run as one kernel, see
- * fs_plan_joined_groups, are counted as the launches they replace).  Their
+ * num_launches = launches of a run in which every group has its own, so the same number.  A run makes
+ * fewer where groups run as one kernel: for each set of fs_plan_joined_groups the set's
+ * number of groups less one.  Their
  * ratio between a stitched and an unfused plan of the same DAG is the paper's fusion ratio
  * (Section 6.3: kernels after fusion / kernels of the baseline).  min_hbm_bytes = every plan
  * input read once + every plan output written once (the memory footprint fusion aims at,
@@ -330,8 +335,10 @@ fs_status fs_plan_workspace_check(fs_plan* plan, const void* workspace, size_t w
 fs_status fs_plan_stats(const fs_plan* plan, int32_t* num_groups, int32_t* num_launches,
                         uint64_t* min_hbm_bytes, uint64_t* unfused_hbm_bytes);
 
-/* Bytes THIS plan's launches move: the sum over its groups of external inputs + outputs (equals
- * min_hbm_bytes for a single-group plan, unfused_hbm_bytes for an unfused one). */
+/* Bytes THIS plan's groups move: the sum over them of external inputs + outputs (equals
+ * min_hbm_bytes for a single-group plan, unfused_hbm_bytes for an unfused one).  A run moves fewer where
+ * groups run as one kernel (fs_plan_joined_groups) that keeps in registers what they share: groups joined over
+ * their column reductions read their inputs once. */
 fs_status fs_plan_launched_hbm_bytes(const fs_plan* plan, uint64_t* bytes);
 
 /*
@@ -389,7 +396,9 @@ fs_status fs_plan_joined_groups(const fs_plan* plan, int32_t index, int32_t* fir
  * runs that kernel on the caller's buffers `reps` times (HIP events on `hip_stream`, the
  * last-level cache flushed before each timed launch when the group moves more than 1 MiB),
  * and inserts the median.  It does not change `plan`: create the plan again to use what was
- * learned.  Unlike fs_plan_run it SYNCHRONISES and ALLOCATES (private scratch for the
+ * learned.  It measures the groups by themselves, also those that fs_plan_run launches as one kernel
+ * with others (fs_plan_joined_groups): what it learns about these has an effect only where they
+ * are launched alone.  Unlike fs_plan_run it SYNCHRONISES and ALLOCATES (private scratch for the
  * candidates' partials and a flush buffer, freed before it returns); the outputs and the
  * workspace hold the results of a normal run afterwards.  inputs / outputs / workspace as for
  * fs_plan_run.  reps <= 0 means 9.  report may be NULL.

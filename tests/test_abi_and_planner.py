@@ -1612,3 +1612,18 @@ def test_launch_without_the_launch_module(built_lib, monkeypatch):
     with pytest.raises(MemoryError, match="the device's buffers"):
         runner.DeviceRun(q)
     q.destroy()
+
+
+def test_the_kernels_a_run_launches():
+    # what bench.py reports as launches: a set of groups that runs as one kernel has one
+    import sys
+    sys.path.insert(0, ROOT)
+    from bench import launched_kernels
+    from workloads.patterns import batchnorm
+    for g, groups, launches in ((random_dag_graph(), 7, 4), (batchnorm(16384, 1024), 3, 1), (multi_reduce_graph(421, 192), 2, 1), (softmax_graph(256, 1024), 1, 1)):
+        p = fs.Plan(g)
+        names = launched_kernels(p)
+        assert p.stats()["num_groups"] == groups and len(set(names)) == len(names) == launches
+        for name in names:
+            assert any("__global__" in src and name + "(const" in src for src in [src for _, _, src in p.joined_groups()] + [p.group_source(k) for k in range(groups)])
+        p.destroy()
