@@ -483,8 +483,8 @@ struct Scheduler {
   // Wide rows of kernels that reduce rows and columns, one workgroup of 512 lanes to a compute unit (plan_lds): such a workgroup asks
   // for the rows of its next trip before it works on those it has.  Rows of whole vectors and trips of whole groups of rows: a branch
   // around the loads or stores would have the compiler wait for all of them.  Where this takes 512 lanes in the place of 1024, from
-  // 12 trips on.  (Fewer would gain as well, LayerNorm backward [3000,4096] 40.2 -> 34.6 us, [2048,8192] 56.9 -> 47.0: the tests of the
-  // planner hold 1024 lanes there.)
+  // 12 trips on.  That is not where the two measure the same: fewer trips gain as well (LayerNorm backward [3000,4096] 40.2 -> 34.6 us,
+  // [2048,8192] 56.9 -> 47.0), and so would row counts that leave a partial trip ([8191,4096] takes 82 us, [8192,4096] 74).
   bool columns_ahead() const {
     const int64_t trips = R / std::max(1, 512 / L);
     return opt.ahead && rowred && colred && !col_tiled && !has_transposed && !has_concat && CT == 1 && C >= 2048 && C % V == 0 && L <= 512 && whole_lanes && row_inputs > 0 &&
