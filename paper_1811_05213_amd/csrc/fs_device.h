@@ -738,6 +738,14 @@ FS_DEV float fs_shfl_xor(float v, int mask) {
   return __builtin_bit_cast(float, __builtin_amdgcn_ds_bpermute((fs_lane_id() ^ mask) << 2, __builtin_bit_cast(int, v)));
 }
 
+// v[0] of N values, folded in pairs (a chain of eight large sums loses half a bit more than the pairs)
+template <int N, typename OP> FS_DEV void fs_pairs(float (&v)[N], OP op) {
+#pragma unroll
+  for (int s = 1; s < N; s *= 2)
+#pragma unroll
+    for (int i = 0; i + s < N; i += 2 * s) v[i] = op(v[i], v[i + s]);
+}
+
 // Stage 1, in-workgroup fold of reduction number KIDX.  acc: the lane's per-column accumulators
 // in the row layout.  Fills the chunks of `vals` that belong to reduction KIDX.  When several
 // row-groups share a wavefront (L < 64) they are folded inside the wavefront first (lanes l,
@@ -795,11 +803,17 @@ FS_DEV void fs_colred_fold_wg(const float (&acc_in)[NVL * V], float (&vals)[CPT]
         const int col0 = (c - KIDX * S::CH) * FV;
         if constexpr (FEW) {
 #pragma unroll
-          for (int f = 0; f < FV; ++f) vals[i][f] = lds[col0 + f];
-#pragma unroll 8
-          for (int g = 1; g < GL; ++g)
+          for (int f = 0; f < FV; ++f) {
+            float a = 0.0f;
+            for (int g0 = 0; g0 < GL; g0 += 8) {
+              float v[8];
 #pragma unroll
-            for (int f = 0; f < FV; ++f) vals[i][f] = fs_red_op<KIND>(vals[i][f], lds[g * C + col0 + f]);
+              for (int u = 0; u < 8; ++u) v[u] = g0 + u < GL ? lds[(g0 + u) * C + col0 + f] : fs_red_identity<KIND>();
+              fs_pairs<8>(v, [](float x, float y) { return fs_red_op<KIND>(x, y); });
+              a = g0 == 0 ? v[0] : fs_red_op<KIND>(a, v[0]);
+            }
+            vals[i][f] = a;
+          }
           continue;
         }
 #pragma unroll
@@ -1138,8 +1152,11 @@ FS_DEV void fs_tile_fold(float (&vals)[CPT][1], const float* part, float* lds) {
           const int j = h * Q::PS + j0 + u;
           fs_load_dev<1>(tmp[u], all, (fs_u32)(j < N ? j : N - 1) * (KC * 4) + (fs_u32)c * 4);
         }
+        float v[FB];
 #pragma unroll
-        for (int u = 0; u < FB; ++u) a = j0 + u < Q::PS && h * Q::PS + j0 + u < N ? KINDS::op(k, a, tmp[u][0]) : a;
+        for (int u = 0; u < FB; ++u) v[u] = j0 + u < Q::PS && h * Q::PS + j0 + u < N ? tmp[u][0] : KINDS::identity(k);
+        fs_pairs<FB>(v, [&](float x, float y) { return KINDS::op(k, x, y); });
+        a = j0 == 0 ? v[0] : KINDS::op(k, a, v[0]);
       }
       if constexpr (Q::H > 1) lds[h * KC + c] = a;
       else vals[i][0] = a;
@@ -1150,8 +1167,13 @@ FS_DEV void fs_tile_fold(float (&vals)[CPT][1], const float* part, float* lds) {
     const int c = (int)threadIdx.x;
     if (c < KC) {
       float a = KINDS::identity(c / S::CH);
+      for (int h0 = 0; h0 < Q::H; h0 += 8) {
+        float v[8];
 #pragma unroll
-      for (int h = 0; h < Q::H; ++h) a = KINDS::op(c / S::CH, a, lds[h * KC + c]);
+        for (int u = 0; u < 8; ++u) v[u] = h0 + u < Q::H ? lds[(h0 + u) * KC + c] : KINDS::identity(c / S::CH);
+        fs_pairs<8>(v, [&](float x, float y) { return KINDS::op(c / S::CH, x, y); });
+        a = h0 == 0 ? v[0] : KINDS::op(c / S::CH, a, v[0]);
+      }
       vals[0][0] = a;
     }
   }

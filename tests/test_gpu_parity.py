@@ -1342,6 +1342,20 @@ def test_joined_groups_repeat_and_replay():
     p.destroy()
 
 
+@pytest.mark.parametrize("rows,cols,bound", [(16384, 1024, 4.65e-8), (8192, 1024, 4.6e-8), (4096, 1024, 4.7e-8)])
+def test_joined_sums_are_no_less_exact_than_separate_ones(rows, cols, bound):
+    # means and variances against 64 bits, 2-norm.  Bounds: what the three separate kernels show (4.67, 4.60, 6.08e-8), of which the
+    # rounding of the results to fp32 is 3.5e-8; sums that run through eight partials in a chain, twice, show 4.9 to 5.0e-8
+    from workloads.patterns import batchnorm
+    rng = np.random.default_rng(1811)
+    x = (rng.standard_normal((rows, cols)) + 0.5).astype(np.float32)
+    out = run_graph(batchnorm(rows, cols), [x, np.ones((1, cols), np.float32), np.zeros((1, cols), np.float32)])
+    x = x.astype(np.float64)
+    for got, exact in ((out[1], x.mean(0, keepdims=True)), (out[2], x.var(0, keepdims=True))):
+        err = np.linalg.norm(got - exact) / np.linalg.norm(exact)
+        assert err < bound, err
+
+
 @pytest.mark.parametrize("rows,cols", [(65536, 64), (16384, 1024), (3000, 200)])
 def test_joined_groups_beside_work_of_another_stream(rows, cols):
     # workgroups that start late, because another stream's hold the compute units: the same bits, and counters that return to zero
