@@ -649,11 +649,11 @@ struct Scheduler {
     }
     // Rows that fill a compute unit's registers, one workgroup to a unit: loads, arithmetic and stores of a row would follow each
     // other.  One workgroup per unit stays instead and asks for its next row, mostly through LDS, before it works on a row (loads
-    // asked for after the stores wait for them: 14-20 % slower).  softmax fp32 [1024,65536] 110.8 -> 103.8 us, [2048,50000] 159.2 -> 155.8,
-    // [2048,32768] 97.9 -> 94.3, [300,65000] 43.6 -> 39.8, [400,50000] 38.2 -> 31.6; a copy in such rows takes 144 us for the second.
+    // asked for after the stores wait for them: 14-20 % slower).  softmax fp32 [1024,65536] 111.1 -> 104.3 us, [2048,50000] 160.0 -> 153.3,
+    // [2048,32768] 97.1 -> 94.3, [300,65000] 53.1 -> 47.1, [400,50000] 35.2 -> 32.5; a copy in such rows takes 144 us for the second.
     // Below 32 elements per lane two workgroups share a unit, which is better ([4096,20000] 108.8 against 115.0).  Rows that start
     // inside a vector cross to LDS in 4-byte pieces, which eats the gain ([2048,33001] 104.7 against 106.3) but for a few rows
-    // ([400,50001] 37.6 -> 31.0).
+    // ([400,50001] 37.8 -> 33.7).
     bool rowv = false;
     for (const ExtTensor& e : gp->ext_in) rowv |= e.kind == KIND_ROWV;
     s.ahead = opt.ahead && rowred && !colred && !chunked && !resident && !has_transposed && !has_concat && CT == 1 && s.G == 1 && WG == 1024 && s.E >= 32 && row_inputs == 1 && !rowv &&
@@ -706,8 +706,8 @@ struct Scheduler {
     // One-trip grids whose workgroups share cache lines with their neighbours: in a transposed tensor, into which a workgroup writes a few rows
     // of a line (8 workgroups of 4 fp32 rows fill one), and at the ends of rows that are no whole lines.  Placed in turn on the XCDs, each of two
     // L2s moves such a line; now 8 or 16 neighbours run on one XCD.  Random DAGs of 200 ops [512,256] 21.4 -> 20.4 us, [700,384] 36.0 -> 31.4, [1500,256]
-    // 31.2 -> 27.6 (4: 28.0, 16: 28.1); masked softmax bf16 [16384,577] 10.5 -> 10.2, [32768,129] 7.6 -> 6.9, softmax fp32 [2048,50001] 164.8 -> 160.2 (4 and 8:
-    // 162.1), elementwise of 6 tensors [16384,1001] 67.8 -> 66.2, LayerNorm+GeLU bf16 [8000,1021] 7.5 -> 7.1.  Rows of whole lines have nothing to gain
+    // 31.2 -> 27.6 (4: 28.0, 16: 28.1); masked softmax bf16 [16384,577] 11.26 -> 11.12, [32768,129] 7.6 -> 7.1, softmax fp32 [2048,50001] 168.7 -> 164.4 (4 and 8:
+    // three fifths of that), elementwise of 6 tensors [16384,1001] 67.8 -> 66.2, LayerNorm+GeLU bf16 [8000,1021] 7.1 -> 6.7.  Rows of whole lines have nothing to gain
     // ([16384,1024] 64.3 and 64.3; an eighth of all rows to an XCD, which meets the same channels, 67.9).
     if (!has_concat && !tiled_transpose && !colred && !chunked && CT == 1 && s.U == 1 && s.grid == s.n_iters) {
       bool shared = false;
