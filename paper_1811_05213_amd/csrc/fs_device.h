@@ -1066,7 +1066,8 @@ FS_DEV void fs_colred_slice(float (&vals)[FV], const float* part, float* lds /* 
 // A kernel must not depend on workgroups that the device has not started (another stream may hold the compute units): after `ticks` of
 // the 100 MHz clock a waiting workgroup claims a partial that is missing, computes it from memory and puts it in its place, and so on
 // until all are there: the missing rows are read once more, shared among those who wait.  A workgroup that starts late puts the same bits
-// to the same place.  Every wait ends: what is missing a running workgroup has claimed, or the next one who waits claims it.
+// to the same place.  Every wait ends: what is missing a running workgroup has claimed, or the next one who waits claims it; and who has
+// waited for claimed ones for kTilePatience does those, too (a claim may be all there is in a workspace that was never cleared).
 //   counter  workgroups whose own partial is there, and kTileLate once one has waited in vain: from then on each sets the bit of what it has put
 //   bits     a bit for each partial that is there, then one for each that is claimed.  All zero before and after the kernel.  (Bits that all
 //            set and read from the start, in the place of the count: [65536,99] 26.7 -> 34.4 us, [1000,1000] 7.4 -> 7.9)
@@ -1087,20 +1088,23 @@ FS_DEV void fs_tile_put(const float (&vals)[CPT][FV], float* part, int idx) {
   __syncthreads();
 }
 constexpr fs_u32 kTileLate = 1u << 30;
+constexpr unsigned long long kTilePatience = 100000;  // 1 ms
 template <int N> FS_DEV fs_u32 fs_tile_missing(fs_u32* counter, fs_u32* bits, int idx) {  // (one lane; one more than the partial to compute)
   constexpr int W = (N + 31) / 32;
   (void)__hip_atomic_fetch_or(&bits[idx / 32], 1u << (idx & 31), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  const unsigned long long t0 = __builtin_amdgcn_s_memrealtime();
   for (;;) {
     __builtin_amdgcn_s_sleep(8);  // (those who wait for the count see that it is late, and set their bits)
     if ((__hip_atomic_load(counter, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) & (kTileLate - 1)) == (fs_u32)N) return 0;
+    const bool patient = __builtin_amdgcn_s_memrealtime() - t0 < kTilePatience;
     bool all = true;
     for (int w = 0; w < W; ++w) {
       const fs_u32 missing = (N - w * 32 >= 32 ? ~0u : (1u << (N - w * 32)) - 1) & ~__hip_atomic_load(&bits[w], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       if (missing == 0) continue;
       all = false;
-      const fs_u32 open = missing & ~__hip_atomic_load(&bits[W + w], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT), after = open & (~0u << (idx & 31));
+      const fs_u32 open = patient ? missing & ~__hip_atomic_load(&bits[W + w], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : missing, after = open & (~0u << (idx & 31));
       const fs_u32 from = after ? after : open, bit = from & (~from + 1);  // (workgroups start at different places)
-      if (bit && !(__hip_atomic_fetch_or(&bits[W + w], bit, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) & bit)) return 1 + (fs_u32)(w * 32 + __builtin_ctz(bit));
+      if (bit && (!(__hip_atomic_fetch_or(&bits[W + w], bit, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) & bit) || !patient)) return 1 + (fs_u32)(w * 32 + __builtin_ctz(bit));
     }
     if (all) return 0;
   }

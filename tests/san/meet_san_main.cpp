@@ -99,7 +99,7 @@ template <int M> struct Tile {
   fs_u32 counters[2] = {0, 0}, bits[4 * W] = {};
   float part[2][M * LANES];
   long taken[2] = {0, 0};
-  int wrong = 0;
+  int wrong = 0, wrong_sums = 0;
   struct Group {
     pthread_barrier_t bar;
     fs_u32 flag = 0;
@@ -130,10 +130,19 @@ template <int M> struct Tile {
           for (int i = 0; i < M * LANES; ++i) {
             float x;
             __atomic_load(&part[st][i], &x, __ATOMIC_RELAXED);
-            if (x != (float)(1 + st * 1000 + i)) __atomic_fetch_add(&wrong, 1, __ATOMIC_RELAXED);
+            if (x != (float)(1 + st * 1000 + i)) __atomic_fetch_add(&wrong, 1, __ATOMIC_RELAXED), __atomic_fetch_add(&wrong_sums, 1, __ATOMIC_RELAXED);
           }
         }
       });
+  }
+  // the words hold what they like (a workspace that was never cleared): no more than an end of every wait is asked for
+  int run_on(fs_u32 rubbish) {
+    for (fs_u32* p : {counters, bits})
+      for (int i = 0; i < (p == counters ? 2 : 4 * W); ++i) p[i] = rubbish;
+    for (int w = 0; w < M; ++w) start(w, 50);
+    for (Group& g : groups)
+      for (std::thread& t : g.lanes) t.join();
+    return 0;
   }
   int run(int early, int ticks) {
     for (float* p : {part[0], part[1]})
@@ -154,10 +163,18 @@ template <int M> struct Tile {
   }
 };
 template <int M> static int tile(int early, int ticks) { return Tile<M>().run(early, ticks); }
+template <int M> static int claimed_by_nobody(int early) {  // the late ones' partials are marked as claimed: the early ones do them in the end
+  Tile<M> t;
+  for (int st = 0; st < 2; ++st)
+    for (int w = 0; w < t.W; ++w) t.bits[(st * 2 + 1) * t.W + w] = ~0u;
+  t.run(early, 50);
+  return t.wrong_sums;
+}
 
 int main() {
   int wrong = scenario(0) + scenario(3) + scenario(N - 1) + scenario(16);
   wrong += tile<2>(2, 1 << 30) + tile<2>(1, 50) + tile<8>(8, 1 << 30) + tile<8>(3, 50) + tile<8>(1, 0) + tile<8>(8, 0) + tile<64>(64, 1 << 30) + tile<64>(40, 50) + tile<70>(70, 1 << 30) +
-           tile<70>(20, 0) + tile<70>(66, 50);
+           tile<70>(20, 0) + tile<70>(66, 50) + claimed_by_nobody<8>(5) + claimed_by_nobody<40>(30) + Tile<8>().run_on(3) + Tile<8>().run_on(8) + Tile<40>().run_on(0x7f7f7f7fu) +
+           Tile<40>().run_on(~0u);
   return printf("%d wrong\n", wrong), wrong != 0;
 }
