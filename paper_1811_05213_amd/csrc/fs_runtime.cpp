@@ -1133,9 +1133,12 @@ fs_status fs_plan_tune(fs_plan* plan, const void* const* inputs, void* const* ou
     rep.best_usec += best_us;
     if (best_us < cur_us) ++rep.improvable;
     ++rep.groups;
-    // leave this group's results as a normal run would, for the groups that follow
+    // this group's results, for the groups that follow
     FS_HIP(launch_group(base, base_fn, tensors, base_part, base_tickets, stream));
   }
+  // leave the results of a normal run (groups joined over their column reductions sum in another order than by themselves)
+  st = enqueue_groups(plan, ld, inputs, outputs, workspace, stream);
+  if (st != FS_OK) return st;
   FS_HIP(hipStreamSynchronize(stream));
 #undef FS_HIP
   if (report) *report = rep;

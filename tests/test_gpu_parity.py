@@ -846,6 +846,24 @@ def test_tuning_fills_the_library_and_tuned_plans_match_the_oracle(tmp_path, mon
     assert text.count("\t") >= 10 and "lanes/row" in text
 
 
+def test_tuning_leaves_the_results_of_a_run(tmp_path, monkeypatch):
+    # also where a run launches groups as one kernel, whose sums are folded in another order: the same bits
+    from workloads.patterns import batchnorm
+    monkeypatch.setenv("FS_PERF_LIBRARY", str(tmp_path / "perflib.tsv"))
+    g = batchnorm(3000, 200)
+    p = fs.Plan(g)
+    assert p.joined_groups()
+    r = DeviceRun(p)
+    r.set_inputs([RNG.standard_normal((g.nodes[i].rows, g.nodes[i].cols)).astype(np.float32) for i in g.input_ids()])
+    r.launch()
+    first = r.results()
+    assert r.tune(reps=1)["groups"] == 3
+    for a, b in zip(first, r.results()):
+        np.testing.assert_array_equal(a.view(np.uint32), b.view(np.uint32))
+    p.workspace_check(r.workspace.data_ptr(), r.ws_bytes)
+    p.destroy()
+
+
 def test_layered_planner_results_match_the_oracle():
     for cfg, rows in ((5, None), (6, 300), (4, 3000)):
         g, ins, name = workload(cfg, rows)
