@@ -297,6 +297,12 @@ def copy_sweep(sizes):
     return rows
 
 
+# Why the survey may not run (empty: it may).  Two trees' surveys were run one after the other; one of the two, it is not known which and in
+# which case, left the GPU faulted.  All kernels of this tree's survey stay inside their buffers (compiled for the host under AddressSanitizer,
+# first, middle and last workgroups), so no cause has been shown yet.
+SURVEY_OFF = "a run of it ended in a GPU fault whose cause is not known"
+
+
 def survey(steps, name_filter):
     """Common fused patterns over a range of shapes, each as ONE stitched plan: the schedule the planner chose and the
     measured time, effective GB/s and fraction of peak, one text line per case (the table kept in profiles/shape_survey.txt)."""
@@ -342,6 +348,8 @@ def main():
     ap.add_argument("--survey", action="store_true", help="only time the common fused patterns of workloads/patterns.py (a text table, not the JSON line)")
     ap.add_argument("--filter", default="", help="with --survey: only patterns whose name contains this")
     args = ap.parse_args()
+    if args.survey and SURVEY_OFF:
+        sys.exit("bench.py --survey is switched off: " + SURVEY_OFF)
     if args.gpus != 1:
         log("bench.py: this build runs on ONE GPU only (no collectives, no sharding); use --gpus 1")
         sys.exit(2)

@@ -653,10 +653,11 @@ struct Scheduler {
     // [2048,32768] 97.1 -> 94.3, [300,65000] 53.1 -> 47.1, [400,50000] 35.2 -> 32.5; a copy in such rows takes 144 us for the second.
     // Below 32 elements per lane two workgroups share a unit, which is better ([4096,20000] 108.8 against 115.0).  Rows that start
     // inside a vector cross to LDS in 4-byte pieces, which eats the gain ([2048,33001] 104.7 against 106.3) but for a few rows
-    // ([400,50001] 37.8 -> 33.7).
-    bool rowv = false;
+    // ([400,50001] 37.8 -> 33.7).  Only for kernels that write rows: all that was measured and checked did.
+    bool rowv = false, writes = false;
     for (const ExtTensor& e : gp->ext_in) rowv |= e.kind == KIND_ROWV;
-    s.ahead = opt.ahead && rowred && !colred && !chunked && !resident && !has_transposed && !has_concat && CT == 1 && s.G == 1 && WG == 1024 && s.E >= 32 && row_inputs == 1 && !rowv &&
+    for (const ExtTensor& e : gp->ext_out) writes |= e.kind == KIND_FULL;
+    s.ahead = opt.ahead && writes && rowred && !colred && !chunked && !resident && !has_transposed && !has_concat && CT == 1 && s.G == 1 && WG == 1024 && s.E >= 32 && row_inputs == 1 && !rowv &&
               whole_lanes && (C % V == 0 ? R > CUS : max_es == 4 && R > CUS && R <= 2 * CUS);
     if (s.ahead) {
       const int lds = opt.lds_budget_given ? opt.lds_budget : device_limits().lds_per_workgroup;

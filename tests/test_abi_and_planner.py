@@ -1627,3 +1627,19 @@ def test_the_kernels_a_run_launches():
         for name in names:
             assert any("__global__" in src and name + "(const" in src for src in [src for _, _, src in p.joined_groups()] + [p.group_source(k) for k in range(groups)])
         p.destroy()
+
+
+@pytest.mark.parametrize("rows,cols", [(8192, 32768), (1024, 65536)])
+def test_long_rows_that_write_no_rows_are_not_asked_for_ahead(rows, cols):
+    from workloads.patterns import logsumexp
+    p = fs.Plan(logsumexp(rows, cols))
+    assert "fs_row_ask<" not in p.group_source(0)
+    p.destroy()
+
+
+def test_the_survey_is_switched_off():
+    # until the cause of the fault that a run of it ended in is known
+    import subprocess
+    import sys
+    r = subprocess.run([sys.executable, os.path.join(ROOT, "bench.py"), "--survey"], capture_output=True, text=True, timeout=300)
+    assert r.returncode != 0 and "switched off" in r.stderr
