@@ -37,8 +37,8 @@
  *                          compilation fails
  *   FS_JOIN_WAIT_TICKS     read by plan creation: how long, in ticks of 10 ns, workgroups
  *                          of a kernel wait for each other before they do each other's
- *                          work or leave it to the last one (default 5000; 0: not at
- *                          all).  Results are the same bits; it is there for tests
+ *                          work (default 5000) or leave it to the last one (10000); 0:
+ *                          not at all.  Results are the same bits; it is there for tests
  */
 #ifndef FS_H_
 #define FS_H_

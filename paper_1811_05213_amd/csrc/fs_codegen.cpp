@@ -1119,7 +1119,7 @@ struct Emitter {
       os << "  float* const lds_tile = lds_pool; float* const lds_rowv = lds_pool + TILE_FLOATS; float* const lds_col = " << (s.ahead ? "(float*)lds_ahead" : "lds_pool") << ";\n";
       os << "  (void)lds_tile; (void)lds_rowv; (void)lds_col; (void)SLOT; (void)PC;\n";
     }
-    if (K > 0) os << "  __shared__ fs_u32 lds_flag;\n";
+    if (K > 0) os << "  __shared__ fs_u32 lds_flag" << (s.meet ? "[9]" : "") << ";\n";
 
     // ---- per-column values ----
     // (looping kernels without LDS staging: loaded into registers once per workgroup, before the loop)
@@ -1551,26 +1551,33 @@ struct Emitter {
            << ", cv, lds_col, lir, rg, " << (ctile ? "vbase" : "0") << ");\n";
       }
       const std::string part = "a.part + (long)tile * " + std::to_string(s.part_stride_floats) + "L", tickets = "a.tickets + tile * " + std::to_string(s.ticket_stride);
+      auto store_results = [&](const std::string& value) {
+        os << "          const int k = c / S::CH; const fs_col_index<C>::type col0 = (fs_col_index<C>::type)tile * CW + (c % S::CH) * FV;\n";
+        for (int k = 0; k < K; ++k) {
+          const int m = gp.col_reduces[k];
+          const ExtTensor* e = find_out(m);
+          if (!e) continue;
+          const fs_node& n = g.nodes[m];
+          os << "          if (k == " << k << ") { _Pragma(\"unroll\") for (int f = 0; f < FV; ++f) if (col0 + f < C) fs_store1<" << e->dtype
+             << ">(a.p[" << e->arg << "], col0 + f, " << value << "[f]" << (n.attr_i == FS_RED_MEAN ? " / (float)a.R" : "") << "); }\n";
+        }
+      };
       if (s.meet) {
-        os << "    const int met = fs_colred_meet<" << K << ", CW, WG, FV>(cv, " << part << ", " << tickets << ", &lds_flag, (fs_u32)rb, (fs_u32)RB, " << gp.wait_ticks << ");\n"
-           << "    constexpr int SC = " << s.meet << ";\n    for (int all = 0; all < met && (all == 0 || fs_colred_left(&lds_flag)); ++all) {\n"
-           << "      for (int sl = all ? 0 : rb; sl * SC < S::NCH; sl += all ? 1 : RB) {\n"
-           << "        fs_colred_slice<" << K << ", CW, WG, FV, SC, RB, " << kname << "_kinds>(cv[0], " << part << ", lds_col, sl);\n"
-           << "        constexpr int i = 0;\n        const int c = sl * SC + tid;\n        if (tid < SC && c < S::NCH) {\n";
+        const std::string fold = std::to_string(K) + ", CW, WG, FV, SC, RB, " + kname + "_kinds";
+        os << "    const int met = fs_colred_meet<" << K << ", CW, WG, FV>(cv, " << part << ", " << tickets << ", lds_flag, (fs_u32)rb, (fs_u32)RB, " << gp.wait_ticks << ");\n"
+           << "    constexpr int SC = " << s.meet << ";\n    for (int sl = rb; met && sl * SC < S::NCH; sl += RB) {\n"
+           << "      fs_colred_slice<" << fold << ">(cv[0], " << part << ", lds_col, sl);\n        const int c = sl * SC + tid;\n        if (tid < SC && c < S::NCH) {\n";
+        store_results("cv[0]");
+        os << "        }\n    }\n    if (met == 2 && fs_colred_left(lds_flag)) {\n      for (int c = tid; c < S::NCH; c += WG)\n        if (fs_colred_gone(lds_flag, c / SC % RB)) {\n"
+           << "          fs_colred_alone<" << fold << ">(cv[0], " << part << ", c);\n";
+        store_results("cv[0]");
+        os << "        }\n    }\n";
       } else {
         os << "    if (fs_colred_fold_grid<" << K << ", CW, WG, FV, " << s.fan_in << ", " << kname << "_kinds>(cv, " << part << ", " << tickets << ", &lds_flag, (fs_u32)rb, (fs_u32)RB)) {\n"
            << "      _Pragma(\"unroll\") for (int i = 0; i < S::CPT; ++i) {\n        const int c = tid + i * WG;\n        if (c < S::NCH) {\n";
+        store_results("cv[i]");
+        os << "        }\n      }\n    }\n";
       }
-      os << "          const int k = c / S::CH; const fs_col_index<C>::type col0 = (fs_col_index<C>::type)tile * CW + (c % S::CH) * FV;\n";
-      for (int k = 0; k < K; ++k) {
-        const int m = gp.col_reduces[k];
-        const ExtTensor* e = find_out(m);
-        if (!e) continue;
-        const fs_node& n = g.nodes[m];
-        os << "          if (k == " << k << ") { _Pragma(\"unroll\") for (int f = 0; f < FV; ++f) if (col0 + f < C) fs_store1<" << e->dtype
-           << ">(a.p[" << e->arg << "], col0 + f, cv[i][f]" << (n.attr_i == FS_RED_MEAN ? " / (float)a.R" : "") << "); }\n";
-      }
-      os << "        }\n      }\n    }\n";
       os << "  }\n";
     }
     os << "}\n";

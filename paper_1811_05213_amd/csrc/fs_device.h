@@ -947,15 +947,17 @@ FS_DEV bool fs_colred_fold_grid(float (&vals)[CPT][FV], float* part, fs_u32* tic
 //   fs_colred_meet   leaves this workgroup's partial and waits until the others have: 1 they have (fold your slices), 2 they have, and this
 //                    is the last one, 0 they have not after `ticks` of the 100 MHz clock (leave: nothing waits for workgroups that the
 //                    device has not started).
-//   fs_colred_left   of the last one: has any left?  (Then it folds all slices.)
+//   fs_colred_left   of the last one: has any left?  (Then it folds their slices.)
 //   counters         [0] groups of 16 workgroups that are complete, [32 * (1 + g)] workgroups of group g that have arrived (256 on one
 //                    counter take 10 us), then a door for each workgroup, opened by the last one.  Zero, and left zero: by the last
 //                    workgroup of a group, the last of all, who passes a door, and, where a workgroup has left, by the last of all.
-//   fs_colred_slice  slice `sl`: SC chunks of FV columns; lanes SC apart take a partial each, and fold in pairs.  In this order whoever
-//                    folds.  The results are those of chunks sl * SC + lane in the first SC lanes.
+//   fs_colred_slice  slice `sl`: SC chunks of FV columns; lanes SC apart take a partial each, and fold in pairs.  The results are those of
+//                    chunks sl * SC + lane in the first SC lanes.
+//   fs_colred_alone  one chunk by one lane, in the same order, for the slices of those who have left: slices one after the other are a
+//                    chain of round trips (LayerNorm backward fp32 [8192,4096] beside a streaming kernel of another stream 1010 us).
 FS_DEV fs_u32* fs_colred_door(fs_u32* counters, fs_u32 idx, fs_u32 n) { return counters + 32 * (1 + (n + 15) / 16) + idx; }
 template <int K, int C, int WG, int FV, int CPT>
-FS_DEV int fs_colred_meet(const float (&vals)[CPT][FV], float* part, fs_u32* counters, fs_u32* flag, fs_u32 idx, fs_u32 n, int ticks) {
+FS_DEV int fs_colred_meet(const float (&vals)[CPT][FV], float* part, fs_u32* counters, fs_u32* flag /* and 8 words: who has left */, fs_u32 idx, fs_u32 n, int ticks) {
   typedef fs_colfold<K, C, WG, FV> S;
   static_assert(CPT == S::CPT, "chunks per thread");
   constexpr int KC = K * C;
@@ -994,12 +996,14 @@ FS_DEV int fs_colred_meet(const float (&vals)[CPT][FV], float* part, fs_u32* cou
   __syncthreads();
   const int met = (int)*flag;
   if (met == 2) {
+    if (t < 8) flag[1 + t] = 0;
     __syncthreads();  // (every wavefront has read the flag before one writes it again)
     for (fs_u32 i = (fs_u32)t; i < n; i += WG) {
       fs_u32* const door = fs_colred_door(counters, i, n);
       if (i != idx && __hip_atomic_exchange(door, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == 2u) {
         __hip_atomic_store(door, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         __hip_atomic_store(flag, 3u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        (void)__hip_atomic_fetch_or(&flag[1 + i / 32], 1u << (i & 31), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
       }
     }
   }
@@ -1056,6 +1060,48 @@ FS_DEV void fs_colred_slice(float (&vals)[FV], const float* part, float* lds /* 
   }
 #pragma unroll
   for (int f = 0; f < FV; ++f) vals[f] = a[f];
+}
+
+FS_DEV bool fs_colred_gone(const fs_u32* flag, int idx) { return (flag[1 + idx / 32] >> (idx & 31) & 1) != 0; }
+template <int K, int C, int WG, int FV, int SC, int N, typename KINDS>
+FS_DEV void fs_colred_alone(float (&vals)[FV], const float* part, int c) {
+  typedef fs_colfold<K, C, WG, FV> S;
+  constexpr int KC = K * C, H = WG / SC, PS = (N + H - 1) / H, Q = 64 / SC, QB = Q < 8 ? Q : 8;  // (as in fs_colred_slice; Q lanes of a wavefront to a chunk)
+  const int k = c / S::CH;
+  const __amdgpu_buffer_rsrc_t all = fs_make_rsrc(part, N * (KC * 4));
+  for (int w = 0; w < WG / 64; ++w) {
+    float wave[Q / QB][FV];
+#pragma unroll
+    for (int b = 0; b < Q / QB; ++b) {
+      float v[FV][QB];
+#pragma unroll
+      for (int f = 0; f < FV; ++f)
+#pragma unroll
+        for (int q = 0; q < QB; ++q) v[f][q] = KINDS::identity(k);
+      for (int i = 0; i < PS; ++i) {
+        float tmp[QB][FV];
+#pragma unroll
+        for (int q = 0; q < QB; ++q) {
+          const int j = i * H + w * Q + b * QB + q;
+          fs_load_dev<FV>(tmp[q], all, (fs_u32)(j < N ? j : N - 1) * (KC * 4) + (fs_u32)c * (FV * 4));
+        }
+#pragma unroll
+        for (int q = 0; q < QB; ++q)
+#pragma unroll
+          for (int f = 0; f < FV; ++f) v[f][q] = i * H + w * Q + b * QB + q < N ? KINDS::op(k, v[f][q], tmp[q][f]) : v[f][q];
+      }
+#pragma unroll
+      for (int f = 0; f < FV; ++f) {
+        fs_pairs<QB>(v[f], [&](float x, float y) { return KINDS::op(k, x, y); });
+        wave[b][f] = v[f][0];
+      }
+    }
+#pragma unroll
+    for (int f = 0; f < FV; ++f) {
+      const float x = Q / QB > 1 ? KINDS::op(k, wave[0][f], wave[Q / QB - 1][f]) : wave[0][f];
+      vals[f] = w == 0 ? x : KINDS::op(k, vals[f], x);
+    }
+  }
 }
 
 // ------------------------------------------------------------------------------------------

@@ -21,11 +21,13 @@ bool tiles_share_lines(const GroupPlan& gp) {
   return shared && gp.s.CT >= 5 && gp.s.grid >= 64;
 }
 
-// how long workgroups wait for each other before they do each other's work (joined kernels) or leave the rest to the last one (column folds):
-// 50 us, several times what those of the largest tiles need from their start to the last load
-int wait_ticks() {
+// How long workgroups wait for each other: several times what those of the largest kernels need from their start to the last load.  Joined
+// kernels 50 us, before they do each other's work.  Column folds 100 us, before they leave the rest to the last one: beside a streaming
+// kernel of another stream LayerNorm backward fp32 [8192,4096] takes 209 us with that, 225 with 50 us, 232 with 20 (201 with the tree), moments
+// [16384,2048] 178, 216, 261 (183); [5000,3000] beside a long softmax 102, 113, 216 (102).
+int wait_ticks(int ticks) {
   const char* e = getenv("FS_JOIN_WAIT_TICKS");
-  return e ? atoi(e) : 5000;
+  return e ? atoi(e) : ticks;
 }
 
 int pow2_floor(int x) {
@@ -784,10 +786,11 @@ struct Scheduler {
     if (opt.meet && colred && !col_tiled && s.RB > s.fan_in && s.RB <= CUS && (int64_t)gp->col_reduces.size() * fold_width >= 4096) {
       const int FV = fold_vector(fold_width), chunks = (int)gp->col_reduces.size() * (fold_width / FV);
       const int SC = std::max(16 / FV, std::min(64, pow2_ceil((chunks + s.RB - 1) / s.RB))), meet_bytes = WG / 64 * SC * FV * 4;
-      if (fixed + std::max({loop_bytes, fold_bytes, meet_bytes}) <= opt.lds_budget) {
+      if (fixed + 32 + std::max({loop_bytes, fold_bytes, meet_bytes}) <= opt.lds_budget) {
         s.meet = SC;
+        fixed += 32;  // (who has left)
         fold_bytes = std::max(fold_bytes, meet_bytes);
-        gp->wait_ticks = wait_ticks();
+        gp->wait_ticks = wait_ticks(10000);
       }
     }
     // Rows asked for ahead in kernels that reduce rows and columns (columns_ahead): without that one workgroup to a compute unit has
@@ -1834,7 +1837,7 @@ fs_status join_groups(const Graph& g, const std::vector<GroupPlan>& groups, int 
     gp.n_tickets = s.ticket_stride * s.CT;
     gp.part_bytes = s.part_stride_floats * s.CT * 4;
   }
-  gp.wait_ticks = wait_ticks();
+  gp.wait_ticks = wait_ticks(5000);
   if (s.WG >= 512 && tiles_share_lines(gp)) s.xcd_rows = 8;  // (smaller tensors: [4096,333] 10.0 against 10.2, [2000,1002] 10.4 against 10.6)
   return FS_OK;
 }

@@ -46,7 +46,7 @@ static fs_u32 counters[32 * 3 + N];
 
 struct Workgroup {
   pthread_barrier_t bar;
-  fs_u32 flag = 0;
+  fs_u32 flag[9] = {};
   int met[WG], folds[WG], ticks;
   std::vector<std::thread> lanes;
   void start(int idx, int t) {
@@ -57,12 +57,12 @@ struct Workgroup {
         threadIdx.x = k;
         barrier = &bar;
         float vals[2][1] = {{1.0f}, {2.0f}};
-        met[k] = fs_colred_meet<1, 32, WG, 1>(vals, part, counters, &flag, (fs_u32)idx, N, ticks);
-        folds[k] = 0;
-        for (int all = 0; all < met[k] && (all == 0 || fs_colred_left(&flag)); ++all) ++folds[k];  // as the generated kernels do
+        met[k] = fs_colred_meet<1, 32, WG, 1>(vals, part, counters, flag, (fs_u32)idx, N, ticks);
+        folds[k] = met[k] != 0;  // (its own slices; as the generated kernels do)
+        if (met[k] == 2 && fs_colred_left(flag)) ++folds[k];
       });
   }
-  // 0 left, 1 its slices, 2 all slices as well; -1 where its lanes disagree
+  // 0 left, 1 its slices, 2 those of workgroups that have left as well; -1 where its lanes disagree
   int end(int* saw) {
     for (std::thread& t : lanes) t.join();
     pthread_barrier_destroy(&bar);
@@ -86,6 +86,8 @@ static int scenario(int gone) {
   for (Workgroup& g : rest) {
     const int folds = g.end(&saw);
     lasts += saw == 2;
+    if (saw == 2 && gone > 0)
+      for (int w = 0; w < N; ++w) wrong += (g.flag[1 + w / 32] >> (w & 31) & 1) != (w < gone);
     wrong += folds != (saw == 2 && gone > 0 ? 2 : 1);
   }
   for (fs_u32 c : counters) wrong += c != 0;

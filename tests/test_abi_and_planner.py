@@ -1643,3 +1643,12 @@ def test_the_survey_is_switched_off():
     import sys
     r = subprocess.run([sys.executable, os.path.join(ROOT, "bench.py"), "--survey"], capture_output=True, text=True, timeout=300)
     assert r.returncode != 0 and "switched off" in r.stderr
+
+
+def test_the_last_of_meeting_workgroups_folds_what_others_left():
+    # a chunk to a lane, and only slices of workgroups that have left: one slice after the other takes a millisecond
+    p = fs.Plan(rows_and_columns_graph(6144, 4096, "f32", 2, 1))
+    src = p.group_source(0)
+    alone = src.index("fs_colred_alone<")
+    assert "fs_colred_gone(" in src[alone - 200:alone] and src.count("fs_colred_slice<") == 1 and "sl += RB" in src
+    p.destroy()

@@ -1502,6 +1502,40 @@ def test_workgroups_meet_to_fold_columns(rows, cols, dt, folds, writes, monkeypa
     p.destroy()
 
 
+def test_workgroups_meet_beside_work_of_another_stream():
+    # some leave before the others have started: the same bits, and counters that return to zero
+    import torch
+    from test_abi_and_planner import rows_and_columns_graph
+    g = rows_and_columns_graph(3072, 8192, "f32", 2, 1)
+    p = fs.Plan(g)
+    assert "fs_colred_meet<" in p.group_source(0)
+    r = DeviceRun(p)
+    r.set_inputs([RNG.standard_normal((3072, 8192)).astype(np.float32), RNG.uniform(0.5, 2, (3072, 1)).astype(np.float32)])
+    p.load()
+    r.launch()
+    first = r.results()
+    e = Graph()
+    e.set_outputs([e.unary("tanh", e.input(8192, 8192))])
+    q = fs.Plan(e)
+    other = DeviceRun(q)
+    other.set_inputs([RNG.standard_normal((8192, 8192)).astype(np.float32)])
+    q.load()
+    mine, theirs = torch.cuda.Stream(), torch.cuda.Stream()
+    torch.cuda.synchronize()
+    for _ in range(15):
+        with torch.cuda.stream(theirs):
+            for _ in range(3):
+                other.launch()
+        with torch.cuda.stream(mine):
+            r.launch()
+        torch.cuda.synchronize()
+        for a, b in zip(first, r.results()):
+            np.testing.assert_array_equal(a.view(np.uint32), b.view(np.uint32))
+    p.workspace_check(r.workspace.data_ptr(), r.ws_bytes)
+    p.destroy()
+    q.destroy()
+
+
 # ------------------------------------------------------------------ neighbouring rows on one XCD
 @pytest.mark.parametrize("rows", [127, 128, 129, 600])
 @pytest.mark.parametrize("transposed", [0, 1])
