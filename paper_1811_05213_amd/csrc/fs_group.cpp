@@ -1267,7 +1267,7 @@ namespace {
 // Section 2.2): a column reduction finished inside a kernel costs a ticketed grid-wide fold, a few
 // microseconds of latency.  That is hidden behind the streaming of a large group, but for a
 // launch-bound group it is dearer than the launch it saves, so small groups do not take one in.
-bool worth_fusing(const GroupPlan& merged) {
+bool worth_fusing(const GroupPlan& merged, bool apart) {
   constexpr uint64_t kFoldWorthBytes = 16ull << 20;
   // A transposed root that cannot leave through an LDS tile (rows spread over a whole workgroup)
   // is written element by element, R elements apart: an order of magnitude slower than handing
@@ -1295,9 +1295,10 @@ bool worth_fusing(const GroupPlan& merged) {
   // Beside row reductions the fold costs what a workgroup's partial weighs, which is what a row holds, and a kernel of its own costs another
   // read of the rows.  Tall tensors pay from 8.5 MB on (column sums + row norms fp32 [65536,33] 14.4 us in kernels side by side, 10.0 in one,
   // [16384,200] 12.4 and 10.3, LayerNorm backward [16384,64] 12.9 and 9.5; [16384,128], 8.4 MB, 8.0 and 8.7).  Below 2048 rows the fold weighs
-  // more than the read as long as the kernels share a launch or nearly so, to 32 MB ([1421,3392] 13.5 and 16.2, LayerNorm backward [400,5000] 12.5
-  // and 17.4, [1300,2000] 15.0 and 21.4; but [1500,8000], 48 MB, 30.8 and 23.2, LayerNorm backward [1500,3000], 54 MB, 25.2 and 20.4).
-  const uint64_t beside = merged.R >= 8192 ? 8500000 : merged.R >= 2048 ? kFoldWorthBytes : 32000000;
+  // more than the read, to 32 MB, as long as the kernels only read the same tensors (apart, folds_exchange_rows: [1421,3392] 13.3 and 16.0, [1000,5000] 11.4
+  // and 17.3, LayerNorm backward [400,5000] 12.3 and 17.3, [1300,2000] 15.3 and 18.3, [300,8192] 12.8 and 18.6; but [1500,8000], 48 MB, 30.8 and 23.2, LayerNorm
+  // backward [1500,3000], 54 MB, 25.2 and 20.4).
+  const uint64_t beside = merged.R >= 8192 ? 8500000 : merged.R >= 2048 || !apart ? kFoldWorthBytes : 32000000;
   const uint64_t worth = flipped >= 2 && merged.exchanges && !merged.row_reduces.empty() ? 64ull << 20 : merged.row_reduces.empty() ? kFoldWorthBytes : beside;
   return merged.col_reduces.empty() || merged.members.size() == 1 || merged.s.grid == 1 || narrow || (merged.row_reduces.empty() ? merged.min_hbm_bytes : merged.fold_bytes) >= worth;
 }
@@ -1416,7 +1417,7 @@ struct Former {
           if (cycle) continue;
           std::vector<int> merged = members[a];
           merged.insert(merged.end(), members[b].begin(), members[b].end());
-          if (analyse_group(g, merged, group_of, (int)a, opt, &merged_plan) != FS_OK || !worth_fusing(merged_plan)) {
+          if (analyse_group(g, merged, group_of, (int)a, opt, &merged_plan) != FS_OK || !worth_fusing(merged_plan, opt.folds_apart)) {
             refused[{a, b}] = {version[a], version[b]};
             continue;
           }
@@ -1514,7 +1515,7 @@ struct Former {
             if (ok) {  // test 3: an optimised schedule (and LDS plan) for the fused computation exists
               std::vector<int> merged = members[grp];
               merged.push_back(hlo);
-              ok = (int)merged.size() <= 96 && analyse_group(g, merged, group_of, grp, opt, &scratch) == FS_OK && worth_fusing(scratch);
+              ok = (int)merged.size() <= 96 && analyse_group(g, merged, group_of, grp, opt, &scratch) == FS_OK && worth_fusing(scratch, opt.folds_apart);
             }
             if (ok) {
               group_of[hlo] = grp;
@@ -1622,7 +1623,7 @@ fs_status form_groups(const Graph& g, const fs_graph_desc* desc, const PlanOptio
         merged.push_back(id);
         if ((int)merged.size() > kMaxGroupMembers) continue;
         if (analyse_group(g, merged, f.group_of, grp, opt, &scratch) != FS_OK) continue;
-        if (!worth_fusing(scratch)) continue;
+        if (!worth_fusing(scratch, opt.folds_apart)) continue;
         joined = grp;
         break;
       }
@@ -1754,7 +1755,7 @@ void recompute_across_kernels(const Graph& g, const PlanOptions& opt, std::vecto
           before += gps[kv.first].min_hbm_bytes;
           after += np[kv.first].min_hbm_bytes;
         }
-        if (!fits || after >= before || !worth_fusing(np[b])) continue;
+        if (!fits || after >= before || !worth_fusing(np[b], opt.folds_apart)) continue;
         // a kernel that changes its form for the copy (rows no longer held in registers, another launch shape class) is not worth it
         if (np[b].s.chunked != gps[b].s.chunked || np[b].s.split_rows != gps[b].s.split_rows || np[b].s.col_tiled != gps[b].s.col_tiled) continue;
         for (auto& kv : mm) {
@@ -1928,6 +1929,30 @@ fs_status join_groups(const Graph& g, const std::vector<GroupPlan>& groups, int 
   gp.wait_ticks = wait_ticks(5000);
   if (s.WG >= 512 && tiles_share_lines(gp)) s.xcd_rows = 8;  // (smaller tensors: [4096,333] 10.0 against 10.2, [2000,1002] 10.4 against 10.6)
   return FS_OK;
+}
+
+// Folds of a few long rows that were kept out of the kernels beside them (worth_fusing) read the same tensors then, or values that they compute
+// again from a number a row.  Where [R,C] values pass through memory between them instead, two or three launches follow each other in the
+// place of one: column sums of a row softmax fp32 [400,8192] 25.4 us apart and 18.9 in one, [1900,2000] 25.9 and 17.1, of x less its row maximum [1500,3000]
+// 27.0 and 14.3, [2000,3900] 33.9 and 18.6 (8192 columns that leave as well, [400,8192], 15.7 and 18.4).  Nor does a single fold pay that
+// waits for numbers of the rows: column sum of a row softmax [300,8192] 11.2 and 12.4, [1000,2500] 13.9 and 11.8, [1900,2100] 19.3 and 14.8, two sums
+// [300,8192] 12.1 and 17.6, [1300,2000] 14.7 and 16.7.
+bool folds_exchange_rows(const Graph& g, const std::vector<std::vector<int>>& ordered, const std::vector<int>& group_of, const PlanOptions& opt) {
+  std::vector<GroupPlan> groups(ordered.size());
+  std::map<int, size_t> stored_by;
+  for (size_t k = 0; k < ordered.size(); ++k) {
+    if (analyse_group(g, ordered[k], group_of, (int)k, opt, &groups[k]) != FS_OK) return false;  // (reported where the kernels are made)
+    for (const ExtTensor& e : groups[k].ext_out) stored_by[e.node] = k;
+  }
+  auto folds = [&](size_t k) { return !groups[k].col_reduces.empty() && groups[k].R < 2048; };
+  for (size_t k = 0; k < groups.size(); ++k)
+    for (const ExtTensor& e : groups[k].ext_in) {
+      auto it = stored_by.find(g.root_of[e.node]);
+      if (it == stored_by.end() || it->second == k) continue;
+      if (e.kind == KIND_FULL && (folds(k) || folds(it->second))) return true;
+      if (e.kind == KIND_COLV && folds(k) && groups[k].col_reduces.size() == 1) return true;
+    }
+  return false;
 }
 
 // -------------------------------------------------------------------------------------------

@@ -261,6 +261,7 @@ struct PlanOptions {
   int wide_level = 2;
   bool narrow_tiles = true;  // column folds may take narrow tiles (plan creation gives them up where the compiled kernel spills)
   bool meet = true;   // the workgroups of a column fold may meet
+  bool folds_apart = true;  // column folds of a few long rows may stay out of the kernels beside them (worth_fusing)
   bool grouped = false;  // the groups are final: schedules no longer decide what is fused
   bool lead = true;   // rows may be held in pieces of whole cache lines
   bool ahead = true;  // long rows may be asked for one ahead (given up where the compiled kernel spills)
@@ -288,6 +289,8 @@ fs_status form_groups(const Graph& g, const fs_graph_desc* desc, const PlanOptio
 // Adds the copies to the consumers' member lists and records them in `clones`.
 void recompute_across_kernels(const Graph& g, const PlanOptions& opt, std::vector<int>* group_of,
                               std::vector<std::vector<int>>* groups_in_launch_order, CloneInfo* clones);
+// Whether column folds that stay out of the kernels beside them wait for what those write (then they are formed again, folds_apart = false).
+bool folds_exchange_rows(const Graph& g, const std::vector<std::vector<int>>& ordered, const std::vector<int>& group_of, const PlanOptions& opt);
 
 // Groups [first, first + count) of a plan as one kernel whose workgroups keep their rows in registers while the column
 // reductions of a tile are folded across workgroups.  FS_ERR_UNSUPPORTED where they are not of that form or do not fit.

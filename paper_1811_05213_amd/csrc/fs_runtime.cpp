@@ -330,24 +330,29 @@ fs_status fs_plan_create(const fs_graph_desc* desc, fs_plan** out_plan) {
     }
   }
 
-  std::vector<std::vector<int>> ordered;
-  st = form_groups(plan->graph, desc, plan->opt, &plan->group_of, &ordered);
-  if (st != FS_OK) {
-    delete plan;
-    return st;
-  }
   const Graph& g = plan->graph;
-  plan->groups.resize(ordered.size());
-  // group ids follow launch order
-  for (size_t gi = 0; gi < ordered.size(); ++gi)
-    for (int m : ordered[gi]) plan->group_of[m] = (int)gi;
-  // the library's own grouping may compute a cheap value in two kernels rather than pass it through memory
-  // (a caller's plan and the one-launch-per-op executor are taken as they are)
-  if (plan->opt.mode != FS_MODE_UNFUSED && !desc->group_of_node) {
+  std::vector<std::vector<int>> ordered;
+  for (;;) {
+    st = form_groups(g, desc, plan->opt, &plan->group_of, &ordered);
+    if (st != FS_OK) {
+      delete plan;
+      return st;
+    }
+    // group ids follow launch order
+    for (size_t gi = 0; gi < ordered.size(); ++gi)
+      for (int m : ordered[gi]) plan->group_of[m] = (int)gi;
+    // the library's own grouping may compute a cheap value in two kernels rather than pass it through memory
+    // (a caller's plan and the one-launch-per-op executor are taken as they are)
+    if (plan->opt.mode == FS_MODE_UNFUSED || desc->group_of_node) break;
     recompute_across_kernels(g, plan->opt, &plan->group_of, &ordered, &plan->clones);
     plan->opt.clones = &plan->clones;
-    plan->groups.resize(ordered.size());
+    if (!plan->opt.folds_apart || !folds_exchange_rows(g, ordered, plan->group_of, plan->opt)) break;
+    plan->opt.folds_apart = false;
+    plan->opt.clones = nullptr;
+    plan->clones = CloneInfo();
+    ordered.clear();
   }
+  plan->groups.resize(ordered.size());
   plan->opt.grouped = plan->opt.mode != FS_MODE_UNFUSED && !desc->group_of_node;
   for (size_t gi = 0; gi < ordered.size(); ++gi) {
     st = analyse_group(g, ordered[gi], plan->group_of, (int)gi, plan->opt, &plan->groups[gi]);
