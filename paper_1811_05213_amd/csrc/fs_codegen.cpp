@@ -1194,14 +1194,14 @@ struct Emitter {
       if (s.lead) os << ind << "const int ask_lead = (int)(" << row0 << " & (LEAD - 1));\n";
       for (const ExtTensor& e : gp.ext_in) {
         if (e.kind != KIND_FULL) continue;
-        const std::string nt = e.streaming ? "true" : "false", p = "a.p[" + std::to_string(e.arg) + "]";
-        os << ind << "fs_row_ask<" << e.dtype << ", V, L, NV, RAGGED, WG, JL, " << nt << ">(lds_ahead + " << k++ << " * (JL * WG * 16), " << p << ", " << row0
+        const std::string nt = e.streaming ? "true" : "false", ua = over && !s.lead ? "true" : "false", p = "a.p[" + std::to_string(e.arg) + "]";
+        os << ind << "fs_row_ask<" << e.dtype << ", V, L, NV, RAGGED, WG, JL, " << ua << ", " << nt << ">(lds_ahead + " << k++ << " * (JL * WG * 16), " << p << ", " << row0
            << (s.lead ? " - ask_lead" : "") << ", lir, tid);\n";
         if (s.ahead_lds < s.NVL && s.lead)
           os << ind << "_Pragma(\"unroll\") for (int j = JL; j < NVL; ++j) n" << loc(e.node) << "[j - JL] = fs_lead_load_raw<" << e.dtype << ", V, L, C, " << nt << ">(" << p << ", " << row0
              << ", ask_lead, lir, " << row0 << " == (R - 1) * C, j);\n";
         else if (s.ahead_lds < s.NVL)
-          os << ind << "_Pragma(\"unroll\") for (int j = JL; j < NVL; ++j) n" << loc(e.node) << "[j - JL] = fs_load_raw<" << e.dtype << ", V, " << nt << ">(" << p << ", " << row0
+          os << ind << "_Pragma(\"unroll\") for (int j = JL; j < NVL; ++j) n" << loc(e.node) << "[j - JL] = fs_load_raw<" << e.dtype << ", V, " << nt << ", " << ua << ">(" << p << ", " << row0
              << " + fs_col_of<V, NV, RAGGED>(j * L + lir));\n";
       }
     };

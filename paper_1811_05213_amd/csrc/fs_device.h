@@ -373,19 +373,29 @@ template <int DT, int V, int NVL, int L> FS_DEV void fs_load_row_chunk_lds(float
 // The next rows on their way while rows are worked on: the first JL vectors of a lane go from memory to LDS without passing
 // registers, the rest waits in registers of their own.  A wavefront reads back what it asked for itself, 64 lanes x 16 bytes that
 // follow each other, so only its own counter of outstanding accesses orders the two; the compiler does not see that dependence, the
-// waits are spelled out (fs_wait_vm).
+// waits are spelled out (fs_wait_vm).  Rows that start inside a vector (UA; whole vectors of one row to a workgroup) are asked for
+// in 4-byte pieces.
 #define FS_LDS_BYTES(p) ((__attribute__((address_space(3))) void*)(p))
 #define FS_GLOBAL_BYTES(p) ((const __attribute__((address_space(1))) void*)(p))
-template <int DT, int V, int L, int NV, int RAGGED, int WG, int JL, bool NT> FS_DEV void fs_row_ask(fs_u8* lds, const void* base, long row_elem0, int lir, int tid) {
+template <int DT, int V, int L, int NV, int RAGGED, int WG, int JL, bool UA, bool NT> FS_DEV void fs_row_ask(fs_u8* lds, const void* base, long row_elem0, int lir, int tid) {
   typedef typename fs_elem<DT>::type T;
-  static_assert(V * sizeof(T) == 16 && WG % 64 == 0, "16 bytes to a lane");
+  static_assert(V * sizeof(T) == 16 && WG % 64 == 0 && (!UA || (sizeof(T) == 4 && L == WG)), "16 bytes to a lane");
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
 #pragma unroll
   for (int j = 0; j < JL; ++j) {
     fs_u8* const to = lds + (j * (WG / 64) + wave) * 1024;
-    const T* const from = static_cast<const T*>(base) + row_elem0 + fs_col_of<V, NV, RAGGED>(j * L + lir);
-    if constexpr (NT) __builtin_amdgcn_global_load_lds(FS_GLOBAL_BYTES(from), FS_LDS_BYTES(to), 16, 0, 2);
-    else __builtin_amdgcn_global_load_lds(FS_GLOBAL_BYTES(from), FS_LDS_BYTES(to), 16, 0, 0);
+    if constexpr (UA) {
+      const T* const from = static_cast<const T*>(base) + row_elem0 + (j * L + wave * 64) * V + (lir & 63);
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        if constexpr (NT) __builtin_amdgcn_global_load_lds(FS_GLOBAL_BYTES(from + q * 64), FS_LDS_BYTES(to + q * 256), 4, 0, 2);
+        else __builtin_amdgcn_global_load_lds(FS_GLOBAL_BYTES(from + q * 64), FS_LDS_BYTES(to + q * 256), 4, 0, 0);
+      }
+    } else {
+      const T* const from = static_cast<const T*>(base) + row_elem0 + fs_col_of<V, NV, RAGGED>(j * L + lir);
+      if constexpr (NT) __builtin_amdgcn_global_load_lds(FS_GLOBAL_BYTES(from), FS_LDS_BYTES(to), 16, 0, 2);
+      else __builtin_amdgcn_global_load_lds(FS_GLOBAL_BYTES(from), FS_LDS_BYTES(to), 16, 0, 0);
+    }
   }
 }
 template <int DT, int V, int NVL, int WG, int JL> FS_DEV void fs_row_take(float (&dst)[NVL * V], const fs_u8* lds, int tid) {

@@ -711,13 +711,14 @@ struct Scheduler {
     // asked for after the stores wait for them: 14-20 % slower).  softmax fp32 [1024,65536] 111.1 -> 104.3 us, [2048,50000] 160.0 -> 153.3,
     // [2048,32768] 97.1 -> 94.3, [300,65000] 53.1 -> 47.1, [400,50000] 35.2 -> 32.5; a copy in such rows takes 144 us for the second.
     // Below 32 elements per lane two workgroups share a unit, which is better ([4096,20000] 108.8 against 115.0).  Rows that are no
-    // whole vectors only in pieces of whole lines (lead_rows): a lane asks for 16 aligned bytes.  Only for kernels that write rows: all that
-    // was measured and checked did.
+    // whole vectors in pieces of whole lines (lead_rows): a lane asks for 16 aligned bytes.  Those whose pieces would need a vector more a lane cross to LDS
+    // in 4-byte pieces, which eats the gain ([2048,33001] 104.7 against 106.3) but for a few rows ([500,53247] 41.0 us, 46.4 without, [400,40959] 24.7
+    // and 28.6, [512,65535] 55.6 and 59.0; a vector more 41.2, 26.5 and 62.4).  Only for kernels that write rows: all that was measured and checked did.
     bool rowv = false, writes = false;
     for (const ExtTensor& e : gp->ext_in) rowv |= e.kind == KIND_ROWV;
     for (const ExtTensor& e : gp->ext_out) writes |= e.kind == KIND_FULL;
     s.ahead = opt.ahead && writes && rowred && !colred && !chunked && !resident && !has_transposed && !has_concat && CT == 1 && s.G == 1 && WG == 1024 && s.E >= 32 && row_inputs == 1 && !rowv &&
-              whole_lanes && R > CUS && (lead || C % V == 0);
+              whole_lanes && R > CUS && (lead || C % V == 0 || (max_es == 4 && R <= 2 * CUS));
     if (s.ahead) {
       const int lds = opt.lds_budget_given ? opt.lds_budget : device_limits().lds_per_workgroup;
       s.ahead_lds = std::min(C / (L * V), (lds - 2048) / (WG * 16));
