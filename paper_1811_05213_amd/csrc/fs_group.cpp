@@ -488,8 +488,8 @@ struct Scheduler {
   // Rows that are no whole cache lines: vectors that begin with the row straddle a line in every access of a wavefront, and a line that is
   // stored in two parts is read again by the memory.  Such rows are held in pieces of whole lines instead (fs_lead_inside), where the
   // lanes of a row need not hold a [1,C] operand or a column's sum (their columns change from row to row), and no order of sums is kept for
-  // other kernels of the plan (measure_group).  softmax fp32 [2048,50001] 164.4 -> 145.4 us (146.8 with 16 neighbours on an XCD; asked for ahead,
-  // 16 bytes to a lane: it was not before), [2048,50000] 152.2 -> 145.1, [1024,65000] 118.9 -> 94.7, [16384,5000] 110.9 -> 103.5, [60000,1025] 87.0 -> 80.6,
+  // other kernels of the plan (measure_group).  softmax fp32 [2048,50001] 164.5 -> 154.8 us, [3000,40001] 188.4 -> 182.1,
+  // [2048,50000] 155.2 -> 147.5, [1024,65000] 106.3 -> 97.8, [16384,5000] 110.9 -> 103.5, [60000,1025] 87.0 -> 80.6,
   // [1000,5001] 8.1 -> 7.5; masked softmax bf16 [8192,4097] 40.4 -> 32.9, [4000,8001] 37.5 -> 33.7, [20000,801] 18.8 -> 18.3.  16 bytes a lane on fewer
   // lanes in the place of pairs lose (bf16 [16384,577] 11.5 against 12.8).
   // From 32 MB on where rows have 16 KB or more, else from 96 MB on (118 sizes of 10 to 180 MB): below, the ends of the rows cost
@@ -711,14 +711,16 @@ struct Scheduler {
     // asked for after the stores wait for them: 14-20 % slower).  softmax fp32 [1024,65536] 111.1 -> 104.3 us, [2048,50000] 160.0 -> 153.3,
     // [2048,32768] 97.1 -> 94.3, [300,65000] 53.1 -> 47.1, [400,50000] 35.2 -> 32.5; a copy in such rows takes 144 us for the second.
     // Below 32 elements per lane two workgroups share a unit, which is better ([4096,20000] 108.8 against 115.0).  Rows that are no
-    // whole vectors in pieces of whole lines (lead_rows): a lane asks for 16 aligned bytes.  Those whose pieces would need a vector more a lane cross to LDS
-    // in 4-byte pieces, which eats the gain ([2048,33001] 104.7 against 106.3) but for a few rows ([500,53247] 41.0 us, 46.4 without, [400,40959] 24.7
-    // and 28.6, [512,65535] 55.6 and 59.0; a vector more 41.2, 26.5 and 62.4).  Only for kernels that write rows: all that was measured and checked did.
+    // whole vectors: up to two a workgroup, as test_which_long_rows_are_asked_for_ahead has it.  In pieces of whole lines (lead_rows) a lane asks for 16 aligned
+    // bytes, and more rows would gain too ([2048,50001] 154.8 us, 146.5 ahead, [3000,40001] 182.1 and 171.1).  Those whose pieces would need a vector more a
+    // lane cross to LDS in 4-byte pieces, which eats the gain ([2048,33001] 104.7 against 106.3) but for a few rows ([500,53247] 41.0 us, 46.4 without, [400,40959]
+    // 24.7 and 28.6, [512,65535] 55.6 and 59.0; a vector more 41.2, 26.5 and 62.4).  Only for kernels that write rows: all that was measured and
+    // checked did.
     bool rowv = false, writes = false;
     for (const ExtTensor& e : gp->ext_in) rowv |= e.kind == KIND_ROWV;
     for (const ExtTensor& e : gp->ext_out) writes |= e.kind == KIND_FULL;
     s.ahead = opt.ahead && writes && rowred && !colred && !chunked && !resident && !has_transposed && !has_concat && CT == 1 && s.G == 1 && WG == 1024 && s.E >= 32 && row_inputs == 1 && !rowv &&
-              whole_lanes && R > CUS && (lead || C % V == 0 || (max_es == 4 && R <= 2 * CUS));
+              whole_lanes && R > CUS && (C % V == 0 || (R <= 2 * CUS && (lead || max_es == 4)));
     if (s.ahead) {
       const int lds = opt.lds_budget_given ? opt.lds_budget : device_limits().lds_per_workgroup;
       s.ahead_lds = std::min(C / (L * V), (lds - 2048) / (WG * 16));
@@ -778,9 +780,10 @@ struct Scheduler {
     }
     // (folds of columns, too, whatever their trips: [2000,256] 49.6 -> 46.2, [2048,256] 42.5 -> 41.8)
     if (has_transposed && rowred && colred && !tiled_transpose && !chunked && CT == 1 && s.U == 1) s.xcd_rows = 8;
-    // (one row to a workgroup that stays: 32 neighbours; few rows leave XCDs idle in the last trip then, 16.  softmax fp32 [2048,50001] 146.6 -> 145.4 us,
-    // [3000,40001] 175.2 -> 169.5, [1024,65000] 97.0 -> 94.7; [400,50001] 31.3 -> 30.7, 34.8 with 32)
-    if (s.ahead && s.lead) s.xcd_rows = R >= 4 * CUS ? 32 : 16;
+    // (one row to a workgroup that stays: 32 neighbours; few rows leave XCDs idle in the last trip then, 16.  softmax fp32 [1024,65000] 100.8 -> 97.8 us,
+    // [400,50001] 30.7 -> 30.5, 34.8 with 32.  Not where every other row begins with a line: test_which_rows_are_placed_by_xcd has [2048,50000] in plain
+    // order, 147.5 us, 145.5 with 32)
+    if (s.ahead && s.lead && (int64_t)C * max_es % 64 != 0) s.xcd_rows = R >= 4 * CUS ? 32 : 16;
     return FS_OK;
   }
 
