@@ -167,6 +167,9 @@ struct Scheduler {
     return l;
   }
 
+  // whether a hint asks for several row tiles a trip: rows in pieces of whole lines and rows asked for ahead come one tile at a time
+  bool several_tiles() const { return opt.has_hint && opt.hint.tiles_per_trip >= 2 && opt.hint.tiles_per_trip <= 4; }
+
   // lanes per row that a hint asks for, 0 when it asks for none or for what the group cannot have
   int hinted_lanes() const {
     const int h = opt.has_hint ? opt.hint.lanes_per_row : 0;
@@ -500,7 +503,7 @@ struct Scheduler {
   // registers to the last vector are held in whole vectors, if not in whole lines: that suffices to ask for them ahead.
   void lead_rows() {
     int min_es = 4;
-    bool plain = opt.lead && rowred && !colred && !chunked && !resident && !split_rows && !has_transposed && !has_concat && CT == 1 && V >= 2 && L >= 8 && !gp->exchanges;
+    bool plain = opt.lead && !several_tiles() && rowred && !colred && !chunked && !resident && !split_rows && !has_transposed && !has_concat && CT == 1 && V >= 2 && L >= 8 && !gp->exchanges;
     for (const auto* list : {&gp->ext_in, &gp->ext_out})
       for (const ExtTensor& e : *list) {
         if (e.kind == KIND_FULL) min_es = std::min(min_es, dtype_size(e.dtype));
@@ -719,7 +722,7 @@ struct Scheduler {
     bool rowv = false, writes = false;
     for (const ExtTensor& e : gp->ext_in) rowv |= e.kind == KIND_ROWV;
     for (const ExtTensor& e : gp->ext_out) writes |= e.kind == KIND_FULL;
-    s.ahead = opt.ahead && writes && rowred && !colred && !chunked && !resident && !has_transposed && !has_concat && CT == 1 && s.G == 1 && WG == 1024 && s.E >= 32 && row_inputs == 1 && !rowv &&
+    s.ahead = opt.ahead && !several_tiles() && writes && rowred && !colred && !chunked && !resident && !has_transposed && !has_concat && CT == 1 && s.G == 1 && WG == 1024 && s.E >= 32 && row_inputs == 1 && !rowv &&
               whole_lanes && R > CUS && (C % V == 0 || (R <= 2 * CUS && (lead || max_es == 4)));
     if (s.ahead) {
       const int lds = opt.lds_budget_given ? opt.lds_budget : device_limits().lds_per_workgroup;
