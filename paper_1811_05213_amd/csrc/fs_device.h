@@ -1043,8 +1043,10 @@ FS_DEV void fs_colred_fold_wg(const float (&acc_in)[NVL * V], float (&vals)[CPT]
 // workgroup barrier, lane 0 then bumps the ticket with an agent-scope atomic, and the folding
 // workgroup reads the partials with sc1 loads (never served by stale lines of its own L2).
 // The F loads of a chunk are independent and issued in batches, so a fold costs a few memory
-// round trips, not F of them; they are combined in index order, whichever workgroup folds.
-template <int K, int C, int WG, int FV, int F, typename KINDS, int CPT>
+// round trips, not F of them; they are combined in index order, whichever workgroup folds, or (PAIRS) in pairs of neighbours: one after the
+// other, 256 partials through two levels of 16 lose as much as the rows do (column sums + row norms [32768,100] 6.4e-8 from float64, 4.1e-8
+// in pairs, [65536,512] 6.8e-8 and 4.4e-8, LayerNorm backward [11403,64] 1.7e-7 and 1.1e-7).  Narrow tiles have 16 partials or so, and few registers.
+template <int K, int C, int WG, int FV, int F, bool PAIRS, typename KINDS, int CPT>
 FS_DEV bool fs_colred_fold_grid(float (&vals)[CPT][FV], float* part, fs_u32* tickets, fs_u32* flag, fs_u32 idx, fs_u32 n) {
   typedef fs_colfold<K, C, WG, FV> S;
   static_assert(CPT == S::CPT, "chunks per thread");
@@ -1088,11 +1090,22 @@ FS_DEV bool fs_colred_fold_grid(float (&vals)[CPT][FV], float* part, fs_u32* tic
             const fs_u32 j = (jb + u) < cnt ? (jb + u) : (cnt - 1);  // clamped: always a valid load
             fs_load_dev<FV>(tmp[u], theirs, j * (KC * 4) + (fs_u32)c * (FV * 4));
           }
+          if constexpr (PAIRS) {
 #pragma unroll
-          for (int u = 0; u < FB; ++u) {
-            const bool use = (jb + u) < cnt;
+            for (int f = 0; f < FV; ++f) {
+              float v[FB];
 #pragma unroll
-            for (int f = 0; f < FV; ++f) a[f] = use ? KINDS::op(k, a[f], tmp[u][f]) : a[f];
+              for (int u = 0; u < FB; ++u) v[u] = (jb + u) < cnt ? tmp[u][f] : KINDS::identity(k);
+              fs_pairs<FB>(v, [&](float x, float y) { return KINDS::op(k, x, y); });
+              a[f] = KINDS::op(k, a[f], v[0]);
+            }
+          } else {
+#pragma unroll
+            for (int u = 0; u < FB; ++u) {
+              const bool use = (jb + u) < cnt;
+#pragma unroll
+              for (int f = 0; f < FV; ++f) a[f] = use ? KINDS::op(k, a[f], tmp[u][f]) : a[f];
+            }
           }
         }
 #pragma unroll
