@@ -1304,11 +1304,12 @@ bool worth_fusing(const GroupPlan& merged, bool apart) {
   for (const ExtTensor& e : merged.ext_out) flipped += e.transposed;
   // Beside row reductions the fold costs what a workgroup's partial weighs, which is what a row holds, and a kernel of its own costs another
   // read of the rows.  Tall tensors pay from 8.5 MB on (column sums + row norms fp32 [65536,33] 14.4 us in kernels side by side, 10.0 in one,
-  // [16384,200] 12.4 and 10.3, LayerNorm backward [16384,64] 12.9 and 9.5; [16384,128], 8.4 MB, 8.0 and 8.7).  Below 2048 rows the fold weighs
+  // [16384,200] 12.4 and 10.3, LayerNorm backward [16384,64] 12.9 and 9.5; [16384,128], 8.4 MB, 8.0 and 8.7; [8192,300] 9.2 and 10.5), unless values leave
+  // transposed (row softmax numerators, transposed, with their column sums [9000,150] 9.0 apart and 12.4 in one, [11403,64] 7.1 and 9.3).  Below 2048 rows the fold weighs
   // more than the read, to 32 MB, as long as the kernels only read the same tensors (apart, folds_exchange_rows: [1421,3392] 13.3 and 16.0, [1000,5000] 11.4
   // and 17.3, LayerNorm backward [400,5000] 12.3 and 17.3, [1300,2000] 15.3 and 18.3, [300,8192] 12.8 and 18.6; but [1500,8000], 48 MB, 30.8 and 23.2, LayerNorm
   // backward [1500,3000], 54 MB, 25.2 and 20.4).
-  const uint64_t beside = merged.R >= 8192 ? 8500000 : merged.R >= 2048 || !apart ? kFoldWorthBytes : 32000000;
+  const uint64_t beside = merged.R >= 8192 && flipped == 0 ? 8500000 : merged.R >= 2048 || !apart ? kFoldWorthBytes : 32000000;
   const uint64_t worth = flipped >= 2 && merged.exchanges && !merged.row_reduces.empty() ? 64ull << 20 : merged.row_reduces.empty() ? kFoldWorthBytes : beside;
   return merged.col_reduces.empty() || merged.members.size() == 1 || merged.s.grid == 1 || narrow || (merged.row_reduces.empty() ? merged.min_hbm_bytes : merged.fold_bytes) >= worth;
 }
