@@ -1020,7 +1020,7 @@ struct Emitter {
     const Schedule& s = gp.s;
     for (int m : gp.members) in_set[m] = 1;
     count_uses();
-    const int C = gp.C;
+    const int C = gp.cols();
     const int NP = (int)(gp.ext_in.size() + gp.ext_out.size());
     const int K = (int)gp.col_reduces.size();
     const int WPR = s.L > 64 ? s.L / 64 : 1;

@@ -103,8 +103,6 @@ struct Analyser {
 
 // [R,C] tensors far larger than the caches
 constexpr uint64_t kStreamBytes = 32ull << 20;
-// elements of a piece of an elementwise group without rows (GroupPlan::flat)
-constexpr int kFlatPiece = 2048;
 
 void add_ext_in(GroupPlan& gp, int node, Kind k, int dtype) {
   for (const ExtTensor& e : gp.ext_in)
@@ -156,7 +154,7 @@ struct Scheduler {
   int row_inputs = 0;        // [R,C] tensors from memory
   bool whole_lanes = true;   // ... of which a lane takes 16 bytes at a time
 
-  Scheduler(const Graph& g_, const PlanOptions& opt_, GroupPlan* gp_) : g(g_), opt(opt_), gp(gp_), s(gp_->s), R(gp_->R), C(gp_->C) {}
+  Scheduler(const Graph& g_, const PlanOptions& opt_, GroupPlan* gp_) : g(g_), opt(opt_), gp(gp_), s(gp_->s), R(gp_->rows()), C(gp_->cols()) {}
 
   // lanes per row are a power of two: when half as many lanes would hold the row with at most
   // 1.5 x a cap below 32, take them (5120 bf16 columns under a cap of 16: 256 lanes x 24 elements,
@@ -1175,7 +1173,7 @@ fs_status analyse_group(const Graph& g, const std::vector<int>& members, const s
   for (int m : gp.members) flat &= gp.kind.at(m) == KIND_FULL && !tf[m] && g.nodes[m].opcode != FS_CONCAT;
   for (const auto* list : {&gp.ext_in, &gp.ext_out})
     for (const ExtTensor& e : *list) flat &= e.kind == KIND_FULL && !e.transposed, max_es = std::max(max_es, dtype_size(e.dtype));
-  if (flat && (int64_t)C * max_es % 128 != 0) gp.flat = R * C, gp.C = kFlatPiece, gp.R = (gp.flat + kFlatPiece - 1) / kFlatPiece;
+  if (flat && (int64_t)C * max_es % 128 != 0) gp.flat = R * C;
   const fs_status st = choose_schedule(g, opt, &gp);
   // Rows that are no multiple of a vector long share cache lines with their neighbours, which other wavefronts read: ordinary
   // loads there.  LayerNorm+GeLU bf16 [30001,1021]: 24.5 -> 22.1 us right after the kernel that wrote the input (28.3 -> 28.7 us

@@ -195,6 +195,8 @@ inline int fold_vector(int width) { return width % 4 == 0 ? 4 : width % 2 == 0 ?
 // what the counters of a tile's stages, and of the workgroups that leave it, take in a joined kernel: whole cache lines (the bits of its partials follow)
 inline int join_counters(int stages) { return (stages + 1 + 31) / 32 * 32; }
 
+constexpr int kFlatPiece = 2048;  // elements of a piece of an elementwise group without rows (GroupPlan::flat)
+
 struct GroupPlan {
   // Groups of a Composite's chain: per-row results that leave in x.<name>, besides memory, for the groups after; what comes in
   // x.<name> instead of from memory: those, and tensors that were asked for before the first group's work.
@@ -223,7 +225,11 @@ struct GroupPlan {
   uint64_t min_hbm_bytes = 0;
   uint64_t fold_bytes = 0; // ... without the [R,C] values that only other kernels of the plan read
   bool reads_alone = true; // no other kernel of the plan touches the [R,C] tensors it reads
-  int flat = 0;  // > 0: elementwise over this many elements, whose rows do not matter: R pieces of C, the last of which ends with them
+  // > 0: elementwise over this many elements, whose rows do not matter: pieces of kFlatPiece, the last of which ends with them, are the kernel's
+  // rows (rows, cols); R and C stay the tensors'
+  int flat = 0;
+  int rows() const { return flat ? (flat + kFlatPiece - 1) / kFlatPiece : R; }
+  int cols() const { return flat ? kFlatPiece : C; }
   bool exchanges = false;  // reads what another kernel of the plan wrote, or writes what another one reads
   // Several groups of the plan in one kernel (join_groups): column reductions and what needs their results, with the rows in
   // registers between them.  level is then the number of column reductions upstream, s.U the rows a lane holds, s.RB the
