@@ -510,9 +510,7 @@ struct Scheduler {
     for (int m : gp->members) plain &= gp->kind.at(m) != KIND_ROWV;
     if (!plain || C % (128 / min_es) == 0 || (int64_t)C * max_es < 1600 || gp->min_hbm_bytes < ((int64_t)C * max_es >= 16000 ? 32u << 20 : 96u << 20)) return;
     for (int line : {128 / min_es, V}) {
-      int step = line;  // rows begin at multiples of this many elements of their lines
-      while (C % step) step /= 2;
-      const int nv = (line - step + C - 1) / V + 1, nvl = (nv + L - 1) / L;
+      const int nv = lead_vectors(C, V, line), nvl = (nv + L - 1) / L;
       if (nvl <= NVL + (V == 4 && NVL * V < 32 && gp->min_hbm_bytes >= (256u << 20))) {
         NV = nv, NVL = nvl, lead = line;
         return;

@@ -192,6 +192,13 @@ struct StageSlot {
 // columns to a chunk of a column fold of this many
 inline int fold_vector(int width) { return width % 4 == 0 ? 4 : width % 2 == 0 ? 2 : 1; }
 
+// vectors of V elements in the longest piece of whole lines that holds a row of C: its first element lies at a multiple of `step` in a line
+constexpr int lead_vectors(int C, int V, int line) {
+  int step = line;
+  while (C % step) step /= 2;
+  return (line - step + C - 1) / V + 1;
+}
+
 // what the counters of a tile's stages, and of the workgroups that leave it, take in a joined kernel: whole cache lines (the bits of its partials follow)
 inline int join_counters(int stages) { return (stages + 1 + 31) / 32 * 32; }
 

@@ -1,5 +1,5 @@
 // The pieces of whole cache lines of fs_device.h (fs_lead_...) on the host, lane after lane, on tensors of exact size: what a row's lanes load,
-// reduce and store against the row itself.  lead.inc is their text.
+// reduce and store against the row itself, with as many vectors a lane as the schedule gives it (lead_vectors).  lead.inc is their text.
 #include <cstdint>
 #include <cstdio>
 #include <cstring>
@@ -39,12 +39,7 @@ static int cases = 0;
 template <int DT, int DT_OUT, int V, int L, int C, int LEAD> void one(int R) {
   typedef typename fs_elem<DT>::type T;
   typedef typename fs_elem<DT_OUT>::type TO;
-  int step = LEAD;
-  while (C % step) step /= 2;
-  constexpr int MOST = (C + LEAD - 2) / V + 1;
-  const int nv = (LEAD - step + C - 1) / V + 1;  // as lead_rows counts them
-  constexpr int NVL = (MOST + L - 1) / L;
-  if ((nv + L - 1) / L > NVL) wrong = "too few vectors";
+  constexpr int NVL = (lead_vectors(C, V, LEAD) + L - 1) / L;
   std::vector<T> x((size_t)R * C);
   std::vector<TO> y((size_t)R * C), seen((size_t)R * C, 0);
   for (size_t i = 0; i < x.size(); ++i) x[i] = (T)(1 + i * 7 % 97);

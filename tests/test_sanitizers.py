@@ -104,7 +104,10 @@ def test_meeting_workgroups_under_thread_sanitizer(workdir):
 def test_rows_in_whole_lines_stay_inside_their_tensors(workdir):
     # loads, reductions and stores of rows that are held in pieces of whole cache lines, over all places where a row may begin and end in a line
     text = open(os.path.join(ROOT, "paper_1811_05213_amd", "csrc", "fs_device.h")).read()
+    internal = open(os.path.join(ROOT, "paper_1811_05213_amd", "csrc", "fs_internal.h")).read()
     with open(os.path.join(workdir, "lead.inc"), "w") as f:
+        a = internal.index("constexpr int lead_vectors(")
+        f.write(internal[a:internal.index("\n}\n", a) + 3])
         for begin, end in (("template <int V, int L, int C, int LEAD> FS_DEV bool fs_lead_inside", "// One chunk of a row kept in LDS"),
                            ("template <int KIND, int V, int NVL, int L, int C, int LEAD> FS_DEV float fs_lead_lane_reduce", "template <int CTRL> FS_DEV float fs_dpp(")):
             a = text.index(begin)
