@@ -563,11 +563,10 @@ struct Scheduler {
       // and the in-workgroup fold area (one row of C floats per wavefront or row-group) fits the budget
       WG = std::max(64, L);
       for (int w = 512; w >= 128; w /= 2)
-        if (w >= L && (int64_t)R * L / w >= (has_transposed && rowred ? CUS * 3 / 4 : CUS)) {
+        if (w >= L && (int64_t)R * L / w >= CUS) {
           WG = w;
           break;
         }
-      // (three quarters of the CUs where values leave transposed, in runs as long as a workgroup has rows: random DAG [2000,256] 46.2 -> 43.8 us)
       // rows across several wavefronts: 16 wavefronts per CU.  8 where rows that no whole vectors fill leave the kernel too, 20 elements
       // to a lane or 512 lanes to a row: such kernels are short of registers at 16 (LayerNorm backward [2500,4101] 58.7 -> 51.3 us, [6000,4801] 108.5 ->
       // 92.5, [4000,6201] 101.5 -> 90.9, [3000,8191] 94.1 -> 89.8; with 16 elements on 256 lanes, [5000,3501], 57.2 against 61.6)
@@ -777,7 +776,9 @@ struct Scheduler {
         for (const ExtTensor& e : *list) shared |= e.kind == KIND_FULL && !e.transposed && (int64_t)s.G * C * dtype_size(e.dtype) % 128 != 0;
       s.xcd_rows = has_transposed ? 8 : shared ? 16 : 0;
     }
-    // (folds of columns, too, whatever their trips: [2000,256] 49.6 -> 46.2, [2048,256] 42.5 -> 41.8)
+    // (folds of columns, too, whatever their trips: row softmax numerators, transposed twice, with row and column sums fp32 [4100,700] 21.9 -> 19.3 us,
+    // [3000,1500] 30.4 -> 25.5, [9000,400] 22.0 -> 20.1, [2048,1024] 15.4 -> 14.7; rows of a power of two in number and few columns lose 1 to 3 %, [4096,512]
+    // 13.0 -> 13.4, [16384,256] 17.9 -> 18.1)
     if (has_transposed && rowred && colred && !tiled_transpose && !chunked && CT == 1 && s.U == 1) s.xcd_rows = 8;
     // (one row to a workgroup that stays: 32 neighbours; few rows leave XCDs idle in the last trip then, 16.  softmax fp32 [1024,65000] 100.8 -> 97.8 us,
     // [400,50001] 30.7 -> 30.5, 34.8 with 32.  Not where every other row begins with a line: test_which_rows_are_placed_by_xcd has [2048,50000] in plain
