@@ -339,6 +339,11 @@ fs_status build_graph(const fs_graph_desc* desc, Graph* g) {
         for (int k = 0; k < n.num_in; ++k) g->exact[n.in[k]] = 1;
     }
   }
+  g->live.assign(N, 0);
+  for (int o : g->outputs) g->live[o] = 1;
+  for (int id = N - 1; id >= 0; --id)
+    if (g->live[id])
+      for (int k = 0; k < g->nodes[id].num_in; ++k) g->live[g->nodes[id].in[k]] = 1;
   return FS_OK;
 }
 

@@ -1123,6 +1123,7 @@ fs_status analyse_group(const Graph& g, const std::vector<int>& members, const s
   auto bytes_of = [&](const ExtTensor& e) { return (uint64_t)g.nodes[e.node].rows * g.nodes[e.node].cols * dtype_size(e.dtype); };
   std::function<bool(int)> used_only_here = [&](int id) {
     for (int u : g.users[id]) {
+      if (!g.live[u]) continue;
       const int uop = g.nodes[u].opcode;
       if (uop == FS_BCAST_ROWVEC || uop == FS_BCAST_COLVEC || op_is_view(uop)) {
         if (!used_only_here(u)) return false;  // (a view that is a plan output consumes nothing)

@@ -60,6 +60,7 @@ struct Graph {
   std::vector<int> input_index;          // node id -> index into inputs[] or -1
   std::vector<int> output_index;         // node id -> index into outputs[] or -1
   std::vector<std::vector<int>> users;   // direct users of each node
+  std::vector<char> live;                // node is a plan output or leads to one: the others are never computed, nor do they read
   std::vector<char> exact;               // node feeds a predicate: its bits must be reproducible (no contraction)
   std::vector<int> root_of;              // the node whose buffer a node's bytes live in: itself, or what its chain of views starts from
   std::vector<int> family_output;        // root -> index of the plan output (the root itself or a view of it) whose buffer holds it, or -1
