@@ -498,7 +498,8 @@ struct Scheduler {
   // [83,20003] bf16 7.4 -> 6.6).  Not for rows of a few lines, all of which the ends touch (softmax fp32 [120000,321] 50.5 against 54.1 us, [60000,385] 31.1 and 31.4,
   // masked softmax bf16 [60000,449] 28.5 and 31.2, [32768,577] 21.2 and 21.1).  A vector more a lane than the row alone needs: fp32 from 256 MB on ([8192,8191] 90.3 -> 86.8, [2048,32767] 101.9 -> 95.3,
   // [65536,1001] 90.3 -> 87.9; at 131 MB [4000,2047] 12.8 -> 13.5; masked softmax bf16 [8192,8191] 72.6 -> 78.4).  Rows that fill a compute unit's
-  // registers to the last vector are held in whole vectors, if not in whole lines: that suffices to ask for them ahead.
+  // registers to the last vector are held in whole vectors, if not in whole lines, where that suffices to ask for them ahead (pick_grid).  Where they are
+  // not, whole vectors gain nothing sure: softmax fp32 [700,36862] 41.5 -> 44.3 us, [1500,61438] 151.9 and 152.1, [2048,65533] 216.9 -> 211.4.
   void lead_rows() {
     int min_es = 4;
     bool plain = opt.lead && !several_tiles() && rowred && !colred && !chunked && !resident && !split_rows && !has_transposed && !has_concat && CT == 1 && V >= 2 && L >= 8 && !gp->exchanges;
@@ -515,7 +516,7 @@ struct Scheduler {
         NV = nv, NVL = nvl, lead = line;
         return;
       }
-      if (C % V == 0 || L != 1024 || NVL * V < 32) return;
+      if (C % V == 0 || L != 1024 || NVL * V < 32 || R <= CUS || R > 2 * CUS) return;
     }
   }
 
