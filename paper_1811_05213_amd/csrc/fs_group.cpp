@@ -850,10 +850,11 @@ struct Scheduler {
     // workgroups meet and fold a slice of the columns each.  LayerNorm backward fp32 [4096,8192] 102.7 -> 93.5 us, [5000,3000] 54.4 ->
     // 47.2, [8192,4096] 85.9 -> 82.3, [16384,2048] 80.3 and 80.2; moments bf16 [8192,8192] 69.5 -> 57.7.  To meet takes 2 us more than
     // to pass two tickets, which smaller partials do not return: [16384,1024] 39.6 against 41.1, moments [65536,512] 26.5 against 28.5.  Beyond 2048
-    // columns in all a lane of the tree's last workgroup folds a second chunk: column sums + row norms [4096,1100] 19.9 -> 12.6 us, [4000,2000] 21.4 -> 17.0,
-    // [20000,1030] 26.3 -> 22.4, [30000,1100] 34.5 -> 29.0, LayerNorm backward [3000,1500] 23.4 -> 20.9, [8000,1200] 31.7 -> 29.4: in rows of more than 1024
-    // columns from 8 KB of partials on, else from 16 KB as ever (test_which_column_folds_meet holds [20000,1024] with three folds to the tree; to
-    // meet takes 37.1 us there against 41.9, [8192,1000] 23.5 against 30.9).
+    // columns in all a lane of the tree's last workgroup folds a second chunk: column sums + row norms [4096,1100] 13.5 or 19.9 -> 12.5 us (the same tree takes
+    // the one in some processes and the other in others), [4000,2000] 21.2 -> 16.8, [8192,1536] 23.6 -> 16.9, [20000,1030] 22.0 or 26.2 -> 22.5, [30000,1100] 27.8 or
+    // 34.1 -> 28.5, LayerNorm backward [3000,1500] 20.1 or 23.2 -> 20.7, [2500,1900] 26.2 -> 23.0, [8000,1200] 31.6 -> 29.3, [16384,1100] 44.9 or 48.5 -> 46.5: in rows of
+    // more than 1024 columns from 8 KB of partials on, else from 16 KB as ever (test_which_column_folds_meet holds [20000,1024] with three folds to the
+    // tree; to meet takes 37.1 us there against 41.9, [8192,1000] 23.5 against 30.9).
     const int64_t fold_columns = (int64_t)gp->col_reduces.size() * fold_width;
     if (opt.meet && colred && !col_tiled && s.RB > s.fan_in && s.RB <= CUS && fold_columns > 2048 && (C > 1024 || fold_columns >= 4096)) {
       const int FV = fold_vector(fold_width), chunks = (int)gp->col_reduces.size() * (fold_width / FV);
