@@ -1170,7 +1170,7 @@ fs_status analyse_group(const Graph& g, const std::vector<int>& members, const s
   // shares with the one before it again.  dropout+residual fp32 [6115,2521] 38.7 -> 30.7 us, [26220,279] 18.3 -> 16.0, [4096,3000] 29.8 -> 24.8, bf16 [16384,4095] 87.3 -> 74.1,
   // [41282,43] 4.8 -> 3.8.  Not where rows are whole lines (as one row fp32 [5922,1088] 13.9 against 14.7, [65536,576] 74.3 and 75.5) or below 8 MB (no
   // difference).  Once the groups are final, and not where other kernels of the plan may take the same rows.
-  bool flat = opt.grouped && !opt.has_hint && !gp.exchanges && R > 1 && C > 1 && (int64_t)R * C < (1 << 30) && gp.min_hbm_bytes >= (8u << 20) && gp.row_reduces.empty() && gp.col_reduces.empty();
+  bool flat = opt.grouped && (!opt.has_hint || opt.keep_flat) && !gp.exchanges && R > 1 && C > 1 && (int64_t)R * C < (1 << 30) && gp.min_hbm_bytes >= (8u << 20) && gp.row_reduces.empty() && gp.col_reduces.empty();
   int max_es = 1;
   for (int m : gp.members) flat &= gp.kind.at(m) == KIND_FULL && !tf[m] && g.nodes[m].opcode != FS_CONCAT;
   for (const auto* list : {&gp.ext_in, &gp.ext_out})
@@ -2026,6 +2026,7 @@ struct Composer {
       o.hint = fs_sched_hint{L, WG, 0, 0};
       o.has_hint = true;
       o.fill_lanes = chain;
+      o.keep_flat = groups[k].flat > 0;
       if (analyse_group(g, groups[k].members, group_of, k, o, out) != FS_OK) return false;
     }
     const Schedule& s = out->s;

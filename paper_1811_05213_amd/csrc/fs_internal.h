@@ -279,6 +279,7 @@ struct PlanOptions {
   bool grouped = false;  // the groups are final: schedules no longer decide what is fused
   bool lead = true;   // rows may be held in pieces of whole cache lines
   bool ahead = true;  // long rows may be asked for one ahead (given up where the compiled kernel spills)
+  bool keep_flat = false;  // an elementwise group stays without rows under the hint (that of the launch it shares)
   bool fill_lanes = false;  // rows may be spread over idle lanes (groups of a chain, which all take the lanes of the widest)
   int min_waves = 0;  // > 0: the kernel asks the compiler for that many wavefronts per SIMD (occupancy feedback at plan creation)
   bool layered = false;  // group with the layered planner of Section 3.2 instead of the default one
