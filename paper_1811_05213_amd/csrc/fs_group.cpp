@@ -1949,6 +1949,7 @@ fs_status join_groups(const Graph& g, const std::vector<GroupPlan>& groups, int 
 // waits for numbers of the rows: column sum of a row softmax [300,8192] 11.2 and 12.4, [1000,2500] 13.9 and 11.8, [1900,2100] 19.3 and 14.8, two sums
 // [300,8192] 12.1 and 17.6, [1300,2000] 14.7 and 16.7.
 bool folds_exchange_rows(const Graph& g, const std::vector<std::vector<int>>& ordered, const std::vector<int>& group_of, const PlanOptions& opt) {
+  if (ordered.size() < 2) return false;
   std::vector<GroupPlan> groups(ordered.size());
   std::map<int, size_t> stored_by;
   for (size_t k = 0; k < ordered.size(); ++k) {
