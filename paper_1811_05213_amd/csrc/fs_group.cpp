@@ -1123,12 +1123,12 @@ fs_status analyse_group(const Graph& g, const std::vector<int>& members, const s
   // Adam [2048,2048]: 23.8 -> 21.2 us; 1 MB tensors: no difference).  Values that pass between kernels stay cacheable.
   constexpr uint64_t kStreamOnceBytes = 2ull << 20;
   auto bytes_of = [&](const ExtTensor& e) { return (uint64_t)g.nodes[e.node].rows * g.nodes[e.node].cols * dtype_size(e.dtype); };
-  std::function<bool(int)> used_only_here = [&](int id) {
+  std::function<bool(int, bool)> used_only_here = [&](int id, bool live) {  // (live: nodes that no output needs do not count)
     for (int u : g.users[id]) {
-      if (!g.live[u]) continue;
+      if (live && !g.live[u]) continue;
       const int uop = g.nodes[u].opcode;
       if (uop == FS_BCAST_ROWVEC || uop == FS_BCAST_COLVEC || op_is_view(uop)) {
-        if (!used_only_here(u)) return false;  // (a view that is a plan output consumes nothing)
+        if (!used_only_here(u, live)) return false;  // (a view that is a plan output consumes nothing)
       } else if (!a.in_set[u]) {
         return false;
       }
@@ -1137,11 +1137,11 @@ fs_status analyse_group(const Graph& g, const std::vector<int>& members, const s
   };
   for (ExtTensor& e : gp.ext_in) {
     const int root = g.root_of[e.node];
-    const bool once = g.nodes[root].opcode == FS_INPUT && used_only_here(root);
+    const bool once = g.nodes[root].opcode == FS_INPUT && used_only_here(root, false);
     e.streaming = e.kind == KIND_FULL && bytes_of(e) >= (once ? kStreamOnceBytes : kStreamBytes);
   }
   for (ExtTensor& e : gp.ext_out) {
-    const bool once = g.family_output[e.node] >= 0 && used_only_here(e.node);
+    const bool once = g.family_output[e.node] >= 0 && used_only_here(e.node, false);
     e.streaming = e.kind == KIND_FULL && !e.transposed && bytes_of(e) >= (once ? kStreamOnceBytes : kStreamBytes);
   }
 
@@ -1161,9 +1161,9 @@ fs_status analyse_group(const Graph& g, const std::vector<int>& members, const s
   for (const ExtTensor& e : gp.ext_in) {
     const int root = g.root_of[e.node];
     gp.exchanges |= g.nodes[root].opcode != FS_INPUT;
-    gp.reads_alone &= e.kind != KIND_FULL || (g.nodes[root].opcode == FS_INPUT && used_only_here(root));
+    gp.reads_alone &= e.kind != KIND_FULL || (g.nodes[root].opcode == FS_INPUT && used_only_here(root, false));
   }
-  for (const ExtTensor& e : gp.ext_out) gp.exchanges |= !used_only_here(e.node);
+  for (const ExtTensor& e : gp.ext_out) gp.exchanges |= !used_only_here(e.node, true);
 
   // Elementwise groups whose tensors all are [R,C] need no rows: where those are no whole cache lines, the elements are cut into pieces of
   // kFlatPiece instead, whose accesses cover whole lines and whose lanes all have work; the last piece begins earlier and stores what it
