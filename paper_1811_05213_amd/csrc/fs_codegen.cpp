@@ -1109,8 +1109,7 @@ struct Emitter {
     // reductions has the same text, hence the same compiled code, whatever the number of rows)
     os << "  constexpr int CW = " << (ctile ? "NVL * L * V" : std::to_string(K > 0 ? s.fold_width : C)) << ", RB = " << (K > 0 || ctile ? s.RB : 1) << ";\n";
     if (ctile) os << "  const int place = " << workgroup_place() << ", tile = place % CT, rb = place / CT, vbase = tile * (NVL * L);\n";
-    // (a workgroup's partial lies where its rows do, also where they are placed by XCD: kernels that share a launch fold in the same order)
-    else os << "  const int tile = 0, rb = " << (K > 0 ? workgroup_place() : "(int)blockIdx.x") << ";\n";
+    else os << "  const int tile = 0, rb = (int)blockIdx.x;\n";
     os << "  (void)tile; (void)rb; (void)CW; (void)RB;\n";
     if (s.ahead) {
       int n_full = 0;

@@ -2148,6 +2148,8 @@ bool generate_composite(const Graph& g, Composite* c) {
     for (size_t k = 0; k < c->plans[t].size(); ++k) {
       const GroupPlan& p = c->plans[t][k];
       const std::string field = "g" + std::to_string(total++), n = p.kernel_name;
+      // (a kernel that folds columns, alone in its track, places its workgroups itself: their partials lie by block, as they do in a launch of its own)
+      const bool folds = !p.col_reduces.empty();
       if (seen.insert(n).second) {
         std::string src = p.source;
         const size_t a = src.find("extern \"C\" __global__"), b = src.find("{\n", a);
@@ -2155,7 +2157,7 @@ bool generate_composite(const Graph& g, Composite* c) {
         replace_all(&src, "struct " + n + "_args", "struct " + n + "_part_args");
         replace_all(&src, "const " + n + "_args&", "const " + n + "_part_args&");
         replace_all(&src, n + "_kinds", n + "_part_kinds");
-        if (p.s.xcd_rows) replace_all(&src, "fs_xcd_place<" + std::to_string(p.s.xcd_rows) + ">((int)blockIdx.x, (int)gridDim.x)", "fs_block");
+        if (p.s.xcd_rows && !folds) replace_all(&src, "fs_xcd_place<" + std::to_string(p.s.xcd_rows) + ">((int)blockIdx.x, (int)gridDim.x)", "fs_block");
         replace_all(&src, "blockIdx.x", "fs_block");
         replace_all(&src, "gridDim.x", "fs_blocks");
         text += src;
@@ -2163,7 +2165,7 @@ bool generate_composite(const Graph& g, Composite* c) {
       args += "  " + n + "_part_args " + field + ";\n";
       // (what a workgroup wrote before the barrier it reads after it: the vector cache of a compute unit writes through)
       if (k > 0 && !p.linked) body += "    __syncthreads();\n";
-      body += "    " + n + "_rows(a." + field + ", " + place + ", " + std::to_string(c->blocks[t]) + (passes ? ", x" : "") + ");\n";
+      body += "    " + n + "_rows(a." + field + ", " + (folds ? "block" : place) + ", " + std::to_string(c->blocks[t]) + (passes ? ", x" : "") + ");\n";
     }
     body += "    return;\n  }\n";
     if (t + 1 < c->tracks.size()) body += "  block -= " + std::to_string(c->blocks[t]) + ";\n";
