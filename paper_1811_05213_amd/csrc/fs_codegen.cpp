@@ -624,7 +624,7 @@ struct Emitter {
     }
     os << "  typedef fs_colfold<" << K << ", 1, WG, 1> SF;\n  float cv[SF::CPT][1];\n  cv[0][0] = 0.0f;\n";
     for (int k = 0; k < K; ++k) os << "  if (tid == " << k << ") cv[0][0] = q" << loc(gp.row_reduces[k]) << ";\n";
-    os << "  if (fs_colred_fold_grid<" << K << ", 1, WG, 1, " << s.fan_in << ", false, " << kname << "_kinds>(cv, a.part + row * " << s.part_stride_floats
+    os << "  if (fs_colred_fold_grid<" << K << ", 1, WG, 1, " << s.fan_in << ", 0, " << kname << "_kinds>(cv, a.part + row * " << s.part_stride_floats
        << "L, a.tickets + row * " << s.ticket_stride << ", &lds_flag, (fs_u32)seg, (fs_u32)S)) {\n";
     os << "    if (tid < " << K << ") lds_vals[tid] = cv[0][0];\n    __syncthreads();\n    if (tid == 0) {\n";
     // thread 0 of the last workgroup: the results, what depends on them, and the stores
@@ -1616,7 +1616,10 @@ struct Emitter {
         store_results("cv[0]");
         os << "        }\n    }\n";
       } else {
-        os << "    if (fs_colred_fold_grid<" << K << ", CW, WG, FV, " << s.fan_in << ", " << (ctile ? "false" : "true") << ", " << kname << "_kinds>(cv, " << part << ", " << tickets << ", &lds_flag, (fs_u32)rb, (fs_u32)RB)) {\n"
+        bool one_kind = true;
+        auto folds_as = [&](int m) { return g.nodes[m].attr_i == FS_RED_MEAN ? (int)FS_RED_SUM : (int)g.nodes[m].attr_i; };
+        for (int m : gp.col_reduces) one_kind &= folds_as(m) == folds_as(gp.col_reduces[0]);
+        os << "    if (fs_colred_fold_grid<" << K << ", CW, WG, FV, " << s.fan_in << ", " << (gp.row_reduces.empty() ? 0 : one_kind ? 1 : 2) << ", " << kname << "_kinds>(cv, " << part << ", " << tickets << ", &lds_flag, (fs_u32)rb, (fs_u32)RB)) {\n"
            << "      _Pragma(\"unroll\") for (int i = 0; i < S::CPT; ++i) {\n        const int c = tid + i * WG;\n        if (c < S::NCH) {\n";
         store_results("cv[i]");
         os << "        }\n      }\n    }\n";

@@ -1043,10 +1043,12 @@ FS_DEV void fs_colred_fold_wg(const float (&acc_in)[NVL * V], float (&vals)[CPT]
 // workgroup barrier, lane 0 then bumps the ticket with an agent-scope atomic, and the folding
 // workgroup reads the partials with sc1 loads (never served by stale lines of its own L2).
 // The F loads of a chunk are independent and issued in batches, so a fold costs a few memory
-// round trips, not F of them; they are combined in index order, whichever workgroup folds, or (PAIRS) in pairs of neighbours: one after the
-// other, 256 partials through two levels of 16 lose as much as the rows do (column sums + row norms [32768,100] 6.4e-8 from float64, 4.1e-8
-// in pairs, [65536,512] 6.8e-8 and 4.4e-8, LayerNorm backward [11403,64] 1.7e-7 and 1.1e-7).  Narrow tiles have 16 partials or so, and few registers.
-template <int K, int C, int WG, int FV, int F, bool PAIRS, typename KINDS, int CPT>
+// round trips, not F of them; they are combined in index order, whichever workgroup folds, or (PAIRS: 1 where all reductions fold alike, 2 where
+// not) in pairs of neighbours: one after the other, 256 partials through two levels of 16 lose as much as the rows do (column sums + row norms
+// [32768,100] 6.4e-8 from float64, 4.1e-8 in pairs, [65536,512] 6.8e-8 and 4.4e-8, LayerNorm backward [11403,64] 1.7e-7 and 1.1e-7).  A kind after
+// the other, each by the lanes whose chunks are of it: chosen per operation, two kinds cost a kernel 2 us (a thousand instructions, run once).  Not in kernels
+// that only fold, whose loads then are in flight in smaller lots (column sums bf16 [36220,447] 12.5 -> 13.2 us).
+template <int K, int C, int WG, int FV, int F, int PAIRS, typename KINDS, int CPT>
 FS_DEV bool fs_colred_fold_grid(float (&vals)[CPT][FV], float* part, fs_u32* tickets, fs_u32* flag, fs_u32 idx, fs_u32 n) {
   typedef fs_colfold<K, C, WG, FV> S;
   static_assert(CPT == S::CPT, "chunks per thread");
@@ -1090,14 +1092,18 @@ FS_DEV bool fs_colred_fold_grid(float (&vals)[CPT][FV], float* part, fs_u32* tic
             const fs_u32 j = (jb + u) < cnt ? (jb + u) : (cnt - 1);  // clamped: always a valid load
             fs_load_dev<FV>(tmp[u], theirs, j * (KC * 4) + (fs_u32)c * (FV * 4));
           }
-          if constexpr (PAIRS) {
+          if constexpr (PAIRS != 0) {
 #pragma unroll
-            for (int f = 0; f < FV; ++f) {
-              float v[FB];
+            for (int kk = 0; kk < (PAIRS == 1 ? 1 : K); ++kk) {
+              if (PAIRS == 2 && k != kk) continue;
 #pragma unroll
-              for (int u = 0; u < FB; ++u) v[u] = (jb + u) < cnt ? tmp[u][f] : KINDS::identity(k);
-              fs_pairs<FB>(v, [&](float x, float y) { return KINDS::op(k, x, y); });
-              a[f] = KINDS::op(k, a[f], v[0]);
+              for (int f = 0; f < FV; ++f) {
+                float v[FB];
+#pragma unroll
+                for (int u = 0; u < FB; ++u) v[u] = (jb + u) < cnt ? tmp[u][f] : KINDS::identity(kk);
+                fs_pairs<FB>(v, [&](float x, float y) { return KINDS::op(kk, x, y); });
+                a[f] = KINDS::op(kk, a[f], v[0]);
+              }
             }
           } else {
 #pragma unroll
