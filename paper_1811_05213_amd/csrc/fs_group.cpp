@@ -1947,7 +1947,8 @@ fs_status join_groups(const Graph& g, const std::vector<GroupPlan>& groups, int 
 // place of one: column sums of a row softmax fp32 [400,8192] 25.4 us apart and 18.9 in one, [1900,2000] 25.9 and 17.1, of x less its row maximum [1500,3000]
 // 27.0 and 14.3, [2000,3900] 33.9 and 18.6 (8192 columns that leave as well, [400,8192], 15.7 and 18.4).  Nor does a single fold pay that
 // waits for numbers of the rows: column sum of a row softmax [300,8192] 11.2 and 12.4, [1000,2500] 13.9 and 11.8, [1900,2100] 19.3 and 14.8, two sums
-// [300,8192] 12.1 and 17.6, [1300,2000] 14.7 and 16.7.
+// [300,8192] 12.1 and 17.6, [1300,2000] 14.7 and 16.7.  Such groups are formed again with their folds beside the row reductions, where that takes fewer
+// kernels (one with five folds of [1000,513], beside a kernel of row reductions and a transpose, 38.1 us in two launches; two with three and two 50.8).
 bool folds_exchange_rows(const Graph& g, const std::vector<std::vector<int>>& ordered, const std::vector<int>& group_of, const PlanOptions& opt) {
   if (ordered.size() < 2) return false;
   std::vector<GroupPlan> groups(ordered.size());

@@ -304,7 +304,7 @@ fs_status form_groups(const Graph& g, const fs_graph_desc* desc, const PlanOptio
 // Adds the copies to the consumers' member lists and records them in `clones`.
 void recompute_across_kernels(const Graph& g, const PlanOptions& opt, std::vector<int>* group_of,
                               std::vector<std::vector<int>>* groups_in_launch_order, CloneInfo* clones);
-// Whether column folds that stay out of the kernels beside them wait for what those write (then they are formed again, folds_apart = false).
+// Whether column folds that stay out of the kernels beside them wait for what those write (then groups are formed again, folds_apart = false).
 bool folds_exchange_rows(const Graph& g, const std::vector<std::vector<int>>& ordered, const std::vector<int>& group_of, const PlanOptions& opt);
 
 // Groups [first, first + count) of a plan as one kernel whose workgroups keep their rows in registers while the column

@@ -332,25 +332,35 @@ fs_status fs_plan_create(const fs_graph_desc* desc, fs_plan** out_plan) {
 
   const Graph& g = plan->graph;
   std::vector<std::vector<int>> ordered;
-  for (;;) {
-    st = form_groups(g, desc, plan->opt, &plan->group_of, &ordered);
-    if (st != FS_OK) {
-      delete plan;
-      return st;
-    }
+  // (a caller's plan and the one-launch-per-op executor are taken as they are)
+  const bool own_groups = plan->opt.mode != FS_MODE_UNFUSED && !desc->group_of_node;
+  auto group_nodes = [&]() -> fs_status {
+    plan->opt.clones = nullptr;
+    ordered.clear();
+    const fs_status formed = form_groups(g, desc, plan->opt, &plan->group_of, &ordered);
+    if (formed != FS_OK) return formed;
     // group ids follow launch order
     for (size_t gi = 0; gi < ordered.size(); ++gi)
       for (int m : ordered[gi]) plan->group_of[m] = (int)gi;
     // the library's own grouping may compute a cheap value in two kernels rather than pass it through memory
-    // (a caller's plan and the one-launch-per-op executor are taken as they are)
-    if (plan->opt.mode == FS_MODE_UNFUSED || desc->group_of_node) break;
-    recompute_across_kernels(g, plan->opt, &plan->group_of, &ordered, &plan->clones);
-    plan->opt.clones = &plan->clones;
-    if (!plan->opt.folds_apart || !folds_exchange_rows(g, ordered, plan->group_of, plan->opt)) break;
+    if (own_groups) {
+      recompute_across_kernels(g, plan->opt, &plan->group_of, &ordered, &plan->clones);
+      plan->opt.clones = &plan->clones;
+    }
+    return FS_OK;
+  };
+  st = group_nodes();
+  if (st == FS_OK && own_groups && folds_exchange_rows(g, ordered, plan->group_of, plan->opt)) {  // folds beside the row reductions, if that takes fewer kernels
+    const std::vector<std::vector<int>> apart = ordered;
+    const std::vector<int> group_of_apart = plan->group_of;
+    const CloneInfo clones_apart = plan->clones;
     plan->opt.folds_apart = false;
-    plan->opt.clones = nullptr;
-    plan->clones = CloneInfo();
-    ordered.clear();
+    st = group_nodes();
+    if (st == FS_OK && ordered.size() >= apart.size()) ordered = apart, plan->group_of = group_of_apart, plan->clones = clones_apart;
+  }
+  if (st != FS_OK) {
+    delete plan;
+    return st;
   }
   plan->groups.resize(ordered.size());
   plan->opt.grouped = plan->opt.mode != FS_MODE_UNFUSED && !desc->group_of_node;
