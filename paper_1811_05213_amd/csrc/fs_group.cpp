@@ -850,13 +850,12 @@ struct Scheduler {
     // workgroups meet and fold a slice of the columns each.  LayerNorm backward fp32 [4096,8192] 102.7 -> 93.5 us, [5000,3000] 54.4 ->
     // 47.2, [8192,4096] 85.9 -> 82.3, [16384,2048] 80.3 and 80.2; moments bf16 [8192,8192] 69.5 -> 57.7.  To meet takes 2 us more than
     // to pass two tickets, which smaller partials do not return: [16384,1024] 39.6 against 41.1, moments [65536,512] 26.5 against 28.5.  Beyond 2048
-    // columns in all a lane of the tree's last workgroup folds a second chunk: column sums + row norms [4096,1100] 13.5 or 19.9 -> 12.5 us (the same tree takes
-    // the one in some processes and the other in others), [4000,2000] 21.2 -> 16.8, [8192,1536] 23.6 -> 16.9, [20000,1030] 22.0 or 26.2 -> 22.5, [30000,1100] 27.8 or
-    // 34.1 -> 28.5, LayerNorm backward [3000,1500] 20.1 or 23.2 -> 20.7, [2500,1900] 26.2 -> 23.0, [8000,1200] 31.6 -> 29.3, [16384,1100] 44.9 or 48.5 -> 46.5: in rows of
-    // more than 1024 columns from 8 KB of partials on, else from 16 KB as ever (test_which_column_folds_meet holds [20000,1024] with three folds to the
-    // tree; to meet takes 37.1 us there against 41.9, [8192,1000] 23.5 against 30.9).
+    // columns in all a lane of the tree's last workgroup folds a second chunk, and kernels of less than 52 MB are short enough to notice: column sums + row
+    // norms [4096,1100] 14.0 -> 12.6 us, [4000,2000] 18.8 -> 16.8, [8192,1536] 18.4 -> 16.9, with a maximum and a mean [4096,1100] 14.6 -> 12.4, [8192,1200] 19.7 ->
+    // 17.7, LayerNorm backward [2100,1300] 18.5 and 18.6; above, the tree is as good or better: column sums + row norms [30000,1100] 28.1 and 28.4, LayerNorm backward
+    // [8000,1200] 28.3 and 29.2, [16384,1100] 45.2 and 46.4, three folds [20000,1024] 35.6 and 37.1, [8192,1000] 22.1 and 23.3 (but [2500,1900] 23.8 and 23.0).
     const int64_t fold_columns = (int64_t)gp->col_reduces.size() * fold_width;
-    if (opt.meet && colred && !col_tiled && s.RB > s.fan_in && s.RB <= CUS && fold_columns > 2048 && (C > 1024 || fold_columns >= 4096)) {
+    if (opt.meet && colred && !col_tiled && s.RB > s.fan_in && s.RB <= CUS && fold_columns > 2048 && (fold_columns >= 4096 || gp->min_hbm_bytes < 52000000)) {
       const int FV = fold_vector(fold_width), chunks = (int)gp->col_reduces.size() * (fold_width / FV);
       const int SC = std::max(16 / FV, std::min(64, pow2_ceil((chunks + s.RB - 1) / s.RB))), meet_bytes = WG / 64 * SC * FV * 4;
       if (fixed + 32 + std::max({loop_bytes, fold_bytes, meet_bytes}) <= opt.lds_budget) {
