@@ -355,8 +355,8 @@ fs_status fs_plan_create(const fs_graph_desc* desc, fs_plan** out_plan) {
     const std::vector<int> group_of_apart = plan->group_of;
     const CloneInfo clones_apart = plan->clones;
     plan->opt.folds_apart = false;
-    st = group_nodes();
-    if (st == FS_OK && ordered.size() >= apart.size()) ordered = apart, plan->group_of = group_of_apart, plan->clones = clones_apart;
+    if (group_nodes() != FS_OK || ordered.size() >= apart.size()) ordered = apart, plan->group_of = group_of_apart, plan->clones = clones_apart;
+    plan->opt.clones = &plan->clones;
   }
   if (st != FS_OK) {
     delete plan;
